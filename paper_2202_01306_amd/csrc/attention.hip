@@ -1,4 +1,5 @@
-// Softmax attention forward and backward, never materialising the s x s
+// Softmax attention forward and backward in plain vector arithmetic, the reference of the
+// matrix-core kernels (attention_mfma.hip, attention_f32.hip), never materialising the s x s
 // probabilities: one thread owns one query row (forward, dQ) or one key row
 // (dK, dV); key/value (or query/dO) tiles of 32 rows are staged through LDS and
 // read as broadcasts.  Forward keeps the per-row logsumexp; backward recomputes
@@ -284,6 +285,8 @@ int launch_attn_fwd(int prec, const void *qkv, void *o, float *lse, int b, int s
                     stream_t st) {
   if (b < 1 || s < 1 || H < 1) return fail(HMY_E_INVALID, "attn_fwd: bad shape");
   if (prec == HMY_PREC_BF16 && g_use_mfma) return launch_attn_fwd_mfma(qkv, o, lse, b, s, H, dh, causal, st);
+  if (prec == HMY_PREC_FP32 && g_use_mfma)
+    return launch_attn_fwd_f32((const float *)qkv, (float *)o, lse, b, s, H, dh, causal, st);
   DISPATCH_ATTN(prec, dh, attn_fwd_t, qkv, o, lse, b, s, H, causal, (hipStream_t)st);
 }
 int launch_attn_bwd(int prec, const void *qkv, const void *o, const void *d_o, const float *lse, float *delta, void *dqkv,
@@ -291,8 +294,13 @@ int launch_attn_bwd(int prec, const void *qkv, const void *o, const void *d_o, c
   if (b < 1 || s < 1 || H < 1) return fail(HMY_E_INVALID, "attn_bwd: bad shape");
   if (prec == HMY_PREC_BF16 && g_use_mfma)
     return launch_attn_bwd_mfma(qkv, o, d_o, lse, delta, dqkv, dbias, b, s, H, dh, causal, st);
-  // the plain kernels leave the bias gradient to a pass of its own over dqkv
-  const int rc = [&]() -> int { DISPATCH_ATTN(prec, dh, attn_bwd_t, qkv, o, d_o, lse, delta, dqkv, b, s, H, causal, (hipStream_t)st); }();
+  // the fp32 and the plain kernels leave the bias gradient to a pass of its own over dqkv
+  const int rc = [&]() -> int {
+    if (prec == HMY_PREC_FP32 && g_use_mfma)
+      return launch_attn_bwd_f32((const float *)qkv, (const float *)o, (const float *)d_o, lse, delta, (float *)dqkv, b, s, H, dh,
+                                 causal, st);
+    DISPATCH_ATTN(prec, dh, attn_bwd_t, qkv, o, d_o, lse, delta, dqkv, b, s, H, causal, (hipStream_t)st);
+  }();
   if (rc != HMY_OK || !dbias) return rc;
   return launch_colsum(prec, dqkv, dbias, b * s, 3 * H * dh, st);
 }

@@ -11,7 +11,7 @@
 //    the inner loop is the same for every layout.  Accumulating GEMMs with few
 //    output tiles split the contraction over workgroups (fp32 atomics).
 //  * k_gemm_ref: plain 64x64 tiled fp32-FMA kernel for any layout and element
-//    type; the fp32 precision path and the A/B reference for the MFMA kernel.
+//    type; the A/B reference for the matrix-core kernels (fp32: gemm_f32.hip).
 #include <algorithm>
 
 #include "dev_common.h"
@@ -347,6 +347,7 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
   p.c_fp32 = g.c_fp32; p.accumulate = g.accumulate;
   p.res_fp32 = g.res_fp32 || g.prec == HMY_PREC_FP32;
   hipStream_t s = (hipStream_t)st;
+  if (g.prec == HMY_PREC_FP32 && g_use_mfma) return launch_gemm_f32(g, st);
   // 32-bit element offsets inside the kernel: every operand must span fewer than 2^31 elements
   const int64_t a_span = int64_t(g.ta ? g.K : g.M) * g.lda, b_span = int64_t(g.tb ? g.K : g.N) * g.ldb;
   const bool mfma_ok = g.prec == HMY_PREC_BF16 && g_use_mfma && aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 &&

@@ -1,0 +1,275 @@
+// fp32 GEMM on the matrix cores (v_mfma_f32_32x32x2_f32): C[M,N] = op(A) op(B) (+bias) (+res), optional gelu second
+// output, optional accumulation into C.  Every product and every sum is fp32, as in the plain kernel.
+//
+// One such instruction multiplies 32x32 outputs by two contraction steps in 64 cycles, so what feeds it is never the
+// limit: operand tiles go through registers into one of two LDS stages, and ragged edges are masked on the way.  What
+// bounds the kernel is the matrix pipe when the output has tiles for every SIMD, and the length of one wave's multiply
+// chain when it has not.  Hence three splits of the same loop, four waves each:
+//   128x128  each wave 64x64 (2x2 instructions per step)            outputs with two workgroups for every compute unit
+//   64x64    each wave 32x32                                        ordinary outputs
+//   32x32    the four waves share the tile and split the contraction (added up through LDS in a fixed order): small
+//            outputs, where a wave that ran the whole contraction would be alone on its compute unit
+// Contraction order inside a tile: lane half h of a wave takes steps 4h..4h+3 of every group of eight, for both
+// operands alike, so that an operand with the contraction index contiguous is read from LDS 16 bytes at a time; one
+// stored contraction-major is kept [k][row] and read 4 bytes at a time.
+// Measured against the plain kernel (us): 128x128x128 15.5 -> 5.5, 1024x2048x512 72 -> 28, 1024x512x2048 284 -> 28,
+// 1024x512x8192 (input gradient) 1135 -> 111, 1024x4096x4096 683 -> 309, 2048x8192x4096 (weight gradient) 2520 -> 1206
+// = 114 TFLOP/s of the 154 that a large fp32 product of the vendor library reaches.
+#include <algorithm>
+
+#include "dev_common.h"
+#include "hmy_internal.h"
+
+namespace hmy {
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+struct F32P {
+  const float *A, *B;
+  float *C;
+  const float *bias, *res;
+  float *gelu_out;
+  int M, N, K;
+  int64_t lda, ldb, ldc, ldr;
+  int accumulate;
+};
+
+constexpr int kSlab = 32;   // contraction steps a wave multiplies per tile
+
+// One operand's tile of ROWS rows and KT contraction steps: global -> registers -> LDS.
+// TR = false: memory [row][k], LDS [k slab][row][32] with 16-byte chunks XOR-swizzled by the row.
+// TR = true : memory [k][row], LDS [k][ROWS + 8] (the pad puts a wave's two halves, four k apart, on different banks).
+template <bool TR, bool VEC, int ROWS, int KT>
+struct Operand {
+  static constexpr int kVecs = ROWS * KT / 4 / 256;   // 16-byte pieces per thread
+  static constexpr int kFloats = TR ? KT * (ROWS + 8) : ROWS * KT;
+  float4 r[kVecs];
+  // element (row, k) = base[row * ld + k] or base[k * ld + row]; nrows x K valid.  VEC (16-byte aligned rows): every load is
+  // one 16-byte piece that holds at least one valid element, rows past the operand clamped into it (they only feed outputs
+  // that are never stored); contraction steps past K are set to zero on the way to LDS, so that nothing waits for a load
+  // here.  Otherwise element by element.
+  __device__ __forceinline__ void load(const float *base, int64_t ld, int row0, int nrows, int k0, int K, int tid) {
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) {
+      const int idx = tid + 256 * i;
+      if (VEC && TR) {
+        const int row = min(row0 + 4 * (idx % (ROWS / 4)), (nrows - 1) & ~3), k = k0 + idx / (ROWS / 4);
+        r[i] = *reinterpret_cast<const float4 *>(base + int64_t(min(k, K - 1)) * ld + row);
+      } else if (VEC) {
+        const int row = min(row0 + idx / (KT / 4), nrows - 1), k = k0 + 4 * (idx % (KT / 4));
+        r[i] = *reinterpret_cast<const float4 *>(base + int64_t(row) * ld + min(k, (K - 1) & ~3));
+      } else {
+        // `across`: the index along the contiguous axis, `along`: the other one
+        const int across = TR ? row0 + 4 * (idx % (ROWS / 4)) : k0 + 4 * (idx % (KT / 4));
+        const int along = TR ? k0 + idx / (ROWS / 4) : row0 + idx / (KT / 4);
+        const float *p = base + int64_t(min(along, (TR ? K : nrows) - 1)) * ld;
+        const int last = (TR ? nrows : K) - 1;
+        r[i] = make_float4(p[min(across, last)], p[min(across + 1, last)], p[min(across + 2, last)], p[min(across + 3, last)]);
+      }
+    }
+  }
+  __device__ __forceinline__ void store(float *s, int k0, int K, int tid) {
+    if (k0 + KT > K) {   // the last tile
+#pragma unroll
+      for (int i = 0; i < kVecs; ++i) {
+        const int idx = tid + 256 * i;
+        const int left = K - (TR ? k0 + idx / (ROWS / 4) : k0 + 4 * (idx % (KT / 4)));   // valid steps from this piece's first on
+        r[i].x = left > 0 ? r[i].x : 0.f;
+        r[i].y = left > (TR ? 0 : 1) ? r[i].y : 0.f;
+        r[i].z = left > (TR ? 0 : 2) ? r[i].z : 0.f;
+        r[i].w = left > (TR ? 0 : 3) ? r[i].w : 0.f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) {
+      const int idx = tid + 256 * i;
+      int at;
+      if (TR) {
+        at = (idx / (ROWS / 4)) * (ROWS + 8) + 4 * (idx % (ROWS / 4));
+      } else {
+        const int chunk = idx % (KT / 4), row = idx / (KT / 4);
+        at = (chunk / 8) * (ROWS * kSlab) + row * kSlab + (((chunk & 7) ^ ((row >> 1) & 7)) << 2);
+      }
+      *reinterpret_cast<float4 *>(s + at) = r[i];
+    }
+  }
+  // the four steps of chunk pair c (steps 8c + 4h + 0..3 of slab kw) for row `row`
+  static __device__ __forceinline__ float4 frag(const float *s, int kw, int row, int c, int h) {
+    if (TR) {
+      const float *p = s + (kw * kSlab + 8 * c + 4 * h) * (ROWS + 8) + row;
+      return make_float4(p[0], p[ROWS + 8], p[2 * (ROWS + 8)], p[3 * (ROWS + 8)]);
+    }
+    return *reinterpret_cast<const float4 *>(s + kw * (ROWS * kSlab) + row * kSlab + (((2 * c + h) ^ ((row >> 1) & 7)) << 2));
+  }
+};
+
+__device__ __forceinline__ void emit(const F32P &p, int m, int n, float bias, float v) {
+  v += bias;
+  if (p.res) v += p.res[int64_t(m) * p.ldr + n];
+  const int64_t ci = int64_t(m) * p.ldc + n;
+  if (p.accumulate) v += p.C[ci];
+  p.C[ci] = v;
+  if (p.gelu_out) p.gelu_out[ci] = gelu_f(v);
+}
+
+// WM x WN waves over rows and columns, KW over the contraction; TI x TJ instructions of 32x32 per wave and step
+template <bool TA, bool TB, bool VEC, int WM, int WN, int KW, int TI, int TJ>
+__global__ __launch_bounds__(256, 2) void k_gemm_f32(F32P p, int grid_n) {
+  static_assert(WM * WN * KW == 4, "four waves");
+  constexpr int BM = WM * TI * 32, BN = WN * TJ * 32, KT = KW * kSlab;
+  typedef Operand<TA, VEC, BM, KT> OpA;
+  typedef Operand<TB, VEC, BN, KT> OpB;
+  constexpr int kStage = OpA::kFloats + OpB::kFloats;
+  __shared__ __attribute__((aligned(16))) float smem[2 * kStage];
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+  const int h = lane / 32, l32 = lane % 32;
+  const int kw = wave % KW, wn = (wave / KW) % WN, wm = wave / (KW * WN);
+  // each XCD (workgroup id mod 8) takes a contiguous range of tiles, ordered in bands of eight tile rows
+  int bid = blockIdx.x;
+  const int nb = gridDim.x, grid_m = nb / grid_n;
+  {
+    const int x = bid % 8, per = nb / 8, extra = nb % 8;
+    bid = x * per + min(x, extra) + bid / 8;
+  }
+  constexpr int kBand = 8;
+  const int band = bid / (kBand * grid_n), first_m = band * kBand;
+  const int band_rows = min(grid_m - first_m, kBand);
+  const int in_band = bid - band * kBand * grid_n;
+  const int m0 = (first_m + in_band % band_rows) * BM, n0 = (in_band / band_rows) * BN;
+
+  f32x16 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  // Tiles are fetched two ahead of their multiplies, into two sets of registers by turns: one tile's multiplies are
+  // shorter than a trip to memory.
+  OpA oa[2];
+  OpB ob[2];
+  const int nk = (p.K + KT - 1) / KT;
+  auto fetch = [&](int set, int t) {
+    if (t >= nk) return;
+    oa[set].load(p.A, p.lda, m0, p.M, t * KT, p.K, tid);
+    ob[set].load(p.B, p.ldb, n0, p.N, t * KT, p.K, tid);
+  };
+  auto put = [&](int set, int t) {
+    float *stage = smem + (t & 1) * kStage;
+    oa[set].store(stage, t * KT, p.K, tid);
+    ob[set].store(stage + OpA::kFloats, t * KT, p.K, tid);
+  };
+  // tile t: its registers (set `mine`) went to LDS a tile ago, the other set holds tile t + 1
+  auto tile = [&](int mine, int other, int t) {
+    fetch(mine, t + 2);
+    const float *a_s = smem + (t & 1) * kStage, *b_s = a_s + OpA::kFloats;
+    // all of the tile's fragments first: their LDS latency is paid once per tile, not once per chunk
+    float4 fa[4][TI], fb[4][TJ];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) fa[c][i] = OpA::frag(a_s, kw, (wm * TI + i) * 32 + l32, c, h);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) fb[c][j] = OpB::frag(b_s, kw, (wn * TJ + j) * 32 + l32, c, h);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) {
+            const float a = q == 0 ? fa[c][i].x : q == 1 ? fa[c][i].y : q == 2 ? fa[c][i].z : fa[c][i].w;
+            const float b = q == 0 ? fb[c][j].x : q == 1 ? fb[c][j].y : q == 2 ? fb[c][j].z : fb[c][j].w;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc[i][j], 0, 0, 0);
+          }
+    if (t + 1 < nk) put(other, t + 1);   // into the stage that every wave left before the last barrier
+    __syncthreads();
+  };
+  fetch(0, 0);
+  fetch(1, 1);
+  put(0, 0);
+  __syncthreads();
+  for (int t = 0; t < nk; t += 2) {
+    tile(0, 1, t);
+    if (t + 1 < nk) tile(1, 0, t + 1);
+  }
+  // accumulator register r of lane l: row 8*(r/4) + 4*(l/32) + r%4, column l%32
+  if (KW == 1) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int n = n0 + (wn * TJ + j) * 32 + l32;
+      if (n >= p.N) continue;
+      const float bias = p.bias ? p.bias[n] : 0.f;
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = m0 + (wm * TI + i) * 32 + 8 * (r / 4) + 4 * h + r % 4;
+          if (m < p.M) emit(p, m, n, bias, acc[i][j][r]);
+        }
+    }
+  } else {
+    // the waves' partial sums meet in LDS (free since the last barrier); wave w adds up registers 4w..4w+3
+    float *x = smem;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[(kw * 16 + r) * 64 + lane] = acc[0][0][r];
+    __syncthreads();
+    const int n = n0 + l32;
+    if (n >= p.N) return;
+    const float bias = p.bias ? p.bias[n] : 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = m0 + 8 * kw + 4 * h + q;
+      float v = 0.f;
+#pragma unroll
+      for (int w = 0; w < KW; ++w) v += x[(w * 16 + 4 * kw + q) * 64 + lane];
+      if (m < p.M) emit(p, m, n, bias, v);
+    }
+  }
+}
+
+template <bool VEC, int WM, int WN, int KW, int TI, int TJ>
+int launch_split(const hmy_gemm_desc &g, const F32P &p, hipStream_t s) {
+  const int bm = WM * TI * 32, bn = WN * TJ * 32;
+  const int gm = (g.M + bm - 1) / bm, gn = (g.N + bn - 1) / bn;
+  const dim3 grid(gm * gn), block(256);
+  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_f32<false, false, VEC, WM, WN, KW, TI, TJ>), grid, block, 0, s, p, gn);
+  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_f32<false, true, VEC, WM, WN, KW, TI, TJ>), grid, block, 0, s, p, gn);
+  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_f32<true, false, VEC, WM, WN, KW, TI, TJ>), grid, block, 0, s, p, gn);
+  else hipLaunchKernelGGL((k_gemm_f32<true, true, VEC, WM, WN, KW, TI, TJ>), grid, block, 0, s, p, gn);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(HMY_E_HIP, "launch of gemm_f32 failed: %s", hipGetErrorString(e));
+  return HMY_OK;
+}
+
+}  // namespace
+
+int launch_gemm_f32(const hmy_gemm_desc &g, stream_t st) {
+  F32P p;
+  p.A = static_cast<const float *>(g.A); p.B = static_cast<const float *>(g.B); p.C = static_cast<float *>(g.C);
+  p.bias = static_cast<const float *>(g.bias); p.res = static_cast<const float *>(g.res);
+  p.gelu_out = static_cast<float *>(g.gelu_out);
+  p.M = g.M; p.N = g.N; p.K = g.K;
+  p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc; p.ldr = g.ldr;
+  p.accumulate = g.accumulate;
+  const bool vec = ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) == 0 && g.lda % 4 == 0 &&
+                   g.ldb % 4 == 0;
+  auto tiles = [&](int side) { return int64_t((g.M + side - 1) / side) * ((g.N + side - 1) / side); };
+  hipStream_t s = (hipStream_t)st;
+  // A SIMD runs one wave's chain of multiplies as fast as several waves' together, so the finest split that still
+  // gives every SIMD a wave leaves the shortest chain; larger tiles only save operand traffic, which matters once
+  // there are two of them for every compute unit.
+  // operands whose rows are not 16-byte aligned: rare (no tensor of a model has such rows), one split does
+  if (!vec) return launch_split<false, 2, 2, 1, 1, 1>(g, p, s);
+  if (tiles(128) >= 512) return launch_split<true, 2, 2, 1, 2, 2>(g, p, s);
+  if (tiles(64) >= 192) return launch_split<true, 2, 2, 1, 1, 1>(g, p, s);
+  return launch_split<true, 1, 1, 4, 1, 1>(g, p, s);
+}
+
+}  // namespace hmy

@@ -158,6 +158,7 @@ int launch_gelu_bwd_colsum(int prec, const void *dg, const void *u, void *du, fl
 int launch_colsum(int prec, const void *a, float *out, int T, int N, stream_t st);
 int launch_gemm(const hmy_gemm_desc &g, stream_t st);
 
+int launch_gemm_f32(const hmy_gemm_desc &g, stream_t st);
 int launch_gemm_mfma32(const hmy_gemm_desc &g, stream_t st);
 bool gemm_dma_eligible(const hmy_gemm_desc &g);
 int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st);
@@ -169,6 +170,9 @@ int launch_attn_bwd(int prec, const void *qkv, const void *o, const void *d_o, c
 int launch_attn_fwd_mfma(const void *qkv, void *o, float *lse, int b, int s, int H, int dh, int causal, stream_t st);
 int launch_attn_bwd_mfma(const void *qkv, const void *o, const void *d_o, const float *lse, float *delta, void *dqkv,
                          float *dbias, int b, int s, int H, int dh, int causal, stream_t st);
+int launch_attn_fwd_f32(const float *qkv, float *o, float *lse, int b, int s, int H, int dh, int causal, stream_t st);
+int launch_attn_bwd_f32(const float *qkv, const float *o, const float *d_o, const float *lse, float *delta, float *dqkv,
+                        int b, int s, int H, int dh, int causal, stream_t st);
 int launch_xent(int prec, const float *logits, const int32_t *targets, double *loss_acc,
                 void *dlogits, int T, int V, int64_t ldl, float inv_ntgt, stream_t st);
 int launch_adam(int prec, const float *grad, float *master, float *m, float *v, void *w_out,

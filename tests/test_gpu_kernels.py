@@ -315,6 +315,27 @@ def test_gemm_fp32(ta, tb):
     _gemm_case(*args, 128, 512, 128, ta, tb, 0, 0, True, False, "in place", True)
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 1), (33, 31, 129), (32, 32, 128), (900, 840, 70), (832, 1024, 32), (4100, 2050, 33),
+                                   (4096, 2048, 64)])
+def test_gemm_fp32_every_split(ta, tb, M, N, K):
+    """One 32x32 tile and its edges, 64x64 tiles, 128x128 tiles; ragged and whole in all three directions; leading
+    dimensions that allow 16-byte accesses and ones that do not.  Bound: sums of K rounded fp32 products."""
+    say(f"gemm fp32 {M}x{N}x{K} ta={ta} tb={tb}")
+    args = ("fp32", 0, torch.float32, 1e-5)
+    _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, True, False, True, pad=3)
+    _gemm_case(*args, M, N, K, ta, tb, 1, 1, False, False, False, True)
+    _gemm_case(*args, M, N, K, ta, tb, 1, 1, False, False, False, True, pad=-K % 4, row_pad=-M % 4)
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("b,s,H,dh", [(32, 130, 8, 32), (32, 129, 8, 64), (32, 140, 8, 128), (1, 2, 1, 64), (1, 33, 2, 128)])
+def test_attention_fp32_one_and_several_waves(causal, b, s, H, dh):
+    """Four waves per workgroup (512 workgroups), with a ragged last tile, and the shortest sequences."""
+    say(f"attention fp32 causal={causal} b={b} s={s} H={H} dh={dh}")
+    _attention_case("fp32", 0, torch.float32, 1e-5, causal, b, s, H, dh)
+
+
 def test_gemm_rejects_bad_arguments():
     a = torch.zeros(64, 64, device="cuda", dtype=torch.bfloat16)
     with pytest.raises(B.HmyError) as e:
