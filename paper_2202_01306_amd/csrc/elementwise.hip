@@ -796,27 +796,50 @@ __global__ void k_xent(const float *logits, const int32_t *targets, double *loss
 }
 
 // ---- fused Adam ---------------------------------------------------------------
+// One parameter's update.  The fused operations are written out, so that every kernel that updates rounds alike.
+__device__ __forceinline__ void adam_step(float g, float &w, float &m, float &v, float lr, float b1, float b2, float eps,
+                                          float inv_bc1, float inv_bc2) {
+  m = __builtin_fmaf(b1, m, (1.f - b1) * g);
+  v = __builtin_fmaf(g, (1.f - b2) * g, b2 * v);
+  w -= lr * (m * inv_bc1) / (sqrtf(v * inv_bc2) + eps);
+}
+
 // mixed: fp32 master/m/v in, updated master/m/v + RNE-rounded compute weight out.
 // fp32:  the fp32 weight is the master (W == float, master == w_out).
+// A stream over seven (five) arrays, bound by HBM: four elements per thread and step as 16-byte accesses (8 for the bf16
+// weight), where every array allows them (the first `n4` groups), the rest element by element.  16.8 M parameters, 30 bytes
+// each: 181 -> 102 us (4.9 TB/s).
 template <typename W>
-__global__ void k_adam(const float *grad, float *master, float *m, float *v, W *w_out, uint64_t n, float lr, float b1,
-                       float b2, float eps, float inv_bc1, float inv_bc2) {
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  const uint64_t n4 = n / 4;
-  for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n4 + (n % 4 ? 1 : 0); i += stride) {
-    const uint64_t base = i * 4;
-    const int cnt = int(min<uint64_t>(4, n - base));
-    for (int k = 0; k < cnt; ++k) {
-      const uint64_t j = base + k;
-      const float g = grad[j];
-      const float mm = b1 * m[j] + (1.f - b1) * g;
-      const float vv = b2 * v[j] + (1.f - b2) * g * g;
-      const float w = master[j] - lr * (mm * inv_bc1) / (sqrtf(vv * inv_bc2) + eps);
-      m[j] = mm;
-      v[j] = vv;
-      master[j] = w;
-      if (sizeof(W) == 2) w_out[j] = from_f32<W>(w);
+__global__ __launch_bounds__(kBlock) void k_adam(const float *grad, float *master, float *m, float *v, W *w_out, uint64_t n, uint64_t n4, float lr,
+                                                 float b1, float b2, float eps, float inv_bc1, float inv_bc2) {
+  auto update = [&](float g, float &w, float &mm, float &vv) { adam_step(g, w, mm, vv, lr, b1, b2, eps, inv_bc1, inv_bc2); };
+  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x, first = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  for (uint64_t i = first; i < n4; i += stride) {
+    float g[4], w[4], a[4], b[4];
+    load_stream<4>(grad + 4 * i, g);
+    load_stream<4>(master + 4 * i, w);
+    load_stream<4>(m + 4 * i, a);
+    load_stream<4>(v + 4 * i, b);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) update(g[k], w[k], a[k], b[k]);
+    store_stream<4>(m + 4 * i, a);
+    store_stream<4>(v + 4 * i, b);
+    store_stream<4>(master + 4 * i, w);
+    if (sizeof(W) == 2) {
+      typedef W w4 __attribute__((ext_vector_type(4)));
+      w4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = from_f32<W>(w[k]);
+      *reinterpret_cast<w4 *>(w_out + 4 * i) = o;
     }
+  }
+  for (uint64_t j = 4 * n4 + first; j < n; j += stride) {
+    float w = master[j], a = m[j], b = v[j];
+    update(grad[j], w, a, b);
+    m[j] = a;
+    v[j] = b;
+    master[j] = w;
+    if (sizeof(W) == 2) w_out[j] = from_f32<W>(w);
   }
 }
 
@@ -875,11 +898,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(8))) void k_adam_out(const float *
       }
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      m[k] = b1 * m[k] + (1.f - b1) * g[k];
-      v[k] = b2 * v[k] + (1.f - b2) * g[k] * g[k];
-      w[k] = w[k] - lr * (m[k] * inv_bc1) / (sqrtf(v[k] * inv_bc2) + eps);
-    }
+    for (int k = 0; k < 8; ++k) adam_step(g[k], w[k], m[k], v[k], lr, b1, b2, eps, inv_bc1, inv_bc2);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (full[h]) {
@@ -1182,15 +1201,19 @@ int launch_adam(int prec, const float *grad, float *master, float *m, float *v, 
   if (hp.step < 1) return fail(HMY_E_INVALID, "adam: step is 1-based");
   const float inv_bc1 = float(1.0 / (1.0 - std::pow(double(hp.beta1), double(hp.step))));
   const float inv_bc2 = float(1.0 / (1.0 - std::pow(double(hp.beta2), double(hp.step))));
-  const int grid = grid_for(n / 4 + 1, kBlock, 4096);
+  auto aligned = [](const void *p, int to) { return (reinterpret_cast<uintptr_t>(p) & uintptr_t(to - 1)) == 0; };
+  const bool vec = aligned(grad, 16) && aligned(master, 16) && aligned(m, 16) && aligned(v, 16) &&
+                   aligned(w_out, prec == HMY_PREC_BF16 ? 8 : 16);
+  const uint64_t n4 = vec ? n / 4 : 0;
+  const int grid = grid_for(vec ? n4 + 1 : n, kBlock, 8192);
   if (prec == HMY_PREC_BF16) {
     if (!master) return fail(HMY_E_INVALID, "adam(bf16): master required");
     hipLaunchKernelGGL(k_adam<bf16_t>, dim3(grid), dim3(kBlock), 0, (hipStream_t)st, grad, master, m, v,
-                       (bf16_t *)w_out, n, hp.lr, hp.beta1, hp.beta2, hp.eps, inv_bc1, inv_bc2);
+                       (bf16_t *)w_out, n, n4, hp.lr, hp.beta1, hp.beta2, hp.eps, inv_bc1, inv_bc2);
   } else if (prec == HMY_PREC_FP32) {
     if (master) return fail(HMY_E_INVALID, "adam(fp32): master must be NULL");
     hipLaunchKernelGGL(k_adam<float>, dim3(grid), dim3(kBlock), 0, (hipStream_t)st, grad, (float *)w_out, m, v,
-                       (float *)w_out, n, hp.lr, hp.beta1, hp.beta2, hp.eps, inv_bc1, inv_bc2);
+                       (float *)w_out, n, n4, hp.lr, hp.beta1, hp.beta2, hp.eps, inv_bc1, inv_bc2);
   } else {
     return fail(HMY_E_INVALID, "unknown precision %d", prec);
   }
