@@ -164,10 +164,12 @@ typedef struct hmy_budget {
 #define HMY_STATE_SWAPPED 0
 #define HMY_STATE_RESIDENT_IN_SPARE_BUDGET 1
 
-/* How device->host traffic leaves (Section 4.4: the swap-out stream).  KERNEL: through the
- * library's own throttled kernels that store to the pinned host arrays (the update kernel
- * writes its results there itself).  MEMCPY: hipMemcpyAsync on the swap-out stream, after an
- * update kernel that leaves its results in HBM.  Same bytes, same counters, same results. */
+/* How swap traffic crosses the link (Section 4.4: the swap-in and swap-out streams).  KERNEL: the
+ * library's own way: copies on copy engines that it names itself, ordered by signals; where the
+ * runtime does not offer those (state outside memory that the HIP runtime allocated, for one),
+ * incoming copies through streams and device->host traffic through throttled kernels that store to
+ * the pinned host arrays.  MEMCPY: hipMemcpyAsync on streams in both directions.  Same bytes, same
+ * counters, same results. */
 #define HMY_SWAP_OUT_KERNEL 0
 #define HMY_SWAP_OUT_MEMCPY 1
 

@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhmy.so")
 
-SOURCES = ["model.cpp", "planner.cpp", "api.cpp", "engine.hip", "elementwise.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip", "attention_mfma.hip", "gemm_tr.hip", "gemm_dma.hip", "host_update.cpp"]
+SOURCES = ["model.cpp", "planner.cpp", "api.cpp", "engine.hip", "copy_engine.cpp", "elementwise.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip", "attention_mfma.hip", "gemm_tr.hip", "gemm_dma.hip", "host_update.cpp"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
@@ -58,7 +58,8 @@ def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
-    cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-pthread", "-o", LIB, *objs]
+    cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-pthread", "-o", LIB, *objs,
+           "-L/opt/rocm/lib", "-lhsa-runtime64"]     # the runtime HIP itself runs on: copies on named copy engines
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)

@@ -1,16 +1,19 @@
 // Swap engine + iteration executor: the layer-pack-major training iteration of
 // the Harmony paper (Section 3; task order of Algorithm 3 at N = 1) on one GPU.
 //
-// Streams (the paper's Runtime uses compute / swap-in / swap-out streams plus
-// events, Section 4.4; p2p streams have no role on one GPU):
-//   s_comp  every layer kernel
-//   s_in    token ids, weight packs (prefetched one visit ahead, in n_micro pieces
-//           interleaved with the microbatch loop) and checkpoints coming back
-//   s_kin   optimizer state coming in, chunk by chunk, up to the ring's depth ahead
-//   s_out   everything going to the host: checkpoints, updated state, gradients; also the
-//           fused Adam kernel, which writes its results to the host itself (s_upd is an
-//           alias of s_out: the engine stays within the 4 hardware queues a process has)
-// All ordering is by events; the host thread only enqueues and finally waits.
+// Queues (the paper's Runtime uses compute / swap-in / swap-out streams plus events, Section
+// 4.4; p2p streams have no role on one GPU):
+//   COMP      stream: every layer kernel
+//   UPD       stream: the Adam kernel of packs whose backward is over, beside COMP
+//   IN        copies: weight packs (prefetched, in n_micro pieces interleaved with the microbatch
+//             loop) and checkpoints coming back
+//   STATE_IN  copies: optimizer state coming in, chunk by chunk, up to the ring's depth ahead
+//   OUT       copies: everything going to the host: checkpoints, updated state, gradients
+// The three copy queues are copy engines that the library names itself (copy_engine.h); all
+// ordering is by signals.  Where the runtime does not offer those engines, and with
+// HMY_SWAP_OUT_MEMCPY, they are streams and the ordering is by events; device->host traffic
+// then leaves through hipMemcpyAsync (MEMCPY) or through kernels that store to the host
+// (fused_swap_out; UPD is the OUT stream then).  The host thread only enqueues and finally waits.
 //
 // A "visit" is one task of the ordered list: forward packs in order, then
 // backward packs in reverse, each followed by its update (jit-update).  The
@@ -27,14 +30,25 @@
 #include <cstdlib>
 #include <cmath>
 #include <cstring>
+#include <deque>
 #include <thread>
 
+#include "copy_engine.h"
 #include "hmy_internal.h"
 
 namespace hmy {
 const char *last_error();
 }
 using namespace hmy;
+
+enum Queue { COMP, UPD, IN, STATE_IN, OUT, N_QUEUES };
+
+// a point on a queue that others can wait for: an event of a stream, or a signal where the copy engines are in use; neither
+// set: nothing to wait for
+struct Point {
+  hipEvent_t event = nullptr;
+  Signal signal = nullptr;
+};
 
 struct Visit {
   bool bwd;
@@ -58,6 +72,15 @@ struct hmy_handle {
   char *base = nullptr;
   bool own_arena = false;
   hipStream_t s_comp = nullptr, s_in = nullptr, s_kin = nullptr, s_upd = nullptr, s_out = nullptr;
+  CopyEngines *engines = nullptr;        // nullptr: copies through streams
+  std::vector<Signal> deps[N_QUEUES];    // copy engines: what the queue's next copy waits for
+  Signal last_copy[N_QUEUES] = {};       // copy engines: the latest copy of the queue in this iteration
+  hipEvent_t ids_event = nullptr;
+  bool arrays_reached = false;           // the bound host arrays lie in memory the copy engines reach
+  bool on_engines() const { return engines && arrays_reached; }
+  hipStream_t stream(Queue q) const {
+    return q == COMP ? s_comp : q == UPD ? s_upd : q == IN ? s_in : q == STATE_IN ? s_kin : s_out;
+  }
   hmy_host_state host{};
   bool bound = false;
   char *stash_host = nullptr;   // pinned: checkpoints [n_ckpt][rows of the minibatch][d]
@@ -75,6 +98,8 @@ struct hmy_handle {
   struct Span { size_t a, b; int what;   int tag = 0;
 };  // what: 0 h2d, 1 d2h, 2 stall, 3 compute
   std::vector<Span> spans;
+  struct CopySpan { Signal done; int what; int tag; };
+  std::vector<CopySpan> copy_spans;   // the same for copies on copy engines
   int tag = 0;   // what the spans recorded now belong to: 1000 * visit + microbatch (timeline dump)
   hmy_stats st{};
   int err = HMY_OK;
@@ -107,22 +132,61 @@ struct hmy_handle {
 
 namespace {
 
-// ---- events -----------------------------------------------------------------
-hipEvent_t rec(hmy_handle *h, hipStream_t s) {
-  if (h->dry || h->err) return nullptr;
+// ---- ordering -----------------------------------------------------------------
+// One lane stores the signal; the stream's order puts it behind everything queued there before.
+__global__ void k_signal(Signal s) { __hip_atomic_store(s, uint64_t(0), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM); }
+
+constexpr bool is_copy_queue(Queue q) { return q >= IN; }
+constexpr CopyQueue copy_queue(Queue q) { return q == IN ? COPY_IN : q == STATE_IN ? COPY_STATE_IN : COPY_OUT; }
+
+Signal new_signal(hmy_handle *h) {
+  Signal s = h->engines->take();
+  if (!s) h->err = fail(HMY_E_HIP, "no memory for a signal");
+  return s;
+}
+Point rec(hmy_handle *h, Queue q) {
+  Point p;
+  if (h->dry || h->err) return p;
+  if (h->on_engines()) {
+    if (is_copy_queue(q)) {   // everything queued before the latest copy is over before it
+      p.signal = h->last_copy[q];
+      return p;
+    }
+    p.signal = new_signal(h);
+    if (h->err) return Point();
+    hipLaunchKernelGGL(k_signal, dim3(1), dim3(1), 0, h->stream(q), p.signal);
+    HIPCHK(h, hipGetLastError());
+    return h->err ? Point() : p;
+  }
   if (h->sync_used == h->sync_events.size()) {
     hipEvent_t e = nullptr;
     HIPCHK(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    if (h->err) return nullptr;
+    if (h->err) return p;
     h->sync_events.push_back(e);
   }
-  hipEvent_t e = h->sync_events[h->sync_used++];
-  HIPCHK(h, hipEventRecord(e, s));
-  return e;
+  p.event = h->sync_events[h->sync_used++];
+  HIPCHK(h, hipEventRecord(p.event, h->stream(q)));
+  return p;
 }
-void wait(hmy_handle *h, hipStream_t s, hipEvent_t e) {
-  if (h->dry || h->err || !e) return;
-  HIPCHK(h, hipStreamWaitEvent(s, e, 0));
+void wait(hmy_handle *h, Queue q, const Point &p) {
+  if (h->dry || h->err) return;
+  if (p.signal && CopyEngines::happened(p.signal)) return;
+  if (p.signal && is_copy_queue(q)) h->deps[q].push_back(p.signal);
+  else if (p.signal) HIPCHK(h, hipStreamWaitValue64(h->stream(q), p.signal, 0, hipStreamWaitValueEq));
+  if (p.event) HIPCHK(h, hipStreamWaitEvent(h->stream(q), p.event, 0));
+}
+// whether a point has been reached, asked by the host
+bool reached(hmy_handle *h, const Point &p) {
+  if (h->dry || h->err) return true;
+  if (p.signal) return CopyEngines::happened(p.signal);
+  if (!p.event) return true;
+  const hipError_t e = hipEventQuery(p.event);
+  if (e == hipErrorNotReady) {
+    (void)hipGetLastError();   // "not ready" is no error, but the runtime may keep it as its last one
+    return false;
+  }
+  HIPCHK(h, e);
+  return true;
 }
 size_t trec(hmy_handle *h, hipStream_t s) {
   if (h->dry || h->err || !h->timing) return size_t(-1);
@@ -149,47 +213,64 @@ void calibrate_event_pair(hmy_handle *h) {
     span(h, a, b, 20);
   }
 }
-// wait on a swap event from the compute stream, measuring the stall
-void comp_wait(hmy_handle *h, hipEvent_t e) {
-  if (h->dry || h->err || !e) return;
+// wait on a swap from the compute stream, measuring the stall
+void comp_wait(hmy_handle *h, const Point &p) {
+  if (h->dry || h->err || !(p.event || p.signal)) return;
   size_t a = trec(h, h->s_comp);
-  wait(h, h->s_comp, e);
+  wait(h, COMP, p);
   size_t b = trec(h, h->s_comp);
   span(h, a, b, 2);
 }
 
 // ---- copies (bytes are counted when enqueued) ---------------------------------
-void h2d(hmy_handle *h, int kind, void *dst, const void *src, uint64_t bytes, hipStream_t s) {
+// device -> pinned host through a throttled copy kernel on the OUT stream (the library's blit
+// for hipMemcpyAsync floods the fabric with stores to the link and stalls the kernels
+// running beside it)
+void copy(hmy_handle *h, Queue q, void *dst, const void *src, uint64_t bytes) {
+  const int what = q == OUT ? 1 : 0;
+  if (h->on_engines()) {
+    Signal done = new_signal(h);
+    if (h->err) return;
+    if (!h->engines->copy(copy_queue(q), dst, src, bytes, h->deps[q], done)) {
+      h->err = fail(HMY_E_HIP, "a copy engine refused %llu bytes", (unsigned long long)bytes);
+      return;
+    }
+    h->deps[q].clear();
+    h->last_copy[q] = done;
+    if (h->timing) h->copy_spans.push_back({done, what, h->tag});
+    return;
+  }
+  hipStream_t s = h->stream(q);
+  size_t a = trec(h, s);
+  if (q == OUT && h->fused_swap_out) h->err = launch_copy_out(dst, src, bytes, s);
+  else HIPCHK(h, hipMemcpyAsync(dst, src, bytes, q == OUT ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice, s));
+  size_t b = trec(h, s);
+  span(h, a, b, what);
+}
+void h2d(hmy_handle *h, int kind, void *dst, const void *src, uint64_t bytes, Queue q) {
   if (!bytes) return;
   h->st.h2d[kind] += bytes;
   if (h->dry || h->err) return;
-  size_t a = trec(h, s);
-  HIPCHK(h, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
-  size_t b = trec(h, s);
+  copy(h, q, dst, src, bytes);
+}
+void d2h(hmy_handle *h, int kind, void *dst, const void *src, uint64_t bytes) {
+  if (!bytes) return;
+  h->st.d2h[kind] += bytes;
+  if (h->dry || h->err) return;
+  copy(h, OUT, dst, src, bytes);
+}
+// token ids and targets: the caller's memory may be pageable, so these two go through a stream in every case
+hipEvent_t copy_ids(hmy_handle *h, const hmy_minibatch *mb, uint64_t n) {
+  h->st.h2d[HMY_KIND_IDS] += 2 * 4 * n;
+  if (h->dry || h->err) return nullptr;
+  size_t a = trec(h, h->s_in);
+  HIPCHK(h, hipMemcpyAsync(h->base + h->arena.res.ids, mb->token_ids, 4 * n, hipMemcpyHostToDevice, h->s_in));
+  HIPCHK(h, hipMemcpyAsync(h->base + h->arena.res.targets, mb->targets, 4 * n, hipMemcpyHostToDevice, h->s_in));
+  size_t b = trec(h, h->s_in);
   span(h, a, b, 0);
-}
-void d2h(hmy_handle *h, int kind, void *dst, const void *src, uint64_t bytes, hipStream_t s) {
-  if (!bytes) return;
-  h->st.d2h[kind] += bytes;
-  if (h->dry || h->err) return;
-  size_t a = trec(h, s);
-  HIPCHK(h, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
-  size_t b = trec(h, s);
-  span(h, a, b, 1);
-}
-
-// device -> pinned host through a throttled copy kernel on stream s (the library's blit
-// for hipMemcpyAsync floods the fabric with stores to the link and stalls the kernels
-// running beside it)
-void d2h_kernel(hmy_handle *h, int kind, void *dst, const void *src, uint64_t bytes, hipStream_t s) {
-  if (!bytes) return;
-  h->st.d2h[kind] += bytes;
-  if (h->dry || h->err) return;
-  size_t a = trec(h, s);
-  int rc = launch_copy_out(dst, src, bytes, s);
-  if (rc) h->err = rc;
-  size_t b = trec(h, s);
-  span(h, a, b, 1);
+  if (!h->ids_event) HIPCHK(h, hipEventCreateWithFlags(&h->ids_event, hipEventDisableTiming));
+  HIPCHK(h, hipEventRecord(h->ids_event, h->s_in));
+  return h->err ? nullptr : h->ids_event;
 }
 
 #define KCHK(h, call)                          \
@@ -417,24 +498,40 @@ void head_forward_backward(hmy_handle *h, const Visit &v, const PackPtrs &pp, in
                                g_lnf_b, nullptr, T, d, h->s_comp));
 }
 
+// every queue is idle here
+void begin_iteration(hmy_handle *h) {
+  std::memset(&h->st, 0, sizeof(h->st));
+  h->sync_used = h->time_used = 0;
+  h->spans.clear();
+  h->copy_spans.clear();
+  if (h->engines) h->engines->recycle();
+  for (int q = 0; q < N_QUEUES; ++q) {
+    h->deps[q].clear();
+    h->last_copy[q] = nullptr;
+  }
+}
+
+// the update of a pack whose backward has been enqueued: chunks whose state has been asked for, and chunks handed over
 struct PendingUpdate {
   const Visit *v = nullptr;
-  hipEvent_t bwd_done = nullptr;
-  int next = 0, n_chunks = 0;
+  Point bwd_done;
+  int asked = 0, run = 0, n_chunks = 0;
 };
 
 struct IterState {
-  PendingUpdate upd;
+  std::deque<PendingUpdate> updates;   // in order
+  std::deque<Point> arrivals;          // per chunk asked for and not yet run, in order: its state has arrived
   bool compute_done = false;   // nothing is left to enqueue on the compute stream
-  hipEvent_t slot_free[kMaxSlots] = {};
-  hipEvent_t in_free[kInRing] = {};
-  hipEvent_t in_ready[kInRing] = {};
-  hipEvent_t out_free[kOutRing] = {};
-  hipEvent_t k_free[kKRing] = {};
-  hipEvent_t stash_all_out = nullptr;
-  bool stash_waited = false;
+  Point slot_free[kMaxSlots];
+  Point in_free[kInRing];
+  Point in_ready[kInRing];
+  bool from_host[kInRing] = {};   // that ring slot holds a checkpoint
+  Point out_free[kOutRing];
+  Point k_free[kKRing];
+  Point stash_all_out;
+  bool stash_asked = false, stash_waited = false;
   int out_count = 0;
-  int k_count = 0;
+  int k_asked = 0, k_run = 0;          // chunks through the ring: asked for, run
   float inv_ntgt = 0.f;
 };
 
@@ -463,11 +560,9 @@ void forward_visit_microbatch(hmy_handle *h, IterState &it, const Visit &v, int 
       comp_wait(h, it.out_free[q]);
       // the checkpoint leaves rounded to the element type (one rounding per pack boundary)
       KCHK(h, launch_convert_f32(s.precision, X, outring(h, q), uint64_t(T) * d, h->s_comp));
-      hipEvent_t e = rec(h, h->s_comp);
-      wait(h, h->s_out, e);
-      if (h->fused_swap_out) d2h_kernel(h, HMY_KIND_SX, stash_slot(h, ck, mb, true), outring(h, q), xb, h->s_out);
-      else d2h(h, HMY_KIND_SX, stash_slot(h, ck, mb, true), outring(h, q), xb, h->s_out);
-      it.out_free[q] = rec(h, h->s_out);
+      wait(h, OUT, rec(h, COMP));
+      d2h(h, HMY_KIND_SX, stash_slot(h, ck, mb, true), outring(h, q), xb);
+      it.out_free[q] = rec(h, OUT);
     }
     if (layer == 0) {
       const int t0 = h->model.first_tensor[0];
@@ -490,7 +585,8 @@ float *first_input(const hmy_handle *h, const Visit &v) {
 void issue_pack_input(hmy_handle *h, IterState &it, const Visit &v, int mb) {
   const int r = mb % kInRing;
   const uint64_t xb = h->arena.res.ck_bytes_B;
-  it.in_ready[r] = nullptr;
+  it.in_ready[r] = Point();
+  it.from_host[r] = false;
   if (v.pack.a == 0) return;  // starts at the embedding: restarts from the token ids
   if (v.last) {               // still resident from the forward pass: straight into the first layer's input buffer
     KCHK(h, launch_copy(first_input(h, v), Xbuf(h, mb, false), h->arena.res.x_bytes_B, h->s_comp));
@@ -498,12 +594,13 @@ void issue_pack_input(hmy_handle *h, IterState &it, const Visit &v, int mb) {
   }
   const int ck = ckpt_index(h, v.pack.a);
   if (!it.stash_waited) {
-    wait(h, h->s_in, it.stash_all_out);
+    wait(h, IN, it.stash_all_out);
     it.stash_waited = true;
   }
-  wait(h, h->s_in, it.in_free[r]);
-  h2d(h, HMY_KIND_SX, inring(h, r), stash_slot(h, ck, mb, false), xb, h->s_in);
-  it.in_ready[r] = rec(h, h->s_in);
+  wait(h, IN, it.in_free[r]);
+  h2d(h, HMY_KIND_SX, inring(h, r), stash_slot(h, ck, mb, false), xb, IN);
+  it.in_ready[r] = rec(h, IN);
+  it.from_host[r] = true;
 }
 
 void backward_visit_microbatch(hmy_handle *h, IterState &it, const Visit &v, int mb) {
@@ -518,7 +615,7 @@ void backward_visit_microbatch(hmy_handle *h, IterState &it, const Visit &v, int
     char *reg = act_region(h, v.pack, layer);
     return (float *)(layer <= L ? reg + h->bacts.x_in : reg + h->hacts.x_in);
   };
-  if (it.in_ready[r])   // a checkpoint has arrived in the ring: widen it into the first layer's input
+  if (it.from_host[r])   // a checkpoint has arrived in the ring: widen it into the first layer's input
     KCHK(h, launch_convert_to_f32(s.precision, inring(h, r), first_input(h, v), uint64_t(T) * d, h->s_comp));
   if (!v.last)          // the gradient handed down by the pack above, rounded for the GEMMs that read it
     KCHK(h, launch_convert_f32(s.precision, D, h->base + h->arena.res.dlow, uint64_t(T) * d, h->s_comp));
@@ -548,130 +645,174 @@ void backward_visit_microbatch(hmy_handle *h, IterState &it, const Visit &v, int
       block_backward(h, v, pp, layer, A, input_of(layer), D);
     }
   }
-  it.in_free[r] = rec(h, h->s_comp);
+  it.in_free[r] = rec(h, COMP);
 }
 
-// jit-update of a visit's pack: optimizer state streams through the ring in chunks
-// (in on s_upd, Adam on s_upd, results out by the same kernel or on s_out) while the
-// next pack computes.  Chunks are enqueued a few at a time from the next visit's
-// microbatch loop: a host->device copy that has to wait for its ring slot holds up every
-// copy queued behind it on the copy engine, checkpoint reads of the running visit
-// included, so no more of them are queued ahead than one microbatch's worth.
-void update_chunk(hmy_handle *h, IterState &it, const hmy_adam &hp) {
-  PendingUpdate &u = it.upd;
-  const Visit &v = *u.v;
+// jit-update of a visit's pack: optimizer state streams through the ring in chunks (in on STATE_IN, Adam on UPD, results
+// out on OUT) while the next packs compute.  The host hands the chunks over as they become ready (pump_updates, called
+// between the microbatches it enqueues and while it waits): a kernel that polled for its chunk's arrival on the device
+// slowed the matrix products beside it by a third, and a stream that waits for an event on a queue shared with others
+// holds those up.  The ring is deep enough that the host's reaction time hides behind the chunks in flight.
+struct Chunk {
+  uint64_t lo, n, g0;        // first parameter inside the pack, count, element offset in the host arrays
+  int resident;              // resident slot, or -1: its state crosses the link
+  float *master, *m, *v;     // its state on the device
+};
+Chunk chunk_of(const hmy_handle *h, const Visit &v, int index, int ring) {
   const Reserved &R = h->arena.res;
+  const bool mixed = h->model.spec.precision == HMY_PREC_BF16;
+  Chunk c;
+  c.lo = uint64_t(index) * R.k_chunk_params;
+  c.n = std::min<uint64_t>(R.k_chunk_params, v.nparams - c.lo);
+  c.g0 = v.poff + c.lo;
+  // a chunk whose state lives on the device: updated in place there, nothing of it crosses the link
+  c.resident = std::max(-1, h->first_chunk[v.index] + index - (h->total_chunks - h->res_chunks));
+  char *at = c.resident >= 0 ? h->base + h->res_off + uint64_t(c.resident) * h->chunk_state_bytes()
+                             : h->base + R.kring + uint64_t(ring) * h->model.k_arrays() * R.karr_bytes;
+  c.master = mixed ? (float *)at : nullptr;
+  c.m = (float *)(at + (mixed ? 1 : 0) * R.karr_bytes);
+  c.v = (float *)(at + (mixed ? 2 : 1) * R.karr_bytes);
+  return c;
+}
+void ask_chunk(hmy_handle *h, IterState &it, PendingUpdate &u) {
+  const int ring = it.k_asked % kKRing;
+  const Chunk c = chunk_of(h, *u.v, u.asked++, ring);
+  Point arrived;
+  // resident state is read once, by the first update since the arrays were bound
+  if (c.resident < 0 || !h->res_loaded[c.resident]) {
+    if (c.resident < 0) {
+      wait(h, STATE_IN, it.k_free[ring]);
+      ++it.k_asked;
+    }
+    if (c.master) h2d(h, HMY_KIND_K, c.master, h->dry ? nullptr : h->host.master + c.g0, c.n * 4, STATE_IN);
+    h2d(h, HMY_KIND_K, c.m, h->dry ? nullptr : h->host.adam_m + c.g0, c.n * 4, STATE_IN);
+    h2d(h, HMY_KIND_K, c.v, h->dry ? nullptr : h->host.adam_v + c.g0, c.n * 4, STATE_IN);
+    arrived = rec(h, STATE_IN);
+    if (c.resident >= 0 && !h->err) h->res_loaded[c.resident] = 1;
+  }
+  it.arrivals.push_back(arrived);
+}
+void run_chunk(hmy_handle *h, IterState &it, PendingUpdate &u, const hmy_adam &hp) {
+  const Visit &v = *u.v;
   const int E = h->model.elem_bytes();
   const bool mixed = h->model.spec.precision == HMY_PREC_BF16;
   const PackPtrs pp = pack_ptrs(h, v);
-  const uint64_t lo = uint64_t(u.next) * R.k_chunk_params;
-  const uint64_t n = std::min<uint64_t>(R.k_chunk_params, v.nparams - lo);
-  const uint64_t g0 = v.poff + lo;  // element offset in the host arrays
-  // a chunk whose state lives on the device: updated in place there, nothing of it crosses the link
-  const int rslot = h->first_chunk[v.index] + u.next - (h->total_chunks - h->res_chunks);
-  const bool resident = rslot >= 0;
-  const int r = resident ? 0 : it.k_count++ % kKRing;
-  char *ring = resident ? h->base + h->res_off + uint64_t(rslot) * h->chunk_state_bytes()
-                        : h->base + R.kring + uint64_t(r) * h->model.k_arrays() * R.karr_bytes;
-  float *r_master = mixed ? (float *)ring : nullptr;
-  float *r_m = (float *)(ring + (mixed ? 1 : 0) * R.karr_bytes);
-  float *r_v = (float *)(ring + (mixed ? 2 : 1) * R.karr_bytes);
-  if (resident) {
-    if (!h->res_loaded[rslot]) {   // first update since the arrays were bound: read it as a swapped chunk would be
-      if (mixed) h2d(h, HMY_KIND_K, r_master, h->dry ? nullptr : h->host.master + g0, n * 4, h->s_kin);
-      h2d(h, HMY_KIND_K, r_m, h->dry ? nullptr : h->host.adam_m + g0, n * 4, h->s_kin);
-      h2d(h, HMY_KIND_K, r_v, h->dry ? nullptr : h->host.adam_v + g0, n * 4, h->s_kin);
-      wait(h, h->s_upd, rec(h, h->s_kin));
-      if (!h->err) h->res_loaded[rslot] = 1;
-    }
-  } else {
-    // on a stream of their own, so that chunk c+1 arrives while chunk c is updated
-    wait(h, h->s_kin, it.k_free[r]);
-    if (mixed) h2d(h, HMY_KIND_K, r_master, h->dry ? nullptr : h->host.master + g0, n * 4, h->s_kin);
-    h2d(h, HMY_KIND_K, r_m, h->dry ? nullptr : h->host.adam_m + g0, n * 4, h->s_kin);
-    h2d(h, HMY_KIND_K, r_v, h->dry ? nullptr : h->host.adam_v + g0, n * 4, h->s_kin);
-    wait(h, h->s_upd, rec(h, h->s_kin));
-  }
-  if (u.next == 0) wait(h, h->s_upd, u.bwd_done);
+  const int ring = it.k_run % kKRing;
+  const Chunk c = chunk_of(h, v, u.run++, ring);
+  const bool resident = c.resident >= 0;
+  if (!resident) ++it.k_run;
   const bool export_g = h->packs.gradients == HMY_GRADIENTS_EXPORTED;
-  if (h->fused_swap_out) {
+  auto host = [&](float *array) { return h->dry ? nullptr : array + c.g0; };
+  char *w_host = h->dry ? nullptr : (char *)h->host.weights + c.g0 * E;
+  const bool by_kernel = h->fused_swap_out && !h->on_engines();
+  if (by_kernel) {
     // the update kernel itself writes state, weights and (if exported) gradients to the host
     // arrays (device->host over the link at vector width); bytes are counted as for copies
-    if (!resident) h->st.d2h[HMY_KIND_K] += uint64_t(h->model.k_arrays()) * n * 4;
-    h->st.d2h[HMY_KIND_W] += n * E;
-    if (export_g) h->st.d2h[HMY_KIND_DW] += n * 4;
+    if (!resident) h->st.d2h[HMY_KIND_K] += uint64_t(h->model.k_arrays()) * c.n * 4;
+    h->st.d2h[HMY_KIND_W] += c.n * E;
+    if (export_g) h->st.d2h[HMY_KIND_DW] += c.n * 4;
     if (!h->dry && !h->err) {
       const size_t a = trec(h, h->s_upd);
-      KCHK(h, launch_adam_out(h->model.spec.precision, pp.dW + lo, mixed ? r_master : (const float *)(pp.W + lo * E),
-                              r_m, r_v, !mixed ? nullptr : resident ? r_master : h->host.master + g0,
-                              resident ? r_m : h->host.adam_m + g0, resident ? r_v : h->host.adam_v + g0,
-                              (char *)h->host.weights + g0 * E,
-                              export_g ? h->host.grads + g0 : nullptr, n, hp, it.compute_done, h->s_upd));
+      KCHK(h, launch_adam_out(h->model.spec.precision, pp.dW + c.lo, mixed ? c.master : (const float *)(pp.W + c.lo * E), c.m,
+                              c.v, !mixed ? nullptr : resident ? c.master : host(h->host.master),
+                              resident ? c.m : host(h->host.adam_m), resident ? c.v : host(h->host.adam_v), w_host,
+                              export_g ? host(h->host.grads) : nullptr, c.n, hp, it.compute_done, h->s_upd));
       const size_t b2 = trec(h, h->s_upd);
       span(h, a, b2, 1);
     }
-    if (!resident) it.k_free[r] = rec(h, h->s_upd);
+    if (!resident) it.k_free[ring] = rec(h, UPD);
   } else {
-    KCHK(h, launch_adam(h->model.spec.precision, pp.dW + lo, r_master, r_m, r_v, pp.W + lo * E, n, hp, h->s_upd));
-    hipEvent_t e = rec(h, h->s_upd);
-    wait(h, h->s_out, e);
+    KCHK(h, launch_adam(h->model.spec.precision, pp.dW + c.lo, c.master, c.m, c.v, pp.W + c.lo * E, c.n, hp, h->s_upd));
+    wait(h, OUT, rec(h, UPD));
     if (!resident) {
-      if (mixed) d2h(h, HMY_KIND_K, h->dry ? nullptr : h->host.master + g0, r_master, n * 4, h->s_out);
-      d2h(h, HMY_KIND_K, h->dry ? nullptr : h->host.adam_m + g0, r_m, n * 4, h->s_out);
-      d2h(h, HMY_KIND_K, h->dry ? nullptr : h->host.adam_v + g0, r_v, n * 4, h->s_out);
+      if (mixed) d2h(h, HMY_KIND_K, host(h->host.master), c.master, c.n * 4);
+      d2h(h, HMY_KIND_K, host(h->host.adam_m), c.m, c.n * 4);
+      d2h(h, HMY_KIND_K, host(h->host.adam_v), c.v, c.n * 4);
+      it.k_free[ring] = rec(h, OUT);
     }
-    d2h(h, HMY_KIND_W, h->dry ? nullptr : (char *)h->host.weights + g0 * E, pp.W + lo * E, n * E, h->s_out);
-    if (export_g) d2h(h, HMY_KIND_DW, h->dry ? nullptr : h->host.grads + g0, pp.dW + lo, n * 4, h->s_out);
-    if (!resident) it.k_free[r] = rec(h, h->s_out);
+    d2h(h, HMY_KIND_W, w_host, pp.W + c.lo * E, c.n * E);
+    if (export_g) d2h(h, HMY_KIND_DW, host(h->host.grads), pp.dW + c.lo, c.n * 4);
   }
-  if (++u.next == u.n_chunks) {   // the pack has left: its slot may be refilled
-    it.slot_free[v.slot] = rec(h, h->fused_swap_out ? h->s_upd : h->s_out);
-    u.v = nullptr;
+  // the pack has left: its slot may be refilled
+  if (u.run == u.n_chunks) it.slot_free[v.slot] = rec(h, by_kernel ? UPD : OUT);
+}
+// hand over what has become ready; true if anything has
+bool pump_updates(hmy_handle *h, IterState &it, const hmy_adam &hp) {
+  bool moved = false;
+  for (bool step = true; step && !it.updates.empty(); moved |= step) {
+    step = false;
+    for (PendingUpdate &u : it.updates) {
+      if (u.asked == u.n_chunks) continue;
+      if (it.arrivals.size() < size_t(kKRing)) {
+        ask_chunk(h, it, u);
+        step = true;
+      }
+      break;
+    }
+    PendingUpdate &u = it.updates.front();
+    if (!it.arrivals.empty() && reached(h, it.arrivals.front()) && (u.run > 0 || reached(h, u.bwd_done))) {
+      run_chunk(h, it, u, hp);
+      it.arrivals.pop_front();
+      if (u.run == u.n_chunks) it.updates.pop_front();
+      step = true;
+    }
   }
+  return moved;
 }
-// enqueue chunks of the pending update until `upto` of them have been (all if negative)
-void update_progress(hmy_handle *h, IterState &it, const hmy_adam &hp, int upto) {
-  while (it.upd.v && (upto < 0 || it.upd.next < upto)) update_chunk(h, it, hp);
+bool update_pending(const IterState &it, int slot) {
+  for (const PendingUpdate &u : it.updates)
+    if (slot < 0 || u.v->slot == slot) return true;
+  return false;
 }
-void update_begin(hmy_handle *h, IterState &it, const Visit &v, hipEvent_t bwd_done, const hmy_adam &hp) {
-  update_progress(h, it, hp, -1);   // nothing of an older update may be left behind
+// until no update of that slot (any slot if negative) is pending
+void finish_updates(hmy_handle *h, IterState &it, const hmy_adam &hp, int slot) {
+  while (update_pending(it, slot))
+    if (!pump_updates(h, it, hp)) std::this_thread::yield();
+}
+void update_begin(hmy_handle *h, IterState &it, const Visit &v, const Point &bwd_done, const hmy_adam &hp) {
   const uint64_t c = h->arena.res.k_chunk_params;
-  it.upd.v = &v;
-  it.upd.bwd_done = bwd_done;
-  it.upd.next = 0;
-  it.upd.n_chunks = int((v.nparams + c - 1) / c);
+  PendingUpdate u;
+  u.v = &v;
+  u.bwd_done = bwd_done;
+  u.n_chunks = int((v.nparams + c - 1) / c);
+  it.updates.push_back(u);
+  pump_updates(h, it, hp);
 }
 
 // Weight Update on the host: the pack's gradient leaves for the pinned gradient array chunk by
 // chunk; each chunk's event is handed to the CPU threads, which apply Adam to the pinned state
 // in place as soon as it has arrived.  Nothing else of the pack crosses the link.
-void host_update_begin(hmy_handle *h, IterState &it, const Visit &v, hipEvent_t bwd_done, const hmy_adam &hp) {
+void host_update_begin(hmy_handle *h, IterState &it, const Visit &v, const Point &bwd_done, const hmy_adam &hp) {
   const uint64_t c = h->arena.res.k_chunk_params;
   const int E = h->model.elem_bytes();
   const bool mixed = h->model.spec.precision == HMY_PREC_BF16;
   const PackPtrs pp = pack_ptrs(h, v);
-  wait(h, h->s_out, bwd_done);
+  wait(h, OUT, bwd_done);
   for (uint64_t lo = 0; lo < v.nparams; lo += c) {
     const uint64_t n = std::min<uint64_t>(c, v.nparams - lo), g0 = v.poff + lo;
     float *dst = h->dry ? nullptr : h->host.grads + g0;
-    if (h->fused_swap_out) d2h_kernel(h, HMY_KIND_DW, dst, pp.dW + lo, n * 4, h->s_out);
-    else d2h(h, HMY_KIND_DW, dst, pp.dW + lo, n * 4, h->s_out);
-    hipEvent_t arrived = rec(h, h->s_out);
+    d2h(h, HMY_KIND_DW, dst, pp.dW + lo, n * 4);
+    const Point arrived = rec(h, OUT);
     if (h->dry || h->err) continue;
-    h->updater->submit(make_host_adam_job(arrived, h->host.grads + g0, mixed ? h->host.master + g0 : nullptr,
+    void *ready = arrived.signal ? static_cast<void *>(arrived.signal) : static_cast<void *>(arrived.event);
+    h->updater->submit(make_host_adam_job(ready, h->host.grads + g0, mixed ? h->host.master + g0 : nullptr,
                                           h->host.adam_m + g0, h->host.adam_v + g0, (char *)h->host.weights + g0 * E, n,
                                           hp));
   }
-  it.slot_free[v.slot] = rec(h, h->s_out);
+  it.slot_free[v.slot] = rec(h, OUT);
 }
 int updater_thread_init(void *arg, void *) {
   return hipSetDevice(static_cast<hmy_handle *>(arg)->device) == hipSuccess ? HMY_OK : HMY_E_HIP;
 }
-int updater_wait(void *, void *ready) {
+int updater_wait(void *arg, void *ready) {
+  if (static_cast<hmy_handle *>(arg)->on_engines()) {
+    CopyEngines::wait(static_cast<Signal>(ready));
+    return HMY_OK;
+  }
   return hipEventSynchronize(static_cast<hipEvent_t>(ready)) == hipSuccess ? HMY_OK : HMY_E_HIP;
 }
 // the update that follows a pack's (last) backward task, wherever the schedule places it
-void pack_update_begin(hmy_handle *h, IterState &it, const Visit &v, hipEvent_t bwd_done, const hmy_adam &hp) {
+void pack_update_begin(hmy_handle *h, IterState &it, const Visit &v, const Point &bwd_done, const hmy_adam &hp) {
   if (h->packs.update_site == HMY_UPDATE_ON_HOST) host_update_begin(h, it, v, bwd_done, hp);
   else update_begin(h, it, v, bwd_done, hp);
 }
@@ -681,9 +822,7 @@ void run_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam &hp) {
   const int M = h->M, E = h->model.elem_bytes();
   const uint64_t T = uint64_t(h->b) * s.seq_len;
   IterState it;
-  std::memset(&h->st, 0, sizeof(h->st));
-  h->sync_used = h->time_used = 0;
-  h->spans.clear();
+  begin_iteration(h);
 
   if (!h->dry) {
     uint64_t nt = 0;
@@ -691,59 +830,56 @@ void run_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam &hp) {
     h->st.n_targets = nt;
     it.inv_ntgt = nt ? float(1.0 / double(nt)) : 0.f;
   }
-  h2d(h, HMY_KIND_IDS, h->base + h->arena.res.ids, h->dry ? nullptr : mb->token_ids, uint64_t(M) * T * 4, h->s_in);
-  h2d(h, HMY_KIND_IDS, h->base + h->arena.res.targets, h->dry ? nullptr : mb->targets, uint64_t(M) * T * 4, h->s_in);
-  hipEvent_t ev_ids = rec(h, h->s_in);
+  Point ev_ids;
+  ev_ids.event = copy_ids(h, mb, uint64_t(M) * T);
   KCHK(h, launch_fill_zero(h->base + h->arena.res.misc, 4096, h->s_comp));
   const size_t t_first = trec(h, h->s_comp);
   calibrate_event_pair(h);
 
   // weight prefetch of a visit in `pieces` pieces.  Its slot was last used by the visit S places earlier: if that
-  // one's update is still being handed out chunk by chunk, all of it has to be enqueued first, or the event
-  // that says "the slot is free" does not exist yet.
+  // one's update is still being handed over chunk by chunk, all of it has to be first, or the point that says
+  // "the slot is free" does not exist yet.
   auto w_piece = [&](const Visit &v, int piece, int pieces) {
     const uint64_t total = uint64_t(E) * v.nparams;
     const uint64_t chunk = a256((total + pieces - 1) / pieces);
     const uint64_t lo = std::min(total, chunk * piece), hi = std::min(total, chunk * (piece + 1));
     if (piece == 0) {
-      if (it.upd.v && it.upd.v->slot == v.slot) update_progress(h, it, hp, -1);
-      wait(h, h->s_in, it.slot_free[v.slot]);
+      finish_updates(h, it, hp, v.slot);
+      wait(h, IN, it.slot_free[v.slot]);
     }
     if (hi > lo) {
       char *dst = h->base + h->arena.slot_off[v.slot] + lo;
       const char *src = h->dry ? nullptr : (const char *)h->host.weights + v.poff * E + lo;
-      h2d(h, HMY_KIND_W, dst, src, hi - lo, h->s_in);
+      h2d(h, HMY_KIND_W, dst, src, hi - lo, IN);
     }
   };
 
   const int nv = int(h->visits.size()), dist = h->packs.distance;
-  std::vector<hipEvent_t> ev_w(size_t(nv), nullptr);   // per visit: its weights have arrived
+  std::vector<Point> ev_w{size_t(nv)};   // per visit: its weights have arrived
   for (int vi = 0; vi < std::min(dist, nv); ++vi) {
     w_piece(h->visits[vi], 0, 1);
-    ev_w[vi] = rec(h, h->s_in);
+    ev_w[vi] = rec(h, IN);
   }
   for (int vi = 0; vi < nv; ++vi) {
     const Visit &v = h->visits[vi];
     const Visit *ahead = vi + dist < nv ? &h->visits[vi + dist] : nullptr;   // the visit whose weights travel now
     const bool final_visit = vi + 1 == nv;
     const int Mv = v.bwd ? M : h->MF;                                        // microbatches of this visit's pass
-    // The slot those weights go to may still belong to the pack whose update is being handed out during this
-    // visit (prefetch distance = slots - 1).  Then the load cannot start before that update has left anyway:
-    // it is requested behind the update's last chunk, in the visit's last microbatch, instead of holding up the
-    // link's queue (checkpoint reads of this visit included) from the visit's start.
-    const bool defer = ahead && it.upd.v && it.upd.v->slot == ahead->slot;
-    // With the update on the host the same slot is held by the gradient export of the visit before this one, which
-    // is already on its way (it is enqueued in one go).  Requested now, the load would sit in the link's queue
-    // until that export is over and hold up this visit's checkpoint reads behind it (measured on 32 blocks of
-    // d = 4096 in two slots: the compute stream waited 45 ms per visit).  So the host thread itself waits for the
-    // export, after it has enqueued all of this visit, and requests the load then: nothing queues behind a copy
-    // that cannot start, and the GPU has this visit's work to go on with meanwhile.
-    const bool after_export = ahead && !defer && h->packs.update_site == HMY_UPDATE_ON_HOST && vi >= 1 &&
+    // The slot those weights go to may still belong to a pack whose update is being handed over (prefetch distance =
+    // slots - 1, or a link that lags behind), or to the gradient export of the visit before this one.  The load cannot
+    // start before that has left, so the host waits for it only after it has enqueued all of this visit, and requests
+    // the load then: nothing queues behind a copy that cannot start (measured on 32 blocks of d = 4096 in two slots,
+    // checkpoint reads held up behind such a load: the compute stream waited 45 ms per visit), and the GPU has this
+    // visit's work to go on with meanwhile.
+    const bool after_update = ahead && update_pending(it, ahead->slot);
+    const bool after_export = ahead && h->packs.update_site == HMY_UPDATE_ON_HOST && vi >= 1 &&
                               h->visits[vi - 1].bwd && h->visits[vi - 1].slot == ahead->slot;
+    const bool later = after_update || after_export;
     comp_wait(h, ev_w[vi]);
     if (vi == 0) comp_wait(h, ev_ids);
     if (v.bwd) {
-      if (!it.stash_all_out) it.stash_all_out = rec(h, h->s_out);  // every checkpoint has been queued out
+      if (!it.stash_asked) it.stash_all_out = rec(h, OUT);  // every checkpoint has been queued out
+      it.stash_asked = true;
       const PackPtrs pp = pack_ptrs(h, v);
       KCHK(h, launch_fill_zero(pp.dW, v.nparams * 4, h->s_comp));
     }
@@ -757,14 +893,8 @@ void run_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam &hp) {
           for (int q = 0; q < (from_host ? std::min(Mv, kInRing - 1) : 1); ++q) issue_pack_input(h, it, v, q);
         if (from_host && m + kInRing - 1 < Mv) issue_pack_input(h, it, v, m + kInRing - 1);
       }
-      if (ahead && !defer && !after_export) w_piece(*ahead, m, Mv);
-      // this microbatch's share of the previous visit's update
-      // (not behind a final visit that is the embedding alone: it is over in a moment, and
-      // what is left of the update then runs at the full link rate)
-      const bool tiny_last = final_visit && v.pack.a == 0 && v.pack.e == 1;
-      if (it.upd.v && !tiny_last) update_progress(h, it, hp, (it.upd.n_chunks * (m + 1) + Mv - 1) / Mv);
-      if (ahead && defer && m == Mv - 1)
-        for (int piece = 0; piece < Mv; ++piece) w_piece(*ahead, piece, Mv);
+      if (ahead && !later) w_piece(*ahead, m, Mv);
+      pump_updates(h, it, hp);
       if (v.bwd) {
         if (m > 0 && (v.last || v.pack.a == 0)) issue_pack_input(h, it, v, m);
         backward_visit_microbatch(h, it, v, m);
@@ -772,24 +902,19 @@ void run_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam &hp) {
         forward_visit_microbatch(h, it, v, m);
       }
     }
-    if (ahead && !after_export) ev_w[vi + dist] = rec(h, h->s_in);
+    if (ahead && !later) ev_w[vi + dist] = rec(h, IN);
     if (!v.bwd) {
-      it.slot_free[v.slot] = rec(h, h->s_comp);
+      it.slot_free[v.slot] = rec(h, COMP);
     } else {
       if (final_visit) it.compute_done = true;   // nothing else will be enqueued on the compute stream
-      pack_update_begin(h, it, v, rec(h, h->s_comp), hp);
+      pack_update_begin(h, it, v, rec(h, COMP), hp);
     }
-    if (after_export) {
-      if (!h->dry && !h->err && it.slot_free[ahead->slot]) {
-        // polled with short sleeps: a spinning wait would take a core from the threads that apply the update
-        hipError_t q;
-        while ((q = hipEventQuery(it.slot_free[ahead->slot])) == hipErrorNotReady)
-          std::this_thread::sleep_for(std::chrono::microseconds(100));
-        (void)hipGetLastError();   // "not ready" is no error, but the runtime may keep it as its last one
-        HIPCHK(h, q);
-      }
+    if (later) {
+      // an export is polled with short sleeps: a spinning wait would take a core from the threads that apply the update
+      if (after_export)
+        while (!reached(h, it.slot_free[ahead->slot])) std::this_thread::sleep_for(std::chrono::microseconds(100));
       w_piece(*ahead, 0, 1);
-      ev_w[vi + dist] = rec(h, h->s_in);
+      ev_w[vi + dist] = rec(h, IN);
     }
     if (h->progress && !h->dry && !h->err) {
       // for runs under a profiler that serialises every dispatch: a line per visit, once its kernels have run
@@ -800,7 +925,7 @@ void run_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam &hp) {
     }
   }
   it.compute_done = true;
-  update_progress(h, it, hp, -1);   // the first pack's update has no visit to hide behind
+  finish_updates(h, it, hp, -1);   // the first pack's update has no visit to hide behind
   const size_t t_last = trec(h, h->s_comp);
   span(h, t_first, t_last, 3);
 }
@@ -817,9 +942,7 @@ void run_iteration_microbatch_major(hmy_handle *h, const hmy_minibatch *mb, cons
   const int M = h->M, E = h->model.elem_bytes();
   const uint64_t T = uint64_t(h->b) * s.seq_len;
   IterState it;
-  std::memset(&h->st, 0, sizeof(h->st));
-  h->sync_used = h->time_used = 0;
-  h->spans.clear();
+  begin_iteration(h);
 
   if (!h->dry) {
     uint64_t nt = 0;
@@ -827,9 +950,8 @@ void run_iteration_microbatch_major(hmy_handle *h, const hmy_minibatch *mb, cons
     h->st.n_targets = nt;
     it.inv_ntgt = nt ? float(1.0 / double(nt)) : 0.f;
   }
-  h2d(h, HMY_KIND_IDS, h->base + h->arena.res.ids, h->dry ? nullptr : mb->token_ids, uint64_t(M) * T * 4, h->s_in);
-  h2d(h, HMY_KIND_IDS, h->base + h->arena.res.targets, h->dry ? nullptr : mb->targets, uint64_t(M) * T * 4, h->s_in);
-  hipEvent_t ev_ids = rec(h, h->s_in);
+  Point ev_ids;
+  ev_ids.event = copy_ids(h, mb, uint64_t(M) * T);
   KCHK(h, launch_fill_zero(h->base + h->arena.res.misc, 4096, h->s_comp));
   const size_t t_first = trec(h, h->s_comp);
   calibrate_event_pair(h);
@@ -844,25 +966,25 @@ void run_iteration_microbatch_major(hmy_handle *h, const hmy_minibatch *mb, cons
       v.slot = int(seq.size() % size_t(h->packs.slots));
       seq.push_back(v);
     }
-  std::vector<hipEvent_t> grads_home(nv, nullptr);   // per visit of a microbatch: its gradient sums have reached the host
+  std::vector<Point> grads_home{size_t(nv)};   // per visit of a microbatch: its gradient sums have reached the host
 
   auto load_weights = [&](const Visit &v) {
-    // the slot's last user may still have its update handed out chunk by chunk: all of it first (see run_iteration)
-    if (it.upd.v && it.upd.v->slot == v.slot) update_progress(h, it, hp, -1);
-    wait(h, h->s_in, it.slot_free[v.slot]);
+    // the slot's last user may still have its update handed over chunk by chunk: all of it first (see run_iteration)
+    finish_updates(h, it, hp, v.slot);
+    wait(h, IN, it.slot_free[v.slot]);
     h2d(h, HMY_KIND_W, h->base + h->arena.slot_off[v.slot], h->dry ? nullptr : (const char *)h->host.weights + v.poff * E,
-        uint64_t(E) * v.nparams, h->s_in);
-    return rec(h, h->s_in);
+        uint64_t(E) * v.nparams, IN);
+    return rec(h, IN);
   };
   // what earlier microbatches added to this pack's gradient; enqueued only after the task that
   // sent those sums out has been enqueued (two consecutive visits can be the same pack)
   auto load_gradient_sums = [&](const Visit &v, int vi) {
-    wait(h, h->s_in, grads_home[vi]);
-    h2d(h, HMY_KIND_DW, pack_ptrs(h, v).dW, h->dry ? nullptr : h->host.grads + v.poff, v.nparams * 4, h->s_in);
-    return rec(h, h->s_in);
+    wait(h, IN, grads_home[vi]);
+    h2d(h, HMY_KIND_DW, pack_ptrs(h, v).dW, h->dry ? nullptr : h->host.grads + v.poff, v.nparams * 4, IN);
+    return rec(h, IN);
   };
 
-  hipEvent_t ev_w = load_weights(seq[0]);
+  Point ev_w = load_weights(seq[0]);
   const int total = M * nv;
   for (int g = 0; g < total; ++g) {
     const Visit &v = seq[g];
@@ -874,32 +996,32 @@ void run_iteration_microbatch_major(hmy_handle *h, const hmy_minibatch *mb, cons
     if (g == 0) comp_wait(h, ev_ids);
     if (v.bwd) {
       if (v.last) {   // first backward task of this microbatch: its checkpoints have all been queued out
-        it.stash_all_out = rec(h, h->s_out);
+        it.stash_all_out = rec(h, OUT);
         it.stash_waited = false;
       }
       if (m == 0) KCHK(h, launch_fill_zero(pack_ptrs(h, v).dW, v.nparams * 4, h->s_comp));
       issue_pack_input(h, it, v, m);
     }
-    if (next) ev_w = load_weights(*next);
-    update_progress(h, it, hp, -1);   // the update of the previous visit, if it had one
+    const bool later = next && update_pending(it, next->slot);
+    if (next && !later) ev_w = load_weights(*next);
+    pump_updates(h, it, hp);
     if (v.bwd) backward_visit_microbatch(h, it, v, m);
     else forward_visit_microbatch(h, it, v, m);
     if (!v.bwd) {
-      it.slot_free[v.slot] = rec(h, h->s_comp);
+      it.slot_free[v.slot] = rec(h, COMP);
     } else if (m == M - 1) {
       if (!next) it.compute_done = true;
-      pack_update_begin(h, it, v, rec(h, h->s_comp), hp);
+      pack_update_begin(h, it, v, rec(h, COMP), hp);
     } else {
-      wait(h, h->s_out, rec(h, h->s_comp));
-      float *dst = h->dry ? nullptr : h->host.grads + v.poff;
-      if (h->fused_swap_out) d2h_kernel(h, HMY_KIND_DW, dst, pack_ptrs(h, v).dW, v.nparams * 4, h->s_out);
-      else d2h(h, HMY_KIND_DW, dst, pack_ptrs(h, v).dW, v.nparams * 4, h->s_out);
-      grads_home[vi] = it.slot_free[v.slot] = rec(h, h->s_out);
+      wait(h, OUT, rec(h, COMP));
+      d2h(h, HMY_KIND_DW, h->dry ? nullptr : h->host.grads + v.poff, pack_ptrs(h, v).dW, v.nparams * 4);
+      grads_home[vi] = it.slot_free[v.slot] = rec(h, OUT);
     }
+    if (later) ev_w = load_weights(*next);
     if (next && next->bwd && next_m > 0) ev_w = load_gradient_sums(*next, next_vi);
   }
   it.compute_done = true;
-  update_progress(h, it, hp, -1);
+  finish_updates(h, it, hp, -1);
   const size_t t_last = trec(h, h->s_comp);
   span(h, t_first, t_last, 3);
 }
@@ -1031,11 +1153,12 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
     return fail(HMY_E_NO_DEVICE, "no usable HIP device %d (found %d)", hip_device, ndev);
   h.device = hip_device;
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  // what runs beside the layers in an iteration: weights and optimizer state arriving (copy engine), results
-  // leaving (the update kernel that writes to the host, launched as it is beside the compute stream: how much it
-  // slows other kernels goes with the rate it reaches); one staging buffer on each side
+  // what runs beside the layers in an iteration: weights and optimizer state arriving, results leaving, on the queues
+  // they take there; one staging buffer on each side
   constexpr uint64_t kLoadBytes = 64ull << 20;
   char *load_host = nullptr, *load_dev = nullptr;
+  CopyEngines *engines = nullptr;
+  Signal last_in = nullptr, last_out = nullptr;
   HIPCHK(&h, hipSetDevice(hip_device));
   HIPCHK(&h, hipMalloc(reinterpret_cast<void **>(&h.base), h.arena.total));
   HIPCHK(&h, hipStreamCreateWithFlags(&h.s_comp, hipStreamNonBlocking));
@@ -1043,6 +1166,7 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
   HIPCHK(&h, hipStreamCreateWithFlags(&h.s_out, hipStreamNonBlocking));
   HIPCHK(&h, hipHostMalloc(reinterpret_cast<void **>(&load_host), 2 * kLoadBytes, hipHostMallocDefault));
   HIPCHK(&h, hipMalloc(reinterpret_cast<void **>(&load_dev), 2 * kLoadBytes));
+  if (!h.err) engines = CopyEngines::create(h.base);
   HIPCHK(&h, hipEventCreate(&e0));
   HIPCHK(&h, hipEventCreate(&e1));
   if (!h.err) {
@@ -1052,19 +1176,8 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
     KCHK(&h, launch_fill_zero(h.base + h.arena.res.ids, uint64_t(micro_batch) * s1.seq_len * 4, h.s_comp));
     KCHK(&h, launch_fill_zero(h.base + h.arena.res.targets, uint64_t(micro_batch) * s1.seq_len * 4, h.s_comp));
     KCHK(&h, launch_fill_zero(h.base + h.arena.res.misc, 4096, h.s_comp));
-    KCHK(&h, launch_fill_zero(load_dev + kLoadBytes, kLoadBytes, h.s_comp));   // the update kernel's inputs: all zero
+    KCHK(&h, launch_fill_zero(load_dev + kLoadBytes, kLoadBytes, h.s_comp));
   }
-  // as many parameters per update launch as both staging buffers hold: 16 bytes each in, at most 20 out
-  const uint64_t upd_n = (kLoadBytes / 20) & ~uint64_t(255);
-  const bool mixed = s1.precision == HMY_PREC_BF16;
-  hmy_adam upd_hp;
-  upd_hp.lr = 1e-4f; upd_hp.beta1 = 0.9f; upd_hp.beta2 = 0.999f; upd_hp.eps = 1e-8f; upd_hp.step = 1;
-  auto update_out = [&]() {
-    const float *in = reinterpret_cast<const float *>(load_dev + kLoadBytes);
-    float *outp = reinterpret_cast<float *>(load_host + kLoadBytes);
-    return launch_adam_out(s1.precision, in, in + upd_n, in + 2 * upd_n, in + 3 * upd_n, mixed ? outp : nullptr,
-                           outp + upd_n, outp + 2 * upd_n, outp + 4 * upd_n, outp + 3 * upd_n, upd_n, upd_hp, false, h.s_out);
-  };
   IterState it;
   it.inv_ntgt = 1.0f / float(uint64_t(micro_batch) * s1.seq_len);
   auto timed = [&](const Visit &v, uint64_t *beside_ns) -> uint64_t {
@@ -1085,17 +1198,36 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
     once();   // warm-up: code objects, caches, clocks
     const double alone_ms = run(reps) / reps;
     if (!h.err) {
-      // enough traffic to last through the timed launches (about 40 GB/s each way beside kernels): incoming copies
-      // for every visit, outgoing stores only for backward visits, whose updates are what writes to the host
-      const int n_copies = int(std::min(400.0, 2.0 * reps * alone_ms * 1e-3 * 40e9 / double(kLoadBytes))) + 2;
+      // enough traffic to last through the timed launches (about 50 GB/s each way beside kernels): incoming copies
+      // for every visit, outgoing ones only for backward visits, whose updates are what writes to the host
+      const int n_copies = int(std::min(400.0, 2.0 * reps * alone_ms * 1e-3 * 50e9 / double(kLoadBytes))) + 2;
       // (each of these queues holds at most a few hundred operations of 64 MiB)
-      for (int c = 0; c < n_copies; ++c) {
-        HIPCHK(&h, hipMemcpyAsync(load_dev, load_host, kLoadBytes, hipMemcpyHostToDevice, h.s_in));
-        if (v.bwd) KCHK(&h, update_out());
+      for (int c = 0; c < n_copies && !h.err; ++c) {
+        if (engines) {
+          last_in = engines->take();
+          bool ok = last_in && engines->copy(COPY_STATE_IN, load_dev, load_host, kLoadBytes, {}, last_in);
+          if (ok && v.bwd) {
+            last_out = engines->take();
+            ok = last_out && engines->copy(COPY_OUT, load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, {}, last_out);
+            if (!ok) last_out = nullptr;
+          }
+          if (!ok) {
+            h.err = fail(HMY_E_HIP, "a copy engine refused the profile's traffic");
+            last_in = last_in && !ok ? nullptr : last_in;
+          }
+        } else {
+          HIPCHK(&h, hipMemcpyAsync(load_dev, load_host, kLoadBytes, hipMemcpyHostToDevice, h.s_in));
+          if (v.bwd) KCHK(&h, launch_copy_out(load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, h.s_out));
+        }
       }
     }
     const double beside_ms = run(reps) / reps;
-    hipStreamSynchronize(h.s_in);   // let what is left of the traffic drain before the next layer's turn
+    // let what is left of the traffic drain before the next layer's turn
+    if (last_in) CopyEngines::wait(last_in);
+    if (last_out) CopyEngines::wait(last_out);
+    last_in = last_out = nullptr;
+    if (engines) engines->recycle();
+    hipStreamSynchronize(h.s_in);
     hipStreamSynchronize(h.s_out);
     *beside_ns = uint64_t(std::max(alone_ms, beside_ms) * 1e6 + 0.5);
     return uint64_t(alone_ms * 1e6 + 0.5);
@@ -1111,6 +1243,7 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
   out->block_bwd_ns = timed(h.visits[3], &out->block_bwd_beside_ns) / nb;
   out->block_bwd_beside_ns /= nb;
   out->embed_bwd_ns = timed(h.visits[4], &out->embed_bwd_beside_ns);
+  delete engines;
   if (h.s_comp) { hipStreamSynchronize(h.s_comp); hipStreamDestroy(h.s_comp); }
   if (h.s_in) { hipStreamSynchronize(h.s_in); hipStreamDestroy(h.s_in); }
   if (h.s_out) { hipStreamSynchronize(h.s_out); hipStreamDestroy(h.s_out); }
@@ -1190,15 +1323,16 @@ int hmy_create(const hmy_model_spec *spec, const hmy_budget *budget, int32_t n_m
     HIPCHK(h, hipMalloc(reinterpret_cast<void **>(&h->base), h->arena.total + uint64_t(h->res_chunks) * h->chunk_state_bytes()));
     h->own_arena = true;
   }
+  // Streams share a pool of four hardware queues per process with each other and with the null stream, each new one taking
+  // the least used: the two that run kernels are created one after the other so that they get different ones.
   HIPCHK(h, hipStreamCreateWithFlags(&h->s_comp, hipStreamNonBlocking));
+  HIPCHK(h, hipStreamCreateWithFlags(&h->s_out, hipStreamNonBlocking));
   HIPCHK(h, hipStreamCreateWithFlags(&h->s_in, hipStreamNonBlocking));
   HIPCHK(h, hipStreamCreateWithFlags(&h->s_kin, hipStreamNonBlocking));
-  HIPCHK(h, hipStreamCreateWithFlags(&h->s_out, hipStreamNonBlocking));
-  // Four streams, not five: a process has 4 hardware queues by default, a fifth stream shares one
-  // with another stream, and every event wait queued on it then also holds up that stream's kernels
-  // (measured: an engine whose update stream landed on the compute stream's queue ran 30 % slower).
-  // The update kernels and the checkpoint writes barely overlap in time, so they share s_out.
+  // Four, not five: a fifth shares a queue with one of these, and every event wait queued on it then also holds up that
+  // one's work.  Update kernels and (where a stream carries them) device->host copies barely overlap, so they share one.
   h->s_upd = h->s_out;
+  if (h->fused_swap_out && !h->err) h->engines = CopyEngines::create(h->base);
   if (h->packs.update_site == HMY_UPDATE_ON_HOST && !h->err) {
     h->updater = new HostUpdater(default_host_threads(), updater_thread_init, updater_wait, h);
   }
@@ -1237,6 +1371,21 @@ int hmy_bind_state(hmy_handle *h, const hmy_host_state *state) {
                 (unsigned long long)h->model.n_params);
   h->host = *state;
   h->bound = true;
+  h->arrays_reached = h->engines != nullptr;
+  const uint64_t P = state->n_params;
+  if (h->arrays_reached) {
+    const bool on_device = h->packs.update_site == HMY_UPDATE_ON_DEVICE;   // else only weights and gradients cross the link
+    auto check = [&](const void *p, uint64_t bytes) {
+      if (p) h->arrays_reached = h->arrays_reached && h->engines->reaches(p, bytes);
+    };
+    check(state->weights, P * h->model.elem_bytes());
+    check(state->grads, P * 4);
+    if (on_device) {
+      check(state->master, P * 4);
+      check(state->adam_m, P * 4);
+      check(state->adam_v, P * 4);
+    }
+  }
   std::fill(h->res_loaded.begin(), h->res_loaded.end(), 0);   // resident state is read afresh from these arrays
   return HMY_OK;
 }
@@ -1287,7 +1436,9 @@ int hmy_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam *adam, 
   h->timing = out != nullptr && h->profile_level >= 1;
   auto t0 = std::chrono::steady_clock::now();
   run_in_order(h, mb, *adam);
-  // always drain, even after an error, so no stream still touches caller memory
+  // always drain, even after an error, so no queue still touches caller memory
+  for (int q = IN; q < N_QUEUES; ++q)
+    if (h->last_copy[q]) CopyEngines::wait(h->last_copy[q]);
   hipStreamSynchronize(h->s_comp);
   hipStreamSynchronize(h->s_in);
   hipStreamSynchronize(h->s_kin);
@@ -1314,6 +1465,10 @@ int hmy_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam *adam, 
       if (pair < 0 || ms * 1e-3 < pair) pair = ms * 1e-3;
     }
     h->st.t_event_pair_s = pair > 0 ? pair : 0.0;
+    for (const auto &c : h->copy_spans) {
+      double begin = 0.0, end = 0.0;
+      if (CopyEngines::times(c.done, &begin, &end)) (c.what ? h->st.t_d2h_busy_s : h->st.t_h2d_busy_s) += end - begin;
+    }
     for (const auto &sp : h->spans) {
       float ms = 0.f;
       if (sp.what == 20 || hipEventElapsedTime(&ms, h->time_events[sp.a], h->time_events[sp.b]) != hipSuccess) continue;
@@ -1336,6 +1491,17 @@ int hmy_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam *adam, 
           if (hipEventElapsedTime(&b, h->time_events[h->spans[0].a], h->time_events[sp.b]) != hipSuccess) continue;
           std::fprintf(f, "%d %d %.3f %.3f\n", sp.what, sp.tag, a, b);
         }
+        // copies on copy engines, on a clock of their own: ms since the first of them started
+        double first = -1.0;
+        for (const auto &c : h->copy_spans) {
+          double begin = 0.0, end = 0.0;
+          if (CopyEngines::times(c.done, &begin, &end) && (first < 0 || begin < first)) first = begin;
+        }
+        for (const auto &c : h->copy_spans) {
+          double begin = 0.0, end = 0.0;
+          if (!CopyEngines::times(c.done, &begin, &end)) continue;
+          std::fprintf(f, "%d %d %.3f %.3f\n", c.what, c.tag, (begin - first) * 1e3, (end - first) * 1e3);
+        }
         std::fclose(f);
       }
     }
@@ -1348,6 +1514,7 @@ int hmy_set_profiling(hmy_handle *h, int32_t level) {
   if (level < 0 || level > 2) return fail(HMY_E_INVALID, "profiling level %d (0..2)", level);
   h->profile_level = level;
   h->profile_gemm = level >= 2;
+  if (level >= 1 && h->engines) CopyEngines::time_copies();
   return HMY_OK;
 }
 
@@ -1370,6 +1537,8 @@ int hmy_destroy(hmy_handle *h) {
     if (h->s_out) { hipStreamSynchronize(h->s_out); hipStreamDestroy(h->s_out); }
     for (hipEvent_t e : h->sync_events) hipEventDestroy(e);
     for (hipEvent_t e : h->time_events) hipEventDestroy(e);
+    if (h->ids_event) hipEventDestroy(h->ids_event);
+    delete h->engines;
     if (h->stash_host) hipHostFree(h->stash_host);
     if (h->own_arena && h->base) hipFree(h->base);
   }

@@ -252,6 +252,18 @@ def test_swap_out_through_memcpy_tiny_fp32(order, update_site):
                         update_site=update_site, swap_out=1)
 
 
+@pytest.mark.parametrize("order,update_site", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_swaps_without_the_named_copy_engines(monkeypatch, precision, order, update_site):
+    """Where the runtime does not offer them: incoming copies through streams, results through kernels that store to the
+    host, packs of several chunks through the ring."""
+    say(f"{precision}, copies through streams, order {order}, update site {update_site}")
+    monkeypatch.setenv("HMY_COPY_ENGINES", "0")
+    cfg = tiny_cfg(n_blocks=4, d_model=128, n_heads=2, d_ffn=512, seq_len=64, vocab=600, precision=precision, M=3, b=2)
+    run_and_compare(cfg, sched_ends=([2, 5], [1, 2, 5, 6]), zero_state=False, steps=(3, 4), weight_scale=3.0, order=order,
+                    update_site=update_site)
+
+
 @pytest.mark.parametrize("gradients,resident", [(0, None), (1, 2)])
 def test_swap_out_through_memcpy_bf16_several_packs(gradients, resident):
     say(f"bf16, swap-out by hipMemcpyAsync, several packs, gradients {gradients}, resident chunks {resident}")
