@@ -352,6 +352,7 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
   const int64_t a_span = int64_t(g.ta ? g.K : g.M) * g.lda, b_span = int64_t(g.tb ? g.K : g.N) * g.ldb;
   const bool mfma_ok = g.prec == HMY_PREC_BF16 && g_use_mfma && aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 &&
                        g.ldb % 8 == 0 && a_span < (int64_t(1) << 31) && b_span < (int64_t(1) << 31);
+  if (mfma_ok && g_use_mfma == 1 && gemm_prefers_small(g)) return launch_gemm_small(g, st);
   if (mfma_ok && g_use_mfma == 1 && gemm_dma_eligible(g)) return launch_gemm_dma(g, st);
   if (mfma_ok && g_use_mfma == 1 && g.K % 32 != 0 && g.K > 256 && g.accumulate && g.c_fp32 && !g.bias && !g.res) {
     // accumulating GEMM with a ragged contraction: the multiple-of-32 part goes to the

@@ -713,6 +713,194 @@ __global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
   }
 }
 
+// ---- small outputs --------------------------------------------------------------------
+// The same GEMM on 64x64 tiles for outputs whose 128x128 tiles leave most compute units idle: what bounds those is the
+// length of one workgroup's life (launch, first tiles' way from memory, K loop, output stage), so four times as many
+// workgroups with a quarter of the work each finish sooner.  Four waves of one 32x32 output each, K tiles of 64, a ring
+// of four stages (64 KiB, two workgroups per unit): a contraction of up to 256 is in flight as a whole before the first
+// multiply.  The contraction is summed in the same order as by the larger kernels: same results, bit for bit.
+// Contractions that are no multiple of 64 are taken as they are: steps past K of the last tile come from a page of zeros,
+// and a 16-byte chunk that K cuts is masked in LDS.
+constexpr int ST = 64, SK = 64, SS = 4;               // tile side, K tile, stages
+constexpr int kSmallOp = ST * SK;                      // elements of one operand and stage
+__device__ __attribute__((aligned(256))) bf16_t g_zero_page[128];   // zero-initialised, never written
+
+// the 16-byte-per-lane copy with a full address per lane
+__device__ __forceinline__ void dma16_at(const void *addr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory");
+}
+// element address inside a [k][64 rows] tile: 8 chunks per k-row of 128 bytes, swizzled so that the four k-rows of a
+// transposed read fall on different banks
+__device__ __forceinline__ int addr_kr64(int k, int col) { return k * ST + ((((col >> 3) ^ ((k & 2) << 1)) & 7) << 3) + (col & 7); }
+
+template <bool TR>
+struct SmallDma {
+  uint32_t off[2];
+  int k_of[2];      // contraction step of the lane's chunk inside a tile (TR: its k-row; else its first element)
+  __device__ __forceinline__ void init(uint32_t ld, int row0, int nrows, int lane, int wave) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (!TR) {   // KiB 4 j + wave: rows 8 c .. 8 c + 7, lane owns slot lane%8 of row lane/8
+        const int row = (4 * j + wave) * 8 + lane / 8, chunk = (lane % 8) ^ ((row >> 1) & 7);
+        off[j] = (uint32_t(min(row0 + row, nrows - 1)) * ld + uint32_t(chunk * 8)) * 2u;
+        k_of[j] = chunk * 8;
+      } else {     // KiB 4 j + wave: k-rows 8 c .. 8 c + 7
+        const int k = (4 * j + wave) * 8 + lane / 8, chunk = (lane % 8) ^ ((k & 2) << 1);
+        const int col = min(row0 + chunk * 8, ((nrows + 7) & ~7) - 8);
+        off[j] = (uint32_t(k) * ld + uint32_t(col)) * 2u;
+        k_of[j] = k;
+      }
+    }
+  }
+  // `left`: contraction steps from this tile's first to the end of the operand
+  __device__ __forceinline__ void issue(const bf16_t *base, uint32_t lds, int wave, int left) const {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t at = lds + uint32_t(4 * j + wave) * 1024u;
+      if (left >= SK) {
+        dma16(base, off[j], at);
+      } else {
+        const char *p = reinterpret_cast<const char *>(base) + off[j];
+        dma16_at(k_of[j] < left ? p : reinterpret_cast<const char *>(g_zero_page), at);
+      }
+    }
+  }
+};
+template <bool TR>
+__device__ __forceinline__ bf16x8 small_frag(const bf16_t *s, int row32, int ks, int lane) {
+  if (!TR) return *reinterpret_cast<const bf16x8 *>(s + addr_rk<64>(row32 + lane % 32, 2 * ks + lane / 32));
+  const int q = lane % 16, g16 = (lane / 16) % 2, h = lane / 32;
+  const int k = 16 * ks + 8 * h + q / 4, col = row32 + 16 * g16 + 4 * (q % 4);
+  typedef __attribute__((address_space(3))) short4v *lds_ptr;
+  union { short4v s4[2]; bf16x8 b; } u;
+  u.s4[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(s + addr_kr64(k, col)));
+  u.s4[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(s + addr_kr64(k + 4, col)));
+  return u.b;
+}
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, int grid_n, int splits) {
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[SS * 2 * kSmallOp];
+  constexpr int L = 4;   // load-to-LDS instructions per thread per K tile
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int wm = wave / 2, wn = wave % 2;
+  int bid = blockIdx.x, split_idx = 0;
+  const int nb = gridDim.x / splits, grid_m = nb / grid_n;
+  if (splits > 1) {   // as in the 128x128 kernel
+    split_idx = bid % splits;
+    bid /= splits;
+  } else {
+    const int x = bid % 8, per = nb / 8, extra = nb % 8;
+    bid = x * per + min(x, extra) + bid / 8;
+  }
+  constexpr int kBand = 8;
+  const int band = bid / (kBand * grid_n), first_m = band * kBand;
+  const int band_rows = min(grid_m - first_m, kBand);
+  const int in_band = bid - band * kBand * grid_n;
+  const int m0 = (first_m + in_band % band_rows) * ST, n0 = (in_band / band_rows) * ST;
+
+  const int kt0 = split_idx * tiles_per_split;
+  const int n = min((p.K + SK - 1) / SK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
+  SmallDma<TA> da;
+  SmallDma<TB> db;
+  da.init(p.lda, m0, p.M, lane, wave);
+  db.init(p.ldb, n0, p.N, lane, wave);
+  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem));
+  const uint64_t a_kstep = TA ? uint64_t(SK) * p.lda : uint64_t(SK), b_kstep = TB ? uint64_t(SK) * p.ldb : uint64_t(SK);
+  auto issue = [&](int t) {   // tile t of this workgroup into stage t % SS
+    const uint32_t at = lds0 + uint32_t(t % SS) * uint32_t(4 * kSmallOp);
+    const int left = p.K - (kt0 + t) * SK;
+    da.issue(p.A + uint64_t(kt0 + t) * a_kstep, at, wave, left);
+    db.issue(p.B + uint64_t(kt0 + t) * b_kstep, at + uint32_t(2 * kSmallOp), wave, left);
+  };
+#pragma unroll
+  for (int t = 0; t < SS; ++t)
+    if (t < n) issue(t);
+
+  Epi e;
+  e.init(p, m0, n0, ST);
+  const bool split = splits > 1;
+  // lane's share of the output: pass q -> row 16 q + lane/4, columns 8 (lane%4) .. +7 of the wave's 32x32
+  const int m_tile = m0 + wm * 32, n_tile = n0 + wn * 32, n_lane = n_tile + 8 * (lane % 4);
+  Epi::Pre pre[2];
+  float4 bias8 = make_float4(0.f, 0.f, 0.f, 0.f);
+
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  for (int t = 0; t < n; ++t) {
+    // tile t has landed once at most the tiles issued after it are outstanding: t + 1 .. t + SS - 1 before the first
+    // refill, up to t + SS - 2 from then on
+    const int later = min(n, t == 0 ? SS : t + SS - 1) - t - 1;
+    if (later >= 3) wait_vm<3 * L>();
+    else if (later == 2) wait_vm<2 * L>();
+    else if (later == 1) wait_vm<L>();
+    else wait_vm<0>();
+    __syncthreads();   // tile t visible to every wave; every wave has read tile t - 1
+    if (t > 0 && t - 1 + SS < n) issue(t - 1 + SS);
+    bf16_t *a_s = smem + (t % SS) * (2 * kSmallOp), *b_s = a_s + kSmallOp;
+    const int left = p.K - (kt0 + t) * SK;
+    if (left < SK && left % 8 && (!TA || !TB)) {   // K cuts a chunk of the operands whose rows run along it
+      if (tid < ST) {
+        const int at = addr_rk<64>(tid, left / 8), keep = left % 8;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (k < keep) continue;
+          if (!TA) a_s[at + k] = from_f32<bf16_t>(0.f);
+          if (!TB) b_s[at + k] = from_f32<bf16_t>(0.f);
+        }
+      }
+      __syncthreads();
+    }
+    bf16x8 fa[4], fb[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      fa[ks] = small_frag<TA>(a_s, wm * 32, ks, lane);
+      fb[ks] = small_frag<TB>(b_s, wn * 32, ks, lane);
+    }
+    if (t + 1 == n && !split && e.fast) {   // what the output stage adds arrives during the last multiplies
+      if (p.bias && (e.inside || n_lane + 8 <= p.N)) bias8 = *reinterpret_cast<const float4 *>(p.bias + n_lane);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) e.prefetch(p, m_tile + 16 * q + lane / 4, n_lane, pre[q]);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
+  }
+  if (split) {
+    const int nn = n_tile + lane % 32;
+    if (nn >= p.N) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m_tile + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+      if (m < p.M) atomicAdd(static_cast<float *>(p.C) + int64_t(m) * p.ldc + nn, acc[r]);
+    }
+    return;
+  }
+  // through LDS, as in the 128x128 kernel: 4 KiB per wave, rows of 32 columns
+  __syncthreads();
+  float *slab = reinterpret_cast<float *>(smem) + wave * 1024;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+    slab[row * 32 + ((lane % 32) ^ ((row & 4) << 1))] = acc[r];
+  }
+  if (e.fast) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int row = 16 * q + lane / 4, c0 = 8 * (lane % 4);
+      e.emit8(p, m_tile + row, n_lane, slab + row * 32 + (c0 ^ ((row & 4) << 1)), pre[q], bias8);
+    }
+  } else {
+#pragma unroll 1
+    for (int idx = lane; idx < 32 * 32; idx += 64) {
+      const int row = idx / 32, col = idx % 32;
+      const int m = m_tile + row, nn = n_tile + col;
+      if (m < p.M && nn < p.N) e.emit_one(p, m, nn, slab[row * 32 + (col ^ ((row & 4) << 1))]);
+    }
+  }
+}
+
 inline int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HMY_E_HIP, "launch of %s failed: %s", what, hipGetErrorString(e));
@@ -741,6 +929,23 @@ int launch_cfg256(const hmy_gemm_desc &g, const DmaP &p, dim3 grid, int gn, hipS
   return check_launch("gemm_dma256");
 }
 
+int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
+  const int gm = (g.M + ST - 1) / ST, gn = (g.N + ST - 1) / ST, nk = (g.K + SK - 1) / SK;
+  // a long contraction over few tiles that may be split (fp32 atomics into C): while it fills idle compute units and
+  // leaves each workgroup at least eight K tiles
+  int splits = 1;
+  if (g.accumulate && g.c_fp32 && !g.bias && !g.res && gm * gn <= 128)
+    splits = std::max(1, std::min(256 / (gm * gn), nk / 8));
+  const int tps = (nk + splits - 1) / splits;
+  splits = (nk + tps - 1) / tps;
+  const dim3 grid(gm * gn * splits), block(NT);
+  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64<false, false>), grid, block, 0, s, p, tps, gn, splits);
+  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma64<false, true>), grid, block, 0, s, p, tps, gn, splits);
+  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64<true, false>), grid, block, 0, s, p, tps, gn, splits);
+  else hipLaunchKernelGGL((k_gemm_dma64<true, true>), grid, block, 0, s, p, tps, gn, splits);
+  return check_launch("gemm_dma64");
+}
+
 int env_int(const char *name, int dflt) {
   const char *v = std::getenv(name);
   return v ? std::atoi(v) : dflt;
@@ -756,7 +961,7 @@ bool gemm_dma_eligible(const hmy_gemm_desc &g) {
   return g.K % 32 == 0 && a_span < (int64_t(1) << 31) && b_span < (int64_t(1) << 31);
 }
 
-int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
+static DmaP dma_params(const hmy_gemm_desc &g) {
   DmaP p;
   p.A = static_cast<const bf16_t *>(g.A); p.B = static_cast<const bf16_t *>(g.B); p.C = g.C;
   p.bias = static_cast<const bf16_t *>(g.bias); p.res = static_cast<const bf16_t *>(g.res);
@@ -764,6 +969,24 @@ int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
   p.M = g.M; p.N = g.N; p.K = g.K;
   p.lda = uint32_t(g.lda); p.ldb = uint32_t(g.ldb); p.ldc = g.ldc; p.ldr = g.ldr;
   p.c_fp32 = g.c_fp32; p.accumulate = g.accumulate; p.res_fp32 = g.res_fp32;
+  return p;
+}
+
+// 64x64 tiles while all of them are resident at once, two per compute unit (measured, us, 128x128 -> 64x64 tiles:
+// 480x768x256 7.3 -> 5.3, 1024x1024x1024 12.6 -> 9.8, 2048x1024x1024 (512 tiles) 12.9 -> 11.8, 1280x1920x1024 (600 tiles)
+// 13.6 -> 19), and for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to
+// register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Sums into an
+// fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
+// contraction.
+bool gemm_prefers_small(const hmy_gemm_desc &g) {
+  if (g.accumulate && !(g.ta && g.tb)) return false;
+  const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
+  return tiles <= 512 || (g.K % 32 != 0 && tiles < 2048);
+}
+int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
+
+int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
+  const DmaP p = dma_params(g);
   static const int force_bk = env_int("HMY_GEMM_BK", 0), force_s = env_int("HMY_GEMM_STAGES", 0);
   static const int force_tile = env_int("HMY_GEMM_TILE", 0);   // 128 | 256: that block tile for every shape it can take
   const bool can_split = g.accumulate && g.c_fp32 && !g.bias && !g.res;

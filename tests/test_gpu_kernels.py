@@ -305,6 +305,32 @@ def test_gemm_bf16_tiles_that_stick_out_of_c():
     _gemm_case(*args, 4000, 3000, 64, 0, 1, 0, 0, True, True, False, True)
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 7), (72, 136, 63), (65, 57, 65), (200, 264, 250), (480, 256, 321),
+                                   (128, 128, 1100), (1288, 1928, 96)])
+def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
+    """64x64 tiles: one tile, its edges, contractions shorter and longer than the ring of four K tiles, whole, cut at a
+    multiple of 8 and inside a group of 8, split; the last shape is the smallest that is left to 128x128 tiles.  What lies
+    behind K in memory must not matter."""
+    say(f"gemm bf16 {M}x{N}x{K} ta={ta} tb={tb}")
+    if (ta and M % 8) or (tb and N % 8):
+        M, N = (M + 7) // 8 * 8, (N + 7) // 8 * 8
+    args = ("bf16", 1, torch.bfloat16, 2e-2)
+    pad = -K % 8
+    _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, True, False, True, pad)
+    _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, False, True, True, pad)
+    _gemm_case(*args, M, N, K, ta, tb, 1, 1, False, False, False, True, pad)
+    _gemm_case(*args, M, N, K, ta, tb, 1, 0, True, True, False, True, pad, res_fp32=1)
+    if pad and not ta and not tb:
+        g = torch.Generator(device="cuda").manual_seed(K)
+        a, b = (torch.randn(r, K + pad, device="cuda", generator=g).bfloat16() for r in (M, N))
+        c = [torch.zeros(M, N, device="cuda") for _ in range(2)]
+        B.hmy_k_gemm(1, M, N, K, a, K + pad, b, K + pad, c[0], N, c_fp32=1)
+        a[:, K:], b[:, K:] = float("nan"), float("inf")
+        B.hmy_k_gemm(1, M, N, K, a, K + pad, b, K + pad, c[1], N, c_fp32=1)
+        assert torch.equal(c[0], c[1])
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1)])
 def test_gemm_fp32(ta, tb):
     say(f"gemm fp32 ta={ta} tb={tb}")
