@@ -34,7 +34,6 @@ constexpr int kThreads = 256;       // 4 wavefronts, 32 rows of the block tile e
 // accumulators in ordinary vector registers.  Left free to use the accumulation registers it moved the
 // score and output tiles back and forth with v_accvgpr_read / write around every softmax and rescaling
 // (about 100 extra vector instructions per 32 x 32 subtile in kernels that are bound by exactly those).
-// The dK/dV kernel at head dimension 128 needs more than 256 registers and keeps the default.
 #define HMY_MFMA_IN_VGPRS __attribute__((amdgpu_waves_per_eu(2)))
 constexpr int kBlockRows = 128;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -162,12 +161,14 @@ __device__ __forceinline__ void bias_grad_sums(float *db, const f32x16 (&acc)[NT
 // XCD and pairs equal weights on a compute unit (16 units on some, 2 on others, where 9 would do).
 // Here the (row block, head, sequence) triples are ranked by weight, heaviest first, and dealt out in
 // rounds of one workgroup per compute unit, every other round backwards: a unit that got a heavy block
-// in one round gets a light one in the next, and each XCD sees every weight equally often.
+// in one round gets a light one in the next, and each XCD sees every weight equally often.  A kernel of which
+// only one workgroup fits a compute unit (`snake` false) keeps the ranking as it is: the unit that finishes
+// first, having had the lightest block of the round, takes the heaviest that is left.
 struct BlockCoord { int rb, head, seq; };
-__device__ __forceinline__ BlockCoord block_coord(int nrb, int H, int causal, bool heaviest_is_last_row_block) {
+__device__ __forceinline__ BlockCoord block_coord(int nrb, int H, int causal, bool heaviest_is_last_row_block, bool snake = true) {
   const int n = gridDim.x, l = blockIdx.x, bh_count = n / nrb;
   int r = l;
-  if (causal) {
+  if (causal && snake) {
     constexpr int kUnits = 256;
     const int round = l / kUnits, first = round * kUnits, len = min(kUnits, n - first);
     if (round & 1) r = first + (len - 1 - (l - first));
@@ -318,19 +319,18 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_fwd_mfma(co
 }
 
 // ---------------------------------------------------------------------------------
-// Forward for key tiles of two 32-key subtiles (head dimensions up to 64): eight waves per workgroup.  Wave w takes
+// Forward for head dimensions 64 and 128: eight waves per workgroup, key tiles of two 32-key subtiles.  Wave w takes
 // the queries q0 + 32 (w % 4) .. + 31 and, of every key tile, only subtile w / 4: two waves share each group of
 // queries and split its keys, each with a running reference, row sum and output accumulator of its own, which the
 // pair merges through LDS at the end.  The same work in twice as many, half as long chains: the kernel is bound by
 // each wave's serial chain (multiplies, maximum, exponentials, multiplies), and with four waves per SIMD instead of
 // two the vector unit of one wave works while the matrix unit of another does.
 template <int DH>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_attn_fwd_mfma_split(const bf16_t *qkv, bf16_t *o, float *lse, int s, int H,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ? 2 : 4))) void k_attn_fwd_mfma_split(const bf16_t *qkv, bf16_t *o, float *lse, int s, int H,
                                                                                                     int causal) {
   typedef Cfg<DH> C;
-  static_assert(C::TILE == 64, "two subtiles per key tile");
-  constexpr int NTHR = 512;
-  constexpr int kTileElems = C::TILE * C::PITCH;
+  constexpr int NTHR = 512, TILE = 64;
+  constexpr int kTileElems = TILE * C::PITCH;
   // K and V tiles, double buffered; afterwards the same bytes carry one wave's state to its partner
   __shared__ __attribute__((aligned(16))) bf16_t smem[4 * kTileElems];
   static_assert(4 * kTileElems * 2 >= 4 * 64 * (2 + 16 * C::DTILES) * 4, "the merge needs 2 + 16 DTILES floats per lane of four waves");
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int rg = wave % 4, sub = wave / 4;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
-  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true);
+  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true, DH != 128);
   const int head = bc.head, seq = bc.seq, q0 = bc.rb * kBlockRows;
   const bf16_t *base = qkv + int64_t(seq) * s * ld + head * DH;
   const int qw = q0 + 32 * rg, q = qw + lane % 32, q_ld = min(q, s - 1);
@@ -358,20 +358,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   float m_run = -INFINITY;
   const float sc = rsqrtf(float(DH)) * kLog2e;   // scores in log2 units
   const int k_end = causal ? min(s, q0 + kBlockRows) : s;
-  const int n_tiles = (k_end + C::TILE - 1) / C::TILE;
-  TileRegs<DH, C::TILE, NTHR> rk, rv;
-  rk.fetch(base + d, ld, min(C::TILE, s), tid);
-  rv.fetch(base + 2 * d, ld, min(C::TILE, s), tid);
+  const int n_tiles = (k_end + TILE - 1) / TILE;
+  TileRegs<DH, TILE, NTHR> rk, rv;
+  rk.fetch(base + d, ld, min(TILE, s), tid);
+  rv.fetch(base + 2 * d, ld, min(TILE, s), tid);
   rk.put(sK(0), tid);
   rv.put(sV(0), tid);
   __syncthreads();
   for (int kt = 0; kt < n_tiles; ++kt) {
-    const int cur = kt & 1, k0 = kt * C::TILE;
+    const int cur = kt & 1, k0 = kt * TILE;
     const bool more = kt + 1 < n_tiles;
     if (more) {   // next tile's loads fly during this tile's multiplies
-      const int kn = k0 + C::TILE;
-      rk.fetch(base + d + int64_t(kn) * ld, ld, min(C::TILE, s - kn), tid);
-      rv.fetch(base + 2 * d + int64_t(kn) * ld, ld, min(C::TILE, s - kn), tid);
+      const int kn = k0 + TILE;
+      rk.fetch(base + d + int64_t(kn) * ld, ld, min(TILE, s - kn), tid);
+      rv.fetch(base + 2 * d + int64_t(kn) * ld, ld, min(TILE, s - kn), tid);
     }
     const int kb = k0 + 32 * sub;   // first key of this wave's subtile
     if (kb < s && (!causal || kb <= qw + 31)) {   // some query of this wave sees some key of it
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
 // ---------------------------------------------------------------------------------
 // dK, dV.  grid (ceil(s/128), H, b).  Wave w owns keys j0+32w..; Q and dO tiles stream.
 template <int DH>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 128 ? 1 : 2))) void k_attn_bwd_dkv_mfma(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
+__global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_mfma(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
                                                                 const float *delta, bf16_t *dqkv, float *dbias, int s,
                                                                 int H, int causal) {
   typedef Cfg<DH> C;
@@ -695,18 +695,322 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
   }
 }
 
+// ---------------------------------------------------------------------------------
+// The backward kernels for head dimensions 64 and 128 on eight waves per workgroup, as in k_attn_fwd_mfma_split: waves
+// w and w + 4 share 32 rows of the output and take one 32-row subtile of every streamed tile each, with an accumulator
+// of their own; at the end each hands the other half of its sums through LDS.  What bounds these kernels is a wave's
+// serial chain (two products, exponentials, conversion, two products), and under a causal mask the heaviest row block's
+// chain is the whole launch: four waves walked 3500 cycles per 32x32 subtile.  Halving the chain also halves the share
+// of a streamed tile that a thread carries in registers, so the next tile is fetched during the multiplies here too.
+// What fits no registers twice (two accumulator sets of dK/dV need more than 128) leaves one such workgroup per compute
+// unit, whose waves pass every barrier together; two four-wave workgroups do not, and where both always have work they
+// are the faster (the rules at the launchers).  Measured, us, four waves -> eight: dK/dV at head dimension 64, causal,
+// 16 heads, s = 4096 184 -> 138, s = 1024 47 -> 33; at head dimension 128, 8 heads, two sequences of 4096, causal
+// 439 -> 227, not causal 676 -> 428; dQ there 150 -> 126.
+template <int DH> struct SplitBwd {
+  static constexpr int TILE = 64, NTHR = 512;
+  static constexpr int TILE_ELEMS = TILE * Cfg<DH>::PITCH;
+  static constexpr int XCH = 4 * 64 * 16 * Cfg<DH>::DTILES * 4;       // bytes: one accumulator set of four waves
+  static constexpr int BIAS = 2 * kBlockRows * kBiasPitch * 4;        // both halves of the workgroup sum columns at once
+  static constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
+  static constexpr int DQ_LDS = max3(4 * TILE_ELEMS * 2, XCH, BIAS);
+  // four tile buffers, the rows' statistics; at head dimension 128 also the workgroup's V rows, which do not fit the
+  // registers beside two accumulator sets of 64
+  static constexpr int STATS = 4 * TILE * 4;
+  static constexpr int DKV_LDS = max3(4 * TILE_ELEMS * 2 + STATS + (DH == 128 ? kBlockRows * Cfg<DH>::PITCH * 2 : 0), 2 * XCH, BIAS);
+};
+
+template <int DH>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ? 2 : 4))) void k_attn_bwd_dq_split(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o,
+                                                               const float *lse, float *delta, bf16_t *dqkv, float *dbias,
+                                                               int s, int H, int causal) {
+  typedef Cfg<DH> C;
+  typedef SplitBwd<DH> S;
+  constexpr int TILE = S::TILE;
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  auto sK = [&](int buf) { return smem + buf * S::TILE_ELEMS; };
+  auto sV = [&](int buf) { return smem + (2 + buf) * S::TILE_ELEMS; };
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int rg = wave % 4, sub = wave / 4;
+  const int d = H * DH;
+  const int64_t ld = 3 * int64_t(d);
+  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true, DH != 128);
+  const int head = bc.head, seq = bc.seq, q0 = bc.rb * kBlockRows;
+  const bf16_t *base = qkv + int64_t(seq) * s * ld + head * DH;
+  const bf16_t *gbase = d_o + int64_t(seq) * s * d + head * DH;
+  const bf16_t *obase = o + int64_t(seq) * s * d + head * DH;
+  const int qw = q0 + 32 * rg, q = qw + lane % 32, q_ld = min(q, s - 1);
+  bf16x8 fq[C::KSTEPS], fg[C::KSTEPS];
+  float dl = 0.f;
+#pragma unroll
+  for (int c = 0; c < C::KSTEPS; ++c) {
+    fq[c] = frag_global(base, ld, q_ld, 16 * c + 8 * h2);
+    fg[c] = frag_global(gbase, d, q_ld, 16 * c + 8 * h2);
+    const bf16x8 fo = frag_global(obase, d, q_ld, 16 * c + 8 * h2);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) dl = fmaf(static_cast<float>(fg[c][k]), static_cast<float>(fo[k]), dl);
+  }
+  dl += __shfl_xor(dl, 32, 64);   // the other half of the row
+  if (sub == 0 && h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
+  const float L = lse[(int64_t(seq) * H + head) * s + q_ld] * kLog2e;   // log2 units
+  const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
+  f32x16 acc_q[C::DTILES];
+#pragma unroll
+  for (int t = 0; t < C::DTILES; ++t) acc_q[t] = zero16();
+  const int k_end = causal ? min(s, q0 + kBlockRows) : s;
+  const int n_tiles = (k_end + TILE - 1) / TILE;
+  TileRegs<DH, TILE, S::NTHR> rk, rv;
+  rk.fetch(base + d, ld, min(TILE, s), tid);
+  rv.fetch(base + 2 * d, ld, min(TILE, s), tid);
+  rk.put(sK(0), tid);
+  rv.put(sV(0), tid);
+  __syncthreads();
+  for (int kt = 0; kt < n_tiles; ++kt) {
+    const int cur = kt & 1, k0 = kt * TILE;
+    const bool more = kt + 1 < n_tiles;
+    if (more) {   // next tile's loads fly during this tile's multiplies
+      const int kn = k0 + TILE;
+      rk.fetch(base + d + int64_t(kn) * ld, ld, min(TILE, s - kn), tid);
+      rv.fetch(base + 2 * d + int64_t(kn) * ld, ld, min(TILE, s - kn), tid);
+    }
+    const int kb = k0 + 32 * sub;   // first key of this wave's subtile
+    if (kb < s && (!causal || kb <= qw + 31)) {   // some query of this wave sees some key of it
+      f32x16 st = zero16(), dp = zero16();
+#pragma unroll
+      for (int c = 0; c < C::KSTEPS; ++c) {
+        st = mfma(frag_row<DH>(sK(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);   // S^T = K Q^T
+        dp = mfma(frag_row<DH>(sV(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T = V dO^T
+      }
+      if (kb + 32 > s || (causal && kb + 31 > qw)) {   // diagonal or ragged subtile: per-element test
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = kb + acc_row(r, h2);
+          const bool ok = key < s && (!causal || key <= q);
+          const float p = ok ? fast_exp2(fmaf(st[r], sc, -L)) : 0.f;
+          st[r] = p * (dp[r] - dl);                                                           // dS^T
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * (dp[r] - dl);
+      }
+      // dQ^T[dh, query] += K^T dS^T
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const bf16x8 fs = acc_to_frag(st, c);
+#pragma unroll
+        for (int t = 0; t < C::DTILES; ++t)
+          acc_q[t] = mfma(frag_col<DH>(sK(cur), 32 * sub + 16 * c, 32 * t, lane), fs, acc_q[t]);
+      }
+    }
+    if (more) {
+      rk.put(sK(cur ^ 1), tid);
+      rv.put(sV(cur ^ 1), tid);
+    }
+    __syncthreads();
+  }
+  // the first wave of a pair finishes the lower half of the head's columns, the second the upper half
+  constexpr int HALF = C::DTILES / 2;
+  float *xch = reinterpret_cast<float *>(smem) + rg * (16 * C::DTILES * 64);   // [value][lane]: conflict-free both ways
+#pragma unroll
+  for (int t = 0; t < HALF; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) xch[((1 - sub) * HALF * 16 + 16 * t + r) * 64 + lane] = sub ? acc_q[t][r] : acc_q[HALF + t][r];
+  __syncthreads();
+  f32x16 res[HALF];
+#pragma unroll
+  for (int t = 0; t < HALF; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      res[t][r] = (sub ? acc_q[HALF + t][r] : acc_q[t][r]) + xch[(sub * HALF * 16 + 16 * t + r) * 64 + lane];
+  const int col0 = head * DH + 32 * HALF * sub;
+  if (q < s) {
+    bf16_t *row = dqkv + (int64_t(seq) * s + q) * ld + col0;
+#pragma unroll
+    for (int t = 0; t < HALF; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        bf16x4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = static_cast<__bf16>(res[t][4 * j + k] * scale);
+        *reinterpret_cast<bf16x4 *>(row + 32 * t + 8 * j + 4 * h2) = v;
+      }
+  }
+  if (dbias) {
+    __syncthreads();   // the exchanged sums have been read
+    bias_grad_sums<HALF>(dbias + col0, res, scale, q < s, reinterpret_cast<float *>(smem) + sub * (kBlockRows * kBiasPitch),
+                         tid % kThreads);
+  }
+}
+
+template <int DH>
+__global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
+                                                                const float *delta, bf16_t *dqkv, float *dbias, int s,
+                                                                int H, int causal) {
+  typedef Cfg<DH> C;
+  typedef SplitBwd<DH> S;
+  constexpr int TILE = S::TILE;
+  constexpr bool kVInLds = DH == 128;
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  auto sQ = [&](int buf) { return smem + buf * S::TILE_ELEMS; };
+  auto sG = [&](int buf) { return smem + (2 + buf) * S::TILE_ELEMS; };
+  float *sL = reinterpret_cast<float *>(smem + 4 * S::TILE_ELEMS), *sD = sL + 2 * TILE;
+  bf16_t *sV = reinterpret_cast<bf16_t *>(sD + 2 * TILE);
+  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int rg = wave % 4, sub = wave / 4;
+  const int d = H * DH;
+  const int64_t ld = 3 * int64_t(d);
+  // the first key blocks are seen by the most queries
+  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, false, false);
+  const int head = bc.head, seq = bc.seq, j0 = bc.rb * kBlockRows;
+  const bf16_t *base = qkv + int64_t(seq) * s * ld + head * DH;
+  const bf16_t *gbase = d_o + int64_t(seq) * s * d + head * DH;
+  const float *lbase = lse + (int64_t(seq) * H + head) * s, *dbase = delta + (int64_t(seq) * H + head) * s;
+  const int jw = j0 + 32 * rg, key = jw + lane % 32, key_ld = min(key, s - 1);
+  bf16x8 fk[C::KSTEPS], fv[kVInLds ? 1 : C::KSTEPS];
+#pragma unroll
+  for (int c = 0; c < C::KSTEPS; ++c) {
+    fk[c] = frag_global(base + d, ld, key_ld, 16 * c + 8 * h2);
+    if constexpr (!kVInLds) fv[c] = frag_global(base + 2 * d, ld, key_ld, 16 * c + 8 * h2);
+  }
+  if constexpr (kVInLds) {
+    TileRegs<DH, kBlockRows, S::NTHR> rv;
+    rv.fetch(base + 2 * d + int64_t(j0) * ld, ld, min(kBlockRows, s - j0), tid);
+    rv.put(sV, tid);
+  }
+  const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
+  f32x16 acc_k[C::DTILES], acc_v[C::DTILES];
+#pragma unroll
+  for (int t = 0; t < C::DTILES; ++t) { acc_k[t] = zero16(); acc_v[t] = zero16(); }
+  // causal: queries before the block's first key see none of its keys
+  const int t_begin = causal ? j0 / TILE : 0;
+  const int n_tiles = (s + TILE - 1) / TILE;
+  TileRegs<DH, TILE, S::NTHR> rq, rgr;
+  float rl = 0.f, rd = 0.f;
+  auto fetch = [&](int i0) {
+    const int nv = min(TILE, s - i0);
+    rq.fetch(base + int64_t(i0) * ld, ld, nv, tid);
+    rgr.fetch(gbase + int64_t(i0) * d, d, nv, tid);
+    if (tid < TILE) {
+      rl = tid < nv ? lbase[i0 + tid] * kLog2e : 0.f;
+      rd = tid < nv ? dbase[i0 + tid] : 0.f;
+    }
+  };
+  auto put = [&](int buf) {
+    rq.put(sQ(buf), tid);
+    rgr.put(sG(buf), tid);
+    if (tid < TILE) {
+      sL[buf * TILE + tid] = rl;
+      sD[buf * TILE + tid] = rd;
+    }
+  };
+  fetch(t_begin * TILE);
+  put(0);
+  __syncthreads();
+  for (int it = t_begin; it < n_tiles; ++it) {
+    const int cur = (it - t_begin) & 1, i0 = it * TILE;
+    const bool more = it + 1 < n_tiles;
+    if (more) fetch(i0 + TILE);   // next tile's loads fly during this tile's multiplies
+    const int ib = i0 + 32 * sub;   // first query of this wave's subtile
+    if (ib < s && (!causal || ib + 31 >= jw)) {   // some query of it sees some key of this wave
+      // S[query, key] = Q K^T and dP[query, key] = dO V^T: lane owns a key, registers run over queries
+      f32x16 sm = zero16(), dp = zero16();
+#pragma unroll
+      for (int c = 0; c < C::KSTEPS; ++c) {
+        sm = mfma(frag_row<DH>(sQ(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fk[c], sm);
+        const bf16x8 v = kVInLds ? frag_row<DH>(sV, 32 * rg + lane % 32, 16 * c + 8 * h2) : fv[kVInLds ? 0 : c];
+        dp = mfma(frag_row<DH>(sG(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), v, dp);
+      }
+      // queries past the sequence end or (causal) before the key: only the diagonal and
+      // the last subtile need the per-element test
+      const bool edge = ib + 32 > s || (causal && ib < jw + 31);
+      // the lane's sixteen queries are four runs of four consecutive rows: 16-byte reads
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float ql[4], qd[4];
+        *reinterpret_cast<float4 *>(ql) = *reinterpret_cast<const float4 *>(sL + cur * TILE + 32 * sub + 8 * g + 4 * h2);
+        *reinterpret_cast<float4 *>(qd) = *reinterpret_cast<const float4 *>(sD + cur * TILE + 32 * sub + 8 * g + 4 * h2);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int r = 4 * g + k, qi = ib + acc_row(r, h2);
+          const bool ok = !edge || (qi < s && (!causal || key <= qi));
+          const float p = ok ? fast_exp2(fmaf(sm[r], sc, -ql[k])) : 0.f;
+          sm[r] = p;                                        // P
+          dp[r] = p * (dp[r] - qd[k]);                      // dS
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
+#pragma unroll
+        for (int t = 0; t < C::DTILES; ++t) {
+          acc_v[t] = mfma(frag_col<DH>(sG(cur), 32 * sub + 16 * c, 32 * t, lane), fp, acc_v[t]);   // dV^T += dO^T P
+          acc_k[t] = mfma(frag_col<DH>(sQ(cur), 32 * sub + 16 * c, 32 * t, lane), fs, acc_k[t]);   // dK^T += Q^T dS
+        }
+      }
+    }
+    if (more) put(cur ^ 1);
+    __syncthreads();
+  }
+  // the first wave of a pair finishes dK, the second dV
+  float *xch = reinterpret_cast<float *>(smem) + rg * (2 * 16 * C::DTILES * 64);
+#pragma unroll
+  for (int t = 0; t < C::DTILES; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) xch[((1 - sub) * C::DTILES * 16 + 16 * t + r) * 64 + lane] = sub ? acc_k[t][r] : acc_v[t][r];
+  __syncthreads();
+  f32x16 res[C::DTILES];
+#pragma unroll
+  for (int t = 0; t < C::DTILES; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      res[t][r] = (sub ? acc_v[t][r] : acc_k[t][r]) + xch[(sub * C::DTILES * 16 + 16 * t + r) * 64 + lane];
+  const float out_scale = sub ? 1.f : scale;
+  const int col0 = (1 + sub) * d + head * DH;
+  if (key < s) {
+    bf16_t *row = dqkv + (int64_t(seq) * s + key) * ld + col0;
+#pragma unroll
+    for (int t = 0; t < C::DTILES; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        bf16x4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = static_cast<__bf16>(res[t][4 * j + k] * out_scale);
+        *reinterpret_cast<bf16x4 *>(row + 32 * t + 8 * j + 4 * h2) = v;
+      }
+  }
+  if (dbias) {
+    __syncthreads();   // the exchanged sums have been read
+    bias_grad_sums<C::DTILES>(dbias + col0, res, out_scale, key < s,
+                              reinterpret_cast<float *>(smem) + sub * (kBlockRows * kBiasPitch), tid % kThreads);
+  }
+}
+
 inline int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HMY_E_HIP, "launch of %s failed: %s", what, hipGetErrorString(e));
   return HMY_OK;
 }
 
+// Head dimension 64, dK/dV.  Up to one workgroup per unit, or two with a causal mask over at least eight row blocks.
+// Measured, us, four waves -> eight: 128 workgroups of s = 256 18.7 -> 15.8; causal, 512 workgroups of s = 1024
+// 52 -> 48, of s = 2048 93 -> 76, of s = 128 20 -> 27; causal, 1024 workgroups of s = 1024 76 -> 93, of s = 512 55 -> 68;
+// not causal, 512 of s = 512 35 -> 45.
+inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
+  return workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512);
+}
+// Head dimension 128: the eight-wave forward and dQ kernels, one workgroup per compute unit, against two of the
+// four-wave ones.  Where there is no second workgroup for a unit, or where a causal mask makes the heaviest row block
+// the whole launch (16 row blocks and more), half the chain wins.  Measured, us, forward and dQ, four waves -> eight:
+// 128 workgroups of s = 512 21 -> 18 and 28 -> 25; 512 of s = 512 31 -> 37 and 46 -> 56; 512 of s = 1024, causal
+// 39 -> 38 and 51 -> 55; 512 of s = 4096, causal 131 -> 104 and 150 -> 126.
+inline bool split_pays_128(int workgroups, int s, int causal) { return workgroups <= 256 || (causal && s >= 2048); }
+
 template <int DH>
 int fwd_t(const void *qkv, void *o, float *lse, int b, int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
   static const bool split = std::getenv("HMY_ATTN_SPLIT") == nullptr || std::atoi(std::getenv("HMY_ATTN_SPLIT")) != 0;
-  if constexpr (DH == 64) {   // two 32-key subtiles per key tile, and enough 16-byte pieces in a tile for 512 threads
-    if (split) {
+  if constexpr (DH >= 64) {   // enough 16-byte pieces in a 64-row tile for 512 threads
+    if (split && (DH == 64 || split_pays_128(int(grid.x), s, causal))) {
       hipLaunchKernelGGL((k_attn_fwd_mfma_split<DH>), grid, dim3(512), 0, st, (const bf16_t *)qkv, (bf16_t *)o, lse, s, H,
                          causal);
       return check_launch("attn_fwd_mfma_split");
@@ -720,10 +1024,25 @@ template <int DH>
 int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, float *delta, void *dqkv, float *dbias, int b,
           int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
-  hipLaunchKernelGGL((k_attn_bwd_dq_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)o,
-                     (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);   // writes delta for the next kernel
-  hipLaunchKernelGGL((k_attn_bwd_dkv_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)d_o,
-                     lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
+  bool dq_split = false, dkv_split = false;
+  if constexpr (DH >= 64) {   // enough 16-byte pieces in a 64-row tile for 512 threads
+    dq_split = DH == 128 && split_pays_128(int(grid.x), s, causal);
+    dkv_split = DH == 128 || dkv_split_pays_64(int(grid.x), s, causal);
+    if (dq_split)
+      hipLaunchKernelGGL((k_attn_bwd_dq_split<DH>), grid, dim3(512), SplitBwd<DH>::DQ_LDS, st, (const bf16_t *)qkv,
+                         (const bf16_t *)o, (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
+  }
+  if (!dq_split)   // either writes delta for the next kernel
+    hipLaunchKernelGGL((k_attn_bwd_dq_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)o,
+                       (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
+  if constexpr (DH >= 64)
+    if (dkv_split)
+      hipLaunchKernelGGL((k_attn_bwd_dkv_split<DH>), grid, dim3(512), SplitBwd<DH>::DKV_LDS, st, (const bf16_t *)qkv,
+                         (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
+  if constexpr (DH != 128)   // at head dimension 128 the eight-wave kernel is the faster one at every size measured
+    if (!dkv_split)
+      hipLaunchKernelGGL((k_attn_bwd_dkv_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)d_o,
+                         lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
   return check_launch("attn_bwd_mfma");
 }
 

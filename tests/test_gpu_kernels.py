@@ -173,6 +173,24 @@ def test_embedding_fwd_bwd_with_repeated_ids(prec, pc, dt, tol):
     assert max_rel_err(host(dwpe), g["wpe"]) < 1e-5
 
 
+# runs of one id: none, exactly as many as one wave sums, one more, all tokens alike; then more tokens than the search
+# through the ids is used for (32 per column)
+@pytest.mark.parametrize("counts,d", [([1], 8), ([16, 1, 3], 264), ([17, 16], 64), ([33, 1] * 3, 1024), ([700], 128), ([130, 125, 2], 8)])
+def test_embedding_bwd_runs(counts, d):
+    say(f"embed runs {counts} d={d}")
+    rng = np.random.default_rng(sum(counts) + d)
+    ids = rng.permutation(np.repeat(np.arange(len(counts)) * 3, counts)).astype(np.int32)
+    T, V = len(ids), 3 * len(counts)
+    dx = rng.standard_normal((T, d)).astype(np.float32)
+    w0 = rng.standard_normal((V, d)).astype(np.float32)
+    dwte, dwpe = dev(w0, torch.float32), torch.zeros(T, d, device="cuda")
+    B.hmy_k_embed_bwd(PRECS[1][1], torch.from_numpy(ids).cuda(), dev(dx, torch.float32), dwte, dwpe, T, d, T, V)
+    ref = w0.astype(np.float64)
+    np.add.at(ref, ids, dx.astype(np.float64))
+    assert max_rel_err(host(dwte), ref) < 1e-5      # up to 700 terms in fp32
+    assert max_rel_err(host(dwpe), dx) == 0
+
+
 def _gemm_case(prec, pc, dt, tol, M, N, K, ta, tb, c_fp32, accumulate, bias, res, gelu, use_mfma, pad=0, res_fp32=0,
                row_pad=0, ldc=None):
     rng = np.random.default_rng(M * 7 + N * 3 + K + ta * 2 + tb)
@@ -429,8 +447,18 @@ def _attention_case(prec, pc, dt, tol, causal, b, s, H, dh):
     assert np.abs(host(dbd) - db0 - sums).max() < 1e-4 * max(np.abs(sums).max(), np.abs(db0).max(), 1.0)
 
 
+# the eight-wave kernels and the four-wave ones on both sides of their rules: few and many workgroups, long causal rows
+@pytest.mark.parametrize("causal,b,s,H,dh", [(1, 1, 1030, 2, 64), (0, 1, 1030, 2, 64), (0, 33, 130, 4, 64), (1, 33, 130, 4, 64),
+                                             (0, 17, 130, 8, 128), (1, 17, 130, 8, 128), (1, 1, 2050, 1, 128), (0, 1, 33, 1, 128),
+                                             (1, 17, 2050, 1, 128)])
+def test_attention_eight_and_four_waves(causal, b, s, H, dh):
+    prec, pc, dt, tol = PRECS[1]
+    say(f"attention split causal={causal} b={b} s={s} H={H} dh={dh}")
+    _attention_case(prec, pc, dt, tol, causal, b, s, H, dh)
+
+
 @pytest.mark.parametrize("prec,pc,dt,tol", PRECS)
-@pytest.mark.parametrize("T,V", [(9, 1000), (33, 50257), (4, 2)])
+@pytest.mark.parametrize("T,V", [(9, 1000), (33, 50257), (4, 2)] + [(2, v + k) for v in (4096, 14336, 32768, 57344) for k in (0, 1)])
 def test_cross_entropy(prec, pc, dt, tol, T, V):
     say(f"xent {prec} T={T} V={V}")
     rng = np.random.default_rng(V)
