@@ -795,6 +795,89 @@ __global__ void k_xent(const float *logits, const int32_t *targets, double *loss
   }
 }
 
+// The same for rows that fit the registers of a workgroup, NG groups of eight columns per thread: one pass over the
+// logits instead of two, one exponential per column instead of two.  The kernel above moves 4 + 4 + E bytes per column
+// and its second reading waits for a reduction over the whole row; this one 4 + E bytes, all of a thread's loads in
+// flight at once.
+// 512 rows of 50257 columns in bf16: 51.7 -> 35.1 us (4.4 TB/s; every workgroup of a launch reads, then writes).
+template <typename E, int NT, int NG>
+__global__ __launch_bounds__(NT) void k_xent_reg(const float *logits, const int32_t *targets, double *loss_acc, E *dlogits, int V,
+                                                 int64_t ldl, float inv_ntgt) {
+  constexpr int kWaves = NT / kWave;
+  __shared__ float scratch[2][kWaves];
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const float *lr = logits + uint64_t(row) * ldl;
+  E *dr = dlogits + uint64_t(row) * ldl;
+  const int tgt = targets[row], groups = int(ldl / 8);
+  auto put = [&](int j, const float (&g)[8]) {
+    constexpr int VEC = ElemTraits<E>::VEC;
+#pragma unroll
+    for (int h = 0; h < 8; h += VEC) {
+      Vec16<E> o;
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) o.v[k] = from_f32<E>(g[h + k]);
+      store16(dr + 8 * j + h, o);
+    }
+  };
+  if (tgt < 0) {
+    const float zero[8] = {};
+    for (int j = tid; j < groups; j += NT) put(j, zero);
+    return;
+  }
+  const float target_logit = lr[tgt];   // now: dlogits may be the logits' own memory
+  float v[NG][8];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const int j = tid + i * NT;
+    if (j < groups) {
+      *reinterpret_cast<float4 *>(v[i]) = *reinterpret_cast<const float4 *>(lr + 8 * j);
+      *reinterpret_cast<float4 *>(v[i] + 4) = *reinterpret_cast<const float4 *>(lr + 8 * j + 4);
+    }
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (8 * (tid + i * NT) + k >= V) v[i][k] = -INFINITY;   // past the row: no weight
+      mx = fmaxf(mx, v[i][k]);
+    }
+  mx = wave_max(mx);
+  if (lane == 0) scratch[0][wave] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, scratch[0][w]);
+  float se = 0.f;
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      v[i][k] = __expf(v[i][k] - mx);
+      se += v[i][k];
+    }
+  se = wave_sum(se);
+  if (lane == 0) scratch[1][wave] = se;
+  __syncthreads();
+  se = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) se += scratch[1][w];
+  if (tid == 0) atomicAdd(loss_acc, double(mx + logf(se) - target_logit) * double(inv_ntgt));
+  const float inv = 1.f / se;
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const int j = tid + i * NT;
+    if (j < groups) {
+      float g[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int col = 8 * j + k;
+        g[k] = col < V ? (v[i][k] * inv - (col == tgt ? 1.f : 0.f)) * inv_ntgt : 0.f;
+      }
+      put(j, g);
+    }
+  }
+}
+
 // ---- fused Adam ---------------------------------------------------------------
 // One parameter's update.  The fused operations are written out, so that every kernel that updates rounds alike.
 __device__ __forceinline__ void adam_step(float g, float &w, float &m, float &v, float lr, float b1, float b2, float eps,
@@ -1188,6 +1271,20 @@ int launch_colsum(int prec, const void *a, float *out, int T, int N, stream_t st
 int launch_xent(int prec, const float *logits, const int32_t *targets, double *loss_acc, void *dlogits, int T, int V,
                 int64_t ldl, float inv_ntgt, stream_t st) {
   if (T < 1 || V < 2 || ldl < V) return fail(HMY_E_INVALID, "xent: bad shape");
+  // rows in registers as far as they fit: up to seven groups of eight columns per thread, on 256 threads while that
+  // covers the row (several workgroups per compute unit), on 1024 up to 57344 columns
+  const int64_t groups = ldl / 8;
+  if (ldl % 8 == 0 && groups <= 7 * 1024 && ((reinterpret_cast<uintptr_t>(logits) | reinterpret_cast<uintptr_t>(dlogits)) & 15) == 0) {
+    DISPATCH_PREC(prec, {
+      const dim3 g(T);
+      const hipStream_t s = (hipStream_t)st;
+      if (groups <= 2 * 256) hipLaunchKernelGGL((k_xent_reg<E, 256, 2>), g, dim3(256), 0, s, logits, targets, loss_acc, (E *)dlogits, V, ldl, inv_ntgt);
+      else if (groups <= 7 * 256) hipLaunchKernelGGL((k_xent_reg<E, 256, 7>), g, dim3(256), 0, s, logits, targets, loss_acc, (E *)dlogits, V, ldl, inv_ntgt);
+      else if (groups <= 4 * 1024) hipLaunchKernelGGL((k_xent_reg<E, 1024, 4>), g, dim3(1024), 0, s, logits, targets, loss_acc, (E *)dlogits, V, ldl, inv_ntgt);
+      else hipLaunchKernelGGL((k_xent_reg<E, 1024, 7>), g, dim3(1024), 0, s, logits, targets, loss_acc, (E *)dlogits, V, ldl, inv_ntgt);
+    });
+    return check_launch("xent_reg");
+  }
   DISPATCH_PREC(prec, {
     hipLaunchKernelGGL(k_xent<E>, dim3(T), dim3(kBlock), 0, (hipStream_t)st, logits, targets, loss_acc, (E *)dlogits, V,
                        ldl, inv_ntgt);
