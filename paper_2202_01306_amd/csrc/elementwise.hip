@@ -131,6 +131,66 @@ __global__ void k_embed_bwd_wte(const int32_t *ids, const float *dx, float *dwte
     for (int k = 0; k < VEC; ++k) atomicAdd(dst + k, g[k]);
   }
 }
+// The same without an atomic per element: a wave per token looks through all ids for those equal to its own.  The
+// first occurrence, and every kRun-th after it, sums the rows of its run and adds them to dwte in one go -- with plain
+// loads and stores where the run is all there is of that id, with atomics where there are several (padding, a frequent
+// word), so that no wave sums more than kRun rows.
+// 4096 tokens x 1024 columns, 30522 ids: 57.5 -> 23.3 us (the atomics; 2.2 TB/s of rows in, sums in and out).
+__global__ __launch_bounds__(256) void k_embed_bwd_wte_runs(const int32_t *ids, const float *dx, float *dwte, int T, int d) {
+  constexpr int kRun = 16, kAhead = 8;
+  __shared__ int runs[4][kRun];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int t = blockIdx.x * 4 + wave;
+  if (t >= T) return;   // no barrier below: every wave has its own part of `runs`
+  const int id = ids[t];
+  int before = 0;
+  for (int base = 0; base < t; base += kWave * kAhead) {
+    int v[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) v[i] = ids[min(base + kWave * i + lane, T - 1)];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) before += __popcll(__ballot(base + kWave * i + lane < t && v[i] == id));
+  }
+  if (before % kRun) return;
+  int *run = runs[wave];
+  int n = 1;        // occurrences found from t on
+  if (lane == 0) run[0] = t;
+  for (int base = t + 1; base < T && n <= kRun; base += kWave * kAhead) {
+    int v[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) v[i] = ids[min(base + kWave * i + lane, T - 1)];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int pos = base + kWave * i + lane;
+      const bool hit = pos < T && v[i] == id;
+      const unsigned long long hits = __ballot(hit);
+      const int at = n + __popcll(hits & ((1ull << lane) - 1));
+      if (hit && at < kRun) run[at] = pos;
+      n += __popcll(hits);
+    }
+  }
+  const bool alone = before == 0 && n <= kRun;
+  n = min(n, kRun);
+  __threadfence_block();   // the wave's positions, written by several of its lanes, before it reads them
+  float *dst = dwte + uint64_t(id) * d;
+  for (int c = 4 * lane; c < d; c += 4 * kWave) {
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < n; ++i) {
+      const float4 g = *reinterpret_cast<const float4 *>(dx + uint64_t(run[i]) * d + c);
+      sum.x += g.x; sum.y += g.y; sum.z += g.z; sum.w += g.w;
+    }
+    if (alone) {
+      float4 a = *reinterpret_cast<const float4 *>(dst + c);
+      a.x += sum.x; a.y += sum.y; a.z += sum.z; a.w += sum.w;
+      *reinterpret_cast<float4 *>(dst + c) = a;
+    } else {
+      atomicAdd(dst + c, sum.x);
+      atomicAdd(dst + c + 1, sum.y);
+      atomicAdd(dst + c + 2, sum.z);
+      atomicAdd(dst + c + 3, sum.w);
+    }
+  }
+}
 // dwpe[j] += sum over sequences of dx[i*s + j]  (one owner per element: no atomics)
 __global__ void k_embed_bwd_wpe(const float *dx, float *dwpe, int T, int d, int s) {
   constexpr int VEC = 4;
@@ -1079,7 +1139,10 @@ int launch_embed_bwd(int prec, const int32_t *ids, const float *dx, float *dwte,
   if (prec != HMY_PREC_FP32 && prec != HMY_PREC_BF16) return fail(HMY_E_INVALID, "unknown precision %d", prec);
   if (T < 1 || d % 8 || s < 1 || T % s) return fail(HMY_E_INVALID, "embed_bwd: bad shape");
   const uint64_t work = uint64_t(T) * (d / 4);
-  hipLaunchKernelGGL(k_embed_bwd_wte, dim3(grid_for(work, kBlock, 4096)), dim3(kBlock), 0, (hipStream_t)st, ids, dx, dwte, T,
+  // looking through the ids costs T * T comparisons, the atomics T * d additions at over a hundred times the price
+  const bool runs = T <= 32 * int64_t(d) && ((reinterpret_cast<uintptr_t>(dx) | reinterpret_cast<uintptr_t>(dwte)) & 15) == 0;
+  if (runs) hipLaunchKernelGGL(k_embed_bwd_wte_runs, dim3((T + 3) / 4), dim3(256), 0, (hipStream_t)st, ids, dx, dwte, T, d);
+  else hipLaunchKernelGGL(k_embed_bwd_wte, dim3(grid_for(work, kBlock, 4096)), dim3(kBlock), 0, (hipStream_t)st, ids, dx, dwte, T,
                      d);
   const uint64_t work2 = uint64_t(s) * (d / 4);
   hipLaunchKernelGGL(k_embed_bwd_wpe, dim3(grid_for(work2, kBlock, 4096)), dim3(kBlock), 0, (hipStream_t)st, dx, dwpe, T, d, s);
