@@ -1204,17 +1204,15 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
       // (each of these queues holds at most a few hundred operations of 64 MiB)
       for (int c = 0; c < n_copies && !h.err; ++c) {
         if (engines) {
-          last_in = engines->take();
-          bool ok = last_in && engines->copy(COPY_STATE_IN, load_dev, load_host, kLoadBytes, {}, last_in);
+          // last_in and last_out stay with the latest copy that was accepted: that one is waited for below
+          Signal in = engines->take(), out = v.bwd ? engines->take() : nullptr;
+          bool ok = in && engines->copy(COPY_STATE_IN, load_dev, load_host, kLoadBytes, {}, in);
+          if (ok) last_in = in;
           if (ok && v.bwd) {
-            last_out = engines->take();
-            ok = last_out && engines->copy(COPY_OUT, load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, {}, last_out);
-            if (!ok) last_out = nullptr;
+            ok = out && engines->copy(COPY_OUT, load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, {}, out);
+            if (ok) last_out = out;
           }
-          if (!ok) {
-            h.err = fail(HMY_E_HIP, "a copy engine refused the profile's traffic");
-            last_in = last_in && !ok ? nullptr : last_in;
-          }
+          if (!ok) h.err = fail(HMY_E_HIP, "a copy engine refused the profile's traffic");
         } else {
           HIPCHK(&h, hipMemcpyAsync(load_dev, load_host, kLoadBytes, hipMemcpyHostToDevice, h.s_in));
           if (v.bwd) KCHK(&h, launch_copy_out(load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, h.s_out));
