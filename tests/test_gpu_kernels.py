@@ -486,6 +486,30 @@ def test_cross_entropy(prec, pc, dt, tol, T, V):
 
 
 @pytest.mark.parametrize("prec,pc,dt,tol", PRECS)
+@pytest.mark.parametrize("V", [1000, 9000, 20000, 40000])
+def test_cross_entropy_of_infinities(prec, pc, dt, tol, V):
+    """Rows in registers against the general kernel (rows that allow no 16-byte access): infinite and undefined logits
+    give the same loss and the same gradient.  Rows: ordinary, +inf beside the target, +inf at it, most of the row -inf,
+    NaN."""
+    say(f"xent infinities {prec} V={V}")
+    inf = float("inf")
+    x = torch.randn(5, V, generator=torch.Generator().manual_seed(V))
+    tgt = torch.tensor([3, 5, 7, 11, 13], dtype=torch.int32)
+    x[1, V // 2], x[2, 7], x[3, 12:], x[4, V - 1] = inf, inf, -inf, float("nan")
+    for row in range(5):
+        got = []
+        for ldl in (V, V + 1):
+            logits = torch.full((1, ldl), 5.0, device="cuda")
+            logits[:, :V] = x[row].cuda()
+            loss, d = torch.zeros(1, dtype=torch.float64, device="cuda"), torch.full((1, ldl), 9.0, device="cuda", dtype=dt)
+            B.hmy_k_xent(pc, logits, tgt[row:row + 1].cuda(), loss, d, 1, V, ldl, 0.5)
+            got.append((loss.cpu(), d[:, :V].float().cpu()))
+        # sums of V fp32 terms in two orders; a gradient on either side of a bf16 rounding boundary
+        assert torch.allclose(got[0][0], got[1][0], rtol=1e-5, equal_nan=True), row
+        assert torch.allclose(got[0][1], got[1][1], rtol=1e-2 if prec == "bf16" else 1e-4, atol=1e-9, equal_nan=True), row
+
+
+@pytest.mark.parametrize("prec,pc,dt,tol", PRECS)
 @pytest.mark.parametrize("step", [1, 10])
 def test_adam(prec, pc, dt, tol, step):
     say(f"adam {prec} step={step}")
