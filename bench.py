@@ -433,14 +433,14 @@ def main() -> int:
                      "event_pair_us_subtracted_per_launch": prof["t_event_pair_s"] * 1e6,
                      "all_variants_TFLOPs": [prof["gemm_flops"][i] / max(prof["gemm_s"][i], 1e-12) / 1e12
                                              if prof["gemm_calls"][i] else None for i in range(4)]},
-        # the kernels that write to the host (fused Adam + write-back, checkpoint copies) own the other stream:
-        # bytes they moved over the time they ran (events of the level-1 step) against the link alone
-        "roofline_host_link": {"bound": "host_link", "kernel": "k_adam_out + k_copy_out (device->host)",
+        # everything that leaves for the host goes through one copy engine: bytes it moved over the time its copies
+        # took (level-1 step) against the link alone
+        "roofline_host_link": {"bound": "host_link", "kernel": "copy engine (device->host)",
                                "achieved": d2h / 1e9 / max(stats["t_d2h_busy_s"], 1e-12), "peak": HOST_LINK_GBPS_ALONE,
                                "unit": "GB/s", "frac": d2h / 1e9 / max(stats["t_d2h_busy_s"], 1e-12) / HOST_LINK_GBPS_ALONE,
                                "busy_ms": stats["t_d2h_busy_s"] * 1e3,
-                               "note": "peak = what the same kernels reach with nothing else running (measured); "
-                                       "throttled on purpose beside the compute stream"},
+                               "note": "peak = what large copies reach with nothing else running (measured); "
+                                       "weights, optimizer state and checkpoints come in at the same time"},
         "step_bound": step_bound(total_flops, h2d, d2h, ms, peak),
         "loss": stats["loss"],
     }
