@@ -929,13 +929,18 @@ int launch_cfg256(const hmy_gemm_desc &g, const DmaP &p, dim3 grid, int gn, hipS
   return check_launch("gemm_dma256");
 }
 
+bool small_may_split(const hmy_gemm_desc &g) { return g.accumulate && g.c_fp32 && !g.bias && !g.res; }
+// a long contraction over few tiles that may be split (fp32 atomics into C): while it fills idle compute units and
+// leaves each workgroup at least eight K tiles
+int small_splits(const hmy_gemm_desc &g) {
+  const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
+  if (!small_may_split(g) || tiles > 128) return 1;
+  return std::max(1, std::min(256 / int(tiles), (g.K + SK - 1) / SK / 8));
+}
+
 int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
   const int gm = (g.M + ST - 1) / ST, gn = (g.N + ST - 1) / ST, nk = (g.K + SK - 1) / SK;
-  // a long contraction over few tiles that may be split (fp32 atomics into C): while it fills idle compute units and
-  // leaves each workgroup at least eight K tiles
-  int splits = 1;
-  if (g.accumulate && g.c_fp32 && !g.bias && !g.res && gm * gn <= 128)
-    splits = std::max(1, std::min(256 / (gm * gn), nk / 8));
+  int splits = small_splits(g);
   const int tps = (nk + splits - 1) / splits;
   splits = (nk + tps - 1) / tps;
   const dim3 grid(gm * gn * splits), block(NT);
@@ -977,11 +982,16 @@ static DmaP dma_params(const hmy_gemm_desc &g) {
 // 13.6 -> 19), and for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to
 // register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Sums into an
 // fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
-// contraction.
+// contraction, and so do weight gradients whose contraction stays long in every workgroup here (sums, 512x512: K = 4096 in
+// four splits 17.7 -> 13.1, 8192 20.1 -> 20.6; 768x768: K = 1024 11.7 -> 11.2, 2048 18.6 -> 18.9, 4096 21 -> 34; 1024x1024:
+// 1024 17.5 -> 11.5, 4096 24 -> 34).  Without a split, 2048x1024 (512 tiles) gains up to K = 2048 (19.6 -> 18.9, 4096
+// 32.5 -> 33.4), 256 tiles at every length measured (1024x1024x8192 56 -> 53).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
-  return tiles <= 512 || (g.K % 32 != 0 && tiles < 2048);
+  if (small_may_split(g) && g.K / small_splits(g) >= 2048) return false;
+  if (g.K % 32 != 0) return tiles < 2048;
+  return tiles <= 256 || (tiles <= 512 && g.K <= 2048);
 }
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
 
