@@ -388,7 +388,8 @@ int hmy_bind_state(hmy_handle *h, const hmy_host_state *state);
  * with recompute from the stashed pack input (Section 4.3.1), each followed by its Weight
  * Update (jit-update); swap-byte counters per tensor kind (appendix "Additional Swap
  * Analysis").  Produces the minibatch's gradients, Adam on every tensor, the loss and the
- * counters.  Returns with all streams idle. */
+ * counters.  Returns with all streams idle.  After HMY_E_HIP (a launch, a copy or its copy
+ * engine failed) the state is partly updated: load it anew and bind it again. */
 int hmy_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam *adam, hmy_stats *out);
 
 /* The Profiler of Section 4.2 for this library's kernels: runs the embedding, a pack of up

@@ -16,6 +16,7 @@
 #include <hsa/hsa.h>
 #include <hsa/hsa_ext_amd.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdlib>
 #include <cstring>
@@ -45,11 +46,15 @@ bool owner_of(const void *p, uint64_t bytes, hsa_agent_t *agent, hsa_device_type
 
 }  // namespace
 
+static void store_signal(Signal s, int64_t v) { hsa_signal_store_screlease(handle_of(s), v); }
+
 struct CopyEngines::Impl {
   hsa_agent_t gpu, cpu;
   hsa_amd_sdma_engine_id_t engine[COPY_QUEUES];
   std::vector<Signal> signals;
   size_t used = 0;
+  SignalWatch watch{store_signal};
+  uint64_t copies = 0, fail_at = 0;   // for tests: the copy of that number (from 1) fails
 };
 
 CopyEngines *CopyEngines::create(void *dev) {
@@ -74,10 +79,10 @@ CopyEngines *CopyEngines::create(void *dev) {
          reinterpret_cast<Signal>(const_cast<hsa_signal_value_t *>(value)) == s;
     // out first, so that what comes in again is what was there
     ok = ok && c->copy(COPY_OUT, probe, dev, 256, {}, s);
-    if (ok) wait(s);
+    ok = ok && c->wait(s);
     Signal t = ok ? c->take() : nullptr;
     ok = t && c->copy(CopyQueue(q), q == COPY_OUT ? probe : dev, q == COPY_OUT ? dev : probe, 256, {}, t);
-    if (ok) wait(t);
+    ok = ok && c->wait(t);
   }
   if (probe) hipHostFree(probe);
   (void)hipGetLastError();
@@ -86,12 +91,15 @@ CopyEngines *CopyEngines::create(void *dev) {
     return nullptr;
   }
   c->recycle();
+  c->p->copies = 0;
+  if (const char *e = std::getenv("HMY_FAIL_COPY")) c->p->fail_at = uint64_t(std::max(0, std::atoi(e)));
   return c;
 }
 
 CopyEngines::~CopyEngines() {
-  for (Signal s : p->signals) hipFree(s);
-  delete p;
+  const std::vector<Signal> signals = p->signals;
+  delete p;   // the thread that looks at them
+  for (Signal s : signals) hipFree(s);
   hsa_shut_down();
 }
 
@@ -112,23 +120,36 @@ Signal CopyEngines::take() {
   return s;
 }
 
-void CopyEngines::recycle() { p->used = 0; }
+void CopyEngines::recycle() {
+  p->used = 0;
+  p->watch.clear();
+}
 
 bool CopyEngines::copy(CopyQueue q, void *dst, const void *src, uint64_t bytes, const std::vector<Signal> &deps, Signal done) {
   std::vector<hsa_signal_t> d;
   d.reserve(deps.size());
   for (Signal s : deps) d.push_back(handle_of(s));
-  const hsa_agent_t from = q == COPY_OUT ? p->gpu : p->cpu, to = q == COPY_OUT ? p->cpu : p->gpu;
-  return hsa_amd_memory_async_copy_on_engine(dst, to, src, from, bytes, uint32_t(d.size()), d.empty() ? nullptr : d.data(),
-                                             handle_of(done), p->engine[q], false) == HSA_STATUS_SUCCESS;
-}
-
-bool CopyEngines::happened(Signal s) { return hsa_signal_load_scacquire(handle_of(s)) < 1; }
-
-void CopyEngines::wait(Signal s) {
-  while (hsa_signal_wait_scacquire(handle_of(s), HSA_SIGNAL_CONDITION_LT, 1, UINT64_MAX, HSA_WAIT_STATE_BLOCKED) >= 1) {
+  if (++p->copies == p->fail_at) {   // as an engine leaves it: nothing copied, the signal negative
+    store_signal(done, -1);
+    p->watch.add(done);
+    return true;
   }
+  const hsa_agent_t from = q == COPY_OUT ? p->gpu : p->cpu, to = q == COPY_OUT ? p->cpu : p->gpu;
+  if (hsa_amd_memory_async_copy_on_engine(dst, to, src, from, bytes, uint32_t(d.size()), d.empty() ? nullptr : d.data(),
+                                          handle_of(done), p->engine[q], false) != HSA_STATUS_SUCCESS)
+    return false;
+  p->watch.add(done);
+  return true;
 }
+
+bool CopyEngines::happened(Signal s) { return p->watch.over(s); }
+
+bool CopyEngines::wait(Signal s) {
+  while (!p->watch.over(s)) hsa_signal_wait_scacquire(handle_of(s), HSA_SIGNAL_CONDITION_LT, 1, UINT64_MAX, HSA_WAIT_STATE_BLOCKED);
+  return p->watch.settle();
+}
+
+bool CopyEngines::failed() { return !p->watch.settle(); }
 
 void CopyEngines::time_copies() { hsa_amd_profiling_async_copy_enable(true); }
 

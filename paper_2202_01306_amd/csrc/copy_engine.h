@@ -5,12 +5,9 @@
 
 #include <vector>
 
-namespace hmy {
+#include "signal_watch.h"
 
-// A signal is a 64-bit word, 1 until what it stands for has happened, then 0: written by a copy engine at the end of a
-// copy, by k_signal (engine.hip) where a stream reaches it; waited for by copy engines, streams (hipStreamWaitValue64)
-// and the host.
-typedef uint64_t *Signal;
+namespace hmy {
 
 // Logical queues: the copies of one run in the order they were submitted.
 enum CopyQueue { COPY_IN = 0, COPY_STATE_IN = 1, COPY_OUT = 2, COPY_QUEUES = 3 };
@@ -31,8 +28,9 @@ class CopyEngines {
   void recycle();
   // Queue a copy that starts once every signal of `deps` has happened and then sets `done`.  True on success.
   bool copy(CopyQueue q, void *dst, const void *src, uint64_t bytes, const std::vector<Signal> &deps, Signal done);
-  static bool happened(Signal s);
-  static void wait(Signal s);           // blocks the calling thread
+  bool happened(Signal s);              // also where its copy, or one it waited for, has failed: failed() then says so
+  bool wait(Signal s);                  // blocks the calling thread; false: a copy has failed
+  bool failed();                        // whether any copy since the last recycle() has
   // copies submitted from now on are timed (process-wide, cannot be taken back)
   static void time_copies();
   // seconds on the device's clock of a finished, timed copy; false if it was not timed

@@ -168,9 +168,13 @@ Point rec(hmy_handle *h, Queue q) {
   HIPCHK(h, hipEventRecord(p.event, h->stream(q)));
   return p;
 }
+// the failure of a copy ends the iteration
+void check_copies(hmy_handle *h) {
+  if (!h->err && h->engines && h->engines->failed()) h->err = fail(HMY_E_HIP, "a copy engine reported a failed copy");
+}
 void wait(hmy_handle *h, Queue q, const Point &p) {
   if (h->dry || h->err) return;
-  if (p.signal && CopyEngines::happened(p.signal)) return;
+  if (p.signal && h->engines->happened(p.signal)) return;
   if (p.signal && is_copy_queue(q)) h->deps[q].push_back(p.signal);
   else if (p.signal) HIPCHK(h, hipStreamWaitValue64(h->stream(q), p.signal, 0, hipStreamWaitValueEq));
   if (p.event) HIPCHK(h, hipStreamWaitEvent(h->stream(q), p.event, 0));
@@ -178,7 +182,7 @@ void wait(hmy_handle *h, Queue q, const Point &p) {
 // whether a point has been reached, asked by the host
 bool reached(hmy_handle *h, const Point &p) {
   if (h->dry || h->err) return true;
-  if (p.signal) return CopyEngines::happened(p.signal);
+  if (p.signal) return h->engines->happened(p.signal);
   if (!p.event) return true;
   const hipError_t e = hipEventQuery(p.event);
   if (e == hipErrorNotReady) {
@@ -751,6 +755,7 @@ bool pump_updates(hmy_handle *h, IterState &it, const hmy_adam &hp) {
     }
     PendingUpdate &u = it.updates.front();
     if (!it.arrivals.empty() && reached(h, it.arrivals.front()) && (u.run > 0 || reached(h, u.bwd_done))) {
+      check_copies(h);   // no update from what a copy that failed should have brought
       run_chunk(h, it, u, hp);
       it.arrivals.pop_front();
       if (u.run == u.n_chunks) it.updates.pop_front();
@@ -805,10 +810,8 @@ int updater_thread_init(void *arg, void *) {
   return hipSetDevice(static_cast<hmy_handle *>(arg)->device) == hipSuccess ? HMY_OK : HMY_E_HIP;
 }
 int updater_wait(void *arg, void *ready) {
-  if (static_cast<hmy_handle *>(arg)->on_engines()) {
-    CopyEngines::wait(static_cast<Signal>(ready));
-    return HMY_OK;
-  }
+  hmy_handle *h = static_cast<hmy_handle *>(arg);
+  if (h->on_engines()) return h->engines->wait(static_cast<Signal>(ready)) ? HMY_OK : HMY_E_HIP;
   return hipEventSynchronize(static_cast<hipEvent_t>(ready)) == hipSuccess ? HMY_OK : HMY_E_HIP;
 }
 // the update that follows a pack's (last) backward task, wherever the schedule places it
@@ -1221,9 +1224,10 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
     }
     const double beside_ms = run(reps) / reps;
     // let what is left of the traffic drain before the next layer's turn
-    if (last_in) CopyEngines::wait(last_in);
-    if (last_out) CopyEngines::wait(last_out);
+    if (last_in) engines->wait(last_in);
+    if (last_out) engines->wait(last_out);
     last_in = last_out = nullptr;
+    if (engines && engines->failed() && !h.err) h.err = fail(HMY_E_HIP, "a copy engine reported a failed copy of the profile's traffic");
     if (engines) engines->recycle();
     hipStreamSynchronize(h.s_in);
     hipStreamSynchronize(h.s_out);
@@ -1436,12 +1440,13 @@ int hmy_iteration(hmy_handle *h, const hmy_minibatch *mb, const hmy_adam *adam, 
   run_in_order(h, mb, *adam);
   // always drain, even after an error, so no queue still touches caller memory
   for (int q = IN; q < N_QUEUES; ++q)
-    if (h->last_copy[q]) CopyEngines::wait(h->last_copy[q]);
+    if (h->last_copy[q]) h->engines->wait(h->last_copy[q]);
   hipStreamSynchronize(h->s_comp);
   hipStreamSynchronize(h->s_in);
   hipStreamSynchronize(h->s_kin);
   hipStreamSynchronize(h->s_upd);
   hipError_t e_last = hipStreamSynchronize(h->s_out);
+  check_copies(h);
   if (h->err == HMY_OK && e_last != hipSuccess) h->err = fail(HMY_E_HIP, "stream sync: %s", hipGetErrorString(e_last));
   if (h->updater) {   // the CPU threads may still be applying the last pack's update
     const int rc = h->updater->drain();

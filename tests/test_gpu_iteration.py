@@ -264,6 +264,41 @@ def test_swaps_without_the_named_copy_engines(monkeypatch, precision, order, upd
                     update_site=update_site)
 
 
+@pytest.mark.parametrize("order,update_site", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("n", [1, 7, 20, 30])
+def test_failed_copy_ends_the_iteration_with_an_error(monkeypatch, n, order, update_site):
+    """The n-th copy leaves its signal as a failed one does (set by the host): weights, checkpoints, state, results.  The
+    iteration returns an error instead of waiting for good or reporting success, and the next one is as ever."""
+    from paper_2202_01306_amd import binding as B
+    from paper_2202_01306_amd.runner import Engine, TrainingState
+    say(f"copy {n} fails, order {order}, update site {update_site}")
+    cfg = dict(synth.CONFIGS["tiny"])
+    params = synth.gen_params(cfg, 3, bench_init=False)
+    m0, v0 = synth.gen_adam_state(cfg, 3, zero=False)
+    ids = synth.gen_tokens(cfg, 3)
+    sched = B.make_schedule([2, 5], [1, 2, 5, 6], order=order, update_site=update_site)
+    got = []
+    for fails in (True, False):
+        monkeypatch.setenv("HMY_FAIL_COPY", str(n if fails else 0))
+        st = TrainingState(cfg)
+        st.load(params, m0, v0)
+        with Engine(st, 1 << 34, cfg["M"], cfg["b"], sched) as eng:
+            eng.set_batch(ids, synth.gen_targets(cfg, ids, 3))
+            if fails:
+                with pytest.raises(B.HmyError) as e:
+                    eng.step(lr=1e-3, step=3)
+                assert e.value.code == B.HMY_E_HIP and "failed copy" in str(e.value)
+                st.load(params, m0, v0)
+                eng.rebind()
+            stats = eng.step(lr=1e-3, step=3)
+            got.append((stats["loss"], st.named("weights"), st.named("grads")))
+        st.close()
+    assert abs(got[0][0] - got[1][0]) <= 1e-6 * abs(got[1][0])
+    for k in got[1][1]:
+        for which in (1, 2):
+            assert max_rel_err(got[0][which][k], got[1][which][k]) < 1e-5, k
+
+
 @pytest.mark.parametrize("gradients,resident", [(0, None), (1, 2)])
 def test_swap_out_through_memcpy_bf16_several_packs(gradients, resident):
     say(f"bf16, swap-out by hipMemcpyAsync, several packs, gradients {gradients}, resident chunks {resident}")

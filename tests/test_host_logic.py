@@ -736,3 +736,56 @@ def test_bench_refuses_more_than_one_gpu_and_has_no_cpu_fallback():
                            capture_output=True, text=True, timeout=300)
         assert r.returncode != 0 and "needs a GPU" in r.stderr and not r.stdout.strip()
 
+
+def test_signals_of_failed_copies_are_released_and_reported(tmp_path):
+    """csrc/signal_watch.h, which is plain C++: a negative signal counts as over, reads 0 soon after whether or not anybody
+    asks for it, and the failure is known to whoever sees that 0; clear() forgets it."""
+    import subprocess
+    src, exe = tmp_path / "w.cpp", tmp_path / "w"
+    src.write_text(r"""
+#include <cstdio>
+#include <cstdlib>
+#include "signal_watch.h"
+using namespace hmy;
+static void store(Signal s, int64_t v) { __atomic_store_n(s, uint64_t(v), __ATOMIC_RELEASE); }
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
+static void until_zero(uint64_t *s) {
+  for (int ms = 0; __atomic_load_n(s, __ATOMIC_ACQUIRE) != 0; ++ms) {
+    CHECK(ms < 20000);
+    std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  }
+}
+int main() {
+  uint64_t s[64];
+  SignalWatch w(store);
+  for (int64_t bad : {int64_t(-1), int64_t(-2), INT64_MIN}) {
+    for (auto &x : s) { x = 1; w.add(&x); }
+    CHECK(!w.over(&s[0]) && w.settle() && !w.failed());
+    for (int i = 0; i < 64; ++i) if (i != 3 && i != 40) store(&s[i], 0);
+    CHECK(w.over(&s[0]) && w.settle());
+    store(&s[40], bad);             // out of order, while an earlier one is pending; seen by nobody
+    until_zero(&s[40]);
+    CHECK(w.failed() && !w.settle() && w.over(&s[40]) && !w.over(&s[3]));
+    store(&s[3], 0);
+    CHECK(w.over(&s[3]) && !w.settle());
+    w.clear();
+    CHECK(!w.failed() && w.settle());
+    uint64_t t = 1;
+    w.add(&t);
+    store(&t, bad);                 // asked for at once
+    CHECK(w.over(&t) && w.failed() && t == 0);
+    w.clear();
+    std::this_thread::sleep_for(std::chrono::milliseconds(3));   // idle, then in use again
+    t = 1;
+    w.add(&t);
+    store(&t, bad);
+    CHECK(!w.settle());
+    w.clear();
+  }
+  return 0;
+}
+""")
+    csrc = os.path.join(ROOT, "paper_2202_01306_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-pthread", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
