@@ -54,7 +54,8 @@ struct CopyEngines::Impl {
   std::vector<Signal> signals;
   size_t used = 0;
   SignalWatch watch{store_signal};
-  uint64_t copies = 0, fail_at = 0;   // for tests: the copy of that number (from 1) fails
+  // for tests: the copy of that number (from 1) fails; every so many are refused
+  uint64_t copies = 0, fail_at = 0, refuse_every = 0;
 };
 
 CopyEngines *CopyEngines::create(void *dev) {
@@ -92,7 +93,9 @@ CopyEngines *CopyEngines::create(void *dev) {
   }
   c->recycle();
   c->p->copies = 0;
-  if (const char *e = std::getenv("HMY_FAIL_COPY")) c->p->fail_at = uint64_t(std::max(0, std::atoi(e)));
+  auto from_env = [](const char *name) { return std::getenv(name) ? uint64_t(std::max(0, std::atoi(std::getenv(name)))) : 0; };
+  c->p->fail_at = from_env("HMY_FAIL_COPY");
+  c->p->refuse_every = from_env("HMY_REFUSE_COPIES");
   return c;
 }
 
@@ -134,6 +137,7 @@ bool CopyEngines::copy(CopyQueue q, void *dst, const void *src, uint64_t bytes, 
     p->watch.add(done);
     return true;
   }
+  if (p->refuse_every && p->copies % p->refuse_every == 0) return false;
   const hsa_agent_t from = q == COPY_OUT ? p->gpu : p->cpu, to = q == COPY_OUT ? p->cpu : p->gpu;
   if (hsa_amd_memory_async_copy_on_engine(dst, to, src, from, bytes, uint32_t(d.size()), d.empty() ? nullptr : d.data(),
                                           handle_of(done), p->engine[q], false) != HSA_STATUS_SUCCESS)
@@ -141,6 +145,8 @@ bool CopyEngines::copy(CopyQueue q, void *dst, const void *src, uint64_t bytes, 
   p->watch.add(done);
   return true;
 }
+
+void CopyEngines::set(Signal s) { store_signal(s, 0); }
 
 bool CopyEngines::happened(Signal s) { return p->watch.over(s); }
 

@@ -26,8 +26,9 @@ class CopyEngines {
   // waits for or will set any of them.  nullptr: out of memory.
   Signal take();
   void recycle();
-  // Queue a copy that starts once every signal of `deps` has happened and then sets `done`.  True on success.
+  // Queue a copy that starts once every signal of `deps` has happened and then sets `done`.  False: refused, nothing queued.
   bool copy(CopyQueue q, void *dst, const void *src, uint64_t bytes, const std::vector<Signal> &deps, Signal done);
+  static void set(Signal s);            // by the host, in place of a copy
   bool happened(Signal s);              // also where its copy, or one it waited for, has failed: failed() then says so
   bool wait(Signal s);                  // blocks the calling thread; false: a copy has failed
   bool failed();                        // whether any copy since the last recycle() has

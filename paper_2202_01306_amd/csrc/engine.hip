@@ -227,25 +227,36 @@ void comp_wait(hmy_handle *h, const Point &p) {
 }
 
 // ---- copies (bytes are counted when enqueued) ---------------------------------
-// device -> pinned host through a throttled copy kernel on the OUT stream (the library's blit
-// for hipMemcpyAsync floods the fabric with stores to the link and stalls the kernels
-// running beside it)
 void copy(hmy_handle *h, Queue q, void *dst, const void *src, uint64_t bytes) {
   const int what = q == OUT ? 1 : 0;
   if (h->on_engines()) {
     Signal done = new_signal(h);
     if (h->err) return;
-    if (!h->engines->copy(copy_queue(q), dst, src, bytes, h->deps[q], done)) {
-      h->err = fail(HMY_E_HIP, "a copy engine refused %llu bytes", (unsigned long long)bytes);
-      return;
+    const bool taken = h->engines->copy(copy_queue(q), dst, src, bytes, h->deps[q], done);
+    if (!taken) {
+      // refused: the host thread itself waits for what the copy waits for, which has all been submitted, brings it over
+      // through a stream, and sets the signal
+      for (Signal s : h->deps[q]) h->engines->wait(s);
+      if (h->last_copy[q]) h->engines->wait(h->last_copy[q]);
+      check_copies(h);
+      hipStream_t s = h->stream(q);
+      size_t a = trec(h, s);
+      HIPCHK(h, hipMemcpyAsync(dst, src, bytes, q == OUT ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice, s));
+      size_t b = trec(h, s);
+      span(h, a, b, what);
+      HIPCHK(h, hipStreamSynchronize(s));
+      if (h->err) return;
+      CopyEngines::set(done);
     }
     h->deps[q].clear();
     h->last_copy[q] = done;
-    if (h->timing) h->copy_spans.push_back({done, what, h->tag});
+    if (taken && h->timing) h->copy_spans.push_back({done, what, h->tag});
     return;
   }
   hipStream_t s = h->stream(q);
   size_t a = trec(h, s);
+  // device -> pinned host through a throttled copy kernel (the library's blit for hipMemcpyAsync floods the fabric with
+  // stores to the link and stalls the kernels running beside it)
   if (q == OUT && h->fused_swap_out) h->err = launch_copy_out(dst, src, bytes, s);
   else HIPCHK(h, hipMemcpyAsync(dst, src, bytes, q == OUT ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice, s));
   size_t b = trec(h, s);
@@ -1205,21 +1216,18 @@ int hmy::run_measure_profile(const Model &m, int micro_batch, int hip_device, in
       // for every visit, outgoing ones only for backward visits, whose updates are what writes to the host
       const int n_copies = int(std::min(400.0, 2.0 * reps * alone_ms * 1e-3 * 50e9 / double(kLoadBytes))) + 2;
       // (each of these queues holds at most a few hundred operations of 64 MiB)
+      // `last` stays with the latest copy that an engine accepted: that one is waited for below
+      auto by_engine = [&](CopyQueue q, void *dst, const void *src, Signal *last) {
+        Signal done = engines ? engines->take() : nullptr;
+        if (!done || !engines->copy(q, dst, src, kLoadBytes, {}, done)) return false;
+        *last = done;
+        return true;
+      };
       for (int c = 0; c < n_copies && !h.err; ++c) {
-        if (engines) {
-          // last_in and last_out stay with the latest copy that was accepted: that one is waited for below
-          Signal in = engines->take(), out = v.bwd ? engines->take() : nullptr;
-          bool ok = in && engines->copy(COPY_STATE_IN, load_dev, load_host, kLoadBytes, {}, in);
-          if (ok) last_in = in;
-          if (ok && v.bwd) {
-            ok = out && engines->copy(COPY_OUT, load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, {}, out);
-            if (ok) last_out = out;
-          }
-          if (!ok) h.err = fail(HMY_E_HIP, "a copy engine refused the profile's traffic");
-        } else {
+        if (!by_engine(COPY_STATE_IN, load_dev, load_host, &last_in))
           HIPCHK(&h, hipMemcpyAsync(load_dev, load_host, kLoadBytes, hipMemcpyHostToDevice, h.s_in));
-          if (v.bwd) KCHK(&h, launch_copy_out(load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, h.s_out));
-        }
+        if (v.bwd && !by_engine(COPY_OUT, load_host + kLoadBytes, load_dev + kLoadBytes, &last_out))
+          KCHK(&h, launch_copy_out(load_host + kLoadBytes, load_dev + kLoadBytes, kLoadBytes, h.s_out));
       }
     }
     const double beside_ms = run(reps) / reps;

@@ -299,6 +299,26 @@ def test_failed_copy_ends_the_iteration_with_an_error(monkeypatch, n, order, upd
             assert max_rel_err(got[0][which][k], got[1][which][k]) < 1e-5, k
 
 
+@pytest.mark.parametrize("order,update_site", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("precision,every", [("fp32", 1), ("bf16", 1), ("bf16", 5)])
+def test_refused_copies_go_another_way(monkeypatch, precision, every, order, update_site):
+    """Copies that a copy engine refuses, all of them or some between others, are brought over by the host thread."""
+    say(f"{precision}, every {every}. copy refused, order {order}, update site {update_site}")
+    monkeypatch.setenv("HMY_REFUSE_COPIES", str(every))
+    cfg = tiny_cfg(n_blocks=4, d_model=128, n_heads=2, d_ffn=512, seq_len=64, vocab=600, precision=precision, M=3, b=2)
+    run_and_compare(cfg, sched_ends=([2, 5], [1, 2, 5, 6]), zero_state=False, steps=(3, 4), weight_scale=3.0, order=order,
+                    update_site=update_site)
+
+
+def test_refused_copies_of_a_measured_profile(monkeypatch):
+    from paper_2202_01306_amd import binding as B
+    say("measured profile, every other copy refused")
+    monkeypatch.setenv("HMY_REFUSE_COPIES", "2")
+    cfg = tiny_cfg(n_blocks=2, d_model=128, n_heads=2, d_ffn=512, seq_len=64, vocab=600, precision="bf16")
+    mp = B.hmy_measure_profile(B.make_spec(cfg), 2, reps=2)
+    assert all(mp[k] > 0 for k in B.MEASURED_FIELDS)
+
+
 @pytest.mark.parametrize("gradients,resident", [(0, None), (1, 2)])
 def test_swap_out_through_memcpy_bf16_several_packs(gradients, resident):
     say(f"bf16, swap-out by hipMemcpyAsync, several packs, gradients {gradients}, resident chunks {resident}")
