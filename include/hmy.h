@@ -408,6 +408,9 @@ int hmy_measure_profile(const hmy_model_spec *spec, int32_t micro_batch, int32_t
 /* Parameters whose optimizer state is resident on the device (0 unless the schedule says
  * HMY_STATE_RESIDENT_IN_SPARE_BUDGET and the budget leaves room for at least one chunk). */
 int hmy_resident_params(const hmy_handle *h, uint64_t *n_params);
+/* *yes = 1 if swap copies of the bound state take the copy engines that the library names itself
+ * (see HMY_SWAP_OUT_KERNEL), 0 if they go through streams. */
+int hmy_copies_on_engines(const hmy_handle *h, int32_t *yes);
 /* Write the resident optimizer state back to the bound host arrays (synchronous; not part
  * of any iteration's counters).  A no-op without resident state.  hmy_destroy does not
  * call it: the arrays may be gone by then. */

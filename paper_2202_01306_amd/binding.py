@@ -147,7 +147,7 @@ class hmy_gemm_desc(C.Structure):
 EXPORTS = [
     "hmy_strerror", "hmy_last_error", "hmy_model_size", "hmy_layout", "hmy_profile", "hmy_plan", "hmy_estimate", "hmy_arena",
     "hmy_arena_regions", "hmy_measure_profile",
-    "hmy_count_swaps", "hmy_host_alloc", "hmy_host_free", "hmy_create", "hmy_get_schedule", "hmy_bind_state", "hmy_resident_params", "hmy_sync_state",
+    "hmy_count_swaps", "hmy_host_alloc", "hmy_host_free", "hmy_create", "hmy_get_schedule", "hmy_bind_state", "hmy_copies_on_engines", "hmy_resident_params", "hmy_sync_state",
     "hmy_iteration", "hmy_destroy", "hmy_set_profiling", "hmy_set_progress", "hmy_set_kernel_path", "hmy_k_embed_fwd", "hmy_k_embed_bwd",
     "hmy_k_layernorm_fwd", "hmy_k_layernorm_bwd", "hmy_k_layernorm_bwd_static", "hmy_k_gelu_fwd", "hmy_k_gelu_bwd", "hmy_k_gelu_bwd_colsum", "hmy_k_colsum",
     "hmy_k_gemm", "hmy_k_attn_fwd", "hmy_k_attn_bwd", "hmy_k_xent", "hmy_k_adam", "hmy_host_adam",
@@ -326,6 +326,13 @@ def hmy_get_schedule(h) -> hmy_schedule:
 def hmy_bind_state(h, weights_ptr, master_ptr, m_ptr, v_ptr, grads_ptr, n_params):
     st = hmy_host_state(weights_ptr, master_ptr, m_ptr, v_ptr, grads_ptr, n_params)
     _check(lib.hmy_bind_state(h, C.byref(st)))
+
+
+def hmy_copies_on_engines(h) -> bool:
+    """Whether swap copies of the bound state take the library's own copy engines (otherwise: streams)."""
+    yes = C.c_int32()
+    _check(lib.hmy_copies_on_engines(h, C.byref(yes)))
+    return bool(yes.value)
 
 
 def hmy_resident_params(h) -> int:

@@ -1400,6 +1400,13 @@ int hmy_bind_state(hmy_handle *h, const hmy_host_state *state) {
   return HMY_OK;
 }
 
+int hmy_copies_on_engines(const hmy_handle *h, int32_t *yes) {
+  if (!h || !yes) return fail(HMY_E_INVALID, "null argument");
+  if (!h->bound) return fail(HMY_E_NOT_BOUND, "hmy_bind_state was not called");
+  *yes = h->on_engines();
+  return HMY_OK;
+}
+
 int hmy_resident_params(const hmy_handle *h, uint64_t *n_params) {
   if (!h || !n_params) return fail(HMY_E_INVALID, "null argument");
   uint64_t total = 0;

@@ -4,6 +4,7 @@ optimizer tensor, and the swap-byte counters (bit-exact against the oracle's
 closed form).  Tolerances (max|x-ref|/max|ref| per tensor): 1e-4 for the fp32
 configuration, 2e-2 for bf16 compute."""
 import math
+import os
 
 import numpy as np
 import pytest
@@ -136,6 +137,8 @@ def run_and_compare(cfg, *, sched_ends=None, budget=None, zero_state=True, steps
         ids_o, tg_o = ids.reshape(D // uB, uB, -1), tg.reshape(D // uB, uB, -1)
         assert eng.arena["total"] <= budget
         assert eng.resident_params() == P_res
+        # the path under test is the one that ran: a device and pinned state offer the named copy engines
+        assert B.hmy_copies_on_engines(eng.handle) == (not sched_kw.get("swap_out") and os.environ.get("HMY_COPY_ENGINES") != "0")
         eng.set_batch(ids, tg)
         for step in steps:
             f32 = lambda x: float(np.float32(x))     # the C ABI carries fp32 hyper-parameters
@@ -262,6 +265,27 @@ def test_swaps_without_the_named_copy_engines(monkeypatch, precision, order, upd
     cfg = tiny_cfg(n_blocks=4, d_model=128, n_heads=2, d_ffn=512, seq_len=64, vocab=600, precision=precision, M=3, b=2)
     run_and_compare(cfg, sched_ends=([2, 5], [1, 2, 5, 6]), zero_state=False, steps=(3, 4), weight_scale=3.0, order=order,
                     update_site=update_site)
+
+
+def test_state_in_ordinary_memory_is_kept_off_the_named_copy_engines():
+    """Which memory they reach is asked at every bind (no iteration here: it would need page-locked memory)."""
+    from paper_2202_01306_amd import binding as B
+    from paper_2202_01306_amd.runner import TrainingState
+    cfg = dict(synth.CONFIGS["tiny"])
+    st = TrainingState(cfg)
+    pageable = np.zeros(st.n_params, np.float32)
+    h = B.hmy_create(st.spec, 1 << 34, cfg["M"], cfg["b"])
+    try:
+        with pytest.raises(B.HmyError) as e:
+            B.hmy_copies_on_engines(h)
+        assert e.value.code == B.HMY_E_NOT_BOUND
+        arrays = [st.weights.ptr, st.adam_m.ptr, st.adam_v.ptr, st.grads.ptr]
+        for i in (None, 0, 1, 2, 3, None):
+            w, m, v, g = (pageable.ctypes.data if k == i else p for k, p in enumerate(arrays))
+            B.hmy_bind_state(h, w, None, m, v, g, st.n_params)
+            assert B.hmy_copies_on_engines(h) == (i is None)
+    finally:
+        B.hmy_destroy(h)
 
 
 @pytest.mark.parametrize("order,update_site", [(0, 0), (1, 0), (0, 1)])
@@ -528,6 +552,8 @@ def test_resident_state_three_iterations_without_touching_the_host_arrays():
     with Engine(st, budget, cfg["M"], cfg["b"], sched) as eng:
         P_F, P_B = eng.packs
         assert eng.resident_params() == P_res
+        # the path under test is the one that ran: a device and pinned state offer the named copy engines
+        assert B.hmy_copies_on_engines(eng.handle) == (not sched_kw.get("swap_out") and os.environ.get("HMY_COPY_ENGINES") != "0")
         eng.set_batch(ids, tg)
         m_before = st.adam_m.a.copy()
         for i, step in enumerate((2, 3, 4)):
