@@ -282,6 +282,8 @@ def main() -> int:
             setattr(sched, n_field, len(ends))
             for i, e in enumerate(ends):
                 getattr(sched, end_field)[i] = e
+    if a.counters:
+        sched.swap_out = B.HMY_SWAP_OUT_MEMCPY   # ordered by events alone: no kernel polls for another one's signal
     if a.slots:
         sched.weight_slots = a.slots
     if a.distance:

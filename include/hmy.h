@@ -426,7 +426,9 @@ int hmy_set_profiling(hmy_handle *h, int32_t level);
 /* on != 0: a layer-pack-major iteration waits for the compute stream after every visit and
  * prints one line per visit to stderr.  For runs under a tool that serialises every kernel
  * dispatch (counter collection), where an iteration takes minutes: the lines show that it
- * advances.  Costs the overlap between visits; never use it for timing. */
+ * advances.  Swap copies then go through streams and all ordering is by events: the wait of a
+ * stream for a copy engine's signal is a kernel that polls, and such a tool might hold back what
+ * it polls for.  Costs the overlap between visits; never use it for timing. */
 int hmy_set_progress(hmy_handle *h, int32_t on);
 
 /* 0 = reference kernels (plain tiled loops); 1 = MFMA kernels where they exist

@@ -77,7 +77,9 @@ struct hmy_handle {
   Signal last_copy[N_QUEUES] = {};       // copy engines: the latest copy of the queue in this iteration
   hipEvent_t ids_event = nullptr;
   bool arrays_reached = false;           // the bound host arrays lie in memory the copy engines reach
-  bool on_engines() const { return engines && arrays_reached; }
+  // not for runs that serialise dispatches (hmy_set_progress): a stream's wait for a signal is a kernel that polls, and what
+  // it polls for may hang on another stream's kernel that such a tool has not let start
+  bool on_engines() const { return engines && arrays_reached && !progress; }
   hipStream_t stream(Queue q) const {
     return q == COMP ? s_comp : q == UPD ? s_upd : q == IN ? s_in : q == STATE_IN ? s_kin : s_out;
   }

@@ -288,6 +288,32 @@ def test_state_in_ordinary_memory_is_kept_off_the_named_copy_engines():
         B.hmy_destroy(h)
 
 
+@pytest.mark.parametrize("swap_out", [0, 1])
+def test_progress_lines_come_with_ordering_by_events(swap_out):
+    """hmy_set_progress is for tools that run one kernel at a time: no kernel of such an iteration polls for a signal.  Same
+    results; switched off again, the engines are in use again."""
+    from paper_2202_01306_amd import binding as B
+    from paper_2202_01306_amd.runner import Engine, TrainingState
+    cfg = dict(synth.CONFIGS["tiny"])
+    params = synth.gen_params(cfg, 3, bench_init=False)
+    m0, v0 = synth.gen_adam_state(cfg, 3, zero=False)
+    ids = synth.gen_tokens(cfg, 3)
+    st = TrainingState(cfg)
+    got = []
+    with Engine(st, 1 << 34, cfg["M"], cfg["b"], B.make_schedule([2, 5], [1, 2, 5, 6], swap_out=swap_out)) as eng:
+        eng.set_batch(ids, synth.gen_targets(cfg, ids, 3))
+        for on in (False, True, False):
+            st.load(params, m0, v0)
+            eng.rebind()
+            B.hmy_set_progress(eng.handle, on)
+            assert B.hmy_copies_on_engines(eng.handle) == (not on and not swap_out)
+            got.append((eng.step(lr=1e-3, step=3), st.named("weights"), st.named("m")))
+    for stats, w, m in got[1:]:
+        assert stats["h2d"] == got[0][0]["h2d"] and stats["d2h"] == got[0][0]["d2h"]
+        for k in w:
+            assert max_rel_err(w[k], got[0][1][k]) < 1e-5 and max_rel_err(m[k], got[0][2][k]) < 1e-5, k
+
+
 @pytest.mark.parametrize("order,update_site", [(0, 0), (1, 0), (0, 1)])
 @pytest.mark.parametrize("n", [1, 7, 20, 30])
 def test_failed_copy_ends_the_iteration_with_an_error(monkeypatch, n, order, update_site):
