@@ -360,6 +360,50 @@ def test_refused_copies_go_another_way(monkeypatch, precision, every, order, upd
                     update_site=update_site)
 
 
+@pytest.mark.parametrize("update_sites", [(0, 0), (0, 1)])
+def test_two_handles_side_by_side(update_sites):
+    """Two handles, a thread each, share hardware queues and copy engines: everything is submitted after what it waits for,
+    so neither can be held up for good behind the other; every step's results are those of the handle on its own."""
+    import threading
+    from paper_2202_01306_amd import binding as B
+    from paper_2202_01306_amd.runner import Engine, TrainingState
+    say(f"two handles in one process, update sites {update_sites}")
+    cfg = tiny_cfg(n_blocks=4, d_model=128, n_heads=2, d_ffn=512, seq_len=64, vocab=600, M=3, b=2)
+    params = synth.gen_params(cfg, 3, bench_init=False)
+    m0, v0 = synth.gen_adam_state(cfg, 3, zero=False)
+    ids = synth.gen_tokens(cfg, 3)
+    states = [TrainingState(cfg) for _ in update_sites]
+    engines = [Engine(st, 1 << 34, cfg["M"], cfg["b"], B.make_schedule([2, 5], [1, 2, 5, 6], update_site=u))
+               for st, u in zip(states, update_sites)]
+    got = [[], []]
+
+    def steps(i, n):
+        for _ in range(n):
+            states[i].load(params, m0, v0)
+            engines[i].rebind()
+            stats = engines[i].step(lr=1e-3, step=3)
+            got[i].append((stats["loss"], states[i].named("weights"), states[i].named("grads")))
+
+    try:
+        for i in (0, 1):
+            engines[i].set_batch(ids, synth.gen_targets(cfg, ids, 3))
+            steps(i, 1)
+        threads = [threading.Thread(target=steps, args=(i, 8)) for i in (0, 1)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        for eng in engines:
+            eng.close()
+    for i in (0, 1):
+        assert len(got[i]) == 9
+        for loss, w, g in got[i][1:]:
+            assert abs(loss - got[i][0][0]) <= 1e-6 * abs(loss)
+            for k in w:
+                assert max_rel_err(w[k], got[i][0][1][k]) < 1e-5 and max_rel_err(g[k], got[i][0][2][k]) < 1e-5, k
+
+
 def test_refused_copies_of_a_measured_profile(monkeypatch):
     from paper_2202_01306_amd import binding as B
     say("measured profile, every other copy refused")
