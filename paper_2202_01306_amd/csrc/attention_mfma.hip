@@ -696,7 +696,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_mfm
 }
 
 // ---------------------------------------------------------------------------------
-// The backward kernels for head dimensions 64 and 128 on eight waves per workgroup, as in k_attn_fwd_mfma_split: waves
+// The backward kernels (dK/dV: head dimensions 64 and 128, dQ: 128) on eight waves per workgroup, as in k_attn_fwd_mfma_split: waves
 // w and w + 4 share 32 rows of the output and take one 32-row subtile of every streamed tile each, with an accumulator
 // of their own; at the end each hands the other half of its sums through LDS.  What bounds these kernels is a wave's
 // serial chain (two products, exponentials, conversion, two products), and under a causal mask the heaviest row block's
@@ -720,10 +720,12 @@ template <int DH> struct SplitBwd {
   static constexpr int DKV_LDS = max3(4 * TILE_ELEMS * 2 + STATS + (DH == 128 ? kBlockRows * Cfg<DH>::PITCH * 2 : 0), 2 * XCH, BIAS);
 };
 
+// dQ: head dimension 128 (64 takes the four-wave kernel).
 template <int DH>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ? 2 : 4))) void k_attn_bwd_dq_split(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o,
+__global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o,
                                                                const float *lse, float *delta, bf16_t *dqkv, float *dbias,
                                                                int s, int H, int causal) {
+  static_assert(DH == 128, "two waves per SIMD, one workgroup per compute unit, workgroups ranked for that");
   typedef Cfg<DH> C;
   typedef SplitBwd<DH> S;
   constexpr int TILE = S::TILE;
@@ -734,7 +736,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
   const int rg = wave % 4, sub = wave / 4;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
-  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true, DH != 128);
+  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true, false);
   const int head = bc.head, seq = bc.seq, q0 = bc.rb * kBlockRows;
   const bf16_t *base = qkv + int64_t(seq) * s * ld + head * DH;
   const bf16_t *gbase = d_o + int64_t(seq) * s * d + head * DH;
@@ -1025,9 +1027,9 @@ int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, flo
           int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
   bool dq_split = false, dkv_split = false;
-  if constexpr (DH >= 64) {   // enough 16-byte pieces in a 64-row tile for 512 threads
-    dq_split = DH == 128 && split_pays_128(int(grid.x), s, causal);
-    dkv_split = DH == 128 || dkv_split_pays_64(int(grid.x), s, causal);
+  if constexpr (DH >= 64) dkv_split = DH == 128 || dkv_split_pays_64(int(grid.x), s, causal);
+  if constexpr (DH == 128) {
+    dq_split = split_pays_128(int(grid.x), s, causal);
     if (dq_split)
       hipLaunchKernelGGL((k_attn_bwd_dq_split<DH>), grid, dim3(512), SplitBwd<DH>::DQ_LDS, st, (const bf16_t *)qkv,
                          (const bf16_t *)o, (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
@@ -1035,7 +1037,7 @@ int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, flo
   if (!dq_split)   // either writes delta for the next kernel
     hipLaunchKernelGGL((k_attn_bwd_dq_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)o,
                        (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
-  if constexpr (DH >= 64)
+  if constexpr (DH >= 64)   // enough 16-byte pieces in a 64-row tile for 512 threads
     if (dkv_split)
       hipLaunchKernelGGL((k_attn_bwd_dkv_split<DH>), grid, dim3(512), SplitBwd<DH>::DKV_LDS, st, (const bf16_t *)qkv,
                          (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
