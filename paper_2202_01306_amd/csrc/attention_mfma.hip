@@ -13,8 +13,8 @@
 // accumulator to operand without leaving registers.
 //
 // qkv is [T, 3d] with q | k | v thirds, head h at columns h*DH..; lse is [b,H,s].
-// HMY_ATTN_SPLIT=0 (read once per process) runs the forward pass at head dimension 64 on the four-wave kernel
-// instead of the eight-wave one, for timing the two against each other.
+// HMY_ATTN_SPLIT=0 (read once per process) takes the four-wave kernels wherever there is one (forward at head dimensions
+// 64 and 128, dQ at 128, dK/dV at 64) instead of the eight-wave ones, for timing the two against each other.
 #include <cstdlib>
 
 #include "dev_common.h"
@@ -1007,12 +1007,16 @@ inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
 // 39 -> 38 and 51 -> 55; 512 of s = 4096, causal 131 -> 104 and 150 -> 126.
 inline bool split_pays_128(int workgroups, int s, int causal) { return workgroups <= 256 || (causal && s >= 2048); }
 
+inline bool eight_waves_allowed() {
+  static const bool allowed = std::getenv("HMY_ATTN_SPLIT") == nullptr || std::atoi(std::getenv("HMY_ATTN_SPLIT")) != 0;
+  return allowed;
+}
+
 template <int DH>
 int fwd_t(const void *qkv, void *o, float *lse, int b, int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
-  static const bool split = std::getenv("HMY_ATTN_SPLIT") == nullptr || std::atoi(std::getenv("HMY_ATTN_SPLIT")) != 0;
   if constexpr (DH >= 64) {   // enough 16-byte pieces in a 64-row tile for 512 threads
-    if (split && (DH == 64 || split_pays_128(int(grid.x), s, causal))) {
+    if (eight_waves_allowed() && (DH == 64 || split_pays_128(int(grid.x), s, causal))) {
       hipLaunchKernelGGL((k_attn_fwd_mfma_split<DH>), grid, dim3(512), 0, st, (const bf16_t *)qkv, (bf16_t *)o, lse, s, H,
                          causal);
       return check_launch("attn_fwd_mfma_split");
@@ -1027,9 +1031,9 @@ int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, flo
           int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
   bool dq_split = false, dkv_split = false;
-  if constexpr (DH >= 64) dkv_split = DH == 128 || dkv_split_pays_64(int(grid.x), s, causal);
+  if constexpr (DH >= 64) dkv_split = DH == 128 || (eight_waves_allowed() && dkv_split_pays_64(int(grid.x), s, causal));
   if constexpr (DH == 128) {
-    dq_split = split_pays_128(int(grid.x), s, causal);
+    dq_split = eight_waves_allowed() && split_pays_128(int(grid.x), s, causal);
     if (dq_split)
       hipLaunchKernelGGL((k_attn_bwd_dq_split<DH>), grid, dim3(512), SplitBwd<DH>::DQ_LDS, st, (const bf16_t *)qkv,
                          (const bf16_t *)o, (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);

@@ -23,7 +23,8 @@
 //
 // Tuning switches (read once per process): HMY_GEMM_BK = 32 | 64 overrides the K tile of
 // both kernels, HMY_GEMM_STAGES = 3 | 4 the ring depth of the 128x128 kernel,
-// HMY_GEMM_TILE = 128 | 256 the choice between it and the 256x256 kernel.
+// HMY_GEMM_TILE = 128 | 256 the choice between it and the 256x256 kernel.  With any of them set no shape takes the
+// 64x64 tiles.
 #include <algorithm>
 #include <cstdlib>
 
