@@ -988,6 +988,8 @@ static DmaP dma_params(const hmy_gemm_desc &g) {
 // 1024 17.5 -> 11.5, 4096 24 -> 34).  Without a split, 2048x1024 (512 tiles) gains up to K = 2048 (19.6 -> 18.9, 4096
 // 32.5 -> 33.4), 256 tiles at every length measured (1024x1024x8192 56 -> 53).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
+  static const bool larger_forced = std::getenv("HMY_GEMM_BK") || std::getenv("HMY_GEMM_STAGES") || std::getenv("HMY_GEMM_TILE");
+  if (larger_forced) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   if (small_may_split(g) && g.K / small_splits(g) >= 2048) return false;
