@@ -719,7 +719,9 @@ __global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
 // length of one workgroup's life (launch, first tiles' way from memory, K loop, output stage), so four times as many
 // workgroups with a quarter of the work each finish sooner.  Four waves of one 32x32 output each, K tiles of 64, a ring
 // of four stages (64 KiB, two workgroups per unit): a contraction of up to 256 is in flight as a whole before the first
-// multiply.  The contraction is summed in the same order as by the larger kernels: same results, bit for bit.
+// multiply.  Where neither splits the contraction and it is a multiple of 32, it is summed in the same order as by the
+// larger kernels: same results, bit for bit.  (Sums of weight gradients are split by this kernel's own count of tiles, and
+// the larger kernels take a ragged contraction in two parts.)
 // Contractions that are no multiple of 64 are taken as they are: steps past K of the last tile come from a page of zeros,
 // and a 16-byte chunk that K cuts is masked in LDS.
 constexpr int ST = 64, SK = 64, SS = 4;               // tile side, K tile, stages

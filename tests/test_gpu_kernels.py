@@ -349,6 +349,30 @@ def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
         assert torch.equal(c[0], c[1])
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("K", [32, 288, 512, 1024])
+def test_gemm_bf16_small_tiles_sum_like_the_larger_ones(ta, tb, K):
+    """The first 256 rows of a product that takes 128x128 tiles, and of one that takes 256x256 tiles, against the same rows as
+    a product of their own (64x64 tiles): equal bits where no contraction is split and it is a multiple of 32."""
+    say(f"gemm bf16 small against large tiles, K={K} ta={ta} tb={tb}")
+    g = torch.Generator(device="cuda").manual_seed(K)
+    for N in (1024, 2048):
+        M = 8192
+        a = torch.randn((K, M) if ta else (M, K), device="cuda", generator=g).bfloat16()
+        b = torch.randn((K, N) if tb else (N, K), device="cuda", generator=g).bfloat16()
+        bias = torch.randn(N, device="cuda", generator=g).bfloat16()
+        for kw in (dict(c_fp32=1, accumulate=1), dict(c_fp32=1), dict(bias=bias)):
+            # sums take small tiles in a weight gradient's layout alone, and are split from sixteen K tiles on
+            if kw.get("accumulate") and not (ta and tb and K <= 512):
+                continue
+            got = []
+            for rows in (M, 256):
+                c = torch.ones(rows, N, device="cuda", dtype=torch.float32 if "c_fp32" in kw else torch.bfloat16)
+                B.hmy_k_gemm(1, rows, N, K, a, a.shape[1], b, b.shape[1], c, N, ta=ta, tb=tb, **kw)
+                got.append(c[:256])
+            assert torch.equal(got[0], got[1]), (N, sorted(kw))
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1)])
 def test_gemm_fp32(ta, tb):
     say(f"gemm fp32 ta={ta} tb={tb}")
