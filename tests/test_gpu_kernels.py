@@ -481,6 +481,44 @@ def test_attention_eight_and_four_waves(causal, b, s, H, dh):
     _attention_case(prec, pc, dt, tol, causal, b, s, H, dh)
 
 
+@pytest.mark.parametrize("causal,b,s,H,dh", [(1, 2, 60, 8, 32), (0, 1, 250, 16, 64), (1, 1, 1100, 4, 64), (0, 4, 500, 16, 64), (1, 2, 60, 8, 128),
+                                             (0, 1, 500, 8, 128), (0, 17, 130, 8, 128), (1, 1, 2050, 2, 128)])
+def test_attention_bf16_against_64_bits_element_by_element(causal, b, s, H, dh):
+    """Each element against what bf16 roundings (eight significant bits: u = 2^-8 at most) can do to it at most, so that one wrong element shows:
+    o: its own, the probabilities' and their sum's; lse: that sum's; dV: its own, the probabilities' and (through lse) the row's;
+    delta: o's; dS: its own, lse's and delta's; dQ, dK: their own and dS's."""
+    say(f"attention bf16 against 64 bits causal={causal} b={b} s={s} H={H} dh={dh}")
+    T, d, u = b * s, H * dh, 2.0 ** -8
+    g = torch.Generator(device="cuda").manual_seed(s + dh)
+    qkv, do = (torch.randn(T, n, device="cuda", generator=g).bfloat16() for n in (3 * d, d))
+    o, dqkv = torch.empty_like(do), torch.empty_like(qkv)
+    lse, delta = torch.empty(b * H * s, device="cuda"), torch.empty(b * H * s, device="cuda")
+    B.hmy_k_attn_fwd(1, qkv, o, lse, b, s, H, dh, causal)
+    B.hmy_k_attn_bwd(1, qkv, o, do, lse, delta, dqkv, b, s, H, dh, causal)
+    heads = lambda x: x.double().view(b, s, -1, H, dh).permute(2, 0, 3, 1, 4).contiguous()   # [.., b, H, s, dh]
+    t = lambda x: x.transpose(-1, -2).contiguous()
+    q, k, v = heads(qkv)
+    G, scale = heads(do)[0], 1.0 / math.sqrt(dh)
+    S = q @ t(k) * scale
+    if causal:
+        S = S.masked_fill(torch.ones(s, s, device="cuda", dtype=torch.bool).triu(1), -math.inf)
+    P, ref_lse = S.softmax(-1), torch.logsumexp(S, -1)
+    ref_o = P @ v
+    off_o = u * (2 * ref_o.abs() + P @ v.abs())
+    dS = P * (G @ t(v) - (G * ref_o).sum(-1, keepdim=True))
+    off_dS = 2 * u * dS.abs() + P * (G.abs() * off_o).sum(-1, keepdim=True)
+    ref = [("o", ref_o, off_o, heads(o)[0])]
+    for (name, r, off), got in zip((("dq", dS @ k * scale, off_dS @ k.abs() * scale), ("dk", t(dS) @ q * scale, t(off_dS) @ q.abs() * scale),
+                                    ("dv", t(P) @ G, 2 * u * (t(P) @ G.abs()))), heads(dqkv)):
+        ref.append((name, r, off + u * r.abs(), got))
+    assert float((lse.double().view(b, H, s) - ref_lse).abs().max()) < 1.05 * u
+    for name, r, off, got in ref:
+        rel = float((got - r).norm() / r.norm())
+        share = float(((got - r).abs() / (off + 1e-6)).max())    # 1e-6: fp32 sums of a few hundred terms of size 1
+        say(f"  {name}: 2-norm {rel:.2e}, largest error {share:.2f} of its bound")
+        assert share < 1.05 and rel < u, name     # independent roundings: two or three of 0.4 u each in the 2-norm
+
+
 @pytest.mark.parametrize("prec,pc,dt,tol", PRECS)
 @pytest.mark.parametrize("T,V", [(9, 1000), (33, 50257), (4, 2)] + [(2, v + k) for v in (4096, 14336, 32768, 57344) for k in (0, 1)])
 def test_cross_entropy(prec, pc, dt, tol, T, V):
