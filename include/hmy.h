@@ -19,6 +19,9 @@
  *     on the handle's GPU; "pinned" host memory was allocated page-locked
  *     (hmy_host_alloc or any hipHostMalloc-backed allocator);
  *   - a handle is used by one thread at a time;
+ *   - arrays that a call adds onto (written with += below) are read, added to and stored
+ *     like any other result: calls that may overlap, on other streams or from other threads,
+ *     each need one of their own;
  *   - layers: 0 = embedding, 1..n_blocks = transformer blocks,
  *     n_blocks+1 = final LayerNorm + LM head + loss; R = n_blocks + 2;
  *   - linear maps store W as [out, in] row-major, y = x W^T + bias;
@@ -74,9 +77,10 @@ typedef struct hmy_model_spec {
  * "runs each layer individually and records ... compute time"), as hmy_measure_profile
  * returns them.  Times are nanoseconds for ONE microbatch of micro_batch sequences.  Every
  * time comes twice: with the device to itself, and (`_beside`) while host-link traffic runs
- * on other streams as it does beside the compute stream in an iteration (copies arriving
- * from pinned host memory; for the backward figures also a throttled kernel writing to it):
- * kernels run some 10-30 % slower then.  A `_beside` field of 0 means "as alone". */
+ * as it does beside the compute stream in an iteration (copies arriving from pinned host
+ * memory; for the backward figures also copies leaving for it).  Copy engines hardly slow the
+ * kernels; where the outgoing copies are kernels themselves (see HMY_SWAP_OUT_KERNEL) the others
+ * run some 10-30 % slower.  A `_beside` field of 0 means "as alone". */
 typedef struct hmy_measured_profile {
   int32_t micro_batch;
   int32_t reserved_;
@@ -169,7 +173,8 @@ typedef struct hmy_budget {
  * runtime does not offer those (state outside memory that the HIP runtime allocated, for one),
  * incoming copies through streams and device->host traffic through throttled kernels that store to
  * the pinned host arrays.  MEMCPY: hipMemcpyAsync on streams in both directions.  Same bytes, same
- * counters, same results. */
+ * counters, same results.  The engines are the same ones for every handle of a device: handles at
+ * work at the same time share their queues. */
 #define HMY_SWAP_OUT_KERNEL 0
 #define HMY_SWAP_OUT_MEMCPY 1
 
@@ -421,7 +426,9 @@ int hmy_destroy(hmy_handle *h);
  * the copies and around the compute stream's waits cost a few percent of the iteration;
  * 1: every copy, every wait of the compute stream on a swap, and the compute span
  * (t_compute_s, t_h2d_busy_s, t_d2h_busy_s, t_stall_s); 2: also every GEMM launch
- * (gemm_s; two more event records per launch). */
+ * (gemm_s; two more event records per launch).  Where copies take the named engines (see
+ * hmy_copies_on_engines), level 1 or 2 makes the runtime time every asynchronous copy of the
+ * process from then on; that stays on at level 0. */
 int hmy_set_profiling(hmy_handle *h, int32_t level);
 /* on != 0: a layer-pack-major iteration waits for the compute stream after every visit and
  * prints one line per visit to stderr.  For runs under a tool that serialises every kernel
@@ -454,7 +461,8 @@ int hmy_set_kernel_path(int32_t use_mfma);
 /* x[T,d] (fp32) = wte[id] + wpe[t % s] */
 int hmy_k_embed_fwd(int32_t prec, const int32_t *ids, const void *wte, const void *wpe, float *x,
                     int32_t T, int32_t d, int32_t s, int32_t vocab, void *stream);
-/* dwte[id] += dx, dwpe[t % s] += dx  (dx fp32; fp32 accumulators) */
+/* dwte[id] += dx, dwpe[t % s] += dx  (dx fp32; fp32 accumulators, to which nothing else may
+ * add while the call runs: rows are read, added to and stored without atomics) */
 int hmy_k_embed_bwd(int32_t prec, const int32_t *ids, const float *dx, float *dwte, float *dwpe,
                     int32_t T, int32_t d, int32_t s, int32_t vocab, void *stream);
 /* y (type E) = gamma * (x-mean)*rstd + beta; x fp32; mean,rstd [T] fp32 saved */

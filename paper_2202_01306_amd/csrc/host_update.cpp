@@ -5,9 +5,9 @@
 // as the chunks arrive.
 //
 // One dispatcher thread takes jobs in submission order, waits until the job's gradient has
-// arrived (a callback of the engine's: it waits for the HIP event of that chunk's
-// device->host copy; this file itself is plain host C++) and runs the update over a pool of
-// worker threads.  The arithmetic is the same as the device kernel's (fp32; bias corrections passed
+// arrived (a callback of the engine's: it waits for the signal of that chunk's device->host
+// copy, or for its HIP event where copies go through streams; this file itself is plain host
+// C++) and runs the update over a pool of worker threads.  The arithmetic is the same as the device kernel's (fp32; bias corrections passed
 // in as reciprocals; bf16 weight = round-to-nearest-even of the fp32 master).  The inner
 // loop is plain C++ compiled three times (AVX-512, AVX2+FMA, baseline) and picked at run
 // time, because the library is built on one machine and runs on another.

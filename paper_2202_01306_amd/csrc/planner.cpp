@@ -387,6 +387,9 @@ static bool balanced_time_packing(const std::vector<int64_t> &t, const std::vect
 //   slowdown : a visit computes for its layers' times alone, stretched towards their times beside link traffic
 //              in proportion to the share of it for which the device->host link has work queued at its start.
 //   result   : when the last queue falls idle.
+// That is the order in which copies through streams run.  On the named copy engines the engine does better in two
+// places, which the walk leaves out: optimizer state has a queue of its own and is asked for while the visit still
+// computes, and copies hardly slow the kernels beside them (the profile's two sets of times are then about equal).
 uint64_t estimate_iteration_ns(const Model &m, const std::vector<hmy_layer_profile> &prof, const Packs &p,
                                const Split &sp, uint64_t link_MBps) {
   const uint64_t E = m.elem_bytes(), kB = 4 * uint64_t(m.k_arrays());
@@ -440,9 +443,9 @@ uint64_t estimate_iteration_ns(const Model &m, const std::vector<hmy_layer_profi
       if (v + D - S >= 0) s0 = std::max(s0, left[v + D - S]);
       w_ready[v + D] = h2d_free = s0 + vs[v + D].w;
     }
-    // kernels run slower while the host-writing update is busy beside them: the visit's time moves from its
-    // time alone towards its time beside link traffic, in proportion to the share of it for which the outgoing
-    // link still has work queued now (earlier updates, this visit's checkpoints)
+    // kernels run slower beside traffic that goes out (much slower where kernels store it to the host): the visit's
+    // time moves from its time alone towards its time beside link traffic, in proportion to the share of it for which
+    // the outgoing link still has work queued now (earlier updates, this visit's checkpoints)
     uint64_t comp = vs[v].comp;
     if (vs[v].comp_beside > comp && d2h_free > comp_start) {
       const uint64_t backlog = std::min(d2h_free - comp_start, comp);
