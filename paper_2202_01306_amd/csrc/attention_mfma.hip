@@ -14,7 +14,7 @@
 //
 // qkv is [T, 3d] with q | k | v thirds, head h at columns h*DH..; lse is [b,H,s].
 // HMY_ATTN_SPLIT=0 (read once per process) takes the four-wave kernels wherever there is one (forward at head dimensions
-// 64 and 128, dQ at 128, dK/dV at 64) instead of the eight-wave ones, for timing the two against each other.
+// 64 and 128, dQ at 128, dK/dV at 64 and 128) instead of the eight-wave ones, for timing the two against each other.
 #include <cstdlib>
 
 #include "dev_common.h"
@@ -34,6 +34,7 @@ constexpr int kThreads = 256;       // 4 wavefronts, 32 rows of the block tile e
 // accumulators in ordinary vector registers.  Left free to use the accumulation registers it moved the
 // score and output tiles back and forth with v_accvgpr_read / write around every softmax and rescaling
 // (about 100 extra vector instructions per 32 x 32 subtile in kernels that are bound by exactly those).
+// The four-wave dK/dV kernel at head dimension 128 needs more than 256 registers and keeps the default.
 #define HMY_MFMA_IN_VGPRS __attribute__((amdgpu_waves_per_eu(2)))
 constexpr int kBlockRows = 128;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
 // ---------------------------------------------------------------------------------
 // dK, dV.  grid (ceil(s/128), H, b).  Wave w owns keys j0+32w..; Q and dO tiles stream.
 template <int DH>
-__global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_mfma(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 128 ? 1 : 2))) void k_attn_bwd_dkv_mfma(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
                                                                 const float *delta, bf16_t *dqkv, float *dbias, int s,
                                                                 int H, int causal) {
   typedef Cfg<DH> C;
@@ -993,19 +994,33 @@ inline int check_launch(const char *what) {
   return HMY_OK;
 }
 
-// Head dimension 64, dK/dV.  Up to one workgroup per unit, or two with a causal mask over at least eight row blocks.
-// Measured, us, four waves -> eight: 128 workgroups of s = 256 18.7 -> 15.8; causal, 512 workgroups of s = 1024
-// 52 -> 48, of s = 2048 93 -> 76, of s = 128 20 -> 27; causal, 1024 workgroups of s = 1024 76 -> 93, of s = 512 55 -> 68;
-// not causal, 512 of s = 512 35 -> 45.
+// Where the eight-wave kernels pay.  They halve a wave's chain over the streamed rows and pay for it with one workgroup per
+// compute unit and a pass of the partial sums through LDS at the end: rows have to be long enough for the first to matter.
+//
+// Head dimension 64, dK/dV.  Two streamed tiles and more, and up to one workgroup per unit, or two with a causal mask over
+// at least eight row blocks.  Measured, us, four waves -> eight: 128 workgroups of s = 256 18.7 -> 15.8; causal, 512
+// workgroups of s = 1024 52 -> 48, of s = 2048 93 -> 76, of s = 128 20 -> 27; causal, 1024 workgroups of s = 1024 76 -> 93,
+// of s = 512 55 -> 68; not causal, 512 of s = 512 35 -> 45; the whole backward, 128 workgroups of s = 64 11.5 -> 12.3, of 80
+// 16.9 -> 16.3, of 160 21.2 -> 19.9.
 inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
-  return workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512);
+  return s > 64 && (workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512));
 }
-// Head dimension 128: the eight-wave forward and dQ kernels, one workgroup per compute unit, against two of the
-// four-wave ones.  Where there is no second workgroup for a unit, or where a causal mask makes the heaviest row block
-// the whole launch (16 row blocks and more), half the chain wins.  Measured, us, forward and dQ, four waves -> eight:
-// 128 workgroups of s = 512 21 -> 18 and 28 -> 25; 512 of s = 512 31 -> 37 and 46 -> 56; 512 of s = 1024, causal
-// 39 -> 38 and 51 -> 55; 512 of s = 4096, causal 131 -> 104 and 150 -> 126.
-inline bool split_pays_128(int workgroups, int s, int causal) { return workgroups <= 256 || (causal && s >= 2048); }
+// Head dimension 128, dK/dV: from rows of nearly a row block on, at every number of workgroups.  The whole backward, us, four
+// waves -> eight: s = 32, 128 workgroups 12.6 -> 15.3, 2048 77 -> 96; s = 96, 128 25.1 -> 25.7, 2048 209 -> 223; s = 120, 128
+// 31.6 -> 29.8, 2048 270 -> 268; s = 256, 256 51 -> 45.5, 1024 176 -> 160.
+inline bool dkv_split_pays_128(int s) { return s >= 112; }
+// Head dimension 128, forward and dQ: one eight-wave workgroup per compute unit against two of the four-wave ones.  Where
+// there is no second workgroup for a unit, or where a causal mask makes the heaviest row block the whole launch (16 row
+// blocks and more), half the chain wins, dQ's from a later length on (it reads its rows' o as well, and exchanges more).
+// Measured, us, four waves -> eight, forward: 128 workgroups of s = 32 4.4 -> 5.5, of s = 96 7.8 -> 8.5 (causal 8.2 -> 8.7), of
+// 120 9.6 -> 9.7 (9.9 -> 9.5), 64 of 192 11.0 -> 10.6, 128 of 512 21 -> 18; 512 of s = 512 31 -> 37; 512 of s = 1024, causal
+// 39 -> 38; 512 of s = 4096, causal 131 -> 104.  dQ, within the whole backward: 128 workgroups of s = 128 31.2 -> 33.0, 256 of
+// 256 51.0 -> 51.0 (causal 47.9 -> 48.5), 96 of 384 57.8 -> 56.8, 128 of 512 71.8 -> 69.8; alone, 512 of s = 512 46 -> 56, 512 of
+// s = 1024, causal 51 -> 55, 512 of s = 4096, causal 150 -> 126.
+inline bool fwd_split_pays_128(int workgroups, int s, int causal) {
+  return (workgroups <= 256 && s >= (causal ? 112 : 192)) || (causal && s >= 2048);
+}
+inline bool dq_split_pays_128(int workgroups, int s, int causal) { return (workgroups <= 256 && s >= 384) || (causal && s >= 2048); }
 
 inline bool eight_waves_allowed() {
   static const bool allowed = std::getenv("HMY_ATTN_SPLIT") == nullptr || std::atoi(std::getenv("HMY_ATTN_SPLIT")) != 0;
@@ -1016,7 +1031,7 @@ template <int DH>
 int fwd_t(const void *qkv, void *o, float *lse, int b, int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
   if constexpr (DH >= 64) {   // enough 16-byte pieces in a 64-row tile for 512 threads
-    if (eight_waves_allowed() && (DH == 64 || split_pays_128(int(grid.x), s, causal))) {
+    if (eight_waves_allowed() && (DH == 64 || fwd_split_pays_128(int(grid.x), s, causal))) {
       hipLaunchKernelGGL((k_attn_fwd_mfma_split<DH>), grid, dim3(512), 0, st, (const bf16_t *)qkv, (bf16_t *)o, lse, s, H,
                          causal);
       return check_launch("attn_fwd_mfma_split");
@@ -1031,9 +1046,10 @@ int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, flo
           int s, int H, int causal, hipStream_t st) {
   const dim3 grid(((s + kBlockRows - 1) / kBlockRows) * H * b);
   bool dq_split = false, dkv_split = false;
-  if constexpr (DH >= 64) dkv_split = DH == 128 || (eight_waves_allowed() && dkv_split_pays_64(int(grid.x), s, causal));
+  if constexpr (DH >= 64)
+    dkv_split = eight_waves_allowed() && (DH == 128 ? dkv_split_pays_128(s) : dkv_split_pays_64(int(grid.x), s, causal));
   if constexpr (DH == 128) {
-    dq_split = eight_waves_allowed() && split_pays_128(int(grid.x), s, causal);
+    dq_split = eight_waves_allowed() && dq_split_pays_128(int(grid.x), s, causal);
     if (dq_split)
       hipLaunchKernelGGL((k_attn_bwd_dq_split<DH>), grid, dim3(512), SplitBwd<DH>::DQ_LDS, st, (const bf16_t *)qkv,
                          (const bf16_t *)o, (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
@@ -1045,10 +1061,9 @@ int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, flo
     if (dkv_split)
       hipLaunchKernelGGL((k_attn_bwd_dkv_split<DH>), grid, dim3(512), SplitBwd<DH>::DKV_LDS, st, (const bf16_t *)qkv,
                          (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
-  if constexpr (DH != 128)   // at head dimension 128 the eight-wave kernel is the faster one at every size measured
-    if (!dkv_split)
-      hipLaunchKernelGGL((k_attn_bwd_dkv_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)d_o,
-                         lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
+  if (!dkv_split)
+    hipLaunchKernelGGL((k_attn_bwd_dkv_mfma<DH>), grid, dim3(kThreads), 0, st, (const bf16_t *)qkv, (const bf16_t *)d_o,
+                       lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
   return check_launch("attn_bwd_mfma");
 }
 

@@ -474,7 +474,9 @@ def _attention_case(prec, pc, dt, tol, causal, b, s, H, dh):
 # the eight-wave kernels and the four-wave ones on both sides of their rules: few and many workgroups, long causal rows
 @pytest.mark.parametrize("causal,b,s,H,dh", [(1, 1, 1030, 2, 64), (0, 1, 1030, 2, 64), (0, 33, 130, 4, 64), (1, 33, 130, 4, 64),
                                              (0, 17, 130, 8, 128), (1, 17, 130, 8, 128), (1, 1, 2050, 1, 128), (0, 1, 33, 1, 128),
-                                             (1, 17, 2050, 1, 128)])
+                                             (1, 17, 2050, 1, 128), (1, 3, 64, 2, 64), (0, 3, 65, 2, 64), (0, 2, 111, 2, 128),
+                                             (1, 2, 112, 2, 128), (0, 2, 191, 2, 128), (0, 2, 192, 2, 128), (1, 1, 383, 2, 128),
+                                             (0, 1, 384, 2, 128), (0, 40, 31, 8, 128)])
 def test_attention_eight_and_four_waves(causal, b, s, H, dh):
     prec, pc, dt, tol = PRECS[1]
     say(f"attention split causal={causal} b={b} s={s} H={H} dh={dh}")
