@@ -1139,8 +1139,10 @@ int launch_embed_bwd(int prec, const int32_t *ids, const float *dx, float *dwte,
   if (prec != HMY_PREC_FP32 && prec != HMY_PREC_BF16) return fail(HMY_E_INVALID, "unknown precision %d", prec);
   if (T < 1 || d % 8 || s < 1 || T % s) return fail(HMY_E_INVALID, "embed_bwd: bad shape");
   const uint64_t work = uint64_t(T) * (d / 4);
-  // looking through the ids costs T * T comparisons, the atomics T * d additions at over a hundred times the price
-  const bool runs = T <= 32 * int64_t(d) && ((reinterpret_cast<uintptr_t>(dx) | reinterpret_cast<uintptr_t>(dwte)) & 15) == 0;
+  // looking through the ids costs T * T comparisons, the atomics T * d additions at over a hundred times the price; few
+  // tokens' wide rows are not worth a wave each, which walks its row alone (64 tokens of 4096 columns, 50 ids: 7.7 us with
+  // atomics, 14.5 with runs; 256 tokens: no slower)
+  const bool runs = T <= 32 * int64_t(d) && (T >= 256 || d <= 1024) && ((reinterpret_cast<uintptr_t>(dx) | reinterpret_cast<uintptr_t>(dwte)) & 15) == 0;
   if (runs) hipLaunchKernelGGL(k_embed_bwd_wte_runs, dim3((T + 3) / 4), dim3(256), 0, (hipStream_t)st, ids, dx, dwte, T, d);
   else hipLaunchKernelGGL(k_embed_bwd_wte, dim3(grid_for(work, kBlock, 4096)), dim3(kBlock), 0, (hipStream_t)st, ids, dx, dwte, T,
                      d);

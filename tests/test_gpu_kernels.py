@@ -174,8 +174,8 @@ def test_embedding_fwd_bwd_with_repeated_ids(prec, pc, dt, tol):
 
 
 # runs of one id: none, exactly as many as one wave sums, one more, all tokens alike; then more tokens than the search
-# through the ids is used for (32 per column)
-@pytest.mark.parametrize("counts,d", [([1], 8), ([16, 1, 3], 264), ([17, 16], 64), ([33, 1] * 3, 1024), ([700], 128), ([130, 125, 2], 8)])
+# through the ids is used for (32 per column); few tokens of wide rows, on both sides of that line
+@pytest.mark.parametrize("counts,d", [([60, 3], 1024), ([60, 3], 1032), ([250, 5], 1032), ([250, 6], 1032), ([1], 8), ([16, 1, 3], 264), ([17, 16], 64), ([33, 1] * 3, 1024), ([700], 128), ([130, 125, 2], 8)])
 def test_embedding_bwd_runs(counts, d):
     say(f"embed runs {counts} d={d}")
     rng = np.random.default_rng(sum(counts) + d)
