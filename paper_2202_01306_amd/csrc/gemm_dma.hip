@@ -986,15 +986,21 @@ static DmaP dma_params(const hmy_gemm_desc &g) {
 // register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Sums into an
 // fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
 // contraction, and so do weight gradients whose contraction stays long in every workgroup here (sums, 512x512: K = 4096 in
-// four splits 17.7 -> 13.1, 8192 20.1 -> 20.6; 768x768: K = 1024 11.7 -> 11.2, 2048 18.6 -> 18.9, 4096 21 -> 34; 1024x1024:
-// 1024 17.5 -> 11.5, 4096 24 -> 34).  Without a split, 2048x1024 (512 tiles) gains up to K = 2048 (19.6 -> 18.9, 4096
+// four splits 17.7 -> 13.1, 8192 20.1 -> 20.6; 768x768: K = 1024 11.7 -> 11.2, 1920 and 1024x1536x1920 11 % slower, 768x768x4096
+// 21 -> 34; 1024x1024: 1024 17.5 -> 11.5, 4096 24 -> 34), or is too short to be split here and not there: ten to fifteen K tiles
+// over at most 128 tiles (128x64x704 7.5 -> 8.3; 256x256, K = 768 to 960, 22 to 28 % slower; 512 and 576 as fast, 1024 4 %
+// faster, and where K is no multiple of 64 the larger kernels lose: 992 20 % faster).  Without a split, 2048x1024 (512 tiles) gains up to K = 2048 (19.6 -> 18.9, 4096
 // 32.5 -> 33.4), 256 tiles at every length measured (1024x1024x8192 56 -> 53).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
   static const bool larger_forced = std::getenv("HMY_GEMM_BK") || std::getenv("HMY_GEMM_STAGES") || std::getenv("HMY_GEMM_TILE");
   if (larger_forced) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
-  if (small_may_split(g) && g.K / small_splits(g) >= 2048) return false;
+  if (small_may_split(g)) {
+    const int splits = small_splits(g);
+    if (g.K / splits >= 1792) return false;
+    if (tiles <= 128 && splits == 1 && g.K >= 640 && g.K % 64 == 0) return false;
+  }
   if (g.K % 32 != 0) return tiles < 2048;
   return tiles <= 256 || (tiles <= 512 && g.K <= 2048);
 }
