@@ -24,14 +24,14 @@ typedef uint64_t *Signal;
 class SignalWatch {
  public:
   // store: puts a value into a signal and wakes those that wait for it
-  explicit SignalWatch(void (*store)(Signal, int64_t)) : store_(store), thread_([this] { run(); }) {}
+  explicit SignalWatch(void (*store)(Signal, int64_t)) : store_(store) {}
   ~SignalWatch() {
     {
       std::lock_guard<std::mutex> lk(mu_);
       stop_ = true;
     }
     wake_.notify_one();
-    thread_.join();
+    if (thread_.joinable()) thread_.join();
   }
   SignalWatch(const SignalWatch &) = delete;
   SignalWatch &operator=(const SignalWatch &) = delete;
@@ -42,6 +42,7 @@ class SignalWatch {
       std::lock_guard<std::mutex> lk(mu_);
       idle = first_ == in_use_.size();
       in_use_.push_back(s);
+      if (!thread_.joinable()) thread_ = std::thread([this] { run(); });   // only where there is something to watch
     }
     if (idle) wake_.notify_one();
   }
@@ -95,7 +96,7 @@ class SignalWatch {
   size_t first_ = 0;   // everything before it is over
   bool stop_ = false;
   std::atomic<bool> failed_{false};
-  std::thread thread_;   // last: it starts when the rest is there
+  std::thread thread_;
 };
 
 }  // namespace hmy
