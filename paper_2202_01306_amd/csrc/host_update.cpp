@@ -102,7 +102,7 @@ HostAdamJob make_host_adam_job(void *ready, const float *grad, float *master, fl
 }
 
 int default_host_threads() {
-  // a GPU machine gives a process 16 cores per GPU whatever the machine has
+  // sixteen: what a machine with several GPUs leaves for each, whatever it has in all
   int nt = int(std::min(16u, std::max(1u, std::thread::hardware_concurrency())));
   if (const char *e = std::getenv("HMY_HOST_THREADS")) nt = std::max(1, std::min(256, std::atoi(e)));
   return nt;
