@@ -21,7 +21,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
-HOST_LINK_GBPS_ALONE = 54.0    # pinned host <-> HBM, one direction, nothing else running (measured on the GPU machine)
+HOST_LINK_GBPS_ALONE = 54.0    # pinned host <-> HBM, one direction, nothing else running (measured)
 PEAK_FP32_TFLOPS = 157.3
 VARIANTS = ("gemm_mfma<A[M,K],B[N,K]> (forward, recompute)", "gemm_mfma<A[M,K],B[K,N]> (input gradient)",
             "gemm_mfma<A[K,M],B[N,K]>", "gemm_mfma<A[K,M],B[K,N]> (weight gradient)")
