@@ -21,10 +21,12 @@
 // ds_read_b64_tr_b16 with k rows 8h..8h+3 and 8h+4..8h+7 (h = lane/32), which is the
 // same contraction order as the 16-byte read of the other layout.
 //
+// Outputs in between go to 256x256 and 256x128 tiles, small ones to 64x64 tiles (further down).
+//
 // Tuning switches (read once per process): HMY_GEMM_BK = 32 | 64 overrides the K tile of
 // both kernels, HMY_GEMM_STAGES = 3 | 4 the ring depth of the 128x128 kernel,
 // HMY_GEMM_TILE = 128 | 256 the choice between it and the 256x256 kernel.  With any of them set no shape takes the
-// 64x64 tiles.
+// 64x64 or 256x128 tiles.
 #include <algorithm>
 #include <cstdlib>
 
@@ -76,6 +78,31 @@ __device__ __forceinline__ void dma16(const void *base, uint32_t byte_off, uint3
                : "v"(byte_off), "s"(base), "s"(lds_addr)
                : "memory");
 }
+
+// the 16-byte-per-lane copy with a full address per lane
+__device__ __forceinline__ void dma16_at(const void *addr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory");
+}
+// The same through a buffer descriptor, in two parts so that several copies share an LDS base: KIB bytes are added to both
+// addresses by the instruction, `tile_off` to the global one.  Bytes past the descriptor's size read as zeros and cost no
+// memory traffic.  Between the two the compiler writes m0 as little as it does elsewhere in this file (see above).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x4 buffer_of(const void *base, uint32_t bytes) {
+  const uint64_t at = reinterpret_cast<uint64_t>(base);
+  u32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane(uint32_t(at));
+  r[1] = __builtin_amdgcn_readfirstlane(uint32_t(at >> 32) & 0xffffu);   // stride 0
+  r[2] = __builtin_amdgcn_readfirstlane(bytes);
+  r[3] = 0x00020000u;
+  return r;
+}
+__device__ __forceinline__ void set_m0(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "memory"); }
+template <int KIB>
+__device__ __forceinline__ void dma16_buffer(u32x4 rsrc, uint32_t lane_off, uint32_t tile_off) {
+  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen offset:%3 lds" : : "v"(lane_off), "s"(rsrc), "s"(tile_off), "n"(KIB) : "memory");
+}
+// contraction steps past the operands' end come from here
+__device__ __attribute__((aligned(256))) bf16_t g_zero_page[128];   // zero-initialised, never written
 
 // Per-thread, loop-invariant byte offsets of this thread's lanes of every KiB it copies.
 // TR = false: memory [row][k]; KiB c holds rows c*R..c*R+R-1 (R = 512/BK), lane i owns slot i%(BK/8) of row i/(BK/8).
@@ -714,6 +741,190 @@ __global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
   }
 }
 
+// ---- 256x128 tiles -------------------------------------------------------------------
+// The same GEMM for outputs that give the compute units one such tile each but too few 256x256 ones: three quarters of the
+// 128x128 kernel's bytes per multiply through the L2 caches, which is what bounds it.  Eight waves of 64x64 (two per SIMD),
+// K tiles of 64 in a ring of three stages (144 KiB), fragments read two 16-deep steps ahead, one barrier per K tile.  A K
+// tile's fetch is spread over the two steps behind that barrier; it goes through buffer descriptors, which end it without
+// a branch in the loop.  K has to be a multiple of 64.
+// Measured, us, 128x128 tiles -> these: 2048x4096, K = 16384 372 -> 242 (1135 TFLOP/s), input gradient 322 -> 230, K = 4096
+// 106 -> 73; K = 1024 25 -> 22.  Four waves of 128x64, one per SIMD, take as long in the K loop (245, 235) and longer
+// around it (K = 1024 22.4 -> 21.6, 4096x1600x1024 26 -> 24.7): a wave alone on its SIMD has nobody to hide its output stage behind.
+template <bool TA, bool TB>
+__global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int grid_n) {
+  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+  constexpr int BK = 64, S = 3, BTM = 256, BTN = 128;
+  constexpr int SUB = BM * BK;        // elements of one 128-row sub-tile
+  constexpr int STAGE = 3 * SUB;      // elements of one stage: A rows 0-127, A rows 128-255, B
+  constexpr int L = 6;                // load-to-LDS instructions per thread per K tile: 48 KiB over eight waves
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int wm = wave / 2, wn = wave % 2;     // this wave's outputs: rows 64 wm .. +63, columns 64 wn .. +63
+  int bid = blockIdx.x;
+  const int nb = gridDim.x, grid_m = nb / grid_n;
+  {
+    const int x = bid % 8, per = nb / 8, extra = nb % 8;
+    bid = x * per + min(x, extra) + bid / 8;
+  }
+  constexpr int kBand = 4;
+  const int band = bid / (kBand * grid_n), first_m = band * kBand;
+  const int band_rows = min(grid_m - first_m, kBand);
+  const int in_band = bid - band * kBand * grid_n;
+  const int m0 = (first_m + in_band % band_rows) * BTM, n0 = (in_band / band_rows) * BTN;
+
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const int n = p.K / BK;   // K tiles
+  // Byte offsets of this thread's lanes of the KiBs its wave copies: KiBs 2 w and 2 w + 1 of each of the three sub-tiles of 16
+  // KiB, so that one LDS base serves two instructions, the KiB being part of the instruction (which adds it to the global
+  // address as well: taken off here).
+  uint32_t off[3][2];
+#pragma unroll
+  for (int sub = 0; sub < 3; ++sub)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const bool is_a = sub < 2;
+      const uint32_t ld = is_a ? p.lda : p.ldb;
+      const int first = is_a ? m0 + BM * sub : n0, rows = is_a ? p.M : p.N, kib = 2 * wave + j;
+      if (is_a ? TA : TB) {   // k rows 4 kib .. + 3
+        const int col = min(first + (((lane % 16) ^ ((lane / 16) << 2)) * 8), ((rows + 7) & ~7) - 8);
+        off[sub][j] = (uint32_t(4 * kib + lane / 16) * ld + uint32_t(col)) * 2u - 1024u * j;
+      } else {                // rows 8 kib .. + 7
+        const int row = 8 * kib + lane / 8;
+        off[sub][j] = (uint32_t(min(first + row, rows - 1)) * ld + uint32_t(((lane % 8) ^ ((row >> 1) & 7)) * 8)) * 2u - 1024u * j;
+      }
+    }
+  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem)) + 2048u * wave;
+  const uint32_t a_kstep = TA ? uint32_t(BK) * p.lda * 2u : uint32_t(BK) * 2u, b_kstep = TB ? uint32_t(BK) * p.ldb * 2u : uint32_t(BK) * 2u;
+  u32x4 a_buf = buffer_of(p.A, uint32_t(TA ? p.K : p.M) * p.lda * 2u), b_buf = buffer_of(p.B, uint32_t(TB ? p.K : p.N) * p.ldb * 2u);
+  uint32_t a_next = 0, b_next = 0;   // byte offset of the next K tile to fetch
+  // instruction q (0 .. L - 1) of a K tile: piece q % 2 of sub-tile q / 2
+  auto fetch_one = [&](int q, int stage) {
+    const int sub = q / 2;
+    if (q % 2 == 0) set_m0(lds0 + uint32_t(stage) * uint32_t(2 * STAGE) + uint32_t(sub) * uint32_t(2 * SUB));
+    const u32x4 buf = sub < 2 ? a_buf : b_buf;
+    const uint32_t at = sub < 2 ? a_next : b_next;
+    if (q % 2 == 0) dma16_buffer<0>(buf, off[sub][0], at);
+    else dma16_buffer<1024>(buf, off[sub][1], at);
+  };
+  // on to K tile `next`; past the last one the fetches go on, from descriptors of no bytes: no branch around them, and one
+  // count to wait for.  (With a tile offset of 0: the range check takes it off the descriptor's size.)
+  auto advance = [&](int next) {
+    a_next = next < n ? a_next + a_kstep : 0;
+    b_next = next < n ? b_next + b_kstep : 0;
+    if (next >= n) a_buf[2] = b_buf[2] = 0;
+  };
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+#pragma unroll
+    for (int q = 0; q < L; ++q) fetch_one(q, s);
+    advance(s + 1);
+  }
+  // fragments of a 16-deep step, read two steps ahead of their multiplies
+  bf16x8 fa[4][2], fb[4][2];
+  const int a_sub = (wm / 2) * SUB, arow = (wm % 2) * 64, b_sub = 2 * SUB, brow = wn * 64;
+  wait_vm<(S - 1) * L>();
+  __syncthreads();
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      fa[ks][i] = frag<TA, BK>(smem + a_sub, arow + 32 * i, ks, lane);
+      fb[ks][i] = frag<TB, BK>(smem + b_sub, brow + 32 * i, ks, lane);
+    }
+#define HMY_FENCE() __builtin_amdgcn_sched_barrier(0)
+  // step `cur` of a K tile: four multiplies, each followed by a fragment read of step `nks` of the tile in `nstage`, and by
+  // the instructions i0, i0 + 1 and i0 + 2 that fetch a tile into `fstage` (none if i0 is negative)
+  auto step = [&](int cur, int nstage, int nks, int i0, int fstage) {
+    const int nxt = (cur + 2) & 3;
+    const bf16_t *a_s = smem + nstage * STAGE + a_sub, *b_s = smem + nstage * STAGE + b_sub;
+    HMY_FENCE();
+    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][0], acc[0][0], 0, 0, 0);
+    HMY_FENCE();
+    fa[nxt][0] = frag<TA, BK>(a_s, arow, nks, lane);
+    HMY_FENCE();
+    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][1], acc[0][1], 0, 0, 0);
+    HMY_FENCE();
+    fb[nxt][0] = frag<TB, BK>(b_s, brow, nks, lane);
+    if (i0 >= 0) fetch_one(i0, fstage);
+    HMY_FENCE();
+    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][1], fb[cur][0], acc[1][0], 0, 0, 0);
+    HMY_FENCE();
+    fb[nxt][1] = frag<TB, BK>(b_s, brow + 32, nks, lane);
+    if (i0 >= 0) fetch_one(i0 + 1, fstage);
+    HMY_FENCE();
+    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][1], fb[cur][1], acc[1][1], 0, 0, 0);
+    HMY_FENCE();
+    fa[nxt][1] = frag<TA, BK>(a_s, arow + 32, nks, lane);
+    if (i0 >= 0) fetch_one(i0 + 2, fstage);
+    HMY_FENCE();
+  };
+  Epi e;
+  e.init(p, m0, n0, BTM);
+  e.inside = m0 + BTM <= p.M && n0 + BTN <= p.N;
+  const int m_tile = m0 + wm * 64, n_tile = n0 + wn * 64;
+  Epi::Pre pre[2][4];
+  float4 bias8 = make_float4(0.f, 0.f, 0.f, 0.f);
+  int stage = 0;   // of tile t
+#pragma unroll 1
+  for (int t = 0; t < n; ++t) {
+    const int next = stage + 1 == S ? 0 : stage + 1;
+    step(0, stage, 2, -1, 0);
+    step(1, stage, 3, -1, 0);
+    wait_vm<(S - 2) * L>();   // tile t + 1 has landed once at most the S - 2 tiles behind it are outstanding
+    __syncthreads();          // tile t + 1 visible to every wave; every wave has read tile t
+    // (behind the last tile the reads bring in what nobody multiplies)
+    step(2, next, 0, 0, stage);
+    step(3, next, 1, 3, stage);
+    advance(t + S + 1);
+    stage = next;
+  }
+#undef HMY_FENCE
+  if (e.fast) {
+    if (p.bias && (e.inside || n_tile + 8 * (lane % 8) + 8 <= p.N))
+      bias8 = *reinterpret_cast<const float4 *>(p.bias + n_tile + 8 * (lane % 8));
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e.prefetch(p, m_tile + 32 * i + 8 * q + lane / 8, n_tile + 8 * (lane % 8), pre[i][q]);
+  }
+  // output stage as in the 128x128 kernel, both slabs of a wave in LDS at once
+  wait_vm<0>();      // the last fetches, of nothing, have been written to LDS
+  __syncthreads();   // every wave has finished reading the operand stages
+  float *slab = reinterpret_cast<float *>(smem) + wave * 4096;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = 8 * (r / 4) + 4 * (lane / 32) + r % 4, col = 32 * j + lane % 32;
+        slab[i * 2048 + row * 64 + (col ^ (((row >> 2) & 1) << 5))] = acc[i][j][r];
+      }
+  if (e.fast) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 8 * q + lane / 8, c0 = 8 * (lane % 8);
+        e.emit8(p, m_tile + 32 * i + row, n_tile + c0, slab + i * 2048 + row * 64 + (c0 ^ (((row >> 2) & 1) << 5)), pre[i][q], bias8);
+      }
+  } else {
+#pragma unroll 1
+    for (int idx = lane; idx < 64 * 64; idx += 64) {   // one row of 64 columns per pass
+      const int row = idx / 64, col = idx % 64;
+      const int m = m_tile + row, nn = n_tile + col;
+      if (m < p.M && nn < p.N) e.emit_one(p, m, nn, slab[row * 64 + (col ^ (((row >> 2) & 1) << 5))]);
+    }
+  }
+}
+
 // ---- small outputs --------------------------------------------------------------------
 // The same GEMM on 64x64 tiles for outputs whose 128x128 tiles leave most compute units idle: what bounds those is the
 // length of one workgroup's life (launch, first tiles' way from memory, K loop, output stage), so four times as many
@@ -726,12 +937,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
 // and a 16-byte chunk that K cuts is masked in LDS.
 constexpr int ST = 64, SK = 64, SS = 4;               // tile side, K tile, stages
 constexpr int kSmallOp = ST * SK;                      // elements of one operand and stage
-__device__ __attribute__((aligned(256))) bf16_t g_zero_page[128];   // zero-initialised, never written
 
-// the 16-byte-per-lane copy with a full address per lane
-__device__ __forceinline__ void dma16_at(const void *addr, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory");
-}
 // element address inside a [k][64 rows] tile: 8 chunks per k-row of 128 bytes, swizzled so that the four k-rows of a
 // transposed read fall on different banks
 __device__ __forceinline__ int addr_kr64(int k, int col) { return k * ST + ((((col >> 3) ^ ((k & 2) << 1)) & 7) << 3) + (col & 7); }
@@ -932,6 +1138,17 @@ int launch_cfg256(const hmy_gemm_desc &g, const DmaP &p, dim3 grid, int gn, hipS
   return check_launch("gemm_dma256");
 }
 
+int launch_256x128(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
+  const int gm = (g.M + 255) / 256, gn = (g.N + 127) / 128;
+  const size_t lds = size_t(3) * 3 * BM * 64 * sizeof(bf16_t);
+  const dim3 grid(gm * gn), block(512);
+  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, false>), grid, block, lds, s, p, gn);
+  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, true>), grid, block, lds, s, p, gn);
+  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<true, false>), grid, block, lds, s, p, gn);
+  else hipLaunchKernelGGL((k_gemm_dma_256x128<true, true>), grid, block, lds, s, p, gn);
+  return check_launch("gemm_dma_256x128");
+}
+
 bool small_may_split(const hmy_gemm_desc &g) { return g.accumulate && g.c_fp32 && !g.bias && !g.res; }
 // a long contraction over few tiles that may be split (fp32 atomics into C): while it fills idle compute units and
 // leaves each workgroup at least eight K tiles
@@ -1017,6 +1234,17 @@ int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
     // (2048 x 4800 x 1600) 49 against 57 us, 175 (1600 x 6400 x 2048) 71 against 72 us, 64 much slower.
     const int gm2 = (g.M + 255) / 256, gn2 = (g.N + 255) / 256, wgs = gm2 * gn2;
     const bool fills = wgs >= 144 && (wgs <= 256 || wgs >= 384);
+    // 256x128 tiles (force_tile: never) where they are one round of nearly all compute units and 256x256 ones are not, or three
+    // rounds against two poorly filled ones.  Speed-up over the kernel taken otherwise, at 144 to 256 tiles: forward and input
+    // gradients K = 512 0.87 to 1.16, 1024 1.03 to 1.25, 2048 1.10 to 1.36, 4096 1.13 to 1.60; sums into C, whose output stage is
+    // twice as long, K = 1024 1.09 to 1.12 up to 156 tiles and 0.96 to 1.01 beyond, 2048 1.01 to 1.17.  128 tiles: 0.86 to 0.93.
+    // Three rounds: 2048x12288x4096 214 -> 186, 3072x6144 (576 tiles) K = 2048 0.98 to 1.08, 4096 1.05 to 1.15.
+    // (Not where 128x128 tiles are one round too, as with few rows over the middle of a tile.)
+    const int w2 = gm2 * ((g.N + 127) / 128), w1 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    const bool one_round = !fills && w1 > 256 && w2 >= 144 && w2 <= 256 && g.K >= (!g.accumulate ? 1024 : w2 <= 160 ? 512 : 2048);
+    const bool three_rounds = wgs > 256 && wgs <= 384 && w2 > 512 && w2 <= 768 && g.K >= 2048 && !g.accumulate;
+    if (force_tile == 0 && force_bk == 0 && force_s == 0 && g.M >= 256 && g.K % 64 == 0 && (one_round || three_rounds))
+      return launch_256x128(g, p, (hipStream_t)st);
     if (force_tile != 128 && g.M >= 256 && g.N >= 256 && (force_tile == 256 || fills)) {
       // K tiles of 64 where an operand has the contraction index contiguous (whole cache lines of its rows)
       bool deep = (!g.ta || !g.tb) && g.K % 64 == 0;

@@ -324,6 +324,22 @@ def test_gemm_bf16_tiles_that_stick_out_of_c():
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+def test_gemm_bf16_256x128_tiles(ta, tb):
+    """One round of them, with edge tiles that stick out of C in both directions, three rounds, and the shortest contractions
+    that go there; every output stage.  Bounds as for the other tiles, of which these have the order of sums."""
+    args = ("bf16", 1, torch.bfloat16, 2e-2)
+    for M, N, K in ((2040, 2296, 1024), (2104, 3840, 1088)):
+        say(f"gemm bf16 256x128 ta={ta} tb={tb} {M}x{N}x{K}")
+        _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, True, False, True)
+        _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, False, True, True)
+        _gemm_case(*args, M, N, K, ta, tb, 1, 0, True, True, False, True, res_fp32=1)
+    _gemm_case(*args, 2040, 2296, 512, ta, tb, 1, 1, False, False, False, True)      # sums into C: few tiles, and many
+    _gemm_case(*args, 2048, 4096, 2048, ta, tb, 1, 1, False, False, False, True)
+    _gemm_case(*args, 2048, 2300 if not tb else 2296, 1024, ta, tb, 1, 0, False, False, False, True)   # rows of C that allow no 16-byte access
+    _gemm_case(*args, 2048, 8968, 2048, ta, tb, 0, 0, True, False, False, True)      # three rounds
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 7), (72, 136, 63), (65, 57, 65), (200, 264, 250), (480, 256, 321),
                                    (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049), (2048, 1024, 2080),
                                    (200, 264, 576), (200, 264, 640), (200, 264, 960), (200, 264, 1000), (768, 776, 1728), (768, 776, 1792)])
