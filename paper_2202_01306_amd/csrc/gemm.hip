@@ -355,8 +355,11 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
   if (mfma_ok && g_use_mfma == 1 && gemm_prefers_small(g)) return launch_gemm_small(g, st);
   if (mfma_ok && g_use_mfma == 1 && gemm_dma_eligible(g)) return launch_gemm_dma(g, st);
   if (mfma_ok && g_use_mfma == 1 && g.K % 32 != 0 && g.K > 256 && g.accumulate && g.c_fp32 && !g.bias && !g.res) {
-    // accumulating GEMM with a ragged contraction: the multiple-of-32 part goes to the
-    // load-to-LDS kernel, the tail is added by the register-staged one (which masks)
+    // accumulating GEMM with a ragged contraction: the multiple-of-32 part goes to the load-to-LDS kernels, the tail is
+    // added on 64x64 tiles, which take any contraction: a single K tile, so a workgroup's life is the way to memory and back
+    // and many short ones do best
+    // (on the register-staged kernel's 128x128 tiles the tail of 17 steps alone took 31 us at 2048x1024: 2048x1024x50257 314 ->
+    // 299 us, 480x256x5003 36 -> 16, weight gradients 4096x4096x1023 110 -> 81, 50257x1024x2047 465 -> 383)
     hmy_gemm_desc body = g, tail = g;
     body.K = g.K / 32 * 32;
     tail.K = g.K - body.K;
@@ -364,7 +367,7 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
     tail.B = static_cast<const bf16_t *>(g.B) + (g.tb ? int64_t(body.K) * g.ldb : int64_t(body.K));
     if (gemm_dma_eligible(body) && aligned16(tail.A) && aligned16(tail.B)) {
       const int rc = launch_gemm_dma(body, st);
-      return rc ? rc : launch_gemm_mfma32(tail, st);
+      return rc ? rc : launch_gemm_small(tail, st);
     }
   }
   if (mfma_ok && g_use_mfma != 2) return launch_gemm_mfma32(g, st);

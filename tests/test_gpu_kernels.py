@@ -305,6 +305,15 @@ def test_gemm_bf16_large_outputs_epilogues():
     _gemm_case(*args, 512, 50257, 64, 0, 0, 1, 0, False, False, False, True, 8)
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 1)])
+@pytest.mark.parametrize("K", [257, 289, 300, 319])
+def test_gemm_bf16_sums_with_a_ragged_contraction(ta, tb, K):
+    """More outputs than any product takes on 64x64 tiles: the multiple of 32 on larger tiles, the 1, 12 or 31 steps behind it on
+    those."""
+    say(f"gemm bf16 sums ta={ta} tb={tb} K={K}")
+    _gemm_case("bf16", 1, torch.bfloat16, 2e-2, 3080, 3336, K, ta, tb, 1, 1, False, False, False, True, -K % 8)
+
+
 def test_gemm_bf16_tiles_that_stick_out_of_c():
     """Outputs whose width is no multiple of the block tile, with 16-byte aligned rows: whole groups of 8 columns of an
     edge tile leave through the vector path, a ragged last group element by element; nothing beyond N is written."""
