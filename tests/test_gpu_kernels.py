@@ -430,6 +430,16 @@ def test_attention_fp32_one_and_several_waves(causal, b, s, H, dh):
     _attention_case("fp32", 0, torch.float32, 1e-5, causal, b, s, H, dh)
 
 
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("b,s,H,dh", [(1, 32, 3, 64), (3, 33, 2, 32), (2, 64, 2, 128), (2, 65, 3, 64), (1, 97, 2, 128), (4, 65, 24, 32),
+                                      (2, 140, 40, 64), (2, 130, 40, 128), (6, 66, 60, 32)])
+def test_attention_fp32_tiles_split_over_waves(causal, b, s, H, dh):
+    """One, two and four waves per 32 rows: a single tile, waves without one, a ragged last tile, and launches on either side of
+    the numbers of rows from which fewer waves share them (288, 400 and 1080 groups)."""
+    say(f"attention fp32 split causal={causal} b={b} s={s} H={H} dh={dh}")
+    _attention_case("fp32", 0, torch.float32, 1e-5, causal, b, s, H, dh)
+
+
 def test_gemm_rejects_bad_arguments():
     a = torch.zeros(64, 64, device="cuda", dtype=torch.bfloat16)
     with pytest.raises(B.HmyError) as e:
