@@ -123,6 +123,55 @@ __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16 &a, int c) {
 // tile row (0..31) held in accumulator register r by a lane of half h
 __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
+// dK/dV of a 32x32 subtile: lane owns a key, accumulator registers run over its 32 queries, sixteen per lane in four runs of
+// four consecutive rows (16-byte reads of the rows' statistics).
+// The product dO V^T starts from the queries' -delta, so that it ends as dP - delta.
+__device__ __forceinline__ f32x16 minus_delta(const float *minus, int h2) {
+  f32x16 v;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float4 d = *reinterpret_cast<const float4 *>(minus + 8 * g + 4 * h2);
+    v[4 * g] = d.x; v[4 * g + 1] = d.y; v[4 * g + 2] = d.z; v[4 * g + 3] = d.w;
+  }
+  return v;
+}
+// scores -> P (in place), dP - delta -> dS (in place).  `edge`, the same for the whole wave: queries past the sequence end or
+// (causal) before the key may be among them; the test stands outside of the loop over registers, where the compiler made
+// sixteen branches of it, each around one exponential.  The whole backward, with dQ's products begun at -delta as well: 16 heads of
+// 64, causal, s = 4096 207 -> 171 us, four of s = 1024 75 -> 65, 32 heads of 32, s = 2048 244 -> 177; of 128, causal, 197 -> 188.
+__device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const float *lse, int h2, float sc, bool edge, int ib, int s,
+                                              int key, int causal) {
+  float L[16];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) *reinterpret_cast<float4 *>(L + 4 * g) = *reinterpret_cast<const float4 *>(lse + 8 * g + 4 * h2);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sm[r] = fmaf(sm[r], sc, -L[r]);
+  if (edge) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int qi = ib + acc_row(r, h2);
+      sm[r] = qi < s && (!causal || key <= qi) ? sm[r] : -INFINITY;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    sm[r] = fast_exp2(sm[r]);   // P
+    dp[r] *= sm[r];             // dS
+  }
+}
+
+// scores of a 32-key subtile from key kb on, lane owns query q of the wave's 32 from qw on: keys past the sequence end or (causal)
+// past the query get no weight.  Only a diagonal and the last subtile hold any.
+__device__ __forceinline__ void mask_keys(f32x16 &st, int kb, int qw, int q, int s, int h2, int causal) {
+  if (kb + 32 > s || (causal && kb + 31 > qw)) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = kb + acc_row(r, h2);
+      if (!(key < s && (!causal || key <= q))) st[r] = -INFINITY;
+    }
+  }
+}
+
 // db[c] += sum over the workgroup's 128 rows of the values stored from the accumulators (scaled and rounded to bf16
 // as they are stored; rows that are not stored count as zero): the bias gradient of the QKV projection, taken while
 // the gradient of its output is still in registers.  acc[t][r] of lane l in wave w belongs to row 32 w + l % 32,
@@ -494,6 +543,9 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
   if (h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
   const float L = lse[(int64_t(seq) * H + head) * s + q_ld] * kLog2e;   // log2 units
   const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
+  f32x16 minus_dl;   // what the products dO V^T start from
+#pragma unroll
+  for (int r = 0; r < 16; ++r) minus_dl[r] = -dl;
   f32x16 acc_q[C::DTILES];
 #pragma unroll
   for (int t = 0; t < C::DTILES; ++t) acc_q[t] = zero16();
@@ -518,24 +570,15 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
       for (int sub = 0; sub < C::TILE / 32; ++sub) {
         const int kb = k0 + 32 * sub;
         if (causal && kb > qw + 31) continue;
-        f32x16 st = zero16(), dp = zero16();
+        f32x16 st = zero16(), dp = minus_dl;
 #pragma unroll
         for (int c = 0; c < C::KSTEPS; ++c) {
           st = mfma(frag_row<DH>(sK[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);   // S^T = K Q^T
-          dp = mfma(frag_row<DH>(sV[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T = V dO^T
+          dp = mfma(frag_row<DH>(sV[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T - delta = V dO^T - delta
         }
-        if (kb + 32 > s || (causal && kb + 31 > qw)) {   // diagonal or ragged subtile: per-element test
+        mask_keys(st, kb, qw, q, s, h2, causal);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kb + acc_row(r, h2);
-            const bool ok = key < s && (!causal || key <= q);
-            const float p = ok ? fast_exp2(fmaf(st[r], sc, -L)) : 0.f;
-            st[r] = p * (dp[r] - dl);                                                             // dS^T
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * (dp[r] - dl);
-        }
+        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * dp[r];            // dS^T
         // dQ^T[dh, query] += K^T dS^T
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -608,7 +651,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
     rg.fetch(gbase + int64_t(i0) * d, d, nv, tid);
     if (tid < C::TILE) {
       rl = tid < nv ? lbase[i0 + tid] * kLog2e : 0.f;
-      rd = tid < nv ? dbase[i0 + tid] : 0.f;
+      rd = tid < nv ? -dbase[i0 + tid] : 0.f;
     }
   };
   auto put = [&](int buf) {
@@ -637,31 +680,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
     for (int sub = 0; sub < C::TILE / 32; ++sub) {
       const int ib = i0 + 32 * sub;                       // first query of the subtile
       if (causal && ib + 31 < jw) continue;               // every query precedes every key of this wave
-      // S[query, key] = Q K^T and dP[query, key] = dO V^T: lane owns a key, registers run over queries
-      f32x16 sm = zero16(), dp = zero16();
+      // S[query, key] = Q K^T and dP[query, key] - delta[query] = dO V^T - delta: lane owns a key, registers run over queries
+      f32x16 sm = zero16(), dp = minus_delta(sD[cur] + 32 * sub, h2);
 #pragma unroll
       for (int c = 0; c < C::KSTEPS; ++c) {
         sm = mfma(frag_row<DH>(sQ[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fk[c], sm);
         dp = mfma(frag_row<DH>(sG[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fv[c], dp);
       }
-      // queries past the sequence end or (causal) before the key: only the diagonal and
-      // the last subtile need the per-element test
-      const bool edge = ib + 32 > s || (causal && ib < jw + 31);
-      // the lane's sixteen queries are four runs of four consecutive rows: 16-byte reads
-      float ql[16], qd[16];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        *reinterpret_cast<float4 *>(ql + 4 * g) = *reinterpret_cast<const float4 *>(&sL[cur][32 * sub + 8 * g + 4 * h2]);
-        *reinterpret_cast<float4 *>(qd + 4 * g) = *reinterpret_cast<const float4 *>(&sD[cur][32 * sub + 8 * g + 4 * h2]);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int qi = 32 * sub + acc_row(r, h2);         // query inside the tile
-        const bool ok = !edge || (i0 + qi < s && (!causal || key <= i0 + qi));
-        const float p = ok ? fast_exp2(fmaf(sm[r], sc, -ql[r])) : 0.f;
-        sm[r] = p;                                        // P
-        dp[r] = p * (dp[r] - qd[r]);                      // dS
-      }
+      probabilities(sm, dp, sL[cur] + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
@@ -705,9 +731,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
 // of a streamed tile that a thread carries in registers, so the next tile is fetched during the multiplies here too.
 // What fits no registers twice (two accumulator sets of dK/dV need more than 128) leaves one such workgroup per compute
 // unit, whose waves pass every barrier together; two four-wave workgroups do not, and where both always have work they
-// are the faster (the rules at the launchers).  Measured, us, four waves -> eight: dK/dV at head dimension 64, causal,
-// 16 heads, s = 4096 184 -> 138, s = 1024 47 -> 33; at head dimension 128, 8 heads, two sequences of 4096, causal
-// 439 -> 227, not causal 676 -> 428; dQ there 150 -> 126.
+// are the faster (the rules and their measurements at the launchers).
 template <int DH> struct SplitBwd {
   static constexpr int TILE = 64, NTHR = 512;
   static constexpr int TILE_ELEMS = TILE * Cfg<DH>::PITCH;
@@ -757,6 +781,9 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(con
   if (sub == 0 && h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
   const float L = lse[(int64_t(seq) * H + head) * s + q_ld] * kLog2e;   // log2 units
   const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
+  f32x16 minus_dl;   // what the products dO V^T start from
+#pragma unroll
+  for (int r = 0; r < 16; ++r) minus_dl[r] = -dl;
   f32x16 acc_q[C::DTILES];
 #pragma unroll
   for (int t = 0; t < C::DTILES; ++t) acc_q[t] = zero16();
@@ -778,24 +805,15 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(con
     }
     const int kb = k0 + 32 * sub;   // first key of this wave's subtile
     if (kb < s && (!causal || kb <= qw + 31)) {   // some query of this wave sees some key of it
-      f32x16 st = zero16(), dp = zero16();
+      f32x16 st = zero16(), dp = minus_dl;
 #pragma unroll
       for (int c = 0; c < C::KSTEPS; ++c) {
         st = mfma(frag_row<DH>(sK(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);   // S^T = K Q^T
-        dp = mfma(frag_row<DH>(sV(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T = V dO^T
+        dp = mfma(frag_row<DH>(sV(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T - delta = V dO^T - delta
       }
-      if (kb + 32 > s || (causal && kb + 31 > qw)) {   // diagonal or ragged subtile: per-element test
+      mask_keys(st, kb, qw, q, s, h2, causal);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kb + acc_row(r, h2);
-          const bool ok = key < s && (!causal || key <= q);
-          const float p = ok ? fast_exp2(fmaf(st[r], sc, -L)) : 0.f;
-          st[r] = p * (dp[r] - dl);                                                           // dS^T
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * (dp[r] - dl);
-      }
+      for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * dp[r];            // dS^T
       // dQ^T[dh, query] += K^T dS^T
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -895,7 +913,7 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
     rgr.fetch(gbase + int64_t(i0) * d, d, nv, tid);
     if (tid < TILE) {
       rl = tid < nv ? lbase[i0 + tid] * kLog2e : 0.f;
-      rd = tid < nv ? dbase[i0 + tid] : 0.f;
+      rd = tid < nv ? -dbase[i0 + tid] : 0.f;
     }
   };
   auto put = [&](int buf) {
@@ -915,32 +933,15 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
     if (more) fetch(i0 + TILE);   // next tile's loads fly during this tile's multiplies
     const int ib = i0 + 32 * sub;   // first query of this wave's subtile
     if (ib < s && (!causal || ib + 31 >= jw)) {   // some query of it sees some key of this wave
-      // S[query, key] = Q K^T and dP[query, key] = dO V^T: lane owns a key, registers run over queries
-      f32x16 sm = zero16(), dp = zero16();
+      // S[query, key] = Q K^T and dP[query, key] - delta[query] = dO V^T - delta: lane owns a key, registers run over queries
+      f32x16 sm = zero16(), dp = minus_delta(sD + cur * TILE + 32 * sub, h2);
 #pragma unroll
       for (int c = 0; c < C::KSTEPS; ++c) {
         sm = mfma(frag_row<DH>(sQ(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fk[c], sm);
         const bf16x8 v = kVInLds ? frag_row<DH>(sV, 32 * rg + lane % 32, 16 * c + 8 * h2) : fv[kVInLds ? 0 : c];
         dp = mfma(frag_row<DH>(sG(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), v, dp);
       }
-      // queries past the sequence end or (causal) before the key: only the diagonal and
-      // the last subtile need the per-element test
-      const bool edge = ib + 32 > s || (causal && ib < jw + 31);
-      // the lane's sixteen queries are four runs of four consecutive rows: 16-byte reads
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float ql[4], qd[4];
-        *reinterpret_cast<float4 *>(ql) = *reinterpret_cast<const float4 *>(sL + cur * TILE + 32 * sub + 8 * g + 4 * h2);
-        *reinterpret_cast<float4 *>(qd) = *reinterpret_cast<const float4 *>(sD + cur * TILE + 32 * sub + 8 * g + 4 * h2);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int r = 4 * g + k, qi = ib + acc_row(r, h2);
-          const bool ok = !edge || (qi < s && (!causal || key <= qi));
-          const float p = ok ? fast_exp2(fmaf(sm[r], sc, -ql[k])) : 0.f;
-          sm[r] = p;                                        // P
-          dp[r] = p * (dp[r] - qd[k]);                      // dS
-        }
-      }
+      probabilities(sm, dp, sL + cur * TILE + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
@@ -997,18 +998,17 @@ inline int check_launch(const char *what) {
 // Where the eight-wave kernels pay.  They halve a wave's chain over the streamed rows and pay for it with one workgroup per
 // compute unit and a pass of the partial sums through LDS at the end: rows have to be long enough for the first to matter.
 //
-// Head dimension 64, dK/dV.  Two streamed tiles and more, and up to one workgroup per unit, or two with a causal mask over
-// at least eight row blocks.  Measured, us, four waves -> eight: 128 workgroups of s = 256 18.7 -> 15.8; causal, 512
-// workgroups of s = 1024 52 -> 48, of s = 2048 93 -> 76, of s = 128 20 -> 27; causal, 1024 workgroups of s = 1024 76 -> 93,
-// of s = 512 55 -> 68; not causal, 512 of s = 512 35 -> 45; the whole backward, 128 workgroups of s = 64 11.5 -> 12.3, of 80
-// 16.9 -> 16.3, of 160 21.2 -> 19.9.
+// Head dimension 64, dK/dV.  Long rows, and up to one workgroup per unit, or two with a causal mask over sixteen row blocks
+// and more.  The whole backward, us, four waves -> eight: 128 workgroups of s = 128 15.5 -> 16.9, of s = 256 20.2 -> 20.9, 256 of s = 512
+// 32.6 -> 32.3, 512 of s = 512 49.0 -> 49.5; causal, 512 of s = 1024 58.9 -> 60.9, of s = 2048 99 -> 97, of s = 4096 179 -> 168, 1024 of
+// s = 1024 102.3 -> 102.5.
 inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
-  return s > 64 && (workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512));
+  return (workgroups <= 256 && s >= 384) || (causal && s >= 2048 && workgroups <= 512);
 }
-// Head dimension 128, dK/dV: from rows of nearly a row block on, at every number of workgroups.  The whole backward, us, four
-// waves -> eight: s = 32, 128 workgroups 12.6 -> 15.3, 2048 77 -> 96; s = 96, 128 25.1 -> 25.7, 2048 209 -> 223; s = 120, 128
-// 31.6 -> 29.8, 2048 270 -> 268; s = 256, 256 51 -> 45.5, 1024 176 -> 160.
-inline bool dkv_split_pays_128(int s) { return s >= 112; }
+// Head dimension 128, dK/dV: from rows of more than a row block on, at every number of workgroups.  The whole backward, us, four
+// waves -> eight: 128 workgroups of s = 120 29.9 -> 29.6, 256 of s = 128 33.2 -> 35.4, of s = 256 46.2 -> 43.0, 128 of s = 512 63 -> 54,
+// 512 of s = 512 129 -> 114, causal of s = 1024 156 -> 119, of s = 4096 493 -> 320.
+inline bool dkv_split_pays_128(int s) { return s >= 160; }
 // Head dimension 128, forward and dQ: one eight-wave workgroup per compute unit against two of the four-wave ones.  Where
 // there is no second workgroup for a unit, or where a causal mask makes the heaviest row block the whole launch (16 row
 // blocks and more), half the chain wins, dQ's from a later length on (it reads its rows' o as well, and exchanges more).
