@@ -1110,6 +1110,160 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, 
   }
 }
 
+// The same for contractions that are a multiple of 64.  What bounds a workgroup that has its SIMDs to itself is each wave's
+// own instruction stream: 128 cycles of multiplies per K tile among branches, waits and LDS reads that follow one another.
+// So: no branch in the loop (the fetches go through buffer descriptors, as on 256x128 tiles, and end by themselves), the
+// next tile's fragments are read while this one's are multiplied, and what the output stage adds is fetched before the loop.
+// Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), x768 8.2 -> 7.1, x256 5.4 -> 5.6;
+// weight gradient 1024x1024x1024 12.1 -> 8.7.
+template <bool TA, bool TB>
+__global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_split, int grid_n, int splits) {
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[SS * 2 * kSmallOp];
+  constexpr int L = 4;   // load-to-LDS instructions per thread per K tile
+  static_assert(SS == 4, "stages are counted modulo 4");
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int wm = wave / 2, wn = wave % 2;
+  int bid = blockIdx.x, split_idx = 0;
+  const int nb = gridDim.x / splits, grid_m = nb / grid_n;
+  if (splits > 1) {   // as in the 128x128 kernel
+    split_idx = bid % splits;
+    bid /= splits;
+  } else {
+    const int x = bid % 8, per = nb / 8, extra = nb % 8;
+    bid = x * per + min(x, extra) + bid / 8;
+  }
+  constexpr int kBand = 8;
+  const int band = bid / (kBand * grid_n), first_m = band * kBand;
+  const int band_rows = min(grid_m - first_m, kBand);
+  const int in_band = bid - band * kBand * grid_n;
+  const int m0 = (first_m + in_band % band_rows) * ST, n0 = (in_band / band_rows) * ST;
+  const int kt0 = split_idx * tiles_per_split;
+  const int n = min(p.K / SK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
+
+  Epi e;
+  e.init(p, m0, n0, ST);
+  const bool split = splits > 1;
+  // lane's share of the output: pass q -> row 16 q + lane/4, columns 8 (lane%4) .. +7 of the wave's 32x32
+  const int m_tile = m0 + wm * 32, n_tile = n0 + wn * 32, n_lane = n_tile + 8 * (lane % 4);
+  Epi::Pre pre[2];
+  float4 bias8 = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (!split && e.fast) {
+    if (p.bias && (e.inside || n_lane + 8 <= p.N)) bias8 = *reinterpret_cast<const float4 *>(p.bias + n_lane);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) e.prefetch(p, m_tile + 16 * q + lane / 4, n_lane, pre[q]);
+  }
+
+  // byte offsets of this thread's lanes of the KiBs its wave copies: 2 w and 2 w + 1 of each operand's eight (see 256x128)
+  uint32_t off[2][2];
+#pragma unroll
+  for (int op = 0; op < 2; ++op)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t ld = op ? p.ldb : p.lda;
+      const int first = op ? n0 : m0, rows = op ? p.N : p.M, line = 8 * (2 * wave + j) + lane / 8;   // row, or k row
+      if (op ? TB : TA) {
+        const int col = min(first + ((lane % 8) ^ ((line & 2) << 1)) * 8, ((rows + 7) & ~7) - 8);
+        off[op][j] = (uint32_t(line) * ld + uint32_t(col)) * 2u;
+      } else {
+        off[op][j] = (uint32_t(min(first + line, rows - 1)) * ld + uint32_t(((lane % 8) ^ ((line >> 1) & 7)) * 8)) * 2u;
+      }
+    }
+  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem)) + 2048u * wave;
+  const uint32_t a_kstep = TA ? uint32_t(SK) * p.lda * 2u : uint32_t(SK) * 2u, b_kstep = TB ? uint32_t(SK) * p.ldb * 2u : uint32_t(SK) * 2u;
+  u32x4 a_buf = buffer_of(p.A, uint32_t(TA ? p.K : p.M) * p.lda * 2u), b_buf = buffer_of(p.B, uint32_t(TB ? p.K : p.N) * p.ldb * 2u);
+  uint32_t a_next = uint32_t(kt0) * a_kstep, b_next = uint32_t(kt0) * b_kstep;   // byte offset of the next K tile to fetch
+  int fetched = 0;
+  auto fetch = [&]() {   // the next tile, or, past the last one, nothing
+    const uint32_t at = lds0 + uint32_t(fetched & 3) * uint32_t(4 * kSmallOp);
+    set_m0(at);
+    dma16_buffer<0>(a_buf, off[0][0], a_next);
+    set_m0(at + 1024u);
+    dma16_buffer<0>(a_buf, off[0][1], a_next);
+    set_m0(at + uint32_t(2 * kSmallOp));
+    dma16_buffer<0>(b_buf, off[1][0], b_next);
+    set_m0(at + uint32_t(2 * kSmallOp) + 1024u);
+    dma16_buffer<0>(b_buf, off[1][1], b_next);
+    ++fetched;
+    a_next = fetched < n ? a_next + a_kstep : 0;
+    b_next = fetched < n ? b_next + b_kstep : 0;
+    if (fetched >= n) a_buf[2] = b_buf[2] = 0;
+  };
+#pragma unroll
+  for (int t = 0; t < SS; ++t) fetch();
+
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  bf16x8 fa[2][4], fb[2][4];
+  auto read = [&](int buf, int stage) {
+    const bf16_t *a_s = smem + stage * (2 * kSmallOp), *b_s = a_s + kSmallOp;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      fa[buf][ks] = small_frag<TA>(a_s, wm * 32, ks, lane);
+      fb[buf][ks] = small_frag<TB>(b_s, wn * 32, ks, lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int buf) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][ks], fb[buf][ks], acc, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // tile t + 1 has landed once at most the SS - 2 behind it are outstanding; past the barrier it is visible to every wave, and
+  // every wave has read tile t, whose stage the next fetch takes
+  auto land = [&]() {
+    wait_vm<(SS - 2) * L>();
+    __syncthreads();
+    fetch();
+  };
+  wait_vm<(SS - 1) * L>();
+  __syncthreads();
+  read(0, 0);
+#pragma unroll 1
+  for (int t = 0; t < n; t += 2) {
+    land();
+    read(1, (t + 1) & 3);   // (past the last tile: what nobody multiplies)
+    multiply(0);
+    land();
+    read(0, (t + 2) & 3);
+    if (t + 1 < n) multiply(1);
+  }
+  if (split) {
+    const int nn = n_tile + lane % 32;
+    if (nn >= p.N) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m_tile + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+      if (m < p.M) atomicAdd(static_cast<float *>(p.C) + int64_t(m) * p.ldc + nn, acc[r]);
+    }
+    return;
+  }
+  // through LDS, as in the kernel above: 4 KiB per wave, rows of 32 columns
+  wait_vm<0>();      // the last fetches, of nothing, have been written to LDS
+  __syncthreads();
+  float *slab = reinterpret_cast<float *>(smem) + wave * 1024;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+    slab[row * 32 + ((lane % 32) ^ ((row & 4) << 1))] = acc[r];
+  }
+  if (e.fast) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int row = 16 * q + lane / 4, c0 = 8 * (lane % 4);
+      e.emit8(p, m_tile + row, n_lane, slab + row * 32 + (c0 ^ ((row & 4) << 1)), pre[q], bias8);
+    }
+  } else {
+#pragma unroll 1
+    for (int idx = lane; idx < 32 * 32; idx += 64) {
+      const int row = idx / 32, col = idx % 32;
+      const int m = m_tile + row, nn = n_tile + col;
+      if (m < p.M && nn < p.N) e.emit_one(p, m, nn, slab[row * 32 + (col ^ ((row & 4) << 1))]);
+    }
+  }
+}
+
 inline int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HMY_E_HIP, "launch of %s failed: %s", what, hipGetErrorString(e));
@@ -1164,6 +1318,13 @@ int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
   const int tps = (nk + splits - 1) / splits;
   splits = (nk + tps - 1) / tps;
   const dim3 grid(gm * gn * splits), block(NT);
+  if (g.K % SK == 0) {
+    if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<false, false>), grid, block, 0, s, p, tps, gn, splits);
+    else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<false, true>), grid, block, 0, s, p, tps, gn, splits);
+    else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<true, false>), grid, block, 0, s, p, tps, gn, splits);
+    else hipLaunchKernelGGL((k_gemm_dma64_even<true, true>), grid, block, 0, s, p, tps, gn, splits);
+    return check_launch("gemm_dma64_even");
+  }
   if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64<false, false>), grid, block, 0, s, p, tps, gn, splits);
   else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma64<false, true>), grid, block, 0, s, p, tps, gn, splits);
   else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64<true, false>), grid, block, 0, s, p, tps, gn, splits);
@@ -1197,29 +1358,24 @@ static DmaP dma_params(const hmy_gemm_desc &g) {
   return p;
 }
 
-// 64x64 tiles while all of them are resident at once, two per compute unit (measured, us, 128x128 -> 64x64 tiles:
-// 480x768x256 7.3 -> 5.3, 1024x1024x1024 12.6 -> 9.8, 2048x1024x1024 (512 tiles) 12.9 -> 11.8, 1280x1920x1024 (600 tiles)
-// 13.6 -> 19), and for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to
-// register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Sums into an
-// fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
-// contraction, and so do weight gradients whose contraction stays long in every workgroup here (sums, 512x512: K = 4096 in
-// four splits 17.7 -> 13.1, 8192 20.1 -> 20.6; 768x768: K = 1024 11.7 -> 11.2, 1920 and 1024x1536x1920 11 % slower, 768x768x4096
-// 21 -> 34; 1024x1024: 1024 17.5 -> 11.5, 4096 24 -> 34), or is too short to be split here and not there: ten to fifteen K tiles
-// over at most 128 tiles (128x64x704 7.5 -> 8.3; 256x256, K = 768 to 960, 22 to 28 % slower; 512 and 576 as fast, 1024 4 %
-// faster, and where K is no multiple of 64 the larger kernels lose: 992 20 % faster).  Without a split, 2048x1024 (512 tiles) gains up to K = 2048 (19.6 -> 18.9, 4096
-// 32.5 -> 33.4), 256 tiles at every length measured (1024x1024x8192 56 -> 53).
+// 64x64 tiles while all of them are resident at once, two per compute unit (us, 128x128 -> 64x64 tiles: 480x768x256 7.3 -> 5.3,
+// 1024x1024x1024 12.6 -> 8.1, 2048x1024 (512 tiles), K = 1024 12.9 -> 10.2, 4096 31.7 -> 28.0; 3072x768x1536 (576 tiles) 16.6 -> 20.4), and
+// for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to register-staged ones
+// (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions that are no multiple of 64 go
+// through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 -> 18.9, 4096 32.5 -> 33.4).
+// Sums into an fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
+// contraction, and so do weight gradients whose contraction stays long in every workgroup here: 768x768, K = 2048 18.1 ->
+// 11.6, 4096 21.4 -> 19.1, 8192 28.8 -> 33.4; 2304x768 (432 tiles), 2048 21.5 -> 18.0, 4096 28.9 -> 30.0; 512x512x8192 (in four splits)
+// 19.8 -> 13.7; no multiple of 64: 768x768x1920 11 % slower.
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
   static const bool larger_forced = std::getenv("HMY_GEMM_BK") || std::getenv("HMY_GEMM_STAGES") || std::getenv("HMY_GEMM_TILE");
   if (larger_forced) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
-  if (small_may_split(g)) {
-    const int splits = small_splits(g);
-    if (g.K / splits >= 1792) return false;
-    if (tiles <= 128 && splits == 1 && g.K >= 640 && g.K % 64 == 0) return false;
-  }
+  const bool even = g.K % SK == 0;
+  if (small_may_split(g) && g.K / small_splits(g) >= (!even ? 1792 : tiles <= 256 ? 4097 : 4096)) return false;
   if (g.K % 32 != 0) return tiles < 2048;
-  return tiles <= 256 || (tiles <= 512 && g.K <= 2048);
+  return tiles <= 256 || (tiles <= 512 && (even || g.K <= 2048));
 }
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
 

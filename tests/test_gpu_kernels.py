@@ -351,10 +351,10 @@ def test_gemm_bf16_256x128_tiles(ta, tb):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 7), (72, 136, 63), (65, 57, 65), (200, 264, 250), (480, 256, 321),
                                    (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049), (2048, 1024, 2080),
-                                   (200, 264, 576), (200, 264, 640), (200, 264, 960), (200, 264, 1000), (768, 776, 1728), (768, 776, 1792)])
+                                   (200, 264, 576), (200, 264, 640), (200, 264, 960), (200, 264, 1000), (768, 776, 1728), (768, 776, 1792), (65, 57, 128), (72, 72, 192), (768, 776, 4096), (264, 200, 4224)])
 def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
-    """64x64 tiles: one tile, its edges, contractions shorter and longer than the ring of four K tiles, whole, cut at a
-    multiple of 8 and inside a group of 8, split; the smallest output that is left to 128x128 tiles, and both sides of the
+    """64x64 tiles: one tile, its edges, contractions shorter and longer than the ring of four K tiles, whole (an odd and
+    an even number of K tiles), cut at a multiple of 8 and inside a group of 8, split; the smallest output that is left to 128x128 tiles, and both sides of the
     length of contraction that is.  What lies behind K in memory must not matter."""
     say(f"gemm bf16 {M}x{N}x{K} ta={ta} tb={tb}")
     if (ta and M % 8) or (tb and N % 8):
