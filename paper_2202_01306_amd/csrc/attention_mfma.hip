@@ -124,28 +124,20 @@ __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16 &a, int c) {
 __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
 // dK/dV of a 32x32 subtile: lane owns a key, accumulator registers run over its 32 queries, sixteen per lane in four runs of
-// four consecutive rows (16-byte reads of the rows' statistics).
-// The product dO V^T starts from the queries' -delta, so that it ends as dP - delta.
-__device__ __forceinline__ f32x16 minus_delta(const float *minus, int h2) {
-  f32x16 v;
+// four consecutive rows (16-byte reads of the rows' statistics): scores -> P (in place), dP -> dS (in place).
+// `edge`, the same for the whole wave: queries past the sequence end or (causal) before the key may be among them; the test stands
+// outside of the loop over registers, where the compiler made sixteen branches of it, each around one exponential.  The whole
+// backward: 16 heads of 64, causal, s = 4096 207 -> 174 us, four of s = 1024 75 -> 62, 32 heads of 32, s = 2048 244 -> 188; of 128, causal,
+// 197 -> 171.
+__device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const float *lse, const float *delta, int h2, float sc,
+                                              bool edge, int ib, int s, int key, int causal) {
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    const float4 d = *reinterpret_cast<const float4 *>(minus + 8 * g + 4 * h2);
-    v[4 * g] = d.x; v[4 * g + 1] = d.y; v[4 * g + 2] = d.z; v[4 * g + 3] = d.w;
+    float L[4];
+    *reinterpret_cast<float4 *>(L) = *reinterpret_cast<const float4 *>(lse + 8 * g + 4 * h2);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sm[4 * g + k] = fmaf(sm[4 * g + k], sc, -L[k]);
   }
-  return v;
-}
-// scores -> P (in place), dP - delta -> dS (in place).  `edge`, the same for the whole wave: queries past the sequence end or
-// (causal) before the key may be among them; the test stands outside of the loop over registers, where the compiler made
-// sixteen branches of it, each around one exponential.  The whole backward, with dQ's products begun at -delta as well: 16 heads of
-// 64, causal, s = 4096 207 -> 171 us, four of s = 1024 75 -> 65, 32 heads of 32, s = 2048 244 -> 177; of 128, causal, 197 -> 188.
-__device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const float *lse, int h2, float sc, bool edge, int ib, int s,
-                                              int key, int causal) {
-  float L[16];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) *reinterpret_cast<float4 *>(L + 4 * g) = *reinterpret_cast<const float4 *>(lse + 8 * g + 4 * h2);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) sm[r] = fmaf(sm[r], sc, -L[r]);
   if (edge) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -154,9 +146,15 @@ __device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const floa
     }
   }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    sm[r] = fast_exp2(sm[r]);   // P
-    dp[r] *= sm[r];             // dS
+  for (int g = 0; g < 4; ++g) {
+    float D[4];
+    *reinterpret_cast<float4 *>(D) = *reinterpret_cast<const float4 *>(delta + 8 * g + 4 * h2);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int r = 4 * g + k;
+      sm[r] = fast_exp2(sm[r]);         // P
+      dp[r] = sm[r] * (dp[r] - D[k]);   // dS
+    }
   }
 }
 
@@ -543,9 +541,6 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
   if (h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
   const float L = lse[(int64_t(seq) * H + head) * s + q_ld] * kLog2e;   // log2 units
   const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
-  f32x16 minus_dl;   // what the products dO V^T start from
-#pragma unroll
-  for (int r = 0; r < 16; ++r) minus_dl[r] = -dl;
   f32x16 acc_q[C::DTILES];
 #pragma unroll
   for (int t = 0; t < C::DTILES; ++t) acc_q[t] = zero16();
@@ -570,15 +565,15 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
       for (int sub = 0; sub < C::TILE / 32; ++sub) {
         const int kb = k0 + 32 * sub;
         if (causal && kb > qw + 31) continue;
-        f32x16 st = zero16(), dp = minus_dl;
+        f32x16 st = zero16(), dp = zero16();
 #pragma unroll
         for (int c = 0; c < C::KSTEPS; ++c) {
           st = mfma(frag_row<DH>(sK[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);   // S^T = K Q^T
-          dp = mfma(frag_row<DH>(sV[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T - delta = V dO^T - delta
+          dp = mfma(frag_row<DH>(sV[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T = V dO^T
         }
         mask_keys(st, kb, qw, q, s, h2, causal);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * dp[r];            // dS^T
+        for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * (dp[r] - dl);     // dS^T
         // dQ^T[dh, query] += K^T dS^T
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -651,7 +646,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
     rg.fetch(gbase + int64_t(i0) * d, d, nv, tid);
     if (tid < C::TILE) {
       rl = tid < nv ? lbase[i0 + tid] * kLog2e : 0.f;
-      rd = tid < nv ? -dbase[i0 + tid] : 0.f;
+      rd = tid < nv ? dbase[i0 + tid] : 0.f;
     }
   };
   auto put = [&](int buf) {
@@ -680,14 +675,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
     for (int sub = 0; sub < C::TILE / 32; ++sub) {
       const int ib = i0 + 32 * sub;                       // first query of the subtile
       if (causal && ib + 31 < jw) continue;               // every query precedes every key of this wave
-      // S[query, key] = Q K^T and dP[query, key] - delta[query] = dO V^T - delta: lane owns a key, registers run over queries
-      f32x16 sm = zero16(), dp = minus_delta(sD[cur] + 32 * sub, h2);
+      // S[query, key] = Q K^T and dP[query, key] = dO V^T: lane owns a key, registers run over queries
+      f32x16 sm = zero16(), dp = zero16();
 #pragma unroll
       for (int c = 0; c < C::KSTEPS; ++c) {
         sm = mfma(frag_row<DH>(sQ[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fk[c], sm);
         dp = mfma(frag_row<DH>(sG[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fv[c], dp);
       }
-      probabilities(sm, dp, sL[cur] + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
+      probabilities(sm, dp, sL[cur] + 32 * sub, sD[cur] + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
@@ -781,9 +776,6 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(con
   if (sub == 0 && h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
   const float L = lse[(int64_t(seq) * H + head) * s + q_ld] * kLog2e;   // log2 units
   const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
-  f32x16 minus_dl;   // what the products dO V^T start from
-#pragma unroll
-  for (int r = 0; r < 16; ++r) minus_dl[r] = -dl;
   f32x16 acc_q[C::DTILES];
 #pragma unroll
   for (int t = 0; t < C::DTILES; ++t) acc_q[t] = zero16();
@@ -805,15 +797,15 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(con
     }
     const int kb = k0 + 32 * sub;   // first key of this wave's subtile
     if (kb < s && (!causal || kb <= qw + 31)) {   // some query of this wave sees some key of it
-      f32x16 st = zero16(), dp = minus_dl;
+      f32x16 st = zero16(), dp = zero16();
 #pragma unroll
       for (int c = 0; c < C::KSTEPS; ++c) {
         st = mfma(frag_row<DH>(sK(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);   // S^T = K Q^T
-        dp = mfma(frag_row<DH>(sV(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T - delta = V dO^T - delta
+        dp = mfma(frag_row<DH>(sV(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T = V dO^T
       }
       mask_keys(st, kb, qw, q, s, h2, causal);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * dp[r];            // dS^T
+      for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * (dp[r] - dl);     // dS^T
       // dQ^T[dh, query] += K^T dS^T
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -913,7 +905,7 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
     rgr.fetch(gbase + int64_t(i0) * d, d, nv, tid);
     if (tid < TILE) {
       rl = tid < nv ? lbase[i0 + tid] * kLog2e : 0.f;
-      rd = tid < nv ? -dbase[i0 + tid] : 0.f;
+      rd = tid < nv ? dbase[i0 + tid] : 0.f;
     }
   };
   auto put = [&](int buf) {
@@ -933,15 +925,15 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
     if (more) fetch(i0 + TILE);   // next tile's loads fly during this tile's multiplies
     const int ib = i0 + 32 * sub;   // first query of this wave's subtile
     if (ib < s && (!causal || ib + 31 >= jw)) {   // some query of it sees some key of this wave
-      // S[query, key] = Q K^T and dP[query, key] - delta[query] = dO V^T - delta: lane owns a key, registers run over queries
-      f32x16 sm = zero16(), dp = minus_delta(sD + cur * TILE + 32 * sub, h2);
+      // S[query, key] = Q K^T and dP[query, key] = dO V^T: lane owns a key, registers run over queries
+      f32x16 sm = zero16(), dp = zero16();
 #pragma unroll
       for (int c = 0; c < C::KSTEPS; ++c) {
         sm = mfma(frag_row<DH>(sQ(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fk[c], sm);
         const bf16x8 v = kVInLds ? frag_row<DH>(sV, 32 * rg + lane % 32, 16 * c + 8 * h2) : fv[kVInLds ? 0 : c];
         dp = mfma(frag_row<DH>(sG(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), v, dp);
       }
-      probabilities(sm, dp, sL + cur * TILE + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
+      probabilities(sm, dp, sL + cur * TILE + 32 * sub, sD + cur * TILE + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
@@ -999,15 +991,15 @@ inline int check_launch(const char *what) {
 // compute unit and a pass of the partial sums through LDS at the end: rows have to be long enough for the first to matter.
 //
 // Head dimension 64, dK/dV.  Long rows, and up to one workgroup per unit, or two with a causal mask over sixteen row blocks
-// and more.  The whole backward, us, four waves -> eight: 128 workgroups of s = 128 15.5 -> 16.9, of s = 256 20.2 -> 20.9, 256 of s = 512
-// 32.6 -> 32.3, 512 of s = 512 49.0 -> 49.5; causal, 512 of s = 1024 58.9 -> 60.9, of s = 2048 99 -> 97, of s = 4096 179 -> 168, 1024 of
-// s = 1024 102.3 -> 102.5.
+// and more.  The whole backward, us, four waves -> eight: 128 workgroups of s = 128 15.8 -> 17.0, of s = 256 21.0 -> 21.4, 256 of s = 512
+// 35.1 -> 33.7, 512 of s = 512 49.6 -> 56.4; causal, 512 of s = 1024 62.0 -> 62.6, of s = 2048 105 -> 99, of s = 4096 192 -> 174, 1024 of
+// s = 1024 103 -> 117.
 inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
   return (workgroups <= 256 && s >= 384) || (causal && s >= 2048 && workgroups <= 512);
 }
 // Head dimension 128, dK/dV: from rows of more than a row block on, at every number of workgroups.  The whole backward, us, four
-// waves -> eight: 128 workgroups of s = 120 29.9 -> 29.6, 256 of s = 128 33.2 -> 35.4, of s = 256 46.2 -> 43.0, 128 of s = 512 63 -> 54,
-// 512 of s = 512 129 -> 114, causal of s = 1024 156 -> 119, of s = 4096 493 -> 320.
+// waves -> eight: 256 workgroups of s = 256 46.4 -> 39.6, 512 of s = 512 131 -> 104, causal of s = 1024 158 -> 110; with dQ's as well, 128
+// of s = 120 30.1 -> 29.6, 256 of s = 128 33.6 -> 34.6, 128 of s = 512 64 -> 51, causal 512 of s = 4096 502 -> 289.
 inline bool dkv_split_pays_128(int s) { return s >= 160; }
 // Head dimension 128, forward and dQ: one eight-wave workgroup per compute unit against two of the four-wave ones.  Where
 // there is no second workgroup for a unit, or where a causal mask makes the heaviest row block the whole launch (16 row
