@@ -990,12 +990,13 @@ inline int check_launch(const char *what) {
 // Where the eight-wave kernels pay.  They halve a wave's chain over the streamed rows and pay for it with one workgroup per
 // compute unit and a pass of the partial sums through LDS at the end: rows have to be long enough for the first to matter.
 //
-// Head dimension 64, dK/dV.  Long rows, and up to one workgroup per unit, or two with a causal mask over sixteen row blocks
-// and more.  The whole backward, us, four waves -> eight: 128 workgroups of s = 128 15.8 -> 17.0, of s = 256 21.0 -> 21.4, 256 of s = 512
-// 35.1 -> 33.7, 512 of s = 512 49.6 -> 56.4; causal, 512 of s = 1024 62.0 -> 62.6, of s = 2048 105 -> 99, of s = 4096 192 -> 174, 1024 of
-// s = 1024 103 -> 117.
+// Head dimension 64, dK/dV.  Two streamed tiles and more, and up to one workgroup per unit, or two with a causal mask over at
+// least eight row blocks.  The whole backward, us, four waves -> eight: 256 workgroups of s = 512 35.1 -> 33.7, of s = 256 (128
+// workgroups) 21.0 -> 21.4, of s = 128 15.8 -> 17.0; 512 of s = 512 49.6 -> 56.4; causal, 512 of s = 1024 62.0 -> 62.6, of s = 2048 105 ->
+// 99, of s = 4096 192 -> 174, 1024 of s = 1024 103 -> 117.  Where the two are even the line is left to the side whose order of sums
+// such rows have had.
 inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
-  return (workgroups <= 256 && s >= 384) || (causal && s >= 2048 && workgroups <= 512);
+  return s > 64 && (workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512));
 }
 // Head dimension 128, dK/dV: from rows of more than a row block on, at every number of workgroups.  The whole backward, us, four
 // waves -> eight: 256 workgroups of s = 256 46.4 -> 39.6, 512 of s = 512 131 -> 104, causal of s = 1024 158 -> 110; with dQ's as well, 128
