@@ -751,7 +751,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
 // 106 -> 73; K = 1024 25 -> 22.  Four waves of 128x64, one per SIMD, take as long in the K loop (245, 235) and longer
 // around it (K = 1024 22.4 -> 21.6, 4096x1600x1024 26 -> 24.7): a wave alone on its SIMD has nobody to hide its output stage behind.
 template <bool TA, bool TB>
-__global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int grid_n) {
+__global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_split, int grid_n, int splits) {
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   constexpr int BK = 64, S = 3, BTM = 256, BTN = 128;
   constexpr int SUB = BM * BK;        // elements of one 128-row sub-tile
@@ -760,9 +760,12 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int grid_n) {
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int wm = wave / 2, wn = wave % 2;     // this wave's outputs: rows 64 wm .. +63, columns 64 wn .. +63
-  int bid = blockIdx.x;
-  const int nb = gridDim.x, grid_m = nb / grid_n;
-  {
+  int bid = blockIdx.x, split_idx = 0;
+  const int nb = gridDim.x / splits, grid_m = nb / grid_n;
+  if (splits > 1) {   // as in the 128x128 kernel
+    split_idx = bid % splits;
+    bid /= splits;
+  } else {
     const int x = bid % 8, per = nb / 8, extra = nb % 8;
     bid = x * per + min(x, extra) + bid / 8;
   }
@@ -780,7 +783,8 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int grid_n) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int n = p.K / BK;   // K tiles
+  const int kt0 = split_idx * tiles_per_split;
+  const int n = min(p.K / BK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
   // Byte offsets of this thread's lanes of the KiBs its wave copies: KiBs 2 w and 2 w + 1 of each of the three sub-tiles of 16
   // KiB, so that one LDS base serves two instructions, the KiB being part of the instruction (which adds it to the global
   // address as well: taken off here).
@@ -803,7 +807,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int grid_n) {
   const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem)) + 2048u * wave;
   const uint32_t a_kstep = TA ? uint32_t(BK) * p.lda * 2u : uint32_t(BK) * 2u, b_kstep = TB ? uint32_t(BK) * p.ldb * 2u : uint32_t(BK) * 2u;
   u32x4 a_buf = buffer_of(p.A, uint32_t(TA ? p.K : p.M) * p.lda * 2u), b_buf = buffer_of(p.B, uint32_t(TB ? p.K : p.N) * p.ldb * 2u);
-  uint32_t a_next = 0, b_next = 0;   // byte offset of the next K tile to fetch
+  uint32_t a_next = uint32_t(kt0) * a_kstep, b_next = uint32_t(kt0) * b_kstep;   // byte offset of the next K tile to fetch
   // instruction q (0 .. L - 1) of a K tile: piece q % 2 of sub-tile q / 2
   auto fetch_one = [&](int q, int stage) {
     const int sub = q / 2;
@@ -886,6 +890,22 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int grid_n) {
     stage = next;
   }
 #undef HMY_FENCE
+  if (splits > 1) {   // fp32 atomics: one column per lane, straight from the accumulator layout
+    wait_vm<0>();     // (no fetch into LDS outlives the workgroup)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int nn = n_tile + 32 * j + lane % 32;
+      if (nn >= p.N) continue;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = m_tile + 32 * i + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+          if (m < p.M) atomicAdd(static_cast<float *>(p.C) + int64_t(m) * p.ldc + nn, acc[i][j][r]);
+        }
+    }
+    return;
+  }
   if (e.fast) {
     if (p.bias && (e.inside || n_tile + 8 * (lane % 8) + 8 <= p.N))
       bias8 = *reinterpret_cast<const float4 *>(p.bias + n_tile + 8 * (lane % 8));
@@ -1292,14 +1312,16 @@ int launch_cfg256(const hmy_gemm_desc &g, const DmaP &p, dim3 grid, int gn, hipS
   return check_launch("gemm_dma256");
 }
 
-int launch_256x128(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
-  const int gm = (g.M + 255) / 256, gn = (g.N + 127) / 128;
+int launch_256x128(const hmy_gemm_desc &g, const DmaP &p, int splits, hipStream_t s) {
+  const int gm = (g.M + 255) / 256, gn = (g.N + 127) / 128, nk = g.K / 64;
+  const int tps = (nk + splits - 1) / splits;
+  splits = (nk + tps - 1) / tps;
   const size_t lds = size_t(3) * 3 * BM * 64 * sizeof(bf16_t);
-  const dim3 grid(gm * gn), block(512);
-  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, false>), grid, block, lds, s, p, gn);
-  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, true>), grid, block, lds, s, p, gn);
-  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<true, false>), grid, block, lds, s, p, gn);
-  else hipLaunchKernelGGL((k_gemm_dma_256x128<true, true>), grid, block, lds, s, p, gn);
+  const dim3 grid(gm * gn * splits), block(512);
+  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, false>), grid, block, lds, s, p, tps, gn, splits);
+  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, true>), grid, block, lds, s, p, tps, gn, splits);
+  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<true, false>), grid, block, lds, s, p, tps, gn, splits);
+  else hipLaunchKernelGGL((k_gemm_dma_256x128<true, true>), grid, block, lds, s, p, tps, gn, splits);
   return check_launch("gemm_dma_256x128");
 }
 
@@ -1400,7 +1422,15 @@ int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
     const bool one_round = !fills && w1 > 256 && w2 >= 144 && w2 <= 256 && g.K >= (!g.accumulate ? 1024 : w2 <= 160 ? 512 : 2048);
     const bool three_rounds = wgs > 256 && wgs <= 384 && w2 > 512 && w2 <= 768 && g.K >= 2048 && !g.accumulate;
     if (force_tile == 0 && force_bk == 0 && force_s == 0 && g.M >= 256 && g.K % 64 == 0 && (one_round || three_rounds))
-      return launch_256x128(g, p, (hipStream_t)st);
+      return launch_256x128(g, p, 1, (hipStream_t)st);
+    // Very long sums over few outputs: these tiles with the contraction split (fp32 atomics into C), where they come to nearly a
+    // workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128 tiles
+    // -> these: 2048x1024, K = 50240 219 -> 190 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280), 512x1600 104 -> 92
+    // (5582); 1024x1024x40960 98 -> 93 (5120), 512x1024x65536 77.7 -> 78.4 (4096), 1024x1024x16384 50 -> 55 (2048).
+    if (force_tile == 0 && force_bk == 0 && force_s == 0 && can_split && w1 <= 128 && g.M >= 256 && g.K % 64 == 0) {
+      const int splits = 256 / w2;
+      if (splits > 1 && w2 * splits >= 200 && g.K / splits >= 4608) return launch_256x128(g, p, splits, (hipStream_t)st);
+    }
     if (force_tile != 128 && g.M >= 256 && g.N >= 256 && (force_tile == 256 || fills)) {
       // K tiles of 64 where an operand has the contraction index contiguous (whole cache lines of its rows)
       bool deep = (!g.ta || !g.tb) && g.K % 64 == 0;

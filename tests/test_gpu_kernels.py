@@ -349,6 +349,15 @@ def test_gemm_bf16_256x128_tiles(ta, tb):
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(1992, 1000, 18432), (1992, 1000, 18560), (264, 3200, 23104)])
+def test_gemm_bf16_256x128_tiles_split(ta, tb, M, N, K):
+    """Sums so long that they are split over 256x128 tiles: parts of equal length, and a shorter last one; edge tiles in both
+    directions."""
+    say(f"gemm bf16 256x128 split ta={ta} tb={tb} {M}x{N}x{K}")
+    _gemm_case("bf16", 1, torch.bfloat16, 2e-2, M, N, K, ta, tb, 1, 1, False, False, False, True)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 7), (72, 136, 63), (65, 57, 65), (200, 264, 250), (480, 256, 321),
                                    (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049), (2048, 1024, 2080),
                                    (200, 264, 576), (200, 264, 640), (200, 264, 960), (200, 264, 1000), (768, 776, 1728), (768, 776, 1792), (65, 57, 128), (72, 72, 192), (768, 776, 4096), (264, 200, 4224)])
