@@ -83,9 +83,11 @@ __device__ __forceinline__ void dma16(const void *base, uint32_t byte_off, uint3
 __device__ __forceinline__ void dma16_at(const void *addr, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory");
 }
-// The same through a buffer descriptor, in two parts so that several copies share an LDS base: KIB bytes are added to both
-// addresses by the instruction, `tile_off` to the global one.  Bytes past the descriptor's size read as zeros and cost no
-// memory traffic.  Between the two the compiler writes m0 as little as it does elsewhere in this file (see above).
+// The same through a buffer descriptor, in two parts: the LDS address, then the copy from `lane_off` of each lane plus `tile_off`
+// of the wave.  Bytes past the descriptor's size read as zeros and cost no memory traffic, and that is decided on the lane
+// offset as an unsigned number: it must never be negative, so the instruction's own constant (added to both addresses) is not
+// used to step from one KiB to the next.  Between the two the compiler writes m0 as little as it does elsewhere in this file
+// (see above).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x4 buffer_of(const void *base, uint32_t bytes) {
   const uint64_t at = reinterpret_cast<uint64_t>(base);
@@ -97,9 +99,8 @@ __device__ __forceinline__ u32x4 buffer_of(const void *base, uint32_t bytes) {
   return r;
 }
 __device__ __forceinline__ void set_m0(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "memory"); }
-template <int KIB>
 __device__ __forceinline__ void dma16_buffer(u32x4 rsrc, uint32_t lane_off, uint32_t tile_off) {
-  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen offset:%3 lds" : : "v"(lane_off), "s"(rsrc), "s"(tile_off), "n"(KIB) : "memory");
+  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" : : "v"(lane_off), "s"(rsrc), "s"(tile_off) : "memory");
 }
 // contraction steps past the operands' end come from here
 __device__ __attribute__((aligned(256))) bf16_t g_zero_page[128];   // zero-initialised, never written
@@ -785,9 +786,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_
 
   const int kt0 = split_idx * tiles_per_split;
   const int n = min(p.K / BK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
-  // Byte offsets of this thread's lanes of the KiBs its wave copies: KiBs 2 w and 2 w + 1 of each of the three sub-tiles of 16
-  // KiB, so that one LDS base serves two instructions, the KiB being part of the instruction (which adds it to the global
-  // address as well: taken off here).
+  // byte offsets of this thread's lanes of the KiBs its wave copies: KiBs 2 w and 2 w + 1 of each of the three sub-tiles of 16 KiB
   uint32_t off[3][2];
 #pragma unroll
   for (int sub = 0; sub < 3; ++sub)
@@ -798,10 +797,10 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_
       const int first = is_a ? m0 + BM * sub : n0, rows = is_a ? p.M : p.N, kib = 2 * wave + j;
       if (is_a ? TA : TB) {   // k rows 4 kib .. + 3
         const int col = min(first + (((lane % 16) ^ ((lane / 16) << 2)) * 8), ((rows + 7) & ~7) - 8);
-        off[sub][j] = (uint32_t(4 * kib + lane / 16) * ld + uint32_t(col)) * 2u - 1024u * j;
+        off[sub][j] = (uint32_t(4 * kib + lane / 16) * ld + uint32_t(col)) * 2u;
       } else {                // rows 8 kib .. + 7
         const int row = 8 * kib + lane / 8;
-        off[sub][j] = (uint32_t(min(first + row, rows - 1)) * ld + uint32_t(((lane % 8) ^ ((row >> 1) & 7)) * 8)) * 2u - 1024u * j;
+        off[sub][j] = (uint32_t(min(first + row, rows - 1)) * ld + uint32_t(((lane % 8) ^ ((row >> 1) & 7)) * 8)) * 2u;
       }
     }
   const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem)) + 2048u * wave;
@@ -810,12 +809,9 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_
   uint32_t a_next = uint32_t(kt0) * a_kstep, b_next = uint32_t(kt0) * b_kstep;   // byte offset of the next K tile to fetch
   // instruction q (0 .. L - 1) of a K tile: piece q % 2 of sub-tile q / 2
   auto fetch_one = [&](int q, int stage) {
-    const int sub = q / 2;
-    if (q % 2 == 0) set_m0(lds0 + uint32_t(stage) * uint32_t(2 * STAGE) + uint32_t(sub) * uint32_t(2 * SUB));
-    const u32x4 buf = sub < 2 ? a_buf : b_buf;
-    const uint32_t at = sub < 2 ? a_next : b_next;
-    if (q % 2 == 0) dma16_buffer<0>(buf, off[sub][0], at);
-    else dma16_buffer<1024>(buf, off[sub][1], at);
+    const int sub = q / 2, j = q % 2;
+    set_m0(lds0 + uint32_t(stage) * uint32_t(2 * STAGE) + uint32_t(sub) * uint32_t(2 * SUB) + 1024u * j);
+    dma16_buffer(sub < 2 ? a_buf : b_buf, off[sub][j], sub < 2 ? a_next : b_next);
   };
   // on to K tile `next`; past the last one the fetches go on, from descriptors of no bytes: no branch around them, and one
   // count to wait for.  (With a tile offset of 0: the range check takes it off the descriptor's size.)
@@ -1197,13 +1193,13 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_sp
   auto fetch = [&]() {   // the next tile, or, past the last one, nothing
     const uint32_t at = lds0 + uint32_t(fetched & 3) * uint32_t(4 * kSmallOp);
     set_m0(at);
-    dma16_buffer<0>(a_buf, off[0][0], a_next);
+    dma16_buffer(a_buf, off[0][0], a_next);
     set_m0(at + 1024u);
-    dma16_buffer<0>(a_buf, off[0][1], a_next);
+    dma16_buffer(a_buf, off[0][1], a_next);
     set_m0(at + uint32_t(2 * kSmallOp));
-    dma16_buffer<0>(b_buf, off[1][0], b_next);
+    dma16_buffer(b_buf, off[1][0], b_next);
     set_m0(at + uint32_t(2 * kSmallOp) + 1024u);
-    dma16_buffer<0>(b_buf, off[1][1], b_next);
+    dma16_buffer(b_buf, off[1][1], b_next);
     ++fetched;
     a_next = fetched < n ? a_next + a_kstep : 0;
     b_next = fetched < n ? b_next + b_kstep : 0;

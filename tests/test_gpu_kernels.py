@@ -357,6 +357,23 @@ def test_gemm_bf16_256x128_tiles_split(ta, tb, M, N, K):
     _gemm_case("bf16", 1, torch.bfloat16, 2e-2, M, N, K, ta, tb, 1, 1, False, False, False, True)
 
 
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("tb,N", [(1, 1), (1, 64), (1, 96), (1, 120), (1, 128), (0, 1), (0, 2), (0, 72)])
+def test_gemm_bf16_long_sums_of_narrow_outputs(ta, tb, N):
+    """The same split where the second operand is narrow (rows of 16 to 256 bytes if it is stored contraction-major, a single row
+    if not), against 64 bits: a row of the contraction that is not read moves an element by about one standard deviation of a
+    product.  Bound: one 16-deep multiply after the other adds to a sum of at most 6 sqrt(K) in 32 bits, K/16 of them."""
+    say(f"gemm bf16 256x128 split, narrow: ta={ta} tb={tb} N={N}")
+    M, K, ld = 8192, 36864, (N + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(N + ta)
+    A = torch.randn((K, M) if ta else (M, K), device="cuda", generator=g).bfloat16()
+    Bm = torch.randn((K, ld) if tb else (N, K), device="cuda", generator=g).bfloat16()
+    C = torch.randn(M, N, device="cuda", generator=g)
+    ref = C.double() + (A.t() if ta else A).double() @ (Bm[:, :N] if tb else Bm.t()).double()
+    B.hmy_k_gemm(1, M, N, K, A, M if ta else K, Bm, ld if tb else K, C, N, ta=ta, tb=tb, c_fp32=1, accumulate=1)
+    assert float((C.double() - ref).abs().max()) < 6 * math.sqrt(K) * (K / 16) * 2.0 ** -24
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 7), (72, 136, 63), (65, 57, 65), (200, 264, 250), (480, 256, 321),
                                    (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049), (2048, 1024, 2080),
