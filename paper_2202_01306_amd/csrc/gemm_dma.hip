@@ -1245,6 +1245,7 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_sp
     read(0, (t + 2) & 3);
     if (t + 1 < n) multiply(1);
   }
+  wait_vm<0>();   // the last fetches, of nothing, have been written to LDS: none outlives the workgroup or meets its output stage
   if (split) {
     const int nn = n_tile + lane % 32;
     if (nn >= p.N) return;
@@ -1256,7 +1257,6 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_sp
     return;
   }
   // through LDS, as in the kernel above: 4 KiB per wave, rows of 32 columns
-  wait_vm<0>();      // the last fetches, of nothing, have been written to LDS
   __syncthreads();
   float *slab = reinterpret_cast<float *>(smem) + wave * 1024;
 #pragma unroll
