@@ -1130,8 +1130,9 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, 
 // own instruction stream: 128 cycles of multiplies per K tile among branches, waits and LDS reads that follow one another.
 // So: no branch in the loop (the fetches go through buffer descriptors, as on 256x128 tiles, and end by themselves), the
 // next tile's fragments are read while this one's are multiplied, and what the output stage adds is fetched before the loop.
-// Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), x768 8.2 -> 7.1, x256 5.4 -> 5.6;
-// weight gradient 1024x1024x1024 12.1 -> 8.7.
+// Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), 480x768x768 8.2 -> 6.9; weight
+// gradient 1024x1024x1024 12.1 -> 8.7.  It takes longer before its first multiply: short contractions stay with the kernel above
+// (`even_pays`).
 template <bool TA, bool TB>
 __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_split, int grid_n, int splits) {
   __shared__ __attribute__((aligned(1024))) bf16_t smem[SS * 2 * kSmallOp];
@@ -1330,13 +1331,23 @@ int small_splits(const hmy_gemm_desc &g) {
   return std::max(1, std::min(256 / int(tiles), (g.K + SK - 1) / SK / 8));
 }
 
+// Where the kernel without branches pays: its descriptors, the whole ring fetched whatever the length, and the output stage's operands
+// in front of the loop have to be made up for, by more K tiles where two workgroups share a compute unit and hide each other's
+// waits.  Kernel with branches -> without, us, up to 256 tiles: 1024x1024x64 4.1 -> 4.6, x192 4.9 -> 5.0, x256 5.2 -> 5.1, x512 6.9
+// -> 6.1; 257 to 512 tiles: 2048x1024x64 4.8 -> 5.9, x256 6.3 -> 6.5, x320 6.8 -> 7.1, x384 7.2 -> 7.1, x512 8.1 -> 7.6; with a
+// residual to add 1536x1024x384 (384 tiles) 8.5 -> 8.3, 2304x768x384 (432) 8.7 -> 8.9, x512 9.8 -> 9.6.
+bool even_pays(const hmy_gemm_desc &g) {
+  const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
+  return g.K % SK == 0 && g.K >= (tiles <= 256 ? 256 : g.res && tiles > 400 ? 512 : 384);
+}
+
 int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
   const int gm = (g.M + ST - 1) / ST, gn = (g.N + ST - 1) / ST, nk = (g.K + SK - 1) / SK;
   int splits = small_splits(g);
   const int tps = (nk + splits - 1) / splits;
   splits = (nk + tps - 1) / tps;
   const dim3 grid(gm * gn * splits), block(NT);
-  if (g.K % SK == 0) {
+  if (even_pays(g)) {
     if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<false, false>), grid, block, 0, s, p, tps, gn, splits);
     else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<false, true>), grid, block, 0, s, p, tps, gn, splits);
     else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<true, false>), grid, block, 0, s, p, tps, gn, splits);
