@@ -1387,22 +1387,52 @@ static DmaP dma_params(const hmy_gemm_desc &g) {
   return p;
 }
 
-// 64x64 tiles while all of them are resident at once, two per compute unit (us, 128x128 -> 64x64 tiles: 480x768x256 7.3 -> 5.3,
+// Weight gradients on 64x64 tiles: while the contraction of a workgroup (K over the splits) is not long.  A workgroup multiplies a
+// K tile in 215 to 230 ns here, and the larger kernels, whose workgroups have four times the multiplies and whose splits are four
+// times as many, start 10 us later and are a third faster from there on.  Measured over 80 outputs, 128x128 tiles -> these, us:
+// - up to 256 tiles the two meet between 4600 and 5600 (768x768x4096 21.7 -> 19.1, x4608 22.5 -> 21.1, x6144 26.2 -> 26.5; 512x512 in
+//   four parts of 4608 24.5 -> 22.5, of 5632 26.2 -> 25.9; 992x864x4096 21.1 -> 19.7, x5120 22.8 -> 23.5);
+// - sooner where rows are no whole half cache lines: a row of a tile then lies in three of them instead of two, of the larger tiles'
+//   in five instead of four (1000x1000x4096 26.6 -> 24.2, x5120 28.5 -> 28.8; 504x392 in four parts of 4096 24.0 -> 23.1), and at 3072 if
+//   the tiles leave many compute units idle (1000x520x3072 19.6 -> 18.5, x3584 19.1 -> 20.8);
+// - the parts of a split contraction are dealt over the eight XCDs in turn.  Unless their number is a power of two an L2 cache sees
+//   several of them: three up to 3072 (800x352 in three parts of 3072 19.8 -> 18.7, of 4096 21.5 -> 23.1), more not at all
+//   (five parts of 2048: 416x416 17.3 -> 21.4, though 480x352 18.4 -> 14.7);
+// - 257 to 512 tiles are two workgroups for some of the compute units: up to 2304 (1280x1024 21.2 -> 21.0, x2560 21.4 -> 23.0), from 400
+//   on 3072 (2304x768x2816 23.9 -> 23.4, x3072 24.7 -> 25.2; 2048x1024x3072 26.7 -> 25.7).  If edge tiles are half empty, not at all
+//   (1056x992x2048 18.1 -> 20.1, 1320x800 18.8 -> 20.7; x1536 18.5 -> 16.8) and 2304 (1984x1000 26.1 -> 21.6 at 2048, 29.7 -> 28.8 at 3072;
+//   1312x1312x2304 22.2 -> 22.2, x2560 23.1 -> 24.1).
+// Short of a first split, at most 64 tiles of such misaligned rows are the other exception: 504x392x704 8.2 -> 7.7, x768 7.4 -> 7.8, x960
+// 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2).
+// Contractions that are no multiple of 64 (the kernel with branches): up to 1792 (768x768x1920 11 % slower).
+bool small_sum_pays(const hmy_gemm_desc &g) {
+  const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
+  const int splits = small_splits(g), length = g.K / splits;
+  const bool half_lines = g.lda % 32 == 0 && g.ldb % 32 == 0;
+  if (length < 1792) return g.K % SK != 0 || half_lines || splits > 1 || tiles > 64 || g.K < 768;
+  if (g.K % SK != 0) return false;
+  if (tiles > 256) {
+    const bool whole = g.M % ST == 0 && g.N % ST == 0;
+    return tiles <= 400 ? whole && length <= 2304 : length <= (whole ? 3072 : 2304);
+  }
+  if ((splits & (splits - 1)) != 0) return (splits % 3 == 0 && 24 % splits == 0) && length <= 3072;   // 3, 6, 12: three parts per XCD
+  return length <= (half_lines ? 4608 : splits == 1 && tiles < 200 ? 3072 : 4096);
+}
+
+// 64x64 tiles while all of them are resident at once, two per compute unit (us, 128x128 -> 64x64 tiles: 480x768x256 7.3 -> 5.0,
 // 1024x1024x1024 12.6 -> 8.1, 2048x1024 (512 tiles), K = 1024 12.9 -> 10.2, 4096 31.7 -> 28.0; 3072x768x1536 (576 tiles) 16.6 -> 20.4), and
 // for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to register-staged ones
 // (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions that are no multiple of 64 go
 // through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 -> 18.9, 4096 32.5 -> 33.4).
 // Sums into an fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
-// contraction, and so do weight gradients whose contraction stays long in every workgroup here: 768x768, K = 2048 18.1 ->
-// 11.6, 4096 21.4 -> 19.1, 8192 28.8 -> 33.4; 2304x768 (432 tiles), 2048 21.5 -> 18.0, 4096 28.9 -> 30.0; 512x512x8192 (in four splits)
-// 19.8 -> 13.7; no multiple of 64: 768x768x1920 11 % slower.
+// contraction, and so do long weight gradients (above).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
   static const bool larger_forced = std::getenv("HMY_GEMM_BK") || std::getenv("HMY_GEMM_STAGES") || std::getenv("HMY_GEMM_TILE");
   if (larger_forced) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   const bool even = g.K % SK == 0;
-  if (small_may_split(g) && g.K / small_splits(g) >= (!even ? 1792 : tiles <= 256 ? 4097 : 4096)) return false;
+  if (small_may_split(g) && !small_sum_pays(g)) return false;
   if (g.K % 32 != 0) return tiles < 2048;
   return tiles <= 256 || (tiles <= 512 && (even || g.K <= 2048));
 }

@@ -379,7 +379,8 @@ def test_gemm_bf16_long_sums_of_narrow_outputs(ta, tb, N):
                                    (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049), (2048, 1024, 2080),
                                    (200, 264, 576), (200, 264, 640), (200, 264, 960), (200, 264, 1000), (768, 776, 1728),
                                    (768, 776, 1792), (65, 57, 128), (72, 72, 192), (768, 776, 4096), (264, 200, 4224), (65, 57, 256),
-                                   (72, 72, 320), (200, 264, 4672), (1000, 1200, 320), (1000, 1200, 384), (1000, 1200, 512)])
+                                   (72, 72, 320), (200, 264, 4672), (1000, 1200, 320), (1000, 1200, 384), (1000, 1200, 512),
+                                   (768, 768, 4608), (1280, 1024, 2304)])
 def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
     """64x64 tiles: one tile, its edges, contractions shorter and longer than the ring of four K tiles, whole (an odd and
     an even number of K tiles), cut at a multiple of 8 and inside a group of 8, split (4672: the last part is one K tile); the
