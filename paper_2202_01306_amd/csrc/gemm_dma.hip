@@ -28,6 +28,7 @@
 // HMY_GEMM_TILE = 128 | 256 the choice between it and the 256x256 kernel.  With any of them set no shape takes the
 // 64x64 or 256x128 tiles.
 #include <algorithm>
+#include <climits>
 #include <cstdlib>
 
 #include "dev_common.h"
@@ -1423,7 +1424,10 @@ bool small_sum_pays(const hmy_gemm_desc &g) {
 // 1024x1024x1024 12.6 -> 8.1, 2048x1024 (512 tiles), K = 1024 12.9 -> 10.2, 4096 31.7 -> 28.0; 3072x768x1536 (576 tiles) 16.6 -> 20.4), and
 // for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to register-staged ones
 // (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions that are no multiple of 64 go
-// through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 -> 18.9, 4096 32.5 -> 33.4).
+// through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 -> 18.9, 4096 32.5 -> 33.4).  Beyond 256
+// tiles an operand stored contraction-major loses on long ones what the tiles gain: from 8192 on (input gradients 2048x1024x8192
+// 59.9 -> 58.9, x12288 86.7 -> 89.4), from 4096 on where its rows are no whole half cache lines (1960x1000x4096 36.8 -> 35.5, x8192 63.0
+// -> 68.1; forward, x16384 109 -> 102).
 // Sums into an fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
 // contraction, and so do long weight gradients (above).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
@@ -1434,7 +1438,8 @@ bool gemm_prefers_small(const hmy_gemm_desc &g) {
   const bool even = g.K % SK == 0;
   if (small_may_split(g) && !small_sum_pays(g)) return false;
   if (g.K % 32 != 0) return tiles < 2048;
-  return tiles <= 256 || (tiles <= 512 && (even || g.K <= 2048));
+  const bool major = g.ta || g.tb, half_lines = (!g.ta || g.lda % 32 == 0) && (!g.tb || g.ldb % 32 == 0);
+  return tiles <= 256 || (tiles <= 512 && g.K <= (!even ? 2048 : !major ? INT_MAX : half_lines ? 8192 : 4096));
 }
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
 
