@@ -367,7 +367,7 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
     tail.B = static_cast<const bf16_t *>(g.B) + (g.tb ? int64_t(body.K) * g.ldb : int64_t(body.K));
     if (gemm_dma_eligible(body) && aligned16(tail.A) && aligned16(tail.B)) {
       const int rc = launch_gemm_dma(body, st);
-      return rc ? rc : launch_gemm_small(tail, st);
+      return rc ? rc : gemm_small_excluded() ? launch_gemm_mfma32(tail, st) : launch_gemm_small(tail, st);
     }
   }
   if (mfma_ok && g_use_mfma != 2) return launch_gemm_mfma32(g, st);

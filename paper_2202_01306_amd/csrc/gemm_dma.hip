@@ -1388,6 +1388,11 @@ static DmaP dma_params(const hmy_gemm_desc &g) {
   return p;
 }
 
+bool gemm_small_excluded() {
+  static const bool larger_forced = std::getenv("HMY_GEMM_BK") || std::getenv("HMY_GEMM_STAGES") || std::getenv("HMY_GEMM_TILE");
+  return larger_forced;
+}
+
 // Weight gradients on 64x64 tiles: while the contraction of a workgroup (K over the splits) is not long.  A workgroup multiplies a
 // K tile in 215 to 230 ns here, and the larger kernels, whose workgroups have four times the multiplies and whose splits are four
 // times as many, start 10 us later and are a third faster from there on.  Measured over 80 outputs, 128x128 tiles -> these, us:
@@ -1431,8 +1436,7 @@ bool small_sum_pays(const hmy_gemm_desc &g) {
 // Sums into an fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
 // contraction, and so do long weight gradients (above).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
-  static const bool larger_forced = std::getenv("HMY_GEMM_BK") || std::getenv("HMY_GEMM_STAGES") || std::getenv("HMY_GEMM_TILE");
-  if (larger_forced) return false;
+  if (gemm_small_excluded()) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   const bool even = g.K % SK == 0;

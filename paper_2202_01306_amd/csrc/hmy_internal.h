@@ -161,6 +161,7 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st);
 int launch_gemm_f32(const hmy_gemm_desc &g, stream_t st);
 int launch_gemm_mfma32(const hmy_gemm_desc &g, stream_t st);
 bool gemm_prefers_small(const hmy_gemm_desc &g);
+bool gemm_small_excluded();   // by a tuning switch that names a larger kernel
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st);
 bool gemm_dma_eligible(const hmy_gemm_desc &g);
 int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st);
