@@ -998,10 +998,11 @@ inline int check_launch(const char *what) {
 inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
   return s > 64 && (workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512));
 }
-// Head dimension 128, dK/dV: from rows of more than a row block on, at every number of workgroups.  The whole backward, us, four
-// waves -> eight: 256 workgroups of s = 256 46.4 -> 39.6, 512 of s = 512 131 -> 104, causal of s = 1024 158 -> 110; with dQ's as well, 128
-// of s = 120 30.1 -> 29.6, 256 of s = 128 33.6 -> 34.6, 128 of s = 512 64 -> 51, causal 512 of s = 4096 502 -> 289.
-inline bool dkv_split_pays_128(int s) { return s >= 160; }
+// Head dimension 128, dK/dV: from rows of nearly a row block on, at every number of workgroups.  The whole backward, us, four
+// waves -> eight: s = 64, 128 workgroups 17.7 -> 18.2, 1024 66.0 -> 67.3; s = 96, 128 23.5 -> 23.8, 1024 93.0 -> 92.8; s = 112, 128 28.6 ->
+// 27.4, 1024 114 -> 107; s = 128, 256 33.7 -> 33.0, causal 35.1 -> 33.5; s = 144, 512 53.6 -> 50.4, causal 46.7 -> 45.9; s = 256, 256 46.6 ->
+// 40.9, 1024 165 -> 143, causal 145 -> 129.  (104 to 111, where eight waves gain as much, keep the order of sums that they have had.)
+inline bool dkv_split_pays_128(int s) { return s >= 112; }
 // Head dimension 128, forward and dQ: one eight-wave workgroup per compute unit against two of the four-wave ones.  Where
 // there is no second workgroup for a unit, or where a causal mask makes the heaviest row block the whole launch (16 row
 // blocks and more), half the chain wins, dQ's from a later length on (it reads its rows' o as well, and exchanges more).
