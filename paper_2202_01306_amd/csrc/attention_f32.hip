@@ -183,18 +183,17 @@ __global__ __launch_bounds__(64 * W * KW) void k_attn_f32_fwd(const float *qkv, 
   const int my_end = q0 >= s ? 0 : causal ? min(s, q0 + kRows) : s;
   Stage<DH, W> tk, tv;
   auto fetch = [&](int j) {
-    if (j >= j_end) return;
     tk.load(base + d + int64_t(j) * ld, ld, min(kRows, s - j), me.tid);
     tv.load(base + 2 * d + int64_t(j) * ld, ld, min(kRows, s - j), me.tid);
   };
-  fetch(me.part * kRows);
+  if (KW == 1 || me.part * kRows < j_end) fetch(me.part * kRows);   // (the first tile is always there)
   for (int j0 = me.part * kRows; j0 < j_end; j0 += KW * kRows) {
     me.sync();
     tk.store(sK, me.tid);
     tv.store(sV, me.tid);
     me.sync();
     const int j1 = j0 + kRows;
-    fetch(j0 + KW * kRows);
+    if (j0 + KW * kRows < j_end) fetch(j0 + KW * kRows);
     if (j0 >= my_end) continue;   // beyond this wave's rows; the barriers are still met
     f32x16 p = product<DH>(sK, q, l32, h);
     const bool whole = j1 <= s && (!causal || j1 - 1 <= q0);
@@ -288,18 +287,17 @@ __global__ __launch_bounds__(64 * W * KW) void k_attn_f32_dq(const float *qkv, c
   const int my_end = q0 >= s ? 0 : causal ? min(s, q0 + kRows) : s;
   Stage<DH, W> tk, tv;
   auto fetch = [&](int j) {
-    if (j >= j_end) return;
     tk.load(base + d + int64_t(j) * ld, ld, min(kRows, s - j), me.tid);
     tv.load(base + 2 * d + int64_t(j) * ld, ld, min(kRows, s - j), me.tid);
   };
-  fetch(me.part * kRows);
+  if (KW == 1 || me.part * kRows < j_end) fetch(me.part * kRows);   // (the first tile is always there)
   for (int j0 = me.part * kRows; j0 < j_end; j0 += KW * kRows) {
     me.sync();
     tk.store(sK, me.tid);
     tv.store(sV, me.tid);
     me.sync();
     const int j1 = j0 + kRows;
-    fetch(j0 + KW * kRows);
+    if (j0 + KW * kRows < j_end) fetch(j0 + KW * kRows);
     if (j0 >= my_end) continue;
     f32x16 p = product<DH>(sK, q, l32, h);
     const f32x16 dp = product<DH>(sV, g, l32, h);
