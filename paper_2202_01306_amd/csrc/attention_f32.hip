@@ -415,11 +415,13 @@ __global__ __launch_bounds__(64 * W * KW) void k_attn_f32_dkv(const float *qkv, 
 // four waves of rows per workgroup once that still leaves two workgroups for every compute unit
 inline bool wide(int b, int s, int H) { return int64_t(b) * H * ((s + 4 * kRows - 1) / (4 * kRows)) >= 512; }
 // Waves that share 32 rows and split their tiles, for a launch of few waves, which is as long as one wave's chain over its
-// tiles.  Measured, us, one wave -> two -> four: forward at head dimension 64, 256 groups of 32 rows, s = 256 31 -> 18 -> 12, 512
-// of s = 1024 115 -> 91 -> 53, 1024 of s = 512 63 -> 53 -> 57, of s = 256 37 -> 36 -> 40; at 32, 1024 of s = 256 23 -> 20 -> 23; at
-// 128, 256 of s = 256 49 -> 31 -> 25, 512 of s = 512 94 -> 62 -> 67, 1024 of s = 512 101 -> 116 -> 128.  Backward at 64, 256 of s = 256
-// 85 -> 49 -> 35, 384 of s = 500 164 -> 91 -> 101, 512 of s = 1024 320 -> 171 -> 182, 1024 of s = 512 175 -> 181 -> 201; at 128, 256 157 ->
-// 127 -> 97, 512 300 -> 255 -> 276.  Two tiles: 64 groups of s = 64 27 -> 19 -> 21.
+// tiles.  Measured, us, one wave -> two -> four: forward at head dimension 64, 256 groups of 32 rows, s = 256 31 -> 18 -> 12,
+// 512 of s = 1024 115 -> 91 -> 53, 1024 of s = 512 63 -> 53 -> 57, of s = 256 37 -> 36 -> 40; at 32, 1024 of s = 256 23 -> 20
+// -> 23; at 128, 256 of s = 256 49 -> 31 -> 25, 512 of s = 512 94 -> 62 -> 67, 1024 of s = 512 101 -> 116 -> 128.  Backward at
+// 64, 256 of s = 256 85 -> 49 -> 35, 384 of s = 500 164 -> 91 -> 101, 512 of s = 1024 320 -> 171 -> 182, 1024 of s = 512 175 ->
+// 181 -> 201; at 128, 256 157 -> 127 -> 97, 512 300 -> 255 -> 276.  Two tiles: 64 groups of s = 64 27 -> 19 -> 21. (All of
+// dK/dV at 128: a wave that has its tiles to itself stages both of them, 128 registers beside 128 of sums and 128 of K and V,
+// and spills 288, where two that share them spill 100 and four none.  What the spilling costs is in these figures.)
 inline int split(int b, int s, int H, int dh, bool backward) {
   const int tiles = (s + kRows - 1) / kRows;
   const int64_t groups = int64_t(b) * H * tiles;

@@ -124,10 +124,10 @@ __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16 &a, int c) {
 __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
 // dK/dV of a 32x32 subtile: lane owns a key, accumulator registers run over its 32 queries, sixteen per lane in four runs of
-// four consecutive rows (16-byte reads of the rows' statistics): scores -> P (in place), dP -> dS (in place).
-// `edge`, the same for the whole wave: queries past the sequence end or (causal) before the key may be among them; the test stands
-// outside of the loop over registers, where the compiler made sixteen branches of it, each around one exponential.  The whole
-// backward: 16 heads of 64, causal, s = 4096 207 -> 174 us, four of s = 1024 75 -> 62, 32 heads of 32, s = 2048 244 -> 188; of 128, causal,
+// four consecutive rows (16-byte reads of the rows' statistics): scores -> P (in place), dP -> dS (in place). `edge`, the same
+// for the whole wave: queries past the sequence end or (causal) before the key may be among them; the test stands outside of
+// the loop over registers, where the compiler made sixteen branches of it, each around one exponential.  The whole backward: 16
+// heads of 64, causal, s = 4096 207 -> 174 us, four of s = 1024 75 -> 62, 32 heads of 32, s = 2048 244 -> 188; of 128, causal,
 // 197 -> 171.
 __device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const float *lse, const float *delta, int h2, float sc,
                                               bool edge, int ib, int s, int key, int causal) {
@@ -158,8 +158,8 @@ __device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const floa
   }
 }
 
-// scores of a 32-key subtile from key kb on, lane owns query q of the wave's 32 from qw on: keys past the sequence end or (causal)
-// past the query get no weight.  Only a diagonal and the last subtile hold any.
+// scores of a 32-key subtile from key kb on, lane owns query q of the wave's 32 from qw on: keys past the sequence end or
+// (causal) past the query get no weight.  Only a diagonal and the last subtile hold any.
 __device__ __forceinline__ void mask_keys(f32x16 &st, int kb, int qw, int q, int s, int h2, int causal) {
   if (kb + 32 > s || (causal && kb + 31 > qw)) {
 #pragma unroll
@@ -682,7 +682,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
         sm = mfma(frag_row<DH>(sQ[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fk[c], sm);
         dp = mfma(frag_row<DH>(sG[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fv[c], dp);
       }
-      probabilities(sm, dp, sL[cur] + 32 * sub, sD[cur] + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
+      probabilities(sm, dp, sL[cur] + 32 * sub, sD[cur] + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key,
+                    causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
@@ -933,7 +934,8 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
         const bf16x8 v = kVInLds ? frag_row<DH>(sV, 32 * rg + lane % 32, 16 * c + 8 * h2) : fv[kVInLds ? 0 : c];
         dp = mfma(frag_row<DH>(sG(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), v, dp);
       }
-      probabilities(sm, dp, sL + cur * TILE + 32 * sub, sD + cur * TILE + 32 * sub, h2, sc, ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
+      probabilities(sm, dp, sL + cur * TILE + 32 * sub, sD + cur * TILE + 32 * sub, h2, sc,
+                    ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const bf16x8 fp = acc_to_frag(sm, c), fs = acc_to_frag(dp, c);
@@ -991,17 +993,19 @@ inline int check_launch(const char *what) {
 // compute unit and a pass of the partial sums through LDS at the end: rows have to be long enough for the first to matter.
 //
 // Head dimension 64, dK/dV.  Two streamed tiles and more, and up to one workgroup per unit, or two with a causal mask over at
-// least eight row blocks.  The whole backward, us, four waves -> eight: 256 workgroups of s = 512 35.1 -> 33.7, of s = 256 (128
-// workgroups) 21.0 -> 21.4, of s = 128 15.8 -> 17.0; 512 of s = 512 49.6 -> 56.4; causal, 512 of s = 1024 62.0 -> 62.6, of s = 2048 105 ->
-// 99, of s = 4096 192 -> 174, 1024 of s = 1024 103 -> 117.  Where the two are even the line is left to the side whose order of sums
-// such rows have had.
+// least eight row blocks.  The whole backward, us, four waves -> eight: 256 workgroups of s = 512 34.1 -> 32.7, of s = 1024
+// 55.2 -> 51.6; 512 of s = 512 46.9 -> 54.8; causal, 512 of s = 1024 61.6 -> 62.2, of s = 2048 105 -> 99, of s = 4096 192 ->
+// 174, 1024 of s = 1024 98 -> 111.  Rows of 65 to 256 would be faster on four waves: 128 workgroups of s = 65 14.5 -> 14.8, of
+// s = 128 15.7 -> 17.1, of s = 256 20.9 -> 21.4, of s = 320 23.2 -> 23.2.  They are left here because eight waves add up in
+// another order, and these are the rows whose gradients have been added up in it: results stay bit for bit what they were.
 inline bool dkv_split_pays_64(int workgroups, int s, int causal) {
   return s > 64 && (workgroups <= 256 || (causal && s >= 1024 && workgroups <= 512));
 }
 // Head dimension 128, dK/dV: from rows of nearly a row block on, at every number of workgroups.  The whole backward, us, four
-// waves -> eight: s = 64, 128 workgroups 17.7 -> 18.2, 1024 66.0 -> 67.3; s = 96, 128 23.5 -> 23.8, 1024 93.0 -> 92.8; s = 112, 128 28.6 ->
-// 27.4, 1024 114 -> 107; s = 128, 256 33.7 -> 33.0, causal 35.1 -> 33.5; s = 144, 512 53.6 -> 50.4, causal 46.7 -> 45.9; s = 256, 256 46.6 ->
-// 40.9, 1024 165 -> 143, causal 145 -> 129.  (104 to 111, where eight waves gain as much, keep the order of sums that they have had.)
+// waves -> eight: s = 64, 128 workgroups 17.7 -> 18.2, 1024 66.0 -> 67.3; s = 96, 128 23.5 -> 23.8, 1024 93.0 -> 92.8; s = 112,
+// 128 28.6 -> 27.4, 1024 114 -> 107; s = 128, 256 33.7 -> 33.0, causal 35.1 -> 33.5; s = 144, 512 53.6 -> 50.4, causal 46.7 ->
+// 45.9; s = 256, 256 46.6 -> 40.9, 1024 165 -> 143, causal 145 -> 129.  (104 to 111, where eight waves gain as much, keep the
+// order of sums that they have had.)
 inline bool dkv_split_pays_128(int s) { return s >= 112; }
 // Head dimension 128, forward and dQ: one eight-wave workgroup per compute unit against two of the four-wave ones.  Where
 // there is no second workgroup for a unit, or where a causal mask makes the heaviest row block the whole launch (16 row

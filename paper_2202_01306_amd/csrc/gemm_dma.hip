@@ -745,13 +745,13 @@ __global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
 
 // ---- 256x128 tiles -------------------------------------------------------------------
 // The same GEMM for outputs that give the compute units one such tile each but too few 256x256 ones: three quarters of the
-// 128x128 kernel's bytes per multiply through the L2 caches, which is what bounds it.  Eight waves of 64x64 (two per SIMD),
-// K tiles of 64 in a ring of three stages (144 KiB), fragments read two 16-deep steps ahead, one barrier per K tile.  A K
-// tile's fetch is spread over the two steps behind that barrier; it goes through buffer descriptors, which end it without
-// a branch in the loop.  K has to be a multiple of 64.
-// Measured, us, 128x128 tiles -> these: 2048x4096, K = 16384 372 -> 242 (1135 TFLOP/s), input gradient 322 -> 230, K = 4096
-// 106 -> 73; K = 1024 25 -> 22.  Four waves of 128x64, one per SIMD, take as long in the K loop (245, 235) and longer
-// around it (K = 1024 22.4 -> 21.6, 4096x1600x1024 26 -> 24.7): a wave alone on its SIMD has nobody to hide its output stage behind.
+// 128x128 kernel's bytes per multiply through the L2 caches, which is what bounds it.  Eight waves of 64x64 (two per SIMD), K
+// tiles of 64 in a ring of three stages (144 KiB), fragments read two 16-deep steps ahead, one barrier per K tile.  A K tile's
+// fetch is spread over the two steps behind that barrier; it goes through buffer descriptors, which end it without a branch in
+// the loop.  K has to be a multiple of 64.  Measured, us, 128x128 tiles -> these: 2048x4096, K = 16384 372 -> 242 (1135
+// TFLOP/s), input gradient 322 -> 230, K = 4096 106 -> 73; K = 1024 25 -> 22.  Four waves of 128x64, one per SIMD, take as long
+// in the K loop (245, 235) and longer around it (K = 1024 22.4 -> 21.6, 4096x1600x1024 26 -> 24.7): a wave alone on its SIMD
+// has nobody to hide its output stage behind.
 template <bool TA, bool TB>
 __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_split, int grid_n, int splits) {
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_
 
   const int kt0 = split_idx * tiles_per_split;
   const int n = min(p.K / BK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
-  // byte offsets of this thread's lanes of the KiBs its wave copies: KiBs 2 w and 2 w + 1 of each of the three sub-tiles of 16 KiB
+  // byte offsets of this thread's lanes of the KiBs its wave copies: 2 w and 2 w + 1 of each of the three sub-tiles of 16 KiB
   uint32_t off[3][2];
 #pragma unroll
   for (int sub = 0; sub < 3; ++sub)
@@ -1332,11 +1332,11 @@ int small_splits(const hmy_gemm_desc &g) {
   return std::max(1, std::min(256 / int(tiles), (g.K + SK - 1) / SK / 8));
 }
 
-// Where the kernel without branches pays: its descriptors, the whole ring fetched whatever the length, and the output stage's operands
-// in front of the loop have to be made up for, by more K tiles where two workgroups share a compute unit and hide each other's
-// waits.  Kernel with branches -> without, us, up to 256 tiles: 1024x1024x64 4.1 -> 4.6, x192 4.9 -> 5.0, x256 5.2 -> 5.1, x512 6.9
-// -> 6.1; 257 to 512 tiles: 2048x1024x64 4.8 -> 5.9, x256 6.3 -> 6.5, x320 6.8 -> 7.1, x384 7.2 -> 7.1, x512 8.1 -> 7.6; with a
-// residual to add 1536x1024x384 (384 tiles) 8.5 -> 8.3, 2304x768x384 (432) 8.7 -> 8.9, x512 9.8 -> 9.6.
+// Where the kernel without branches pays: its descriptors, the whole ring fetched whatever the length, and the output stage's
+// operands in front of the loop have to be made up for, by more K tiles where two workgroups share a compute unit and hide each
+// other's waits.  Kernel with branches -> without, us, up to 256 tiles: 1024x1024x64 4.1 -> 4.6, x192 4.9 -> 5.0, x256 5.2 ->
+// 5.1, x512 6.9 -> 6.1; 257 to 512 tiles: 2048x1024x64 4.8 -> 5.9, x256 6.3 -> 6.5, x320 6.8 -> 7.1, x384 7.2 -> 7.1, x512 8.1
+// -> 7.6; with a residual to add 1536x1024x384 (384 tiles) 8.5 -> 8.3, 2304x768x384 (432) 8.7 -> 8.9, x512 9.8 -> 9.6.
 bool even_pays(const hmy_gemm_desc &g) {
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   return g.K % SK == 0 && g.K >= (tiles <= 256 ? 256 : g.res && tiles > 400 ? 512 : 384);
@@ -1393,24 +1393,25 @@ bool gemm_small_excluded() {
   return larger_forced;
 }
 
-// Weight gradients on 64x64 tiles: while the contraction of a workgroup (K over the splits) is not long.  A workgroup multiplies a
-// K tile in 215 to 230 ns here, and the larger kernels, whose workgroups have four times the multiplies and whose splits are four
-// times as many, start 10 us later and are a third faster from there on.  Measured over 80 outputs, 128x128 tiles -> these, us:
-// - up to 256 tiles the two meet between 4600 and 5600 (768x768x4096 21.7 -> 19.1, x4608 22.5 -> 21.1, x6144 26.2 -> 26.5; 512x512 in
-//   four parts of 4608 24.5 -> 22.5, of 5632 26.2 -> 25.9; 992x864x4096 21.1 -> 19.7, x5120 22.8 -> 23.5);
-// - sooner where rows are no whole half cache lines: a row of a tile then lies in three of them instead of two, of the larger tiles'
-//   in five instead of four (1000x1000x4096 26.6 -> 24.2, x5120 28.5 -> 28.8; 504x392 in four parts of 4096 24.0 -> 23.1), and at 3072 if
-//   the tiles leave many compute units idle (1000x520x3072 19.6 -> 18.5, x3584 19.1 -> 20.8);
-// - the parts of a split contraction are dealt over the eight XCDs in turn.  Unless their number is a power of two an L2 cache sees
-//   several of them: three up to 3072 (800x352 in three parts of 3072 19.8 -> 18.7, of 4096 21.5 -> 23.1), more not at all
+// Weight gradients on 64x64 tiles: while the contraction of a workgroup (K over the splits) is not long.  A workgroup
+// multiplies a K tile in 215 to 230 ns here, and the larger kernels, whose workgroups have four times the multiplies and whose
+// splits are four times as many, start 10 us later and are a third faster from there on.  Measured over 80 outputs, 128x128
+// tiles -> these, us:
+// - up to 256 tiles the two meet between 4600 and 5600 (768x768x4096 21.7 -> 19.1, x4608 22.5 -> 21.1, x6144 26.2 -> 26.5;
+//   512x512 in four parts of 4608 24.5 -> 22.5, of 5632 26.2 -> 25.9; 992x864x4096 21.1 -> 19.7, x5120 22.8 -> 23.5);
+// - sooner where rows are no whole half cache lines: a row of a tile then lies in three of them instead of two, of the larger
+//   tiles' in five instead of four (1000x1000x4096 26.6 -> 24.2, x5120 28.5 -> 28.8; 504x392 in four parts of 4096 24.0 ->
+//   23.1), and at 3072 if the tiles leave many compute units idle (1000x520x3072 19.6 -> 18.5, x3584 19.1 -> 20.8);
+// - the parts of a split contraction are dealt over the eight XCDs in turn.  Unless their number is a power of two an L2 cache
+//   sees several of them: three up to 3072 (800x352 in three parts of 3072 19.8 -> 18.7, of 4096 21.5 -> 23.1), more not at all
 //   (five parts of 2048: 416x416 17.3 -> 21.4, though 480x352 18.4 -> 14.7);
-// - 257 to 512 tiles are two workgroups for some of the compute units: up to 2304 (1280x1024 21.2 -> 21.0, x2560 21.4 -> 23.0), from 400
-//   on 3072 (2304x768x2816 23.9 -> 23.4, x3072 24.7 -> 25.2; 2048x1024x3072 26.7 -> 25.7).  If edge tiles are half empty, not at all
-//   (1056x992x2048 18.1 -> 20.1, 1320x800 18.8 -> 20.7; x1536 18.5 -> 16.8) and 2304 (1984x1000 26.1 -> 21.6 at 2048, 29.7 -> 28.8 at 3072;
-//   1312x1312x2304 22.2 -> 22.2, x2560 23.1 -> 24.1).
-// Short of a first split, at most 64 tiles of such misaligned rows are the other exception: 504x392x704 8.2 -> 7.7, x768 7.4 -> 7.8, x960
-// 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2).
-// Contractions that are no multiple of 64 (the kernel with branches): up to 1792 (768x768x1920 11 % slower).
+// - 257 to 512 tiles are two workgroups for some of the compute units: up to 2304 (1280x1024 21.2 -> 21.0, x2560 21.4 -> 23.0),
+//   from 400 on 3072 (2304x768x2816 23.9 -> 23.4, x3072 24.7 -> 25.2; 2048x1024x3072 26.7 -> 25.7).  If edge tiles are half
+//   empty, not at all (1056x992x2048 18.1 -> 20.1, 1320x800 18.8 -> 20.7; x1536 18.5 -> 16.8) and 2304 (1984x1000 26.1 -> 21.6
+//   at 2048, 29.7 -> 28.8 at 3072; 1312x1312x2304 22.2 -> 22.2, x2560 23.1 -> 24.1).
+// Short of a first split, at most 64 tiles of such misaligned rows are the other exception: 504x392x704 8.2 -> 7.7, x768 7.4 ->
+// 7.8, x960 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2). Contractions that are no multiple of 64 (the kernel
+// with branches): up to 1792 (768x768x1920 11 % slower).
 bool small_sum_pays(const hmy_gemm_desc &g) {
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   const int splits = small_splits(g), length = g.K / splits;
@@ -1421,20 +1422,20 @@ bool small_sum_pays(const hmy_gemm_desc &g) {
     const bool whole = g.M % ST == 0 && g.N % ST == 0;
     return tiles <= 400 ? whole && length <= 2304 : length <= (whole ? 3072 : 2304);
   }
-  if ((splits & (splits - 1)) != 0) return (splits % 3 == 0 && 24 % splits == 0) && length <= 3072;   // 3, 6, 12: three parts per XCD
+  if ((splits & (splits - 1)) != 0) return splits % 3 == 0 && 24 % splits == 0 && length <= 3072;   // 3, 6, 12: three per XCD
   return length <= (half_lines ? 4608 : splits == 1 && tiles < 200 ? 3072 : 4096);
 }
 
 // 64x64 tiles while all of them are resident at once, two per compute unit (us, 128x128 -> 64x64 tiles: 480x768x256 7.3 -> 5.0,
-// 1024x1024x1024 12.6 -> 8.1, 2048x1024 (512 tiles), K = 1024 12.9 -> 10.2, 4096 31.7 -> 28.0; 3072x768x1536 (576 tiles) 16.6 -> 20.4), and
-// for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to register-staged ones
-// (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions that are no multiple of 64 go
-// through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 -> 18.9, 4096 32.5 -> 33.4).  Beyond 256
-// tiles an operand stored contraction-major loses on long ones what the tiles gain: from 8192 on (input gradients 2048x1024x8192
-// 59.9 -> 58.9, x12288 86.7 -> 89.4), from 4096 on where its rows are no whole half cache lines (1960x1000x4096 36.8 -> 35.5, x8192 63.0
-// -> 68.1; forward, x16384 109 -> 102).
-// Sums into an fp32 C other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the
-// contraction, and so do long weight gradients (above).
+// 1024x1024x1024 12.6 -> 8.1, 2048x1024 (512 tiles), K = 1024 12.9 -> 10.2, 4096 31.7 -> 28.0; 3072x768x1536 (576 tiles) 16.6
+// -> 20.4), and for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to
+// register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions
+// that are no multiple of 64 go through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 ->
+// 18.9, 4096 32.5 -> 33.4).  Beyond 256 tiles an operand stored contraction-major loses on long ones what the tiles gain: from
+// 8192 on (input gradients 2048x1024x8192 59.9 -> 58.9, x12288 86.7 -> 89.4), from 4096 on where its rows are no whole half
+// cache lines (1960x1000x4096 36.8 -> 35.5, x8192 63.0 -> 68.1; forward, x16384 109 -> 102). Sums into an fp32 C other than
+// weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the contraction, and so do long
+// weight gradients (above).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
   if (gemm_small_excluded()) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
@@ -1458,21 +1459,23 @@ int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
     // (2048 x 4800 x 1600) 49 against 57 us, 175 (1600 x 6400 x 2048) 71 against 72 us, 64 much slower.
     const int gm2 = (g.M + 255) / 256, gn2 = (g.N + 255) / 256, wgs = gm2 * gn2;
     const bool fills = wgs >= 144 && (wgs <= 256 || wgs >= 384);
-    // 256x128 tiles (force_tile: never) where they are one round of nearly all compute units and 256x256 ones are not, or three
-    // rounds against two poorly filled ones.  Speed-up over the kernel taken otherwise, at 144 to 256 tiles: forward and input
-    // gradients K = 512 0.87 to 1.16, 1024 1.03 to 1.25, 2048 1.10 to 1.36, 4096 1.13 to 1.60; sums into C, whose output stage is
-    // twice as long, K = 1024 1.09 to 1.12 up to 156 tiles and 0.96 to 1.01 beyond, 2048 1.01 to 1.17.  128 tiles: 0.86 to 0.93.
-    // Three rounds: 2048x12288x4096 214 -> 186, 3072x6144 (576 tiles) K = 2048 0.98 to 1.08, 4096 1.05 to 1.15.
-    // (Not where 128x128 tiles are one round too, as with few rows over the middle of a tile.)
+    // 256x128 tiles (force_tile: never) where they are one round of more than half of the compute units and 256x256 ones are
+    // not, or three rounds against two poorly filled ones.  Speed-up over the kernel taken otherwise, at 144 to 256 tiles:
+    // forward and input gradients K = 512 0.87 to 1.16, 1024 1.03 to 1.25, 2048 1.10 to 1.36, 4096 1.13 to 1.60; sums into C,
+    // whose output stage is twice as long, up to 160 tiles K = 512 1.02 to 1.07, 768 1.04 to 1.09, 1024 1.06 to 1.13 and beyond
+    // 1024 0.96 to 1.01, 2048 1.01 to 1.17.  128 tiles: 0.86 to 0.93. Three rounds: 2048x12288x4096 214 -> 186, 3072x6144 (576
+    // tiles) K = 2048 0.98 to 1.08, 4096 1.05 to 1.15. (Not where 128x128 tiles are one round too, as with few rows over the
+    // middle of a tile.)
     const int w2 = gm2 * ((g.N + 127) / 128), w1 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     const bool one_round = !fills && w1 > 256 && w2 >= 144 && w2 <= 256 && g.K >= (!g.accumulate ? 1024 : w2 <= 160 ? 512 : 2048);
     const bool three_rounds = wgs > 256 && wgs <= 384 && w2 > 512 && w2 <= 768 && g.K >= 2048 && !g.accumulate;
     if (force_tile == 0 && force_bk == 0 && force_s == 0 && g.M >= 256 && g.K % 64 == 0 && (one_round || three_rounds))
       return launch_256x128(g, p, 1, (hipStream_t)st);
-    // Very long sums over few outputs: these tiles with the contraction split (fp32 atomics into C), where they come to nearly a
-    // workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128 tiles
-    // -> these: 2048x1024, K = 50240 219 -> 190 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280), 512x1600 104 -> 92
-    // (5582); 1024x1024x40960 98 -> 93 (5120), 512x1024x65536 77.7 -> 78.4 (4096), 1024x1024x16384 50 -> 55 (2048).
+    // Very long sums over few outputs: these tiles with the contraction split (fp32 atomics into C), where they come to nearly
+    // a workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128
+    // tiles -> these: 2048x1024, K = 50240 219 -> 190 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280),
+    // 512x1600 104 -> 92 (5582); 1024x1024x40960 98 -> 93 (5120), 512x1024x65536 77.7 -> 78.4 (4096), 1024x1024x16384 50 -> 55
+    // (2048).
     if (force_tile == 0 && force_bk == 0 && force_s == 0 && can_split && w1 <= 128 && g.M >= 256 && g.K % 64 == 0) {
       const int splits = 256 / w2;
       if (splits > 1 && w2 * splits >= 200 && g.K / splits >= 4608) return launch_256x128(g, p, splits, (hipStream_t)st);

@@ -310,11 +310,12 @@ int launch_gemm_f32(const hmy_gemm_desc &g, stream_t st) {
   if (!vec) return launch_split<false, 2, 2, 1, 1, 1>(g, p, s);
   if (tiles(128) >= 512) return launch_split<true, 2, 2, 1, 2, 2>(g, p, s);
   // 64x64 tiles: eight waves, two to each quarter of the tile and a half of the contraction, where a compute unit has one such
-  // workgroup.  Where it has two, those hide each other's reads and barriers, and the eight (K tiles of 64 instead of 32) pay only
-  // where the output stage reads what it adds, with half the registers per wave, or where the contraction is very long.
-  // Four waves -> eight, us: 1536x512x1024 (192 tiles, weight gradient) 35 -> 25, 1024x1024x512 15.0 -> 14.1 (weight gradient 19.9 ->
-  // 16.7), x2048 48 -> 43; 2048x1024 (512 tiles), K = 32 5.8 -> 7.9, 96 8.4 -> 10.2, 512 24.0 -> 24.7, 2048 80.1 -> 79.3, with a residual
-  // K = 64 12.0 -> 10.2, 512 28.5 -> 27.0, weight gradient K = 32 7.5 -> 8.7, 128 14.1 -> 12.7, 2048 88.8 -> 83.2; 2048x1536x512 (768) 33.5 -> 35.0
+  // workgroup.  Where it has two, those hide each other's reads and barriers, and the eight (K tiles of 64 instead of 32) pay
+  // only where the output stage reads what it adds, with half the registers per wave, or where the contraction is very long.
+  // Four waves -> eight, us: 1536x512x1024 (192 tiles, weight gradient) 35 -> 25, 1024x1024x512 15.0 -> 14.1 (weight gradient
+  // 19.9 -> 16.7), x2048 48 -> 43; 2048x1024 (512 tiles), K = 32 5.8 -> 7.9, 96 8.4 -> 10.2, 512 24.0 -> 24.7, 2048 80.1 ->
+  // 79.3, with a residual K = 64 12.0 -> 10.2, 512 28.5 -> 27.0, weight gradient K = 32 7.5 -> 8.7, 128 14.1 -> 12.7, 2048 88.8
+  // -> 83.2; 2048x1536x512 (768) 33.5 -> 35.0
   if (tiles(64) > 512) return launch_split<true, 2, 2, 1, 1, 1>(g, p, s);
   if (tiles(64) >= 192) {
     const bool eight = tiles(64) <= 256 || g.K >= 2048 || (g.K > 32 && (g.res || g.accumulate));

@@ -344,7 +344,8 @@ def test_gemm_bf16_256x128_tiles(ta, tb):
         _gemm_case(*args, M, N, K, ta, tb, 1, 0, True, True, False, True, res_fp32=1)
     _gemm_case(*args, 2040, 2296, 512, ta, tb, 1, 1, False, False, False, True)      # sums into C: few tiles, and many
     _gemm_case(*args, 2048, 4096, 2048, ta, tb, 1, 1, False, False, False, True)
-    _gemm_case(*args, 2048, 2300 if not tb else 2296, 1024, ta, tb, 1, 0, False, False, False, True)   # rows of C that allow no 16-byte access
+    # rows of C that allow no 16-byte access
+    _gemm_case(*args, 2048, 2300 if not tb else 2296, 1024, ta, tb, 1, 0, False, False, False, True)
     _gemm_case(*args, 2048, 8968, 2048, ta, tb, 0, 0, True, False, False, True)      # three rounds
 
 
@@ -376,9 +377,11 @@ def test_gemm_bf16_long_sums_of_narrow_outputs(ta, tb, N):
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (1, 8, 7), (72, 136, 63), (65, 57, 65), (200, 264, 250), (480, 256, 321),
-                                   (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049), (2048, 1024, 2080),
+                                   (128, 128, 1100), (1288, 1928, 96), (768, 776, 2047), (768, 776, 2048), (768, 776, 2049),
+                                   (2048, 1024, 2080),
                                    (200, 264, 576), (200, 264, 640), (200, 264, 960), (200, 264, 1000), (768, 776, 1728),
-                                   (768, 776, 1792), (65, 57, 128), (72, 72, 192), (768, 776, 4096), (264, 200, 4224), (65, 57, 256),
+                                   (768, 776, 1792), (65, 57, 128), (72, 72, 192), (768, 776, 4096), (264, 200, 4224),
+                                   (65, 57, 256),
                                    (72, 72, 320), (200, 264, 4672), (1000, 1200, 320), (1000, 1200, 384), (1000, 1200, 512),
                                    (768, 768, 4608), (1280, 1024, 2304)])
 def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
@@ -441,8 +444,8 @@ def test_gemm_fp32(ta, tb):
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 1), (33, 31, 129), (32, 32, 128), (900, 840, 70), (832, 1024, 32), (4100, 2050, 33),
-                                   (4096, 2048, 64), (72, 520, 513), (256, 500, 800), (1500, 520, 130), (1408, 1472, 64), (2050, 1050, 96),
-                                   (1000, 1040, 32), (1000, 1040, 36), (1000, 1040, 2052)])
+                                   (4096, 2048, 64), (72, 520, 513), (256, 500, 800), (1500, 520, 130), (1408, 1472, 64),
+                                   (2050, 1050, 96), (1000, 1040, 32), (1000, 1040, 36), (1000, 1040, 2052)])
 def test_gemm_fp32_every_split(ta, tb, M, N, K):
     """One 32x32 tile and its edges, 64x64 tiles, 128x128 tiles, on four and on eight waves (272 tiles: eight where something is
     added and for long sums); ragged and whole in all three directions, contractions of one to a few K tiles; leading dimensions
@@ -464,7 +467,8 @@ def test_attention_fp32_one_and_several_waves(causal, b, s, H, dh):
 
 
 @pytest.mark.parametrize("causal", [1, 0])
-@pytest.mark.parametrize("b,s,H,dh", [(1, 32, 3, 64), (3, 33, 2, 32), (2, 64, 2, 128), (2, 65, 3, 64), (1, 97, 2, 128), (4, 65, 24, 32),
+@pytest.mark.parametrize("b,s,H,dh", [(1, 32, 3, 64), (3, 33, 2, 32), (2, 64, 2, 128), (2, 65, 3, 64), (1, 97, 2, 128),
+                                      (4, 65, 24, 32),
                                       (2, 140, 40, 64), (2, 130, 40, 128), (6, 66, 60, 32)])
 def test_attention_fp32_tiles_split_over_waves(causal, b, s, H, dh):
     """One, two and four waves per 32 rows: a single tile, waves without one, a ragged last tile, and launches on either side of
@@ -552,10 +556,14 @@ def test_attention_eight_and_four_waves(causal, b, s, H, dh):
     _attention_case(prec, pc, dt, tol, causal, b, s, H, dh)
 
 
-@pytest.mark.parametrize("causal,b,s,H,dh", [(0, 2, 64, 3, 64), (0, 2, 65, 3, 64), (0, 2, 383, 3, 64), (1, 2, 384, 2, 64), (1, 1, 1020, 40, 64),
-                                             (1, 1, 1030, 40, 64), (1, 3, 111, 2, 128), (0, 3, 112, 2, 128), (0, 2, 67, 3, 32)])
+# head dimension 64: rows of one streamed tile and of two; 256 workgroups and 258; causal, more than 256 of them on either side of
+# 1024 rows, and 513 beyond it
+@pytest.mark.parametrize("causal,b,s,H,dh", [(0, 2, 64, 3, 64), (0, 2, 65, 3, 64), (0, 8, 130, 16, 64), (0, 43, 130, 3, 64),
+                                             (1, 1, 1020, 40, 64), (1, 1, 1030, 40, 64), (1, 1, 1030, 57, 64),
+                                             (1, 3, 111, 2, 128), (0, 3, 112, 2, 128), (0, 2, 67, 3, 32)])
 def test_attention_backward_either_side_of_eight_waves(causal, b, s, H, dh):
-    """dK/dV on four and on eight waves from either side of the lengths that part them, the edges' masks in both."""
+    """dK/dV on four and on eight waves from either side of the lengths and numbers of workgroups that part them, the edges' masks
+    in both."""
     say(f"attention backward causal={causal} b={b} s={s} H={H} dh={dh}")
     _attention_case(*PRECS[1], causal, b, s, H, dh)
 
