@@ -126,9 +126,8 @@ __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r / 4) + 4 * 
 // dK/dV of a 32x32 subtile: lane owns a key, accumulator registers run over its 32 queries, sixteen per lane in four runs of
 // four consecutive rows (16-byte reads of the rows' statistics): scores -> P (in place), dP -> dS (in place). `edge`, the same
 // for the whole wave: queries past the sequence end or (causal) before the key may be among them; the test stands outside of
-// the loop over registers, where the compiler made sixteen branches of it, each around one exponential.  The whole backward: 16
-// heads of 64, causal, s = 4096 207 -> 174 us, four of s = 1024 75 -> 62, 32 heads of 32, s = 2048 244 -> 188; of 128, causal,
-// 197 -> 171.
+// the loop over registers, where the compiler made sixteen branches of it, each around one exponential.  The whole backward, us,
+// causal: 16 heads of 64, s = 4096 202 -> 175, four sequences of 1024 71 -> 63; 32 heads of s = 2048: of 32 108 -> 76, of 128 197 -> 169.
 __device__ __forceinline__ void probabilities(f32x16 &sm, f32x16 &dp, const float *lse, const float *delta, int h2, float sc,
                                               bool edge, int ib, int s, int key, int causal) {
 #pragma unroll

@@ -12,9 +12,9 @@
 // Contraction order inside a tile: lane half h of a wave takes steps 4h..4h+3 of every group of eight, for both
 // operands alike, so that an operand with the contraction index contiguous is read from LDS 16 bytes at a time; one
 // stored contraction-major is kept [k][row] and read 4 bytes at a time.
-// Measured against the plain kernel (us): 128x128x128 15.5 -> 5.5, 1024x2048x512 72 -> 24.5, 1024x512x2048 284 -> 26.6,
-// 1024x512x8192 (input gradient) 1135 -> 106, 4096x1536x2048 224, 2048x8192x4096 (weight gradient) 2520 -> 1206
-// = 114 TFLOP/s of the 154 that a large fp32 product of the vendor library reaches.
+// Measured against the plain kernel (us): 128x128x128 15.5 -> 5.5, 1024x2048x512 72 -> 24.0, 1024x512x2048 284 -> 26.0,
+// 1024x512x8192 (input gradient) 1135 -> 103, 4096x1536x2048 224, 2048x8192x4096 (weight gradient) 2520 -> 1186
+// = 116 TFLOP/s of the 154 that a large fp32 product of the vendor library reaches.
 #include <algorithm>
 
 #include "dev_common.h"
