@@ -321,9 +321,13 @@ int launch_gemm_f32(const hmy_gemm_desc &g, stream_t st) {
     const bool eight = tiles(64) <= 256 || g.K >= 2048 || (g.K > 32 && (g.res || g.accumulate));
     return eight ? launch_split<true, 2, 2, 2, 1, 1>(g, p, s) : launch_split<true, 2, 2, 1, 1, 1>(g, p, s);
   }
-  // 32x32 tiles: eight waves to a tile where a compute unit has one and the contraction is long: 512x512x2048 17.7 -> 16.0 us,
-  // x512 7.2 -> 6.6, x128 5.7 -> 5.7; 1024x512x512 (512 tiles) 9.8 -> 11.1
-  if (tiles(32) <= 256 && g.K >= 512) return launch_split<true, 1, 1, 8, 1, 1>(g, p, s);
+  // 32x32 tiles: eight waves to a tile where a compute unit has one and the contraction is long, unless its last K tile, 256
+  // deep instead of 128, would be less than half full and the others are few.  Four waves -> eight, us: 512x512x512 7.0 -> 6.6,
+  // x640 7.9 -> 8.3, x768 8.8 -> 8.2, x896 10.0 -> 10.3, x1152 11.9 -> 12.0, x2048 17.8 -> 16.1; weight gradient x640 8.1 -> 8.5,
+  // x1152 13.2 -> 12.8; input gradient x640 7.8 -> 8.4, x1152 11.9 -> 12.3, x1408 13.7 -> 13.9, x1600 15.8 -> 15.6; with a residual
+  // x800 11.4 -> 10.9; 512x512x128 5.7 -> 5.7; 1024x512x512 (512 tiles) 9.8 -> 11.1
+  const bool filled = (g.K + 127) / 128 % 2 == 0 || g.K > (g.res ? 768 : g.tb && !g.ta ? 1536 : 1024);
+  if (tiles(32) <= 256 && g.K >= 512 && filled) return launch_split<true, 1, 1, 8, 1, 1>(g, p, s);
   return launch_split<true, 1, 1, 4, 1, 1>(g, p, s);
 }
 

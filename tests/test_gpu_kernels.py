@@ -445,10 +445,11 @@ def test_gemm_fp32(ta, tb):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(1, 8, 1), (33, 31, 129), (32, 32, 128), (900, 840, 70), (832, 1024, 32), (4100, 2050, 33),
                                    (4096, 2048, 64), (72, 520, 513), (256, 500, 800), (1500, 520, 130), (1408, 1472, 64),
-                                   (2050, 1050, 96), (1000, 1040, 32), (1000, 1040, 36), (1000, 1040, 2052)])
+                                   (2050, 1050, 96), (1000, 1040, 32), (1000, 1040, 36), (1000, 1040, 2052),
+                                   (72, 520, 640), (72, 520, 644), (72, 520, 1092), (72, 520, 1540)])
 def test_gemm_fp32_every_split(ta, tb, M, N, K):
     """One 32x32 tile and its edges, 64x64 tiles, 128x128 tiles, on four and on eight waves (272 tiles: eight where something is
-    added and for long sums); ragged and whole in all three directions, contractions of one to a few K tiles; leading dimensions
+    added and for long sums; 51 of 32x32: unless that leaves the last K tile nearly empty); ragged and whole in all three directions, contractions of one to a few K tiles; leading dimensions
     that allow 16-byte accesses and ones that do not.  Bound: sums of K rounded fp32 products."""
     say(f"gemm fp32 {M}x{N}x{K} ta={ta} tb={tb}")
     args = ("fp32", 0, torch.float32, 1e-5)
