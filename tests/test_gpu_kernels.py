@@ -449,8 +449,9 @@ def test_gemm_fp32(ta, tb):
                                    (72, 520, 640), (72, 520, 644), (72, 520, 1092), (72, 520, 1540)])
 def test_gemm_fp32_every_split(ta, tb, M, N, K):
     """One 32x32 tile and its edges, 64x64 tiles, 128x128 tiles, on four and on eight waves (272 tiles: eight where something is
-    added and for long sums; 51 of 32x32: unless that leaves the last K tile nearly empty); ragged and whole in all three directions, contractions of one to a few K tiles; leading dimensions
-    that allow 16-byte accesses and ones that do not.  Bound: sums of K rounded fp32 products."""
+    added and for long sums; 51 of 32x32: unless that leaves the last K tile nearly empty); ragged and whole in all three
+    directions, contractions of one to a few K tiles; leading dimensions that allow 16-byte accesses and ones that do not.  Bound:
+    sums of K rounded fp32 products."""
     say(f"gemm fp32 {M}x{N}x{K} ta={ta} tb={tb}")
     args = ("fp32", 0, torch.float32, 1e-5)
     _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, True, False, True, pad=3)
