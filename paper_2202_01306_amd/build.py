@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhmy.so")
 
-SOURCES = ["model.cpp", "planner.cpp", "api.cpp", "engine.hip", "copy_engine.cpp", "elementwise.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip", "attention_mfma.hip", "gemm_tr.hip", "gemm_dma.hip", "host_update.cpp"]
+SOURCES = ["model.cpp", "planner.cpp", "api.cpp", "engine.hip", "copy_engine.cpp", "elementwise.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip", "attention_mfma.hip", "gemm_tr.hip", "gemm_dma.hip", "gemm_tile.hip", "host_update.cpp"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",

@@ -21,39 +21,22 @@
 // ds_read_b64_tr_b16 with k rows 8h..8h+3 and 8h+4..8h+7 (h = lane/32), which is the
 // same contraction order as the 16-byte read of the other layout.
 //
-// Outputs in between go to 256x256 and 256x128 tiles, small ones to 64x64 tiles (further down).
+// Larger outputs go to tiles of 256 rows (gemm_tile.hip), small ones to 64x64 tiles (further down).
 //
-// Tuning switches (read once per process): HMY_GEMM_BK = 32 | 64 overrides the K tile of
-// both kernels, HMY_GEMM_STAGES = 3 | 4 the ring depth of the 128x128 kernel,
-// HMY_GEMM_TILE = 128 | 256 the choice between it and the 256x256 kernel.  With any of them set no shape takes the
-// 64x64 or 256x128 tiles.
+// Tuning switches (read once per process): HMY_GEMM_BK = 32 | 64 overrides the K tile of the 128x128 kernel,
+// HMY_GEMM_STAGES = 3 | 4 its ring's depth, and with either of them every shape takes it; HMY_GEMM_TILE = 128 | 256 names it or
+// tiles of 256x256.  With any of them set no shape takes the 64x64 tiles.
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
 
-#include "dev_common.h"
-#include "hmy_internal.h"
+#include "gemm_dma.h"
 
 namespace hmy {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 constexpr int BM = 128, NT = 256;  // square block tile, threads
-
-struct DmaP {
-  const bf16_t *A, *B;
-  void *C;
-  const bf16_t *bias, *res;
-  bf16_t *gelu_out;
-  int M, N, K;
-  uint32_t lda, ldb;
-  int64_t ldc, ldr;
-  int c_fp32, accumulate, res_fp32;
-};
 
 // element address inside a [row][k] tile of BK columns (BK/8 chunks per row)
 template <int BK>
@@ -66,42 +49,9 @@ __device__ __forceinline__ int addr_kr(int k, int col) {
   return k * BM + ((((col >> 3) ^ ((k & 3) << 2)) & 15) << 3) + (col & 7);
 }
 
-// one wavefront-wide 16-byte-per-lane copy HBM -> LDS.  lds_addr is wave-uniform (the
-// hardware adds 16 * lane); the global address is base + byte offset per lane.
-// The statement overwrites m0 and cannot say so: the compiler rejects m0 in a clobber list as a
-// reserved register ("may lead to undefined behaviour").  That is safe here because the compiler
-// keeps no value of its own in m0 across statements: whenever code it generates reads m0 (indexed
-// register moves, messages, its own LDS-direct loads) it writes m0 immediately before, and this
-// file uses none of those constructs.
-__device__ __forceinline__ void dma16(const void *base, uint32_t byte_off, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(byte_off), "s"(base), "s"(lds_addr)
-               : "memory");
-}
-
 // the 16-byte-per-lane copy with a full address per lane
 __device__ __forceinline__ void dma16_at(const void *addr, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory");
-}
-// The same through a buffer descriptor, in two parts: the LDS address, then the copy from `lane_off` of each lane plus `tile_off`
-// of the wave.  Bytes past the descriptor's size read as zeros and cost no memory traffic, and that is decided on the lane
-// offset as an unsigned number: it must never be negative, so the instruction's own constant (added to both addresses) is not
-// used to step from one KiB to the next.  Between the two the compiler writes m0 as little as it does elsewhere in this file
-// (see above).
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x4 buffer_of(const void *base, uint32_t bytes) {
-  const uint64_t at = reinterpret_cast<uint64_t>(base);
-  u32x4 r;
-  r[0] = __builtin_amdgcn_readfirstlane(uint32_t(at));
-  r[1] = __builtin_amdgcn_readfirstlane(uint32_t(at >> 32) & 0xffffu);   // stride 0
-  r[2] = __builtin_amdgcn_readfirstlane(bytes);
-  r[3] = 0x00020000u;
-  return r;
-}
-__device__ __forceinline__ void set_m0(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds_addr) : "memory"); }
-__device__ __forceinline__ void dma16_buffer(u32x4 rsrc, uint32_t lane_off, uint32_t tile_off) {
-  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" : : "v"(lane_off), "s"(rsrc), "s"(tile_off) : "memory");
 }
 // contraction steps past the operands' end come from here
 __device__ __attribute__((aligned(256))) bf16_t g_zero_page[128];   // zero-initialised, never written
@@ -158,143 +108,6 @@ __device__ __forceinline__ bf16x8 frag(const bf16_t *s, int row32, int ks, int l
     return u.b;
   }
 }
-
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
-// Output stage for 8 consecutive columns of one row.  `fast`: every pointer and leading
-// dimension allows 16-byte accesses; `inside`: the workgroup's tile lies inside C.  A
-// tile that sticks out still leaves through the 16-byte path wherever a row's group of
-// 8 columns lies inside C (a 1600-wide output ends in the middle of a tile: element by
-// element that tile took longer than the whole K loop); what remains, and everything
-// when `fast` is false, goes element by element through a loop kept rolled, so that it
-// costs no instruction-cache space.
-struct Epi {
-  bool fast, inside;
-  __device__ __forceinline__ bool whole8(const DmaP &p, int m, int nn) const {
-    return inside || (m < p.M && nn + 8 <= p.N);
-  }
-  __device__ __forceinline__ void init(const DmaP &p, int m0, int n0, int side = BM) {
-    const int esz = p.c_fp32 ? 4 : 2;
-    bool ok = (reinterpret_cast<uintptr_t>(p.C) & 15) == 0 && (p.ldc * esz) % 16 == 0;
-    if (p.res) ok = ok && (reinterpret_cast<uintptr_t>(p.res) & 15) == 0 && p.ldr % 8 == 0;
-    if (p.res && p.res_fp32 && p.accumulate) ok = false;   // both would want the prefetch registers
-    if (p.bias) ok = ok && (reinterpret_cast<uintptr_t>(p.bias) & 15) == 0;
-    if (p.gelu_out) ok = ok && (reinterpret_cast<uintptr_t>(p.gelu_out) & 15) == 0;
-    fast = ok;
-    inside = m0 + side <= p.M && n0 + side <= p.N;
-  }
-  // tanh-form GELU with the hardware exponential: the argument is a bf16 value and so is
-  // the result, which the 2-ulp exponential does not disturb.  Written as u * sigmoid(2z),
-  // the same function as u/2 (1 + tanh z), z = c (u + a u^3), in fewer instructions: the
-  // epilogue's arithmetic runs with the matrix cores idle, so it is paid in full.
-  static __device__ __forceinline__ float gelu_fast(float u) {
-    // exp(-2z) as one exp2 with the constants folded, and the hardware reciprocal: __fdividef and
-    // __expf expand to a ten-instruction IEEE division and an extra multiply
-    const float k = -2.f * 0.7978845608028654f * 1.4426950408889634f, a = 0.044715f;
-    return u * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(k * (u + a * u * u * u)));
-  }
-  // what the output stage reads from global memory for 8 columns of one row: the residual
-  // (bf16) or, for an accumulating fp32 C, C itself.  Fetched before the last K tile so
-  // that its latency hides behind that tile's multiplies.
-  struct Pre { float4 lo, hi; };
-  __device__ __forceinline__ void prefetch(const DmaP &p, int m, int nn, Pre &r) const {
-    if (!whole8(p, m, nn)) return;
-    if (p.res && p.res_fp32) {   // the fp32 residual stream: 8 columns are 32 bytes
-      const float *x = reinterpret_cast<const float *>(p.res) + int64_t(m) * p.ldr + nn;
-      r.lo = *reinterpret_cast<const float4 *>(x);
-      r.hi = *reinterpret_cast<const float4 *>(x + 4);
-    } else if (p.res) {
-      r.lo = *reinterpret_cast<const float4 *>(p.res + int64_t(m) * p.ldr + nn);
-    } else if (p.c_fp32 && p.accumulate) {
-      const float *c = static_cast<const float *>(p.C) + int64_t(m) * p.ldc + nn;
-      r.lo = *reinterpret_cast<const float4 *>(c);
-      r.hi = *reinterpret_cast<const float4 *>(c + 4);
-    }
-  }
-  // v[0..7] += the eight bf16 values held in the 16 bytes of `raw`, taken apart with integer operations on
-  // the registers: reading them through a pointer of another type made the compiler keep `raw` in scratch memory
-  static __device__ __forceinline__ void add_bf16x8(float (&v)[8], const float4 &raw) {
-    const uint32_t u[4] = {__float_as_uint(raw.x), __float_as_uint(raw.y), __float_as_uint(raw.z), __float_as_uint(raw.w)};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      v[2 * c] += __uint_as_float(u[c] << 16);
-      v[2 * c + 1] += __uint_as_float(u[c] & 0xffff0000u);
-    }
-  }
-  // `bias8`: the lane's 8 bias values, the same for every row it emits.  Loaded once with the prefetch: a
-  // load inside this function would wait on the memory counter, which also counts the stores of the
-  // previous call, and so serialise the eight store rounds of a wave.
-  __device__ __forceinline__ void emit_fast(const DmaP &p, int m, int nn, float (&v)[8], const Pre &r,
-                                            const float4 &bias8) const {
-    if (p.bias) add_bf16x8(v, bias8);
-    if (p.res && p.res_fp32) {
-      v[0] += r.lo.x; v[1] += r.lo.y; v[2] += r.lo.z; v[3] += r.lo.w;
-      v[4] += r.hi.x; v[5] += r.hi.y; v[6] += r.hi.z; v[7] += r.hi.w;
-    } else if (p.res) {
-      add_bf16x8(v, r.lo);
-    }
-    const int64_t ci = int64_t(m) * p.ldc + nn;
-    if (p.c_fp32) {
-      float *c = static_cast<float *>(p.C) + ci;
-      float4 lo = *reinterpret_cast<float4 *>(v), hi = *reinterpret_cast<float4 *>(v + 4);
-      if (p.accumulate) {
-        if (p.res) {   // the prefetch slot held the residual: read C now
-          const float4 a = *reinterpret_cast<const float4 *>(c), b = *reinterpret_cast<const float4 *>(c + 4);
-          lo.x += a.x; lo.y += a.y; lo.z += a.z; lo.w += a.w;
-          hi.x += b.x; hi.y += b.y; hi.z += b.z; hi.w += b.w;
-        } else {
-          lo.x += r.lo.x; lo.y += r.lo.y; lo.z += r.lo.z; lo.w += r.lo.w;
-          hi.x += r.hi.x; hi.y += r.hi.y; hi.z += r.hi.z; hi.w += r.hi.w;
-        }
-      }
-      *reinterpret_cast<float4 *>(c) = lo;
-      *reinterpret_cast<float4 *>(c + 4) = hi;
-    } else {
-      Vec16<bf16_t> o;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) o.v[k] = from_f32<bf16_t>(v[k]);
-      // gelu_out == C: only the activation is wanted (a forward pass that keeps nothing for a backward pass)
-      if (p.gelu_out != static_cast<bf16_t *>(p.C)) store16(static_cast<bf16_t *>(p.C) + ci, o);
-      if (p.gelu_out) {
-        Vec16<bf16_t> g;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) g.v[k] = from_f32<bf16_t>(gelu_fast(to_f32(o.v[k])));
-        store16(p.gelu_out + ci, g);
-      }
-    }
-  }
-  // one element; src points at its fp32 value in LDS
-  __device__ __forceinline__ void emit_one(const DmaP &p, int m, int nn, float v) const {
-    if (p.bias) v += to_f32(p.bias[nn]);
-    if (p.res)
-      v += p.res_fp32 ? reinterpret_cast<const float *>(p.res)[int64_t(m) * p.ldr + nn]
-                      : to_f32(p.res[int64_t(m) * p.ldr + nn]);
-    const int64_t ci = int64_t(m) * p.ldc + nn;
-    if (p.c_fp32) {
-      float *c = static_cast<float *>(p.C) + ci;
-      *c = p.accumulate ? *c + v : v;
-    } else {
-      const bf16_t o = from_f32<bf16_t>(v);
-      static_cast<bf16_t *>(p.C)[ci] = o;
-      if (p.gelu_out) p.gelu_out[ci] = from_f32<bf16_t>(gelu_f(to_f32(o)));
-    }
-  }
-  // a row's group of 8 columns, whose fp32 values lie at src in LDS: in one piece where the group lies inside C,
-  // else whatever of it does, element by element
-  __device__ __forceinline__ void emit8(const DmaP &p, int m, int nn, const float *src, const Pre &r,
-                                        const float4 &bias8) const {
-    if (whole8(p, m, nn)) {
-      float v[8];
-      *reinterpret_cast<float4 *>(v) = *reinterpret_cast<const float4 *>(src);
-      *reinterpret_cast<float4 *>(v + 4) = *reinterpret_cast<const float4 *>(src + 4);
-      emit_fast(p, m, nn, v, r, bias8);
-    } else if (m < p.M) {
-#pragma unroll 1
-      for (int k = 0; k < 8; ++k)
-        if (nn + k < p.N) emit_one(p, m, nn + k, src[k]);
-    }
-  }
-};
 
 template <bool TA, bool TB, int BK, int S>
 __global__ __launch_bounds__(NT) void k_gemm_dma(DmaP p, int tiles_per_split, int grid_n, int splits) {
@@ -413,7 +226,7 @@ __global__ __launch_bounds__(NT) void k_gemm_dma(DmaP p, int tiles_per_split, in
   int freed = S - 1;  // stage of tile t-1: free since the barrier inside that tile
   const bool split = splits > 1;
   Epi e;
-  e.init(p, m0, n0);
+  e.init(p, m0, n0, BM);
   const int m_tile = m0 + wm * 64, n_tile = n0 + wn * 64;
   Epi::Pre pre[2][4];
   float4 bias8 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -530,414 +343,6 @@ __global__ __launch_bounds__(NT) void k_gemm_dma(DmaP p, int tiles_per_split, in
         const int m = m_tile + 32 * i + row, nn = n_tile + col;
         if (m < p.M && nn < p.N) e.emit_one(p, m, nn, slab[row * 64 + (col ^ (((row >> 2) & 1) << 5))]);
       }
-    }
-  }
-}
-
-// The same GEMM on a 256x256 block tile for outputs large enough to give every compute unit one: what bounds the
-// 128x128 kernel is the rate at which the L2 caches feed the load-to-LDS instructions of all compute units together,
-// and a tile of twice the side moves half the bytes per multiply.  Eight waves of 128x64 (4x2 multiplies of 32x32x16
-// per 16-deep step, two waves per SIMD) over 128 KiB of LDS: a ring of four stages of K tiles of 32, or two stages of
-// K tiles of 64.  With the contraction index contiguous in memory a K tile of 32 takes 64 bytes of every operand
-// row, half a cache line, and the other half a tile later, when the line has left the compute unit's cache again;
-// a K tile of 64 takes whole lines, and the loads to LDS alone then run a quarter faster.  Two stages mean that a
-// tile is requested only when the tile before the one being multiplied has been left by every wave, one tile (64
-// multiplies per SIMD) before its first use.  Each operand's 256 rows are kept as two 128-row sub-tiles in the
-// layouts of the 128x128 kernel; waves 0-3 copy the first sub-tile of A and of B, waves 4-7 the second, each group
-// splitting its sub-tile the way the four waves of that kernel do.
-template <bool TA, bool TB, int BK, int S>
-__global__ __launch_bounds__(512) void k_gemm_dma256(DmaP p, int grid_n) {
-  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
-  constexpr int BT = 256;
-  constexpr int SUB = BM * BK;        // elements of one 128-row sub-tile
-  constexpr int STAGE = 4 * SUB;      // elements of one stage: A rows 0-127, A rows 128-255, B likewise
-  constexpr int NJ = BK / 16;         // load-to-LDS instructions per thread, operand and K tile
-  constexpr int L = 2 * NJ;           // load-to-LDS instructions per thread per K tile
-  constexpr int KS = BK / 16;         // 16-deep steps per K tile
-  static_assert(S >= 2, "one stage is multiplied while the others are in flight");
-  static_assert((S - 1) * L <= 63, "vmcnt is a 6-bit counter");
-  static_assert(S * STAGE * 2 >= 128 * 1024, "the output stage needs 16 KiB of LDS per wave");
-  const int tid = threadIdx.x, lane = tid % 64;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int wm = wave / 4, wn = wave % 4;     // this wave's outputs: rows 128 wm .. +127, columns 64 wn .. +63
-  const int half = wave / 4, w4 = wave % 4;   // the sub-tile of each operand this wave copies, and its share of it
-  // workgroup -> tile as in the 128x128 kernel (the contraction is never split here: the fp32 atomics of a split
-  // make the sum's order, and with it a result that is rounded afterwards, differ from run to run)
-  int bid = blockIdx.x;
-  const int nb = gridDim.x, grid_m = nb / grid_n;
-  {
-    const int x = bid % 8, per = nb / 8, extra = nb % 8;
-    bid = x * per + min(x, extra) + bid / 8;
-  }
-  constexpr int kBand = 4;
-  const int band = bid / (kBand * grid_n), first_m = band * kBand;
-  const int band_rows = min(grid_m - first_m, kBand);
-  const int in_band = bid - band * kBand * grid_n;
-  const int m0 = (first_m + in_band % band_rows) * BT, n0 = (in_band / band_rows) * BT;
-
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int n = p.K / BK;   // K tiles
-  Dma<TA, BK> da;
-  Dma<TB, BK> db;
-  da.init(p.lda, m0 + BM * half, p.M, lane, w4);
-  db.init(p.ldb, n0 + BM * half, p.N, lane, w4);
-  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem));
-  const uint32_t a_off = uint32_t(half) * uint32_t(2 * SUB), b_off = uint32_t(4 * SUB) + a_off;   // bytes inside a stage
-  const uint64_t a_kstep = TA ? uint64_t(BK) * p.lda : uint64_t(BK);
-  const uint64_t b_kstep = TB ? uint64_t(BK) * p.ldb : uint64_t(BK);
-  const bf16_t *a_next = p.A, *b_next = p.B;
-#pragma unroll
-  for (int s = 0; s < S; ++s)
-    if (s < n) {
-      da.issue(a_next, lds0 + uint32_t(s) * uint32_t(2 * STAGE) + a_off, w4);
-      db.issue(b_next, lds0 + uint32_t(s) * uint32_t(2 * STAGE) + b_off, w4);
-      a_next += a_kstep;
-      b_next += b_kstep;
-    }
-
-  const int a_sub = wm * SUB, b_sub = 2 * SUB + (wn / 2) * SUB, brow = (wn % 2) * 64;
-  bf16x8 fa[2][4], fb[2][2];   // fragments of one 16-deep step, read one step ahead of their multiplies
-  if (n > S - 1) wait_vm<(S - 1) * L>();
-  else wait_vm<0>();
-  __syncthreads();
-  if (n > 0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) fa[0][i] = frag<TA, BK>(smem + a_sub, 32 * i, 0, lane);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) fb[0][j] = frag<TB, BK>(smem + b_sub, brow + 32 * j, 0, lane);
-  }
-#define HMY_FENCE() __builtin_amdgcn_sched_barrier(0)
-#define HMY_MFMA(i, j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0)
-  // One 16-deep step: eight multiplies on fragment buffer `cur`; behind six of them one of the six fragment reads of the
-  // next step (from stage `nstage`, step `nks`, into buffer `nxt`); with `fetch`, the load-to-LDS instructions that
-  // bring the next tile into stage `fstage`, one behind a multiply each: four of them (K tile 32) behind the last
-  // five multiplies, eight (K tile 64) behind all.
-  auto step = [&](int cur, int nxt, bool reads, int nstage, int nks, bool fetch, int fstage) {
-    const bf16_t *a_s = smem + nstage * STAGE + a_sub, *b_s = smem + nstage * STAGE + b_sub;
-    const uint32_t fl = lds0 + uint32_t(fstage) * uint32_t(2 * STAGE);
-    // slot k = behind the k-th multiply
-    auto fetch_slot = [&](int k) {
-      if (!fetch) return;
-      const int i = NJ == 2 ? k - 3 : k;   // which of the tile's L instructions
-      if (i < 0 || i >= L) return;
-      if (i % 2 == 0) da.issue_one(a_next, fl + a_off, w4, i / 2);
-      else db.issue_one(b_next, fl + b_off, w4, i / 2);
-    };
-    HMY_FENCE();
-    HMY_MFMA(0, 0);
-    HMY_FENCE();
-    if (reads) fa[nxt][0] = frag<TA, BK>(a_s, 0, nks, lane);
-    fetch_slot(0);
-    HMY_FENCE();
-    HMY_MFMA(0, 1);
-    HMY_FENCE();
-    if (reads) fb[nxt][0] = frag<TB, BK>(b_s, brow, nks, lane);
-    fetch_slot(1);
-    HMY_FENCE();
-    HMY_MFMA(1, 0);
-    HMY_FENCE();
-    if (reads) fb[nxt][1] = frag<TB, BK>(b_s, brow + 32, nks, lane);
-    fetch_slot(2);
-    HMY_FENCE();
-    HMY_MFMA(1, 1);
-    HMY_FENCE();
-    if (reads) fa[nxt][1] = frag<TA, BK>(a_s, 32, nks, lane);
-    fetch_slot(3);
-    HMY_FENCE();
-    HMY_MFMA(2, 0);
-    HMY_FENCE();
-    if (reads) fa[nxt][2] = frag<TA, BK>(a_s, 64, nks, lane);
-    fetch_slot(4);
-    HMY_FENCE();
-    HMY_MFMA(2, 1);
-    HMY_FENCE();
-    if (reads) fa[nxt][3] = frag<TA, BK>(a_s, 96, nks, lane);
-    fetch_slot(5);
-    HMY_FENCE();
-    HMY_MFMA(3, 0);
-    HMY_FENCE();
-    fetch_slot(6);
-    HMY_FENCE();
-    HMY_MFMA(3, 1);
-    HMY_FENCE();
-    fetch_slot(7);
-    HMY_FENCE();
-  };
-  int stage = 0;      // stage holding tile t
-  Epi e;
-  e.init(p, m0, n0, BT);
-  const int m_tile = m0 + wm * 128, n_tile = n0 + wn * 64;
-  // what the output stage adds, fetched one 32-row slab ahead: slab i, pass q -> row 32 i + 8 q + lane/8, columns 8 (lane%8) .. +7
-  Epi::Pre pre[2][4];
-  float4 bias8 = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto prefetch_slab = [&](int i, int buf) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) e.prefetch(p, m_tile + 32 * i + 8 * q + lane / 8, n_tile + 8 * (lane % 8), pre[buf][q]);
-  };
-  for (int t = 0; t + 1 < n; ++t) {
-    const int next = stage + 1 == S ? 0 : stage + 1;
-#pragma unroll
-    for (int ks = 0; ks + 1 < KS; ++ks) step(ks % 2, (ks + 1) % 2, true, stage, ks + 1, false, 0);
-    // every read of tile t has been issued.  Tiles up to t+S-1 have been requested: tile t+1 has landed once at most
-    // the S-2 behind it are outstanding.
-    if (t + S - 1 < n) wait_vm<(S - 2) * L>();
-    else wait_vm<0>();
-    __syncthreads();   // tile t+1 visible to every wave; every wave is done reading tile t
-    const bool fetch = t + S < n;   // tile t+S goes to the stage tile t has just left: S-1 tiles ahead of its use
-    step((KS - 1) % 2, 0, true, next, 0, fetch, stage);
-    if (fetch) {
-      a_next += a_kstep;
-      b_next += b_kstep;
-    }
-    stage = next;
-  }
-  if (e.fast) {
-    if (p.bias && (e.inside || n_tile + 8 * (lane % 8) + 8 <= p.N))
-      bias8 = *reinterpret_cast<const float4 *>(p.bias + n_tile + 8 * (lane % 8));
-    prefetch_slab(0, 0);
-  }
-  if (n > 0) {   // last tile: nothing left to fetch or wait for
-#pragma unroll
-    for (int ks = 0; ks + 1 < KS; ++ks) step(ks % 2, (ks + 1) % 2, true, stage, ks + 1, false, 0);
-    step((KS - 1) % 2, 0, false, stage, 0, false, 0);
-  }
-#undef HMY_MFMA
-#undef HMY_FENCE
-
-  // output stage as in the 128x128 kernel: 32 rows at a time through LDS, alternating between two 8 KiB buffers per
-  // wave so that one slab's stores to memory overlap the next slab's way through LDS
-  __syncthreads();   // every wave has finished reading the operand stages
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float *slab = reinterpret_cast<float *>(smem) + wave * 4096 + (i & 1) * 2048;
-    if (e.fast && i + 1 < 4) prefetch_slab(i + 1, (i + 1) & 1);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r / 4) + 4 * (lane / 32) + r % 4, col = 32 * j + lane % 32;
-        slab[row * 64 + (col ^ (((row >> 2) & 1) << 5))] = acc[i][j][r];
-      }
-    if (e.fast) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = 8 * q + lane / 8, c0 = 8 * (lane % 8);
-        const float *src = slab + row * 64 + (c0 ^ (((row >> 2) & 1) << 5));
-        e.emit8(p, m_tile + 32 * i + row, n_tile + c0, src, pre[i & 1][q], bias8);
-      }
-    } else {
-#pragma unroll 1
-      for (int idx = lane; idx < 32 * 64; idx += 64) {   // one row of 64 columns per pass
-        const int row = idx / 64, col = idx % 64;
-        const int m = m_tile + 32 * i + row, nn = n_tile + col;
-        if (m < p.M && nn < p.N) e.emit_one(p, m, nn, slab[row * 64 + (col ^ (((row >> 2) & 1) << 5))]);
-      }
-    }
-  }
-}
-
-// ---- 256x128 tiles -------------------------------------------------------------------
-// The same GEMM for outputs that give the compute units one such tile each but too few 256x256 ones: three quarters of the
-// 128x128 kernel's bytes per multiply through the L2 caches, which is what bounds it.  Eight waves of 64x64 (two per SIMD), K
-// tiles of 64 in a ring of three stages (144 KiB), fragments read two 16-deep steps ahead, one barrier per K tile.  A K tile's
-// fetch is spread over the two steps behind that barrier; it goes through buffer descriptors, which end it without a branch in
-// the loop.  K has to be a multiple of 64.  Measured, us, 128x128 tiles -> these: 2048x4096, K = 16384 372 -> 242 (1135
-// TFLOP/s), input gradient 322 -> 230, K = 4096 106 -> 73; K = 1024 25 -> 22.  Four waves of 128x64, one per SIMD, take as long
-// in the K loop (245, 235) and longer around it (K = 1024 22.4 -> 21.6, 4096x1600x1024 26 -> 24.7): a wave alone on its SIMD
-// has nobody to hide its output stage behind.
-template <bool TA, bool TB>
-__global__ __launch_bounds__(512) void k_gemm_dma_256x128(DmaP p, int tiles_per_split, int grid_n, int splits) {
-  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
-  constexpr int BK = 64, S = 3, BTM = 256, BTN = 128;
-  constexpr int SUB = BM * BK;        // elements of one 128-row sub-tile
-  constexpr int STAGE = 3 * SUB;      // elements of one stage: A rows 0-127, A rows 128-255, B
-  constexpr int L = 6;                // load-to-LDS instructions per thread per K tile: 48 KiB over eight waves
-  const int tid = threadIdx.x, lane = tid % 64;
-  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int wm = wave / 2, wn = wave % 2;     // this wave's outputs: rows 64 wm .. +63, columns 64 wn .. +63
-  int bid = blockIdx.x, split_idx = 0;
-  const int nb = gridDim.x / splits, grid_m = nb / grid_n;
-  if (splits > 1) {   // as in the 128x128 kernel
-    split_idx = bid % splits;
-    bid /= splits;
-  } else {
-    const int x = bid % 8, per = nb / 8, extra = nb % 8;
-    bid = x * per + min(x, extra) + bid / 8;
-  }
-  constexpr int kBand = 4;
-  const int band = bid / (kBand * grid_n), first_m = band * kBand;
-  const int band_rows = min(grid_m - first_m, kBand);
-  const int in_band = bid - band * kBand * grid_n;
-  const int m0 = (first_m + in_band % band_rows) * BTM, n0 = (in_band / band_rows) * BTN;
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int kt0 = split_idx * tiles_per_split;
-  const int n = min(p.K / BK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
-  // byte offsets of this thread's lanes of the KiBs its wave copies: 2 w and 2 w + 1 of each of the three sub-tiles of 16 KiB
-  uint32_t off[3][2];
-#pragma unroll
-  for (int sub = 0; sub < 3; ++sub)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const bool is_a = sub < 2;
-      const uint32_t ld = is_a ? p.lda : p.ldb;
-      const int first = is_a ? m0 + BM * sub : n0, rows = is_a ? p.M : p.N, kib = 2 * wave + j;
-      if (is_a ? TA : TB) {   // k rows 4 kib .. + 3
-        const int col = min(first + (((lane % 16) ^ ((lane / 16) << 2)) * 8), ((rows + 7) & ~7) - 8);
-        off[sub][j] = (uint32_t(4 * kib + lane / 16) * ld + uint32_t(col)) * 2u;
-      } else {                // rows 8 kib .. + 7
-        const int row = 8 * kib + lane / 8;
-        off[sub][j] = (uint32_t(min(first + row, rows - 1)) * ld + uint32_t(((lane % 8) ^ ((row >> 1) & 7)) * 8)) * 2u;
-      }
-    }
-  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem)) + 2048u * wave;
-  const uint32_t a_kstep = TA ? uint32_t(BK) * p.lda * 2u : uint32_t(BK) * 2u, b_kstep = TB ? uint32_t(BK) * p.ldb * 2u : uint32_t(BK) * 2u;
-  u32x4 a_buf = buffer_of(p.A, uint32_t(TA ? p.K : p.M) * p.lda * 2u), b_buf = buffer_of(p.B, uint32_t(TB ? p.K : p.N) * p.ldb * 2u);
-  uint32_t a_next = uint32_t(kt0) * a_kstep, b_next = uint32_t(kt0) * b_kstep;   // byte offset of the next K tile to fetch
-  // instruction q (0 .. L - 1) of a K tile: piece q % 2 of sub-tile q / 2
-  auto fetch_one = [&](int q, int stage) {
-    const int sub = q / 2, j = q % 2;
-    set_m0(lds0 + uint32_t(stage) * uint32_t(2 * STAGE) + uint32_t(sub) * uint32_t(2 * SUB) + 1024u * j);
-    dma16_buffer(sub < 2 ? a_buf : b_buf, off[sub][j], sub < 2 ? a_next : b_next);
-  };
-  // on to K tile `next`; past the last one the fetches go on, from descriptors of no bytes: no branch around them, and one
-  // count to wait for.  (With a tile offset of 0: the range check takes it off the descriptor's size.)
-  auto advance = [&](int next) {
-    a_next = next < n ? a_next + a_kstep : 0;
-    b_next = next < n ? b_next + b_kstep : 0;
-    if (next >= n) a_buf[2] = b_buf[2] = 0;
-  };
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-#pragma unroll
-    for (int q = 0; q < L; ++q) fetch_one(q, s);
-    advance(s + 1);
-  }
-  // fragments of a 16-deep step, read two steps ahead of their multiplies
-  bf16x8 fa[4][2], fb[4][2];
-  const int a_sub = (wm / 2) * SUB, arow = (wm % 2) * 64, b_sub = 2 * SUB, brow = wn * 64;
-  wait_vm<(S - 1) * L>();
-  __syncthreads();
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      fa[ks][i] = frag<TA, BK>(smem + a_sub, arow + 32 * i, ks, lane);
-      fb[ks][i] = frag<TB, BK>(smem + b_sub, brow + 32 * i, ks, lane);
-    }
-#define HMY_FENCE() __builtin_amdgcn_sched_barrier(0)
-  // step `cur` of a K tile: four multiplies, each followed by a fragment read of step `nks` of the tile in `nstage`, and by
-  // the instructions i0, i0 + 1 and i0 + 2 that fetch a tile into `fstage` (none if i0 is negative)
-  auto step = [&](int cur, int nstage, int nks, int i0, int fstage) {
-    const int nxt = (cur + 2) & 3;
-    const bf16_t *a_s = smem + nstage * STAGE + a_sub, *b_s = smem + nstage * STAGE + b_sub;
-    HMY_FENCE();
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][0], acc[0][0], 0, 0, 0);
-    HMY_FENCE();
-    fa[nxt][0] = frag<TA, BK>(a_s, arow, nks, lane);
-    HMY_FENCE();
-    acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][0], fb[cur][1], acc[0][1], 0, 0, 0);
-    HMY_FENCE();
-    fb[nxt][0] = frag<TB, BK>(b_s, brow, nks, lane);
-    if (i0 >= 0) fetch_one(i0, fstage);
-    HMY_FENCE();
-    acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][1], fb[cur][0], acc[1][0], 0, 0, 0);
-    HMY_FENCE();
-    fb[nxt][1] = frag<TB, BK>(b_s, brow + 32, nks, lane);
-    if (i0 >= 0) fetch_one(i0 + 1, fstage);
-    HMY_FENCE();
-    acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][1], fb[cur][1], acc[1][1], 0, 0, 0);
-    HMY_FENCE();
-    fa[nxt][1] = frag<TA, BK>(a_s, arow + 32, nks, lane);
-    if (i0 >= 0) fetch_one(i0 + 2, fstage);
-    HMY_FENCE();
-  };
-  Epi e;
-  e.init(p, m0, n0, BTM);
-  e.inside = m0 + BTM <= p.M && n0 + BTN <= p.N;
-  const int m_tile = m0 + wm * 64, n_tile = n0 + wn * 64;
-  Epi::Pre pre[2][4];
-  float4 bias8 = make_float4(0.f, 0.f, 0.f, 0.f);
-  int stage = 0;   // of tile t
-#pragma unroll 1
-  for (int t = 0; t < n; ++t) {
-    const int next = stage + 1 == S ? 0 : stage + 1;
-    step(0, stage, 2, -1, 0);
-    step(1, stage, 3, -1, 0);
-    wait_vm<(S - 2) * L>();   // tile t + 1 has landed once at most the S - 2 tiles behind it are outstanding
-    __syncthreads();          // tile t + 1 visible to every wave; every wave has read tile t
-    // (behind the last tile the reads bring in what nobody multiplies)
-    step(2, next, 0, 0, stage);
-    step(3, next, 1, 3, stage);
-    advance(t + S + 1);
-    stage = next;
-  }
-#undef HMY_FENCE
-  if (splits > 1) {   // fp32 atomics: one column per lane, straight from the accumulator layout
-    wait_vm<0>();     // (no fetch into LDS outlives the workgroup)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int nn = n_tile + 32 * j + lane % 32;
-      if (nn >= p.N) continue;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = m_tile + 32 * i + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
-          if (m < p.M) atomicAdd(static_cast<float *>(p.C) + int64_t(m) * p.ldc + nn, acc[i][j][r]);
-        }
-    }
-    return;
-  }
-  if (e.fast) {
-    if (p.bias && (e.inside || n_tile + 8 * (lane % 8) + 8 <= p.N))
-      bias8 = *reinterpret_cast<const float4 *>(p.bias + n_tile + 8 * (lane % 8));
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) e.prefetch(p, m_tile + 32 * i + 8 * q + lane / 8, n_tile + 8 * (lane % 8), pre[i][q]);
-  }
-  // output stage as in the 128x128 kernel, both slabs of a wave in LDS at once
-  wait_vm<0>();      // the last fetches, of nothing, have been written to LDS
-  __syncthreads();   // every wave has finished reading the operand stages
-  float *slab = reinterpret_cast<float *>(smem) + wave * 4096;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r / 4) + 4 * (lane / 32) + r % 4, col = 32 * j + lane % 32;
-        slab[i * 2048 + row * 64 + (col ^ (((row >> 2) & 1) << 5))] = acc[i][j][r];
-      }
-  if (e.fast) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = 8 * q + lane / 8, c0 = 8 * (lane % 8);
-        e.emit8(p, m_tile + 32 * i + row, n_tile + c0, slab + i * 2048 + row * 64 + (c0 ^ (((row >> 2) & 1) << 5)), pre[i][q], bias8);
-      }
-  } else {
-#pragma unroll 1
-    for (int idx = lane; idx < 64 * 64; idx += 64) {   // one row of 64 columns per pass
-      const int row = idx / 64, col = idx % 64;
-      const int m = m_tile + row, nn = n_tile + col;
-      if (m < p.M && nn < p.N) e.emit_one(p, m, nn, slab[row * 64 + (col ^ (((row >> 2) & 1) << 5))]);
     }
   }
 }
@@ -1129,7 +534,7 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, 
 
 // The same for contractions that are a multiple of 64.  What bounds a workgroup that has its SIMDs to itself is each wave's
 // own instruction stream: 128 cycles of multiplies per K tile among branches, waits and LDS reads that follow one another.
-// So: no branch in the loop (the fetches go through buffer descriptors, as on 256x128 tiles, and end by themselves), the
+// So: no branch in the loop (the fetches go through buffer descriptors, as on tiles of 256 rows, and end by themselves), the
 // next tile's fragments are read while this one's are multiplied, and what the output stage adds is fetched before the loop.
 // Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), 480x768x768 8.2 -> 6.9; weight
 // gradient 1024x1024x1024 12.1 -> 8.7.  It takes longer before its first multiply: short contractions stay with the kernel above
@@ -1172,7 +577,7 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_sp
     for (int q = 0; q < 2; ++q) e.prefetch(p, m_tile + 16 * q + lane / 4, n_lane, pre[q]);
   }
 
-  // byte offsets of this thread's lanes of the KiBs its wave copies: 2 w and 2 w + 1 of each operand's eight (see 256x128)
+  // byte offsets of this thread's lanes of the KiBs its wave copies: 2 w and 2 w + 1 of each operand's eight
   uint32_t off[2][2];
 #pragma unroll
   for (int op = 0; op < 2; ++op)
@@ -1299,30 +704,6 @@ int launch_cfg(const hmy_gemm_desc &g, const DmaP &p, dim3 grid, int tiles_per_s
   return check_launch("gemm_dma");
 }
 
-template <int BK, int S>
-int launch_cfg256(const hmy_gemm_desc &g, const DmaP &p, dim3 grid, int gn, hipStream_t s) {
-  const size_t lds = size_t(S) * 4 * BM * BK * sizeof(bf16_t);
-  dim3 block(512);
-  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma256<false, false, BK, S>), grid, block, lds, s, p, gn);
-  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma256<false, true, BK, S>), grid, block, lds, s, p, gn);
-  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma256<true, false, BK, S>), grid, block, lds, s, p, gn);
-  else hipLaunchKernelGGL((k_gemm_dma256<true, true, BK, S>), grid, block, lds, s, p, gn);
-  return check_launch("gemm_dma256");
-}
-
-int launch_256x128(const hmy_gemm_desc &g, const DmaP &p, int splits, hipStream_t s) {
-  const int gm = (g.M + 255) / 256, gn = (g.N + 127) / 128, nk = g.K / 64;
-  const int tps = (nk + splits - 1) / splits;
-  splits = (nk + tps - 1) / tps;
-  const size_t lds = size_t(3) * 3 * BM * 64 * sizeof(bf16_t);
-  const dim3 grid(gm * gn * splits), block(512);
-  if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, false>), grid, block, lds, s, p, tps, gn, splits);
-  else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<false, true>), grid, block, lds, s, p, tps, gn, splits);
-  else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma_256x128<true, false>), grid, block, lds, s, p, tps, gn, splits);
-  else hipLaunchKernelGGL((k_gemm_dma_256x128<true, true>), grid, block, lds, s, p, tps, gn, splits);
-  return check_launch("gemm_dma_256x128");
-}
-
 bool small_may_split(const hmy_gemm_desc &g) { return g.accumulate && g.c_fp32 && !g.bias && !g.res; }
 // a long contraction over few tiles that may be split (fp32 atomics into C): while it fills idle compute units and
 // leaves each workgroup at least eight K tiles
@@ -1375,17 +756,6 @@ int env_int(const char *name, int dflt) {
 bool gemm_dma_eligible(const hmy_gemm_desc &g) {
   const int64_t a_span = int64_t(g.ta ? g.K : g.M) * g.lda, b_span = int64_t(g.tb ? g.K : g.N) * g.ldb;
   return g.K % 32 == 0 && a_span < (int64_t(1) << 31) && b_span < (int64_t(1) << 31);
-}
-
-static DmaP dma_params(const hmy_gemm_desc &g) {
-  DmaP p;
-  p.A = static_cast<const bf16_t *>(g.A); p.B = static_cast<const bf16_t *>(g.B); p.C = g.C;
-  p.bias = static_cast<const bf16_t *>(g.bias); p.res = static_cast<const bf16_t *>(g.res);
-  p.gelu_out = static_cast<bf16_t *>(g.gelu_out);
-  p.M = g.M; p.N = g.N; p.K = g.K;
-  p.lda = uint32_t(g.lda); p.ldb = uint32_t(g.ldb); p.ldc = g.ldc; p.ldr = g.ldr;
-  p.c_fp32 = g.c_fp32; p.accumulate = g.accumulate; p.res_fp32 = g.res_fp32;
-  return p;
 }
 
 bool gemm_small_excluded() {
@@ -1448,45 +818,59 @@ bool gemm_prefers_small(const hmy_gemm_desc &g) {
 }
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
 
+static int64_t tiles_of(const hmy_gemm_desc &g, int rows, int cols) {
+  return int64_t((g.M + rows - 1) / rows) * ((g.N + cols - 1) / cols);
+}
+// Estimated time, in us, of a product on tiles of 256 x 32 nb outputs (gemm_tile.hip), or (nb = 0) on the 128x128 ones: rounds
+// of 256 tiles, each of which costs its multiplies, its output stage (longer if it reads as much as it writes; several 128x128
+// workgroups of a compute unit overlap theirs) and its start.  The last round costs most of a whole one, however few tiles it
+// has: fewest outputs in flight for nothing is what the width is chosen for.  Fitted to 746 random products of all layouts and
+// output stages, K = 64 to 8192, on all six tiles: the tile with the smallest estimate takes 0.6 % longer than the fastest on
+// average from K = 480 on, 2.0 % below (where only 128x128 and 256x256 are asked for: there the start and the output stage are
+// everything).  Some, us, on 128x128 | 256x128, 160, 192, 224, 256: 2048x4800x1600 (forward) 56 | 44 33 33 40 38, 512x50257x1024
+// (fp32) 109 | 87 83 84 66 73, 2048x12288x4096 214 | 164 202 157 171 175, 4800x1600x2048 (weight gradient) 46 | 42 52 55 61 63,
+// 8192x4096x256 (weight gradient) 65 | 73 98 91 95 78.
+static float tile_time(const hmy_gemm_desc &g, int nb) {
+  static constexpr float per_1024_steps[] = {9.f, 0.f, 0.f, 0.f, 10.9f, 15.f, 16.6f, 18.2f, 19.4f};
+  const int64_t tiles = nb ? tiles_of(g, 256, 32 * nb) : tiles_of(g, BM, BM), whole = tiles / 256;
+  const float part = float(tiles % 256) / 256.f;
+  const float rounds = float(whole) + (part == 0.f ? 0.f : whole == 0 ? 0.56f + 0.44f * part : 0.78f + 0.22f * part);
+  const bool both = g.c_fp32 || g.gelu_out;   // twice the bytes of a bf16 C
+  const float kind = g.accumulate ? (nb || !(g.ta && g.tb) ? 2.f : 1.2f) : g.res && g.res_fp32 ? 2.2f : both ? (nb ? 1.35f : 1.9f) : 1.f;
+  float out = 7.9f * kind * (nb ? float(nb) / 8.f : 0.25f);
+  if (nb % 2 && !g.c_fp32) out += 1.f;   // tiles whose rows end inside a cache line
+  return rounds * (per_1024_steps[nb] * float(g.K) / 1024.f + out + (nb ? 5.3f : 0.8f));
+}
+// Columns, over 32, of the tiles of 256 rows that a product takes, or 0 for 128x128 tiles.
+static int tile_columns(const hmy_gemm_desc &g) {
+  if (g.M < 256 || g.N < 128) return 0;
+  int best = 0;
+  for (int nb = g.K < 480 ? 8 : 4; nb <= 8; ++nb)
+    if (tile_time(g, nb) < tile_time(g, best)) best = nb;
+  return best;
+}
+
 int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
   const DmaP p = dma_params(g);
   static const int force_bk = env_int("HMY_GEMM_BK", 0), force_s = env_int("HMY_GEMM_STAGES", 0);
   static const int force_tile = env_int("HMY_GEMM_TILE", 0);   // 128 | 256: that block tile for every shape it can take
   const bool can_split = g.accumulate && g.c_fp32 && !g.bias && !g.res;
-  {
-    // 256x256 tiles when they still give most compute units a workgroup (and a second round, if there is one, is
-    // at least half full): half the operand bytes per multiply through the L2 caches.  Measured: 152 such tiles
-    // (2048 x 4800 x 1600) 49 against 57 us, 175 (1600 x 6400 x 2048) 71 against 72 us, 64 much slower.
-    const int gm2 = (g.M + 255) / 256, gn2 = (g.N + 255) / 256, wgs = gm2 * gn2;
-    const bool fills = wgs >= 144 && (wgs <= 256 || wgs >= 384);
-    // 256x128 tiles (force_tile: never) where they are one round of more than half of the compute units and 256x256 ones are
-    // not, or three rounds against two poorly filled ones.  Speed-up over the kernel taken otherwise, at 144 to 256 tiles:
-    // forward and input gradients K = 512 0.87 to 1.16, 1024 1.03 to 1.25, 2048 1.10 to 1.36, 4096 1.13 to 1.60; sums into C,
-    // whose output stage is twice as long, up to 160 tiles K = 512 1.02 to 1.07, 768 1.04 to 1.09, 1024 1.06 to 1.13 and beyond
-    // 1024 0.96 to 1.01, 2048 1.01 to 1.17.  128 tiles: 0.86 to 0.93. Three rounds: 2048x12288x4096 214 -> 186, 3072x6144 (576
-    // tiles) K = 2048 0.98 to 1.08, 4096 1.05 to 1.15. (Not where 128x128 tiles are one round too, as with few rows over the
-    // middle of a tile.)
-    const int w2 = gm2 * ((g.N + 127) / 128), w1 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const bool one_round = !fills && w1 > 256 && w2 >= 144 && w2 <= 256 && g.K >= (!g.accumulate ? 1024 : w2 <= 160 ? 512 : 2048);
-    const bool three_rounds = wgs > 256 && wgs <= 384 && w2 > 512 && w2 <= 768 && g.K >= 2048 && !g.accumulate;
-    if (force_tile == 0 && force_bk == 0 && force_s == 0 && g.M >= 256 && g.K % 64 == 0 && (one_round || three_rounds))
-      return launch_256x128(g, p, 1, (hipStream_t)st);
-    // Very long sums over few outputs: these tiles with the contraction split (fp32 atomics into C), where they come to nearly
+  if (force_tile == 256 && g.M >= 256 && g.N >= 256) return launch_gemm_tile(g, 8, 1, st);
+  if (force_tile == 0 && force_bk == 0 && force_s == 0) {
+    // Very long sums over few outputs: 256x128 tiles with the contraction split (fp32 atomics into C), where they come to nearly
     // a workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128
-    // tiles -> these: 2048x1024, K = 50240 219 -> 190 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280),
+    // tiles -> these: 2048x1024, K = 50240 219 -> 184 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280),
     // 512x1600 104 -> 92 (5582); 1024x1024x40960 98 -> 93 (5120), 512x1024x65536 77.7 -> 78.4 (4096), 1024x1024x16384 50 -> 55
-    // (2048).
-    if (force_tile == 0 && force_bk == 0 && force_s == 0 && can_split && w1 <= 128 && g.M >= 256 && g.K % 64 == 0) {
-      const int splits = 256 / w2;
-      if (splits > 1 && w2 * splits >= 200 && g.K / splits >= 4608) return launch_256x128(g, p, splits, (hipStream_t)st);
+    // (2048).  Not where 128x128 tiles fill the compute units (4096x1024x50257 in two parts 563 -> 465): the logits' input gradient
+    // is rounded to bf16 next, and from another order of its sum every gradient below moves by some 6e-3.
+    const bool few = tiles_of(g, BM, BM) <= 128;
+    if (can_split && few && g.M >= 256 && g.K % 64 == 0) {
+      const int w2 = int(tiles_of(g, 256, 128)), splits = 256 / w2;
+      if (splits > 1 && w2 * splits >= 200 && g.K / splits >= 4608) return launch_gemm_tile(g, 4, splits, st);
     }
-    if (force_tile != 128 && g.M >= 256 && g.N >= 256 && (force_tile == 256 || fills)) {
-      // K tiles of 64 where an operand has the contraction index contiguous (whole cache lines of its rows)
-      bool deep = (!g.ta || !g.tb) && g.K % 64 == 0;
-      if (force_bk == 32 || (force_bk == 64 && g.K % 64 == 0)) deep = force_bk == 64;
-      return deep ? launch_cfg256<64, 2>(g, p, dim3(wgs), gn2, (hipStream_t)st)
-                  : launch_cfg256<32, 4>(g, p, dim3(wgs), gn2, (hipStream_t)st);
-    }
+    // sums over few outputs split the contraction over 128x128 tiles instead (below)
+    const int nb = can_split && few ? 0 : tile_columns(g);
+    if (nb) return launch_gemm_tile(g, nb, 1, st);
   }
   const int gm = (g.M + BM - 1) / BM, gn = (g.N + BM - 1) / BM;
   // split the contraction over workgroups (fp32 atomics into C) only while that fills

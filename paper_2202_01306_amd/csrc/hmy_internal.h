@@ -165,6 +165,7 @@ bool gemm_small_excluded();   // by a tuning switch that names a larger kernel
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st);
 bool gemm_dma_eligible(const hmy_gemm_desc &g);
 int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st);
+int launch_gemm_tile(const hmy_gemm_desc &g, int nb, int splits, stream_t st);   // tiles of 256 x 32 nb outputs, nb = 4 .. 8
 int launch_attn_fwd(int prec, const void *qkv, void *o, float *lse, int b, int s, int H, int dh,
                     int causal, stream_t st);
 int launch_attn_bwd(int prec, const void *qkv, const void *o, const void *d_o, const float *lse,

@@ -432,6 +432,45 @@ def test_gemm_bf16_small_tiles_sum_like_the_larger_ones(ta, tb, K):
             assert torch.equal(got[0], got[1]), (N, sorted(kw))
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(400, 8248, 480), (400, 8248, 512), (3256, 2528, 736), (1080, 7208, 480), (3664, 3360, 736),
+                                   (1352, 8144, 480), (1352, 8144, 1024), (1352, 8144, 32), (1352, 8144, 64), (1352, 8144, 96)])
+def test_gemm_bf16_tiles_of_every_width(ta, tb, M, N, K):
+    """Tiles of 256 rows and 128 to 256 columns (which one, the rule decides by output stage too): edge tiles in both directions,
+    contractions that end in half a K tile, of one and of two K tiles.  The rows a few at a time go to 64x64 tiles, which sum in
+    the same order: equal bits."""
+    say(f"gemm bf16 256 rows ta={ta} tb={tb} {M}x{N}x{K}")
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    a = torch.randn((K, M) if ta else (M, K), device="cuda", generator=g).bfloat16()
+    b = torch.randn((K, N) if tb else (N, K), device="cuda", generator=g).bfloat16()
+    bias, low = torch.randn(N, device="cuda", generator=g).bfloat16(), torch.randn(M, N, device="cuda", generator=g)
+    tiles_n = (N + 63) // 64
+    rows = 64 * ((129 + tiles_n - 1) // tiles_n)       # more than 128 tiles: no sum is split
+    for kind in ("res", "gelu", "stream", "sum"):
+        if kind == "sum" and not (ta and tb):
+            continue
+        c32 = kind in ("stream", "sum")
+        c = low.clone() if c32 else torch.zeros(M, N, device="cuda", dtype=torch.bfloat16)
+        act, res = torch.zeros_like(c), low if c32 else low.bfloat16()
+        want, want_act = c.clone(), act.clone()
+
+        def product(r0, n, c, act):
+            kw = dict(c_fp32=1, accumulate=1) if kind == "sum" else dict(bias=bias)
+            if kind in ("res", "stream"):
+                kw.update(c_fp32=int(c32), res=res[r0:], ldr=N, res_fp32=int(c32))
+            if kind == "gelu":
+                kw.update(gelu_out=act[r0:])
+            B.hmy_k_gemm(1, n, N, K, a[:, r0:] if ta else a[r0:], a.shape[1], b, b.shape[1], c[r0:], N, ta=ta, tb=tb, **kw)
+
+        product(0, M, c, act)
+        for r0 in range(0, M, rows):
+            product(r0, min(rows, M - r0), want, want_act)
+        assert torch.equal(c, want) and torch.equal(act, want_act), kind
+        if kind == "stream":
+            ref = (a.t() if ta else a).double() @ (b if tb else b.t()).double() + bias.double() + low.double()
+            assert float((c.double() - ref).abs().max()) < 6 * math.sqrt(K) * (K / 32 + 2) * 2.0 ** -24
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1)])
 def test_gemm_fp32(ta, tb):
     say(f"gemm fp32 ta={ta} tb={tb}")
