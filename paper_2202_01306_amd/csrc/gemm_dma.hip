@@ -532,12 +532,13 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, 
   }
 }
 
-// The same for contractions that are a multiple of 64.  What bounds a workgroup that has its SIMDs to itself is each wave's
+// The same for contractions that are a multiple of 64, and for any where both operands are stored contraction-major: steps past
+// K of the last tile are rows past the operand, which the descriptors read as zeros.  What bounds a workgroup that has its SIMDs to itself is each wave's
 // own instruction stream: 128 cycles of multiplies per K tile among branches, waits and LDS reads that follow one another.
 // So: no branch in the loop (the fetches go through buffer descriptors, as on tiles of 256 rows, and end by themselves), the
 // next tile's fragments are read while this one's are multiplied, and what the output stage adds is fetched before the loop.
 // Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), 480x768x768 8.2 -> 6.9; weight
-// gradient 1024x1024x1024 12.1 -> 8.7.  It takes longer before its first multiply: short contractions stay with the kernel above
+// gradient 1024x1024x1024 12.1 -> 8.7, 768x3072x600 16.2 -> 14.0, 256x1024x480 6.6 -> 5.4.  It takes longer before its first multiply: short contractions stay with the kernel above
 // (`even_pays`).
 template <bool TA, bool TB>
 __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_split, int grid_n, int splits) {
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_sp
   const int in_band = bid - band * kBand * grid_n;
   const int m0 = (first_m + in_band % band_rows) * ST, n0 = (in_band / band_rows) * ST;
   const int kt0 = split_idx * tiles_per_split;
-  const int n = min(p.K / SK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
+  const int n = min((p.K + SK - 1) / SK, kt0 + tiles_per_split) - kt0;   // K tiles of this workgroup
 
   Epi e;
   e.init(p, m0, n0, ST);
@@ -720,7 +721,7 @@ int small_splits(const hmy_gemm_desc &g) {
 // -> 7.6; with a residual to add 1536x1024x384 (384 tiles) 8.5 -> 8.3, 2304x768x384 (432) 8.7 -> 8.9, x512 9.8 -> 9.6.
 bool even_pays(const hmy_gemm_desc &g) {
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
-  return g.K % SK == 0 && g.K >= (tiles <= 256 ? 256 : g.res && tiles > 400 ? 512 : 384);
+  return (g.K % SK == 0 || (g.ta && g.tb)) && g.K >= (tiles <= 256 ? 256 : g.res && tiles > 400 ? 512 : 384);
 }
 
 int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
@@ -780,14 +781,14 @@ bool gemm_small_excluded() {
 //   empty, not at all (1056x992x2048 18.1 -> 20.1, 1320x800 18.8 -> 20.7; x1536 18.5 -> 16.8) and 2304 (1984x1000 26.1 -> 21.6
 //   at 2048, 29.7 -> 28.8 at 3072; 1312x1312x2304 22.2 -> 22.2, x2560 23.1 -> 24.1).
 // Short of a first split, at most 64 tiles of such misaligned rows are the other exception: 504x392x704 8.2 -> 7.7, x768 7.4 ->
-// 7.8, x960 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2). Contractions that are no multiple of 64 (the kernel
-// with branches): up to 1792 (768x768x1920 11 % slower).
+// 7.8, x960 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2).  Contractions that
+// are no multiple of 64 gain more, since the larger kernels take them in two parts (1024x1024x2008 23.3 -> 12.0, 2048x2048x3000
+// 57 -> 45, 4096x1024x3000 54 -> 51).
 bool small_sum_pays(const hmy_gemm_desc &g) {
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   const int splits = small_splits(g), length = g.K / splits;
   const bool half_lines = g.lda % 32 == 0 && g.ldb % 32 == 0;
   if (length < 1792) return g.K % SK != 0 || half_lines || splits > 1 || tiles > 64 || g.K < 768;
-  if (g.K % SK != 0) return false;
   if (tiles > 256) {
     const bool whole = g.M % ST == 0 && g.N % ST == 0;
     return tiles <= 400 ? whole && length <= 2304 : length <= (whole ? 3072 : 2304);
@@ -800,7 +801,8 @@ bool small_sum_pays(const hmy_gemm_desc &g) {
 // 1024x1024x1024 12.6 -> 8.1, 2048x1024 (512 tiles), K = 1024 12.9 -> 10.2, 4096 31.7 -> 28.0; 3072x768x1536 (576 tiles) 16.6
 // -> 20.4), and for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to
 // register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions
-// that are no multiple of 64 go through the kernel with branches: up to 2048 of them beyond 256 tiles (2048x1024x2048 19.6 ->
+// that are no multiple of 64, weight gradients aside, go through the kernel with branches: up to 2048 of them beyond 256 tiles
+// (2048x1024x2048 19.6 ->
 // 18.9, 4096 32.5 -> 33.4).  Beyond 256 tiles an operand stored contraction-major loses on long ones what the tiles gain: from
 // 8192 on (input gradients 2048x1024x8192 59.9 -> 58.9, x12288 86.7 -> 89.4), from 4096 on where its rows are no whole half
 // cache lines (1960x1000x4096 36.8 -> 35.5, x8192 63.0 -> 68.1; forward, x16384 109 -> 102). Sums into an fp32 C other than
@@ -810,7 +812,7 @@ bool gemm_prefers_small(const hmy_gemm_desc &g) {
   if (gemm_small_excluded()) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
-  const bool even = g.K % SK == 0;
+  const bool even = g.K % SK == 0 || (g.ta && g.tb);
   if (small_may_split(g) && !small_sum_pays(g)) return false;
   if (g.K % 32 != 0) return tiles < 2048;
   const bool major = g.ta || g.tb, half_lines = (!g.ta || g.lda % 32 == 0) && (!g.tb || g.ldb % 32 == 0);

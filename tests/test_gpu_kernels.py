@@ -408,6 +408,21 @@ def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
         assert torch.equal(c[0], c[1])
 
 
+@pytest.mark.parametrize("M,N,K", [(64, 64, 257), (264, 200, 300), (768, 3072, 600), (1000, 1208, 481), (72, 136, 999),
+                                   (1024, 1024, 2047), (1160, 1024, 2080), (2048, 2048, 1801)])
+def test_gemm_bf16_weight_gradients_of_any_length(M, N, K):
+    """Contractions that are no multiple of 64 on 64x64 tiles: the rows behind K, which lie in memory and are undefined numbers
+    here, count as zeros; one part, several, more than 512 tiles."""
+    say(f"gemm bf16 weight gradient {M}x{N}x{K}")
+    g = torch.Generator(device="cuda").manual_seed(K)
+    a, b = (torch.full((K + 192, n), float("nan"), device="cuda").bfloat16() for n in (M, N))
+    a[:K], b[:K] = (torch.randn(K, n, device="cuda", generator=g) for n in (M, N))
+    c = torch.randn(M, N, device="cuda", generator=g)
+    ref = c.double() + a[:K].double().t() @ b[:K].double()
+    B.hmy_k_gemm(1, M, N, K, a, M, b, N, c, N, ta=1, tb=1, c_fp32=1, accumulate=1)
+    assert float((c.double() - ref).abs().max()) < 6 * math.sqrt(K) * (K / 16 + 2) * 2.0 ** -24
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("K", [32, 288, 512, 1024])
 def test_gemm_bf16_small_tiles_sum_like_the_larger_ones(ta, tb, K):
