@@ -120,6 +120,17 @@ __device__ __forceinline__ bf16x8 acc_to_frag(const f32x16 &a, int c) {
   for (int k = 0; k < 8; ++k) f[k] = static_cast<__bf16>(a[8 * c + k]);
   return f;
 }
+// the larger of x and the value that the lane 32 further holds, without a trip through LDS
+__device__ __forceinline__ float pair_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// the wave's number within its workgroup, known to the compiler to be the same for all of its lanes: what a wave decides
+// from it (which subtile, masked or not) becomes scalar arithmetic and branches instead of vector compares and saved masks
+__device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirstlane(threadIdx.x / 64); }
+// what stands before is issued before what stands behind: the compiler otherwise sinks each read of an operand to the multiply
+// that takes it, and every one of a chain's multiplies then waits for a read of its own
+__device__ __forceinline__ void reads_first() { __builtin_amdgcn_sched_barrier(0); }
 // tile row (0..31) held in accumulator register r by a lane of half h
 __device__ __forceinline__ int acc_row(int r, int h) { return 8 * (r / 4) + 4 * h + r % 4; }
 
@@ -236,7 +247,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_fwd_mfma(co
   typedef Cfg<DH> C;
   __shared__ __attribute__((aligned(16))) bf16_t sK[2][C::TILE * C::PITCH];
   __shared__ __attribute__((aligned(16))) bf16_t sV[2][C::TILE * C::PITCH];
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
   const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true);   // the last query blocks see the most keys
@@ -314,7 +325,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_fwd_mfma(co
       for (int sub = 0; sub < NS; ++sub)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, st[sub][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sc;     // log2 units (sc > 0)
+      mx = pair_max(mx) * sc;     // log2 units (sc > 0)
       if (__any(mx > m_run + kSlack)) {   // some row outgrew its reference: raise it, rescale what was accumulated
         const float m_new = fmaxf(m_run, mx);
         const float corr = m_new == -INFINITY ? 1.f : fast_exp2(m_run - m_new);
@@ -371,7 +382,12 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_fwd_mfma(co
 // queries and split its keys, each with a running reference, row sum and output accumulator of its own, which the
 // pair merges through LDS at the end.  The same work in twice as many, half as long chains: the kernel is bound by
 // each wave's serial chain (multiplies, maximum, exponentials, multiplies), and with four waves per SIMD instead of
-// two the vector unit of one wave works while the matrix unit of another does.
+// two the vector unit of one wave works while the matrix unit of another does.  So what counts is the length of the chain:
+// a subtile's operands are read from LDS together, ahead of where they are wanted, the halves of a row's maximum meet by a swap
+// of lanes instead of through LDS, and branches are scalar.  us, before -> after: 16 heads of 64, s = 4096, causal 64.8 -> 56.8
+// (the swap alone 61.5, with scalar branches 59.6); four sequences of 1024 20.7 -> 18.7, eight of 512, not causal, 17.8 -> 16.7;
+// 32 heads of 128, s = 2048, 92.3 -> 88.6.  Four tiles in flight and a barrier for every second one instead of two and one:
+// 57.2 -> 63.1, not causal 48.4 -> 48.7.
 template <int DH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ? 2 : 4))) void k_attn_fwd_mfma_split(const bf16_t *qkv, bf16_t *o, float *lse, int s, int H,
                                                                                                     int causal) {
@@ -383,7 +399,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
   static_assert(4 * kTileElems * 2 >= 4 * 64 * (2 + 16 * C::DTILES) * 4, "the merge needs 2 + 16 DTILES floats per lane of four waves");
   auto sK = [&](int buf) { return smem + buf * kTileElems; };
   auto sV = [&](int buf) { return smem + (2 + buf) * kTileElems; };
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int rg = wave % 4, sub = wave / 4;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
@@ -424,9 +440,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
     if (kb < s && (!causal || kb <= qw + 31)) {   // some query of this wave sees some key of it
       // S^T[key, query] = K Q^T
       f32x16 st = zero16();
+      bf16x8 fk[C::KSTEPS];
 #pragma unroll
-      for (int c = 0; c < C::KSTEPS; ++c)
-        st = mfma(frag_row<DH>(sK(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);
+      for (int c = 0; c < C::KSTEPS; ++c) fk[c] = frag_row<DH>(sK(cur), 32 * sub + lane % 32, 16 * c + 8 * h2);
+      reads_first();
+#pragma unroll
+      for (int c = 0; c < C::KSTEPS; ++c) st = mfma(fk[c], fq[c], st);
       if (kb + 32 > s || (causal && kb + 31 > qw)) {   // ragged or diagonal subtile: per-element test
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -434,10 +453,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
           if (!(key < s && (!causal || key <= q))) st[r] = -INFINITY;
         }
       }
+      bf16x8 fv[2][C::DTILES];   // V^T, wanted behind the exponentials
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int t = 0; t < C::DTILES; ++t) fv[c][t] = frag_col<DH>(sV(cur), 32 * sub + 16 * c, 32 * t, lane);
+      reads_first();
       float mx = st[0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) mx = fmaxf(mx, st[r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sc;     // log2 units (sc > 0)
+      mx = pair_max(mx) * sc;     // log2 units (sc > 0)
       if (__any(mx > m_run + kSlack)) {   // some row outgrew its reference: raise it, rescale what was accumulated
         const float m_new = fmaxf(m_run, mx);
         const float corr = m_new == -INFINITY ? 1.f : fast_exp2(m_run - m_new);
@@ -457,7 +482,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
         const bf16x8 fp = acc_to_frag(st, c);
 #pragma unroll
         for (int t = 0; t < C::DTILES; ++t)
-          acc_o[t] = mfma(frag_col<DH>(sV(cur), 32 * sub + 16 * c, 32 * t, lane), fp, acc_o[t]);
+          acc_o[t] = mfma(fv[c][t], fp, acc_o[t]);
         acc_l = mfma(ones, fp, acc_l);
       }
     }
@@ -509,15 +534,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
 // Also delta[seq,head,q] = sum_c dO[q,c] * O[q,c], which this kernel needs per query and the dK/dV kernel, launched
 // behind it, reads per streamed query row: each lane holds half of its query's dO row as multiply operands already, so
 // the sum is 4 DH / 16 multiply-adds and one exchange with the lane that holds the other half, and no kernel of its own.
+// The bias gradient's sums take the tiles' LDS, which are done with by then: 37 KB instead of 70 let three workgroups share a
+// compute unit where two did; and a subtile's operands are read together, as in the forward.  The whole backward, us, before ->
+// with the LDS -> with both: 16 heads of 64, causal, s = 4096 171.9 -> 164.1 -> 161.2, sixteen sequences of 1024 195.0 -> 185.8
+// -> 183.9.  (Both subtiles of a tile side by side, for chains half as long, need 196 registers: 171 -> 179.)
 template <int DH>
 __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o,
                                                                const float *lse, float *delta, bf16_t *dqkv, float *dbias,
                                                                int s, int H, int causal) {
   typedef Cfg<DH> C;
-  __shared__ __attribute__((aligned(16))) bf16_t sK[2][C::TILE * C::PITCH];
-  __shared__ __attribute__((aligned(16))) bf16_t sV[2][C::TILE * C::PITCH];
-  __shared__ float sB[kBlockRows * kBiasPitch];   // the bias gradient's way through LDS
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  constexpr int kTile = C::TILE * C::PITCH, kBias = 2 * kBlockRows * kBiasPitch;
+  // K and V tiles, double buffered; afterwards the bias gradient's way through LDS
+  __shared__ __attribute__((aligned(16))) bf16_t smem[4 * kTile > kBias ? 4 * kTile : kBias];
+  bf16_t (*sK)[kTile] = reinterpret_cast<bf16_t (*)[kTile]>(smem), (*sV)[kTile] = sK + 2;
+  float *sB = reinterpret_cast<float *>(smem);
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
   const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true);
@@ -565,11 +596,26 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
         const int kb = k0 + 32 * sub;
         if (causal && kb > qw + 31) continue;
         f32x16 st = zero16(), dp = zero16();
+        // at head dimension 128 the fragments of a whole subtile do not fit the registers (20 of them spilled: 274 -> 282 us)
+        constexpr bool kAhead = DH <= 64;
+        bf16x8 fk[C::KSTEPS], fv[C::KSTEPS];
 #pragma unroll
         for (int c = 0; c < C::KSTEPS; ++c) {
-          st = mfma(frag_row<DH>(sK[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fq[c], st);   // S^T = K Q^T
-          dp = mfma(frag_row<DH>(sV[cur], 32 * sub + lane % 32, 16 * c + 8 * h2), fg[c], dp);   // dP^T = V dO^T
+          fk[c] = frag_row<DH>(sK[cur], 32 * sub + lane % 32, 16 * c + 8 * h2);
+          fv[c] = frag_row<DH>(sV[cur], 32 * sub + lane % 32, 16 * c + 8 * h2);
         }
+        if constexpr (kAhead) reads_first();
+#pragma unroll
+        for (int c = 0; c < C::KSTEPS; ++c) {
+          st = mfma(fk[c], fq[c], st);   // S^T = K Q^T
+          dp = mfma(fv[c], fg[c], dp);   // dP^T = V dO^T
+        }
+        bf16x8 ft[2][C::DTILES];   // K^T, wanted behind the exponentials
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int t = 0; t < C::DTILES; ++t) ft[c][t] = frag_col<DH>(sK[cur], 32 * sub + 16 * c, 32 * t, lane);
+        if constexpr (kAhead) reads_first();
         mask_keys(st, kb, qw, q, s, h2, causal);
 #pragma unroll
         for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], sc, -L)) * (dp[r] - dl);     // dS^T
@@ -579,7 +625,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
           const bf16x8 fs = acc_to_frag(st, c);
 #pragma unroll
           for (int t = 0; t < C::DTILES; ++t)
-            acc_q[t] = mfma(frag_col<DH>(sK[cur], 32 * sub + 16 * c, 32 * t, lane), fs, acc_q[t]);
+            acc_q[t] = mfma(ft[c][t], fs, acc_q[t]);
         }
       }
     }
@@ -615,7 +661,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH == 
   __shared__ __attribute__((aligned(16))) bf16_t sG[2][C::TILE * C::PITCH];
   __shared__ __attribute__((aligned(16))) float sL[2][C::TILE], sD[2][C::TILE];
   __shared__ float sB[kBlockRows * kBiasPitch];   // the bias gradient's way through LDS
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
   const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, false);   // the first key blocks are seen by the most queries
@@ -752,7 +798,7 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(con
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   auto sK = [&](int buf) { return smem + buf * S::TILE_ELEMS; };
   auto sV = [&](int buf) { return smem + (2 + buf) * S::TILE_ELEMS; };
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int rg = wave % 4, sub = wave / 4;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
@@ -868,7 +914,7 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
   auto sG = [&](int buf) { return smem + (2 + buf) * S::TILE_ELEMS; };
   float *sL = reinterpret_cast<float *>(smem + 4 * S::TILE_ELEMS), *sD = sL + 2 * TILE;
   bf16_t *sV = reinterpret_cast<bf16_t *>(sD + 2 * TILE);
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64, h2 = lane / 32;
+  const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int rg = wave % 4, sub = wave / 4;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
