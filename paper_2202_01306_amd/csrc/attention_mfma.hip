@@ -190,7 +190,7 @@ __device__ __forceinline__ void mask_keys(f32x16 &st, int kb, int qw, int q, int
 constexpr int kBiasCols = 64, kBiasPitch = kBiasCols + 1;
 template <int NT>
 __device__ __forceinline__ void bias_grad_sums(float *db, const f32x16 (&acc)[NT], float scale, bool row_stored, float *lds,
-                                               int tid) {
+                                               int tid, bool adds = true) {
   const int lane = tid % 64, h = lane / 32, row = 32 * (tid / 64) + lane % 32;
   constexpr int G = NT < 2 ? NT : 2, W = 32 * G;   // accumulator tiles and columns per pass
 #pragma unroll
@@ -206,7 +206,7 @@ __device__ __forceinline__ void bias_grad_sums(float *db, const f32x16 (&acc)[NT
     constexpr int kParts = kThreads / W;
     float sum = 0.f;
     for (int rr = part; rr < kBlockRows; rr += kParts) sum += lds[rr * kBiasPitch + col];
-    atomicAdd(db + 32 * g + col, sum);
+    if (adds) atomicAdd(db + 32 * g + col, sum);
     __syncthreads();
   }
 }
@@ -223,8 +223,8 @@ __device__ __forceinline__ void bias_grad_sums(float *db, const f32x16 (&acc)[NT
 // only one workgroup fits a compute unit (`snake` false) keeps the ranking as it is: the unit that finishes
 // first, having had the lightest block of the round, takes the heaviest that is left.
 struct BlockCoord { int rb, head, seq; };
-__device__ __forceinline__ BlockCoord block_coord(int nrb, int H, int causal, bool heaviest_is_last_row_block, bool snake = true) {
-  const int n = gridDim.x, l = blockIdx.x, bh_count = n / nrb;
+__device__ __forceinline__ BlockCoord block_coord(int nrb, int H, int causal, bool heaviest_is_last_row_block, bool snake, int n, int l) {
+  const int bh_count = n / nrb;
   int r = l;
   if (causal && snake) {
     constexpr int kUnits = 256;
@@ -237,6 +237,23 @@ __device__ __forceinline__ BlockCoord block_coord(int nrb, int H, int causal, bo
   c.head = bh % H;
   c.seq = bh / H;
   return c;
+}
+__device__ __forceinline__ BlockCoord block_coord(int nrb, int H, int causal, bool heaviest_is_last_row_block, bool snake = true) {
+  return block_coord(nrb, H, causal, heaviest_is_last_row_block, snake, gridDim.x, blockIdx.x);
+}
+
+// delta of one row, sum_c dO[c] O[c]: lane (row, h2) takes half of the columns and keeps its dO as multiply operands
+template <int DH>
+__device__ __forceinline__ float row_delta(const bf16_t *g, const bf16_t *o, int d, int row, int h2, bf16x8 (&fg)[DH / 16]) {
+  float dl = 0.f;
+#pragma unroll
+  for (int c = 0; c < DH / 16; ++c) {
+    fg[c] = frag_global(g, d, row, 16 * c + 8 * h2);
+    const bf16x8 fo = frag_global(o, d, row, 16 * c + 8 * h2);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) dl = fmaf(static_cast<float>(fg[c][k]), static_cast<float>(fo[k]), dl);
+  }
+  return dl + __shfl_xor(dl, 32, 64);   // the other half of the row
 }
 
 // ---------------------------------------------------------------------------------
@@ -538,37 +555,35 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(DH == 128 ?
 // compute unit where two did; and a subtile's operands are read together, as in the forward.  The whole backward, us, before ->
 // with the LDS -> with both: 16 heads of 64, causal, s = 4096 171.9 -> 164.1 -> 161.2, sixteen sequences of 1024 195.0 -> 185.8
 // -> 183.9.  (Both subtiles of a tile side by side, for chains half as long, need 196 registers: 171 -> 179.)
-template <int DH>
-__global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o,
-                                                               const float *lse, float *delta, bf16_t *dqkv, float *dbias,
-                                                               int s, int H, int causal) {
+//
+// NT threads: waves 4 and up only help to fetch the tiles (`smem` then holds twice the room for the bias gradient).
+template <int DH> struct DqLds {
+  static constexpr int TILE = Cfg<DH>::TILE * Cfg<DH>::PITCH, BIAS = 2 * kBlockRows * kBiasPitch;   // in elements
+  static constexpr int ELEMS = 4 * TILE > BIAS ? 4 * TILE : BIAS;
+};
+template <int DH, int NT>
+__device__ __forceinline__ void dq_rows(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse, float *delta,
+                                        bf16_t *dqkv, float *dbias, int s, int H, int causal, bf16_t *smem, int n_wg, int wg) {
   typedef Cfg<DH> C;
-  constexpr int kTile = C::TILE * C::PITCH, kBias = 2 * kBlockRows * kBiasPitch;
+  constexpr int kTile = DqLds<DH>::TILE;
   // K and V tiles, double buffered; afterwards the bias gradient's way through LDS
-  __shared__ __attribute__((aligned(16))) bf16_t smem[4 * kTile > kBias ? 4 * kTile : kBias];
   bf16_t (*sK)[kTile] = reinterpret_cast<bf16_t (*)[kTile]>(smem), (*sV)[kTile] = sK + 2;
   float *sB = reinterpret_cast<float *>(smem);
   const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
-  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true);
+  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, true, NT == kThreads, n_wg, wg);
   const int head = bc.head, seq = bc.seq, q0 = bc.rb * kBlockRows;
   const bf16_t *base = qkv + int64_t(seq) * s * ld + head * DH;
   const bf16_t *gbase = d_o + int64_t(seq) * s * d + head * DH;
   const bf16_t *obase = o + int64_t(seq) * s * d + head * DH;
-  const int qw = q0 + 32 * wave, q = qw + lane % 32, q_ld = min(q, s - 1);
+  const bool works = NT == kThreads || wave < kThreads / 64;
+  const int qw = q0 + 32 * (wave % 4), q = qw + lane % 32, q_ld = min(q, s - 1);
   bf16x8 fq[C::KSTEPS], fg[C::KSTEPS];
-  float dl = 0.f;
 #pragma unroll
-  for (int c = 0; c < C::KSTEPS; ++c) {
-    fq[c] = frag_global(base, ld, q_ld, 16 * c + 8 * h2);
-    fg[c] = frag_global(gbase, d, q_ld, 16 * c + 8 * h2);
-    const bf16x8 fo = frag_global(obase, d, q_ld, 16 * c + 8 * h2);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) dl = fmaf(static_cast<float>(fg[c][k]), static_cast<float>(fo[k]), dl);
-  }
-  dl += __shfl_xor(dl, 32, 64);   // the other half of the row
-  if (h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
+  for (int c = 0; c < C::KSTEPS; ++c) fq[c] = frag_global(base, ld, q_ld, 16 * c + 8 * h2);
+  const float dl = row_delta<DH>(gbase, obase, d, q_ld, h2, fg);
+  if (works && h2 == 0 && q < s) delta[(int64_t(seq) * H + head) * s + q] = dl;
   const float L = lse[(int64_t(seq) * H + head) * s + q_ld] * kLog2e;   // log2 units
   const float scale = rsqrtf(float(DH)), sc = scale * kLog2e;
   f32x16 acc_q[C::DTILES];
@@ -576,7 +591,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
   for (int t = 0; t < C::DTILES; ++t) acc_q[t] = zero16();
   const int k_end = causal ? min(s, q0 + kBlockRows) : s;
   const int n_tiles = (k_end + C::TILE - 1) / C::TILE;
-  TileRegs<DH, C::TILE> rk, rv;
+  TileRegs<DH, C::TILE, NT> rk, rv;
   rk.fetch(base + d, ld, min(C::TILE, s), tid);
   rv.fetch(base + 2 * d, ld, min(C::TILE, s), tid);
   rk.put(sK[0], tid);
@@ -590,7 +605,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
       rk.fetch(base + d + int64_t(kn) * ld, ld, min(C::TILE, s - kn), tid);
       rv.fetch(base + 2 * d + int64_t(kn) * ld, ld, min(C::TILE, s - kn), tid);
     }
-    if (!causal || k0 <= qw + 31) {
+    if (works && (!causal || k0 <= qw + 31)) {
 #pragma unroll
       for (int sub = 0; sub < C::TILE / 32; ++sub) {
         const int kb = k0 + 32 * sub;
@@ -635,7 +650,7 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
     }
     __syncthreads();
   }
-  if (q < s) {
+  if (works && q < s) {
     bf16_t *row = dqkv + (int64_t(seq) * s + q) * ld + head * DH;
 #pragma unroll
     for (int t = 0; t < C::DTILES; ++t)
@@ -647,7 +662,16 @@ __global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma
         *reinterpret_cast<bf16x4 *>(row + 32 * t + 8 * j + 4 * h2) = v;
       }
   }
-  if (dbias) bias_grad_sums<C::DTILES>(dbias + head * DH, acc_q, scale, q < s, sB, tid);
+  if (dbias)
+    bias_grad_sums<C::DTILES>(dbias + head * DH, acc_q, scale, q < s, sB + (works ? 0 : kBlockRows * kBiasPitch),
+                              tid % kThreads, works);
+}
+template <int DH>
+__global__ __launch_bounds__(kThreads) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_mfma(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o,
+                                                               const float *lse, float *delta, bf16_t *dqkv, float *dbias,
+                                                               int s, int H, int causal) {
+  __shared__ __attribute__((aligned(16))) bf16_t smem[DqLds<DH>::ELEMS];
+  dq_rows<DH, kThreads>(qkv, o, d_o, lse, delta, dqkv, dbias, s, H, causal, smem, gridDim.x, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------
@@ -901,25 +925,28 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dq_split(con
   }
 }
 
-template <int DH>
-__global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
-                                                                const float *delta, bf16_t *dqkv, float *dbias, int s,
-                                                                int H, int causal) {
+// `o` for a caller that does not have delta yet: the workgroup then takes it of all the rows that it streams, ahead of them,
+// into LDS behind the tiles (`delta` is not read).
+template <int DH, bool OWN_DELTA>
+__device__ __forceinline__ void dkv_split_rows(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse,
+                                               const float *delta, bf16_t *dqkv, float *dbias, int s, int H, int causal,
+                                               bf16_t *smem, int n_wg, int wg) {
   typedef Cfg<DH> C;
   typedef SplitBwd<DH> S;
   constexpr int TILE = S::TILE;
   constexpr bool kVInLds = DH == 128;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  static_assert(!(OWN_DELTA && kVInLds), "V lies where the rows' delta would");
   auto sQ = [&](int buf) { return smem + buf * S::TILE_ELEMS; };
   auto sG = [&](int buf) { return smem + (2 + buf) * S::TILE_ELEMS; };
   float *sL = reinterpret_cast<float *>(smem + 4 * S::TILE_ELEMS), *sD = sL + 2 * TILE;
   bf16_t *sV = reinterpret_cast<bf16_t *>(sD + 2 * TILE);
+  float *sDelta = sD + 2 * TILE;
   const int tid = threadIdx.x, lane = tid % 64, wave = wave_number(), h2 = lane / 32;
   const int rg = wave % 4, sub = wave / 4;
   const int d = H * DH;
   const int64_t ld = 3 * int64_t(d);
   // the first key blocks are seen by the most queries
-  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, false, false);
+  const BlockCoord bc = block_coord((s + kBlockRows - 1) / kBlockRows, H, causal, false, false, n_wg, wg);
   const int head = bc.head, seq = bc.seq, j0 = bc.rb * kBlockRows;
   const bf16_t *base = qkv + int64_t(seq) * s * ld + head * DH;
   const bf16_t *gbase = d_o + int64_t(seq) * s * d + head * DH;
@@ -951,7 +978,7 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
     rgr.fetch(gbase + int64_t(i0) * d, d, nv, tid);
     if (tid < TILE) {
       rl = tid < nv ? lbase[i0 + tid] : 0.f;
-      rd = tid < nv ? dbase[i0 + tid] : 0.f;
+      if constexpr (!OWN_DELTA) rd = tid < nv ? dbase[i0 + tid] : 0.f;
     }
   };
   auto put = [&](int buf) {
@@ -962,10 +989,19 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
       // barrier, for that wave.  The whole backward, us: 32 heads of 128, s = 2048 282 -> 275, causal 165.9 -> 163.2; 50
       // sequences x heads of 64, s = 1024, causal 57.2 -> 55.4
       sL[buf * TILE + tid] = rl * kLog2e;
-      sD[buf * TILE + tid] = rd;
+      if constexpr (!OWN_DELTA) sD[buf * TILE + tid] = rd;
     }
   };
   fetch(t_begin * TILE);
+  if constexpr (OWN_DELTA) {
+    const bf16_t *obase = o + int64_t(seq) * s * d + head * DH;
+    for (int r = t_begin * TILE + 32 * wave; r < n_tiles * TILE; r += 32 * (S::NTHR / 64)) {
+      const int row = r + lane % 32;
+      bf16x8 unused[C::KSTEPS];
+      const float dl = row_delta<DH>(gbase, obase, d, min(row, s - 1), h2, unused);
+      if (h2 == 0) sDelta[row] = row < s ? dl : 0.f;
+    }
+  }
   put(0);
   __syncthreads();
   for (int it = t_begin; it < n_tiles; ++it) {
@@ -982,7 +1018,7 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
         const bf16x8 v = kVInLds ? frag_row<DH>(sV, 32 * rg + lane % 32, 16 * c + 8 * h2) : fv[kVInLds ? 0 : c];
         dp = mfma(frag_row<DH>(sG(cur), 32 * sub + lane % 32, 16 * c + 8 * h2), v, dp);
       }
-      probabilities(sm, dp, sL + cur * TILE + 32 * sub, sD + cur * TILE + 32 * sub, h2, sc,
+      probabilities(sm, dp, sL + cur * TILE + 32 * sub, OWN_DELTA ? sDelta + ib : sD + cur * TILE + 32 * sub, h2, sc,
                     ib + 32 > s || (causal && ib < jw + 31), ib, s, key, causal);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -1031,6 +1067,27 @@ __global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(co
   }
 }
 
+template <int DH>
+__global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_dkv_split(const bf16_t *qkv, const bf16_t *d_o, const float *lse,
+                                                                const float *delta, bf16_t *dqkv, float *dbias, int s,
+                                                                int H, int causal) {
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  dkv_split_rows<DH, false>(qkv, nullptr, d_o, lse, delta, dqkv, dbias, s, H, causal, smem, gridDim.x, blockIdx.x);
+}
+// Both in one launch, for as many workgroups as leave half of the compute units to each: the first half of the grid takes
+// dK/dV, the second dQ.  Of the one thing that the former needs of the latter, delta, every workgroup makes its own.
+template <int DH>
+__global__ __launch_bounds__(512) HMY_MFMA_IN_VGPRS void k_attn_bwd_both(const bf16_t *qkv, const bf16_t *o, const bf16_t *d_o, const float *lse,
+                                                           float *delta, bf16_t *dqkv, float *dbias, int s, int H, int causal) {
+  static_assert(DqLds<DH>::ELEMS * 2 <= SplitBwd<DH>::DKV_LDS && SplitBwd<DH>::BIAS <= SplitBwd<DH>::DKV_LDS, "one size for both");
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  const int n = gridDim.x / 2, l = blockIdx.x;
+  if (l < n)
+    dkv_split_rows<DH, true>(qkv, o, d_o, lse, nullptr, dqkv, dbias, s, H, causal, smem, n, l);
+  else
+    dq_rows<DH, 512>(qkv, o, d_o, lse, delta, dqkv, dbias, s, H, causal, smem, n, l - n);
+}
+
 inline int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HMY_E_HIP, "launch of %s failed: %s", what, hipGetErrorString(e));
@@ -1068,6 +1125,20 @@ inline bool fwd_split_pays_128(int workgroups, int s, int causal) {
 }
 inline bool dq_split_pays_128(int workgroups, int s, int causal) { return (workgroups <= 256 && s >= 384) || (causal && s >= 2048); }
 
+// Head dimension 64, where dK/dV takes eight waves: dQ and dK/dV side by side instead of one after the other.  Each of the two is
+// a chain over the streamed rows that more compute units do not shorten, so a launch that leaves half of the device idle costs
+// as long as a full one.  It pays up to 160 workgroups of each, and, where a causal mask leaves most of them short, up to one
+// per unit from rows of 256 on.  The whole backward, us, apart -> together: 12 heads, three sequences of 200 20.5 -> 13.2; 4
+// heads, four of 120 15.6 -> 9.7; 8 heads of s = 1024 44.7 -> 31.5, of s = 4096 (128 workgroups) 143.8 -> 105.8; 160 workgroups
+// of s = 128 16.4 -> 15.2, of 1024 45.4 -> 41.7, of 4096 144 -> 133; 168 of 128 16.6 -> 17.3, of 512 29.5 -> 32.0, of 1024 46.2 ->
+// 51.1; causal, 168 of 128 17.1 -> 17.9, of 256 21.2 -> 18.5, 256 of 256 21.9 -> 20.8, of 512 30.2 -> 26.7, of 1024 46.5 -> 38.1,
+// of 4096 144.5 -> 107.4, 252 of 200 21.1 -> 21.4, 320 of 1024 49.1 -> 48.5, 384 53.3 -> 57.0.  The rows' delta has to fit LDS
+// behind the tiles.  Results are the same bit for bit.
+inline bool both_at_once_pays_64(int workgroups, int s, int causal) {
+  constexpr int kRoom = (SplitBwd<64>::DKV_LDS - 4 * SplitBwd<64>::TILE_ELEMS * 2 - SplitBwd<64>::STATS) / 4 / 64 * 64;
+  return s <= kRoom && (workgroups <= 160 || (causal && s >= 256 && workgroups <= 256));
+}
+
 inline bool eight_waves_allowed() {
   static const bool allowed = std::getenv("HMY_ATTN_SPLIT") == nullptr || std::atoi(std::getenv("HMY_ATTN_SPLIT")) != 0;
   return allowed;
@@ -1094,6 +1165,12 @@ int bwd_t(const void *qkv, const void *o, const void *d_o, const float *lse, flo
   bool dq_split = false, dkv_split = false;
   if constexpr (DH >= 64)
     dkv_split = eight_waves_allowed() && (DH == 128 ? dkv_split_pays_128(s) : dkv_split_pays_64(int(grid.x), s, causal));
+  if constexpr (DH == 64)
+    if (dkv_split && both_at_once_pays_64(int(grid.x), s, causal)) {
+      hipLaunchKernelGGL((k_attn_bwd_both<DH>), dim3(2 * grid.x), dim3(512), SplitBwd<DH>::DKV_LDS, st, (const bf16_t *)qkv,
+                         (const bf16_t *)o, (const bf16_t *)d_o, lse, delta, (bf16_t *)dqkv, dbias, s, H, causal);
+      return check_launch("attn_bwd_both");
+    }
   if constexpr (DH == 128) {
     dq_split = eight_waves_allowed() && dq_split_pays_128(int(grid.x), s, causal);
     if (dq_split)

@@ -624,6 +624,16 @@ def test_attention_backward_either_side_of_eight_waves(causal, b, s, H, dh):
     _attention_case(*PRECS[1], causal, b, s, H, dh)
 
 
+# 160 workgroups and 162; causal, rows of 255 and 256 beyond 160 of them, 256 of them and 258; as many rows as their delta has room
+# for in LDS, and one more
+@pytest.mark.parametrize("causal,b,s,H", [(0, 10, 130, 8), (0, 27, 130, 3), (1, 10, 130, 8), (1, 41, 255, 2), (1, 41, 256, 2),
+                                          (1, 32, 256, 4), (1, 43, 256, 3), (0, 1, 66, 1), (1, 1, 7168, 1), (1, 1, 7169, 1)])
+def test_attention_backward_in_one_launch_and_in_two(causal, b, s, H):
+    """dQ and dK/dV side by side, where dK/dV makes its own delta, and one after the other."""
+    say(f"attention backward in one launch or two causal={causal} b={b} s={s} H={H}")
+    _attention_case(*PRECS[1], causal, b, s, H, 64)
+
+
 @pytest.mark.parametrize("causal,b,s,H,dh", [(1, 2, 60, 8, 32), (0, 1, 250, 16, 64), (1, 1, 1100, 4, 64), (0, 4, 500, 16, 64), (1, 2, 60, 8, 128),
                                              (0, 1, 500, 8, 128), (0, 17, 130, 8, 128), (1, 1, 2050, 2, 128)])
 def test_attention_bf16_against_64_bits_element_by_element(causal, b, s, H, dh):
