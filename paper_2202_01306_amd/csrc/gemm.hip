@@ -330,7 +330,7 @@ inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 }  // namespace
 
-int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
+static int check_gemm(const hmy_gemm_desc &g) {
   if (g.M < 1 || g.N < 1 || g.K < 1) return fail(HMY_E_INVALID, "gemm: empty shape %dx%dx%d", g.M, g.N, g.K);
   if (!g.A || !g.B || !g.C) return fail(HMY_E_INVALID, "gemm: null operand");
   if (g.accumulate && !g.c_fp32) return fail(HMY_E_INVALID, "gemm: accumulate needs an fp32 C");
@@ -340,6 +340,28 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
   const int64_t min_lda = g.ta ? g.M : g.K, min_ldb = g.tb ? g.N : g.K;
   if (g.lda < min_lda || g.ldb < min_ldb || g.ldc < g.N || (g.res && g.ldr < g.N))
     return fail(HMY_E_INVALID, "gemm: leading dimension too small");
+  return HMY_OK;
+}
+// what the matrix-core kernels for bf16 can read, with 32-bit element offsets: every operand spans fewer than 2^31 elements
+static bool mfma_bf16_ok(const hmy_gemm_desc &g) {
+  const int64_t a_span = int64_t(g.ta ? g.K : g.M) * g.lda, b_span = int64_t(g.tb ? g.K : g.N) * g.ldb;
+  return g.prec == HMY_PREC_BF16 && g_use_mfma && aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
+         a_span < (int64_t(1) << 31) && b_span < (int64_t(1) << 31);
+}
+
+// dX = dY W and dW += dY^T X of a linear layer: in one launch where both are few enough 64x64 tiles, else one after the other
+int launch_gemm_pair(const hmy_gemm_desc &input, const hmy_gemm_desc &weight, stream_t st) {
+  int rc = check_gemm(input);
+  if (!rc) rc = check_gemm(weight);
+  if (rc) return rc;
+  const bool small = g_use_mfma == 1 && mfma_bf16_ok(input) && mfma_bf16_ok(weight) && gemm_prefers_small(input) && gemm_prefers_small(weight);
+  if (small && launch_gemm_small_pair(input, weight, st, &rc)) return rc;
+  rc = launch_gemm(input, st);
+  return rc ? rc : launch_gemm(weight, st);
+}
+
+int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
+  if (const int rc = check_gemm(g)) return rc;
   GemmP p;
   p.A = g.A; p.B = g.B; p.C = g.C; p.bias = g.bias; p.res = g.res; p.gelu_out = g.gelu_out;
   p.M = g.M; p.N = g.N; p.K = g.K;
@@ -348,10 +370,7 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
   p.res_fp32 = g.res_fp32 || g.prec == HMY_PREC_FP32;
   hipStream_t s = (hipStream_t)st;
   if (g.prec == HMY_PREC_FP32 && g_use_mfma) return launch_gemm_f32(g, st);
-  // 32-bit element offsets inside the kernel: every operand must span fewer than 2^31 elements
-  const int64_t a_span = int64_t(g.ta ? g.K : g.M) * g.lda, b_span = int64_t(g.tb ? g.K : g.N) * g.ldb;
-  const bool mfma_ok = g.prec == HMY_PREC_BF16 && g_use_mfma && aligned16(g.A) && aligned16(g.B) && g.lda % 8 == 0 &&
-                       g.ldb % 8 == 0 && a_span < (int64_t(1) << 31) && b_span < (int64_t(1) << 31);
+  const bool mfma_ok = mfma_bf16_ok(g);
   if (mfma_ok && g_use_mfma == 1 && gemm_prefers_small(g)) return launch_gemm_small(g, st);
   if (mfma_ok && g_use_mfma == 1 && gemm_dma_eligible(g)) return launch_gemm_dma(g, st);
   if (mfma_ok && g_use_mfma == 1 && g.K % 32 != 0 && g.K > 256 && g.accumulate && g.c_fp32 && !g.bias && !g.res) {

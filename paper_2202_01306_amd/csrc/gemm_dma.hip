@@ -540,16 +540,17 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, 
 // Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), 480x768x768 8.2 -> 6.9; weight
 // gradient 1024x1024x1024 12.1 -> 8.7, 768x3072x600 16.2 -> 14.0, 256x1024x480 6.6 -> 5.4.  It takes longer before its first multiply: short contractions stay with the kernel above
 // (`even_pays`).
+// `bid` of `workgroups`: a launch may hold more than this product.
 template <bool TA, bool TB>
-__global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_split, int grid_n, int splits) {
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[SS * 2 * kSmallOp];
+__device__ __forceinline__ void even_tile(const DmaP &p, int tiles_per_split, int grid_n, int splits, int bid, int workgroups,
+                                          bf16_t *smem) {
   constexpr int L = 4;   // load-to-LDS instructions per thread per K tile
   static_assert(SS == 4, "stages are counted modulo 4");
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int wm = wave / 2, wn = wave % 2;
-  int bid = blockIdx.x, split_idx = 0;
-  const int nb = gridDim.x / splits, grid_m = nb / grid_n;
+  int split_idx = 0;
+  const int nb = workgroups / splits, grid_m = nb / grid_n;
   if (splits > 1) {   // as in the 128x128 kernel
     split_idx = bid % splits;
     bid /= splits;
@@ -687,6 +688,19 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_sp
     }
   }
 }
+template <bool TA, bool TB>
+__global__ __launch_bounds__(NT) void k_gemm_dma64_even(DmaP p, int tiles_per_split, int grid_n, int splits) {
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[SS * 2 * kSmallOp];
+  even_tile<TA, TB>(p, tiles_per_split, grid_n, splits, blockIdx.x, gridDim.x, smem);
+}
+// An input gradient (the first `wgs` workgroups) and a weight gradient (the others), which do not depend on each other.
+struct EvenPart { DmaP p; int tiles_per_split, grid_n, splits, wgs; };
+__global__ __launch_bounds__(NT) void k_gemm_dma64_pair(EvenPart input, EvenPart weight) {
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[SS * 2 * kSmallOp];
+  const int l = blockIdx.x;
+  if (l < input.wgs) even_tile<false, true>(input.p, input.tiles_per_split, input.grid_n, input.splits, l, input.wgs, smem);
+  else even_tile<true, true>(weight.p, weight.tiles_per_split, weight.grid_n, weight.splits, l - input.wgs, weight.wgs, smem);
+}
 
 inline int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
@@ -724,12 +738,19 @@ bool even_pays(const hmy_gemm_desc &g) {
   return (g.K % SK == 0 || (g.ta && g.tb)) && g.K >= (tiles <= 256 ? 256 : g.res && tiles > 400 ? 512 : 384);
 }
 
-int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
+// how a product is laid out over 64x64 tiles
+EvenPart small_part(const hmy_gemm_desc &g, const DmaP &p) {
   const int gm = (g.M + ST - 1) / ST, gn = (g.N + ST - 1) / ST, nk = (g.K + SK - 1) / SK;
   int splits = small_splits(g);
   const int tps = (nk + splits - 1) / splits;
   splits = (nk + tps - 1) / tps;
-  const dim3 grid(gm * gn * splits), block(NT);
+  return {p, tps, gn, splits, gm * gn * splits};
+}
+
+int launch_small(const hmy_gemm_desc &g, const DmaP &p, hipStream_t s) {
+  const EvenPart part = small_part(g, p);
+  const int tps = part.tiles_per_split, gn = part.grid_n, splits = part.splits;
+  const dim3 grid(part.wgs), block(NT);
   if (even_pays(g)) {
     if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<false, false>), grid, block, 0, s, p, tps, gn, splits);
     else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_dma64_even<false, true>), grid, block, 0, s, p, tps, gn, splits);
@@ -819,6 +840,19 @@ bool gemm_prefers_small(const hmy_gemm_desc &g) {
   return tiles <= 256 || (tiles <= 512 && g.K <= (!even ? 2048 : !major ? INT_MAX : half_lines ? 8192 : 4096));
 }
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
+
+// A linear layer's two gradients in one launch: each is one workgroup's chain over its K tiles long, however few workgroups there
+// are, and they depend on nothing of each other.  Up to one workgroup per compute unit in all: iterations of an encoder of width
+// 256 over 480 tokens (96 to 192 workgroups a pair) 5416 -> 5157 us; with 257 to 512 workgroups (width 512) there was nothing to
+// gain, 12.01 ms either way.
+bool launch_gemm_small_pair(const hmy_gemm_desc &input, const hmy_gemm_desc &weight, stream_t st, int *rc) {
+  if (input.ta || !input.tb || !weight.ta || !weight.tb || !even_pays(input) || !even_pays(weight)) return false;
+  const EvenPart i = small_part(input, dma_params(input)), w = small_part(weight, dma_params(weight));
+  if (i.wgs + w.wgs > 256) return false;
+  hipLaunchKernelGGL(k_gemm_dma64_pair, dim3(i.wgs + w.wgs), dim3(NT), 0, (hipStream_t)st, i, w);
+  *rc = check_launch("gemm_dma64_pair");
+  return true;
+}
 
 static int64_t tiles_of(const hmy_gemm_desc &g, int rows, int cols) {
   return int64_t((g.M + rows - 1) / rows) * ((g.N + cols - 1) / cols);

@@ -157,12 +157,14 @@ int launch_gelu_bwd(int prec, const void *dg, const void *u, void *du, uint64_t 
 int launch_gelu_bwd_colsum(int prec, const void *dg, const void *u, void *du, float *db, int T, int N, stream_t st);
 int launch_colsum(int prec, const void *a, float *out, int T, int N, stream_t st);
 int launch_gemm(const hmy_gemm_desc &g, stream_t st);
+int launch_gemm_pair(const hmy_gemm_desc &input, const hmy_gemm_desc &weight, stream_t st);
 
 int launch_gemm_f32(const hmy_gemm_desc &g, stream_t st);
 int launch_gemm_mfma32(const hmy_gemm_desc &g, stream_t st);
 bool gemm_prefers_small(const hmy_gemm_desc &g);
 bool gemm_small_excluded();   // by a tuning switch that names a larger kernel
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st);
+bool launch_gemm_small_pair(const hmy_gemm_desc &input, const hmy_gemm_desc &weight, stream_t st, int *rc);   // false: not taken
 bool gemm_dma_eligible(const hmy_gemm_desc &g);
 int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st);
 int launch_gemm_tile(const hmy_gemm_desc &g, int nb, int splits, stream_t st);   // tiles of 256 x 32 nb outputs, nb = 4 .. 8

@@ -237,6 +237,15 @@ def test_weight_slots_bf16_planned_several_packs(slots, distance, update_site):
     assert stats["h2d"]["sX"] > 0
 
 
+# a ragged number of tokens and of hidden units; the fewest tokens for it; a weight gradient split over workgroups beside its input
+# gradient; 198 workgroups for the pair of the second MLP layer (5 x 22 and 4 x 22) and 288 (5 x 32 and 4 x 32), which go apart
+@pytest.mark.parametrize("d_ffn,seq,b", [(520, 75, 4), (512, 128, 2), (512, 515, 2), (1408, 150, 2), (2048, 150, 2)])
+def test_gradient_pairs_of_a_linear_layer_in_one_launch(d_ffn, seq, b):
+    say(f"bf16, input and weight gradients in one launch: d_ffn {d_ffn}, {b} x {seq} tokens")
+    cfg = tiny_cfg(n_blocks=2, d_model=256, n_heads=4, d_ffn=d_ffn, seq_len=seq, vocab=1000, precision="bf16", M=2, b=b)
+    run_and_compare(cfg, sched_ends=([2], [1, 2, 4]), zero_state=False, steps=(5,), weight_scale=3.0)
+
+
 def test_planner_sweeping_slots_gives_a_schedule_that_runs():
     say("bf16, planner free to choose 2..4 slots and the pack count")
     cfg = tiny_cfg(n_blocks=4, d_model=128, n_heads=2, d_ffn=512, seq_len=128, vocab=1000, precision="bf16", M=3, b=2)
