@@ -526,6 +526,13 @@ typedef struct hmy_gemm_desc {
   int32_t res_fp32;
 } hmy_gemm_desc;
 int hmy_k_gemm(const hmy_gemm_desc *g, void *stream);
+/* Which output tiles of the load-to-LDS kernels hmy_k_gemm takes for a bf16 product: rows and columns of one (64x64, 128x128,
+ * 256 x 128 to 256; 0x0 if another kernel runs), parts that the contraction is split into at most (their sums meet in C by
+ * fp32 atomics), and steps at its end that are left to a launch of their own.  Launches nothing and reads no operand; for
+ * tests and measurement, like the call below it: the product on tiles of that size whatever hmy_k_gemm would take.
+ * HMY_E_INVALID for sizes that do not exist and for products that those tiles cannot take. */
+int hmy_gemm_tiles(const hmy_gemm_desc *g, int32_t tiles[4]);
+int hmy_k_gemm_on_tiles(const hmy_gemm_desc *g, int32_t rows, int32_t cols, void *stream);
 
 /* qkv[T,3d] (q|k|v thirds, head h = columns h*dh..) -> o[T,d], lse[b,H,s] fp32 */
 int hmy_k_attn_fwd(int32_t prec, const void *qkv, void *o, float *lse, int32_t b, int32_t s,

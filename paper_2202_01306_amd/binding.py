@@ -150,7 +150,7 @@ EXPORTS = [
     "hmy_count_swaps", "hmy_host_alloc", "hmy_host_free", "hmy_create", "hmy_get_schedule", "hmy_bind_state", "hmy_copies_on_engines", "hmy_resident_params", "hmy_sync_state",
     "hmy_iteration", "hmy_destroy", "hmy_set_profiling", "hmy_set_progress", "hmy_set_kernel_path", "hmy_k_embed_fwd", "hmy_k_embed_bwd",
     "hmy_k_layernorm_fwd", "hmy_k_layernorm_bwd", "hmy_k_layernorm_bwd_static", "hmy_k_gelu_fwd", "hmy_k_gelu_bwd", "hmy_k_gelu_bwd_colsum", "hmy_k_colsum",
-    "hmy_k_gemm", "hmy_k_attn_fwd", "hmy_k_attn_bwd", "hmy_k_xent", "hmy_k_adam", "hmy_host_adam",
+    "hmy_k_gemm", "hmy_gemm_tiles", "hmy_k_gemm_on_tiles", "hmy_k_attn_fwd", "hmy_k_attn_bwd", "hmy_k_xent", "hmy_k_adam", "hmy_host_adam",
 ]
 
 lib.hmy_strerror.restype = C.c_char_p
@@ -422,10 +422,25 @@ def hmy_k_colsum(prec, a, out, T, N, stream=None):
 
 
 def hmy_k_gemm(prec, M, N, K, A, lda, B, ldb, Cc, ldc, ta=0, tb=0, c_fp32=0, accumulate=0, bias=None, res=None,
-               ldr=0, gelu_out=None, stream=None, res_fp32=0):
+               ldr=0, gelu_out=None, stream=None, res_fp32=0, tiles=None):
+    """tiles = (rows, columns): on those (hmy_k_gemm_on_tiles), for tests and measurement."""
     g = hmy_gemm_desc(prec, M, N, K, ta, tb, c_fp32, accumulate, _p(A), lda, _p(B), ldb, _p(Cc), ldc,
                       _p(bias), _p(res), ldr, _p(gelu_out), res_fp32)
-    _check(lib.hmy_k_gemm(C.byref(g), _p(stream)))
+    _check(lib.hmy_k_gemm(C.byref(g), _p(stream)) if tiles is None
+           else lib.hmy_k_gemm_on_tiles(C.byref(g), *tiles, _p(stream)))
+
+
+def hmy_gemm_tiles(prec, M, N, K, ta=0, tb=0, c_fp32=0, accumulate=0, bias=0, res=0, gelu=0, res_fp32=0, lda=None, ldb=None,
+                   ldc=None):
+    """(rows, columns, parts, tail) of the tiles that hmy_k_gemm takes for such a product of aligned operands, densely stored
+    (rows of multiples of 8 elements) unless leading dimensions are given."""
+    up8 = lambda n: (n + 7) // 8 * 8
+    at = C.c_void_p(256)     # looked at for its alignment only
+    g = hmy_gemm_desc(prec, M, N, K, ta, tb, c_fp32, accumulate, at, lda or up8(M if ta else K), at, ldb or up8(N if tb else K),
+                      at, ldc or N, at if bias else None, at if res else None, N, at if gelu else None, res_fp32)
+    out = (C.c_int32 * 4)()
+    _check(lib.hmy_gemm_tiles(C.byref(g), out))
+    return tuple(out)
 
 
 def hmy_k_attn_fwd(prec, qkv, o, lse, b, s, H, dh, causal, stream=None):

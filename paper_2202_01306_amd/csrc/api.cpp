@@ -240,6 +240,16 @@ int hmy_k_gemm(const hmy_gemm_desc *g, void *stream) {
   NOTNULL(g);
   return launch_gemm(*g, stream);
 }
+int hmy_gemm_tiles(const hmy_gemm_desc *g, int32_t tiles[4]) {
+  NOTNULL(g); NOTNULL(tiles);
+  const GemmTiles t = gemm_tiles(*g);
+  tiles[0] = t.rows; tiles[1] = t.cols; tiles[2] = t.splits; tiles[3] = t.tail;
+  return HMY_OK;
+}
+int hmy_k_gemm_on_tiles(const hmy_gemm_desc *g, int32_t rows, int32_t cols, void *stream) {
+  NOTNULL(g);
+  return launch_gemm_on_tiles(*g, rows, cols, stream);
+}
 int hmy_k_attn_fwd(int32_t prec, const void *qkv, void *o, float *lse, int32_t b, int32_t s, int32_t H, int32_t dh,
                    int32_t causal, void *stream) {
   NOTNULL(qkv); NOTNULL(o); NOTNULL(lse);

@@ -349,6 +349,51 @@ static bool mfma_bf16_ok(const hmy_gemm_desc &g) {
          a_span < (int64_t(1) << 31) && b_span < (int64_t(1) << 31);
 }
 
+// the part of a product's contraction that is a multiple of 32, and the rest
+static hmy_gemm_desc body_of(const hmy_gemm_desc &g, hmy_gemm_desc *tail) {
+  hmy_gemm_desc body = g;
+  body.K = g.K / 32 * 32;
+  *tail = g;
+  tail->K = g.K - body.K;
+  tail->A = static_cast<const bf16_t *>(g.A) + (g.ta ? int64_t(body.K) * g.lda : int64_t(body.K));
+  tail->B = static_cast<const bf16_t *>(g.B) + (g.tb ? int64_t(body.K) * g.ldb : int64_t(body.K));
+  return body;
+}
+
+GemmTiles gemm_tiles(const hmy_gemm_desc &g) {
+  if (!mfma_bf16_ok(g) || g_use_mfma != 1) return {};
+  if (gemm_prefers_small(g)) return gemm_small_tiles(g);
+  if (gemm_dma_eligible(g)) return gemm_dma_tiles(g);
+  if (g.K > 256 && g.accumulate && g.c_fp32 && !g.bias && !g.res) {
+    // accumulating GEMM with a ragged contraction: the multiple-of-32 part goes to the load-to-LDS kernels, the tail is
+    // added on 64x64 tiles, which take any contraction: a single K tile, so a workgroup's life is the way to memory and back
+    // and many short ones do best
+    // (on the register-staged kernel's 128x128 tiles the tail of 17 steps alone took 31 us at 2048x1024: 2048x1024x50257 314 ->
+    // 299 us, 480x256x5003 36 -> 16, weight gradients 4096x4096x1023 110 -> 81, 50257x1024x2047 465 -> 383)
+    hmy_gemm_desc tail;
+    const hmy_gemm_desc body = body_of(g, &tail);
+    if (gemm_dma_eligible(body)) {
+      GemmTiles t = gemm_dma_tiles(body);
+      t.tail = tail.K;
+      return t;
+    }
+  }
+  return {};
+}
+
+// the product on the tiles that the caller names
+int launch_gemm_on_tiles(const hmy_gemm_desc &g, int rows, int cols, stream_t st) {
+  if (const int rc = check_gemm(g)) return rc;
+  const bool known = rows == cols ? rows == 64 || rows == 128 || rows == 256 : rows == 256 && cols % 32 == 0 && cols >= 128 && cols < 256;
+  if (!known) return fail(HMY_E_INVALID, "gemm: no tiles of %d rows and %d columns", rows, cols);
+  if (!mfma_bf16_ok(g) || (rows > 64 && !gemm_dma_eligible(g)))
+    return fail(HMY_E_INVALID, "gemm: tiles of %d rows do not take this product (bf16, 16-byte aligned operands%s)", rows,
+                rows > 64 ? ", K a multiple of 32" : "");
+  if (rows == 64) return launch_gemm_small(g, st);
+  if (rows == 128) return launch_gemm_dma(g, gemm_128_tiles(g), st);
+  return launch_gemm_tile(g, cols / 32, 1, st);
+}
+
 // dX = dY W and dW += dY^T X of a linear layer: in one launch where both are few enough 64x64 tiles, else one after the other
 int launch_gemm_pair(const hmy_gemm_desc &input, const hmy_gemm_desc &weight, stream_t st) {
   int rc = check_gemm(input);
@@ -370,25 +415,16 @@ int launch_gemm(const hmy_gemm_desc &g, stream_t st) {
   p.res_fp32 = g.res_fp32 || g.prec == HMY_PREC_FP32;
   hipStream_t s = (hipStream_t)st;
   if (g.prec == HMY_PREC_FP32 && g_use_mfma) return launch_gemm_f32(g, st);
-  const bool mfma_ok = mfma_bf16_ok(g);
-  if (mfma_ok && g_use_mfma == 1 && gemm_prefers_small(g)) return launch_gemm_small(g, st);
-  if (mfma_ok && g_use_mfma == 1 && gemm_dma_eligible(g)) return launch_gemm_dma(g, st);
-  if (mfma_ok && g_use_mfma == 1 && g.K % 32 != 0 && g.K > 256 && g.accumulate && g.c_fp32 && !g.bias && !g.res) {
-    // accumulating GEMM with a ragged contraction: the multiple-of-32 part goes to the load-to-LDS kernels, the tail is
-    // added on 64x64 tiles, which take any contraction: a single K tile, so a workgroup's life is the way to memory and back
-    // and many short ones do best
-    // (on the register-staged kernel's 128x128 tiles the tail of 17 steps alone took 31 us at 2048x1024: 2048x1024x50257 314 ->
-    // 299 us, 480x256x5003 36 -> 16, weight gradients 4096x4096x1023 110 -> 81, 50257x1024x2047 465 -> 383)
-    hmy_gemm_desc body = g, tail = g;
-    body.K = g.K / 32 * 32;
-    tail.K = g.K - body.K;
-    tail.A = static_cast<const bf16_t *>(g.A) + (g.ta ? int64_t(body.K) * g.lda : int64_t(body.K));
-    tail.B = static_cast<const bf16_t *>(g.B) + (g.tb ? int64_t(body.K) * g.ldb : int64_t(body.K));
-    if (gemm_dma_eligible(body) && aligned16(tail.A) && aligned16(tail.B)) {
-      const int rc = launch_gemm_dma(body, st);
-      return rc ? rc : gemm_small_excluded() ? launch_gemm_mfma32(tail, st) : launch_gemm_small(tail, st);
-    }
+  const GemmTiles t = gemm_tiles(g);
+  if (t.rows == 64) return launch_gemm_small(g, st);
+  if (t.rows) {
+    hmy_gemm_desc tail;
+    const hmy_gemm_desc body = body_of(g, &tail);
+    const int rc = launch_gemm_dma(body, t, st);
+    if (rc || !t.tail) return rc;
+    return gemm_small_excluded() ? launch_gemm_mfma32(tail, st) : launch_gemm_small(tail, st);
   }
+  const bool mfma_ok = mfma_bf16_ok(g);
   if (mfma_ok && g_use_mfma != 2) return launch_gemm_mfma32(g, st);
   if (mfma_ok) {
     const int gm = (g.M + BM - 1) / BM, gn = (g.N + BN - 1) / BN, nk = (g.K + BK - 1) / BK;

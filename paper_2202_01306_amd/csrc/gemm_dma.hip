@@ -839,6 +839,7 @@ bool gemm_prefers_small(const hmy_gemm_desc &g) {
   const bool major = g.ta || g.tb, half_lines = (!g.ta || g.lda % 32 == 0) && (!g.tb || g.ldb % 32 == 0);
   return tiles <= 256 || (tiles <= 512 && g.K <= (!even ? 2048 : !major ? INT_MAX : half_lines ? 8192 : 4096));
 }
+GemmTiles gemm_small_tiles(const hmy_gemm_desc &g) { return {ST, ST, small_part(g, dma_params(g)).splits, 0, 0, 0}; }
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st) { return launch_small(g, dma_params(g), (hipStream_t)st); }
 
 // A linear layer's two gradients in one launch: each is one workgroup's chain over its K tiles long, however few workgroups there
@@ -886,12 +887,25 @@ static int tile_columns(const hmy_gemm_desc &g) {
   return best;
 }
 
-int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
-  const DmaP p = dma_params(g);
+// 128x128 tiles: the contraction is split over workgroups (fp32 atomics into C) only while that fills idle compute units: with one
+// workgroup per unit already, a deeper K loop beats more workgroups that each pay a prologue and an atomic epilogue.
+GemmTiles gemm_128_tiles(const hmy_gemm_desc &g) {
   static const int force_bk = env_int("HMY_GEMM_BK", 0), force_s = env_int("HMY_GEMM_STAGES", 0);
-  static const int force_tile = env_int("HMY_GEMM_TILE", 0);   // 128 | 256: that block tile for every shape it can take
-  const bool can_split = g.accumulate && g.c_fp32 && !g.bias && !g.res;
-  if (force_tile == 256 && g.M >= 256 && g.N >= 256) return launch_gemm_tile(g, 8, 1, st);
+  const int wgs = int(tiles_of(g, BM, BM));
+  int splits = 1;
+  if (small_may_split(g) && wgs <= 128) splits = std::max(1, std::min(256 / wgs, g.K / 256));
+  // few workgroups: one per compute unit, deep K tiles and a deep ring; many: smaller
+  // stages so that several are resident and overlap each other's prologue and epilogue
+  int bk = g.K % 64 == 0 && wgs * splits <= 256 ? 64 : 32;
+  if (force_bk == 32 || (force_bk == 64 && g.K % 64 == 0)) bk = force_bk;
+  return {BM, BM, splits, bk, force_s == 3 ? 3 : 4, 0};
+}
+
+GemmTiles gemm_dma_tiles(const hmy_gemm_desc &g) {
+  // 128 | 256: that block tile for every shape it can take
+  static const int force_bk = env_int("HMY_GEMM_BK", 0), force_s = env_int("HMY_GEMM_STAGES", 0), force_tile = env_int("HMY_GEMM_TILE", 0);
+  const bool can_split = small_may_split(g);
+  if (force_tile == 256 && g.M >= 256 && g.N >= 256) return {256, 256, 1, 0, 0, 0};
   if (force_tile == 0 && force_bk == 0 && force_s == 0) {
     // Very long sums over few outputs: 256x128 tiles with the contraction split (fp32 atomics into C), where they come to nearly
     // a workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128
@@ -902,36 +916,24 @@ int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st) {
     const bool few = tiles_of(g, BM, BM) <= 128;
     if (can_split && few && g.M >= 256 && g.K % 64 == 0) {
       const int w2 = int(tiles_of(g, 256, 128)), splits = 256 / w2;
-      if (splits > 1 && w2 * splits >= 200 && g.K / splits >= 4608) return launch_gemm_tile(g, 4, splits, st);
+      if (splits > 1 && w2 * splits >= 200 && g.K / splits >= 4608) return {256, 128, splits, 0, 0, 0};
     }
     // sums over few outputs split the contraction over 128x128 tiles instead (below)
     const int nb = can_split && few ? 0 : tile_columns(g);
-    if (nb) return launch_gemm_tile(g, nb, 1, st);
+    if (nb) return {256, 32 * nb, 1, 0, 0, 0};
   }
-  const int gm = (g.M + BM - 1) / BM, gn = (g.N + BM - 1) / BM;
-  // split the contraction over workgroups (fp32 atomics into C) only while that fills
-  // idle compute units: with one workgroup per unit already, a deeper K loop beats more
-  // workgroups that each pay a prologue and an atomic epilogue
-  int splits = 1;
-  if (can_split && gm * gn <= 128)
-    splits = std::max(1, std::min(256 / (gm * gn), g.K / 256));
-  // few workgroups: one per compute unit, deep K tiles and a deep ring; many: smaller
-  // stages so that several are resident and overlap each other's prologue and epilogue
-  int bk = g.K % 64 == 0 && gm * gn * splits <= 256 ? 64 : 32;
-  if (force_bk == 32 || (force_bk == 64 && g.K % 64 == 0)) bk = force_bk;
-  int stages = 4;
-  if (force_s >= 3 && force_s <= 4) stages = force_s;
-  const int nk = g.K / bk;
-  const int tps = (nk + splits - 1) / splits;
-  splits = (nk + tps - 1) / tps;
+  return gemm_128_tiles(g);
+}
+
+int launch_gemm_dma(const hmy_gemm_desc &g, const GemmTiles &t, stream_t st) {
+  if (t.rows == 256) return launch_gemm_tile(g, t.cols / 32, t.splits, st);
+  const DmaP p = dma_params(g);
+  const int gm = (g.M + BM - 1) / BM, gn = (g.N + BM - 1) / BM, nk = g.K / t.bk;
+  const int tps = (nk + t.splits - 1) / t.splits, splits = (nk + tps - 1) / tps;
   dim3 grid(gm * gn * splits);
   hipStream_t s = (hipStream_t)st;
-  if (bk == 64) {
-    if (stages == 3) return launch_cfg<64, 3>(g, p, grid, tps, gn, splits, s);
-    return launch_cfg<64, 4>(g, p, grid, tps, gn, splits, s);
-  }
-  if (stages == 3) return launch_cfg<32, 3>(g, p, grid, tps, gn, splits, s);
-  return launch_cfg<32, 4>(g, p, grid, tps, gn, splits, s);
+  if (t.bk == 64) return t.stages == 3 ? launch_cfg<64, 3>(g, p, grid, tps, gn, splits, s) : launch_cfg<64, 4>(g, p, grid, tps, gn, splits, s);
+  return t.stages == 3 ? launch_cfg<32, 3>(g, p, grid, tps, gn, splits, s) : launch_cfg<32, 4>(g, p, grid, tps, gn, splits, s);
 }
 
 }  // namespace hmy

@@ -166,7 +166,16 @@ bool gemm_small_excluded();   // by a tuning switch that names a larger kernel
 int launch_gemm_small(const hmy_gemm_desc &g, stream_t st);
 bool launch_gemm_small_pair(const hmy_gemm_desc &input, const hmy_gemm_desc &weight, stream_t st, int *rc);   // false: not taken
 bool gemm_dma_eligible(const hmy_gemm_desc &g);
-int launch_gemm_dma(const hmy_gemm_desc &g, stream_t st);
+// Tiles that a bf16 product goes on: 64x64, 128x128 or 256 x 128 .. 256; rows 0: on another kernel.  splits: parts of the
+// contraction, which meet in C by fp32 atomics; bk, stages: the ring of the 128x128 kernel; tail: steps of the contraction that
+// are left to a launch of their own on 64x64 tiles.
+struct GemmTiles { int rows = 0, cols = 0, splits = 1, bk = 0, stages = 0, tail = 0; };
+GemmTiles gemm_tiles(const hmy_gemm_desc &g);          // for any product
+GemmTiles gemm_small_tiles(const hmy_gemm_desc &g);    // for one that goes on 64x64 tiles
+GemmTiles gemm_dma_tiles(const hmy_gemm_desc &g);      // for one that gemm_dma_eligible() and goes on larger ones
+GemmTiles gemm_128_tiles(const hmy_gemm_desc &g);      // on 128x128 ones
+int launch_gemm_dma(const hmy_gemm_desc &g, const GemmTiles &t, stream_t st);
+int launch_gemm_on_tiles(const hmy_gemm_desc &g, int rows, int cols, stream_t st);
 int launch_gemm_tile(const hmy_gemm_desc &g, int nb, int splits, stream_t st);   // tiles of 256 x 32 nb outputs, nb = 4 .. 8
 int launch_attn_fwd(int prec, const void *qkv, void *o, float *lse, int b, int s, int H, int dh,
                     int causal, stream_t st);

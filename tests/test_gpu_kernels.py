@@ -192,7 +192,7 @@ def test_embedding_bwd_runs(counts, d):
 
 
 def _gemm_case(prec, pc, dt, tol, M, N, K, ta, tb, c_fp32, accumulate, bias, res, gelu, use_mfma, pad=0, res_fp32=0,
-               row_pad=0, ldc=None):
+               row_pad=0, ldc=None, tiles=None):
     rng = np.random.default_rng(M * 7 + N * 3 + K + ta * 2 + tb)
     lda = M + row_pad if ta else K + pad        # pad: rows whose contiguous axis is K; row_pad: A stored [K, M]
     ldb = N if tb else K + pad
@@ -221,7 +221,7 @@ def _gemm_case(prec, pc, dt, tol, M, N, K, ta, tb, c_fp32, accumulate, bias, res
         B.hmy_k_gemm(pc, M, N, K, dev(A, dt), lda, dev(Bm, dt), ldb, Cd, ldc, ta=ta, tb=tb, c_fp32=c_fp32,
                      accumulate=accumulate, bias=dev(biasv, dt) if bias else None,
                      res=dev(resv, torch.float32 if res_fp32 else dt) if res else None, ldr=N, gelu_out=gout,
-                     res_fp32=res_fp32)
+                     res_fp32=res_fp32, tiles=tiles)
         got = host(Cd)
     finally:
         B.hmy_set_kernel_path(True)
@@ -279,30 +279,30 @@ def test_gemm_bf16_epilogues(use_mfma):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("K", [96, 320])
 def test_gemm_bf16_large_outputs_all_layouts(ta, tb, K):
-    """Outputs large enough for the 256x256 block tile (one workgroup per compute unit or more), with a ragged last
-    tile row and column; K of fewer and of more tiles than the ring has stages."""
+    """256x256 tiles, one workgroup per compute unit or nearly, with a ragged last tile row and column; K of fewer and of
+    more tiles than the ring has stages."""
     say(f"gemm bf16 large ta={ta} tb={tb} K={K}")
-    _gemm_case("bf16", 1, torch.bfloat16, 2e-2, 3600, 3336, K, ta, tb, 0, 0, False, False, False, True)
+    _gemm_case("bf16", 1, torch.bfloat16, 2e-2, 3600, 3336, K, ta, tb, 0, 0, False, False, False, True, tiles=(256, 256))
 
 
 def test_gemm_bf16_large_outputs_epilogues():
-    args = ("bf16", 1, torch.bfloat16, 2e-2)
+    args, big = ("bf16", 1, torch.bfloat16, 2e-2), dict(tiles=(256, 256))
     say("gemm bf16 large: bias + gelu")
-    _gemm_case(*args, 4096, 3072, 64, 0, 0, 0, 0, True, False, True, True)
+    _gemm_case(*args, 4096, 3072, 64, 0, 0, 0, 0, True, False, True, True, **big)
     say("gemm bf16 large: bias + gelu in place")
-    _gemm_case(*args, 4096, 3072, 64, 0, 0, 0, 0, True, False, "in place", True)
+    _gemm_case(*args, 4096, 3072, 64, 0, 0, 0, 0, True, False, "in place", True, **big)
     say("gemm bf16 large: bias + fp32 residual stream")
-    _gemm_case(*args, 4096, 3072, 160, 0, 0, 1, 0, True, True, False, True, res_fp32=1)
+    _gemm_case(*args, 4096, 3072, 160, 0, 0, 1, 0, True, True, False, True, res_fp32=1, **big)
     say("gemm bf16 large: bias + bf16 residual")
-    _gemm_case(*args, 4096, 3072, 64, 0, 0, 0, 0, True, True, False, True)
+    _gemm_case(*args, 4096, 3072, 64, 0, 0, 0, 0, True, True, False, True, **big)
     say("gemm bf16 large: fp32 C +=")
-    _gemm_case(*args, 3072, 4096, 128, 1, 1, 1, 1, False, False, False, True)
-    _gemm_case(*args, 50257, 1024, 96, 1, 1, 1, 1, False, False, False, True, row_pad=47)   # vocabulary rows, ragged
+    _gemm_case(*args, 3072, 4096, 128, 1, 1, 1, 1, False, False, False, True, **big)
+    _gemm_case(*args, 50257, 1024, 96, 1, 1, 1, 1, False, False, False, True, row_pad=47, **big)   # vocabulary rows, ragged
     say("gemm bf16: fp32 C +=, contraction split over workgroups (128x128 tiles)")
     _gemm_case(*args, 1024, 1024, 4096, 1, 1, 1, 1, False, False, False, True)
     _gemm_case(*args, 1536, 1024, 2048 + 32, 0, 1, 1, 1, False, False, False, True)    # the last split has two K tiles
     say("gemm bf16 large: fp32 logits, ragged vocabulary, padded leading dimensions")
-    _gemm_case(*args, 512, 50257, 64, 0, 0, 1, 0, False, False, False, True, 8)
+    _gemm_case(*args, 512, 50257, 64, 0, 0, 1, 0, False, False, False, True, 8, **big)
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 1), (1, 1)])
@@ -327,26 +327,28 @@ def test_gemm_bf16_tiles_that_stick_out_of_c():
     _gemm_case(*args, 2048, 1600, 64, 0, 0, 1, 0, True, True, False, True, res_fp32=1)
     _gemm_case(*args, 1600, 1608, 256, 1, 1, 1, 1, False, False, False, True)            # weight gradient, ragged rows too
     say("gemm bf16 edge tiles, 256x256: fp32 C with a ragged width; bf16 C with bias + gelu")
-    _gemm_case(*args, 4096, 2999, 64, 0, 0, 1, 0, False, False, False, True, ldc=3008)
-    _gemm_case(*args, 4000, 3000, 96, 0, 0, 0, 0, True, False, True, True)
-    _gemm_case(*args, 4000, 3000, 64, 0, 1, 0, 0, True, True, False, True)
+    big = dict(tiles=(256, 256))
+    _gemm_case(*args, 4096, 2999, 64, 0, 0, 1, 0, False, False, False, True, ldc=3008, **big)
+    _gemm_case(*args, 4000, 3000, 96, 0, 0, 0, 0, True, False, True, True, **big)
+    _gemm_case(*args, 4000, 3000, 64, 0, 1, 0, 0, True, True, False, True, **big)
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 def test_gemm_bf16_256x128_tiles(ta, tb):
-    """One round of them, with edge tiles that stick out of C in both directions, three rounds, and the shortest contractions
-    that go there; every output stage.  Bounds as for the other tiles, of which these have the order of sums."""
-    args = ("bf16", 1, torch.bfloat16, 2e-2)
+    """One round of them, with edge tiles that stick out of C in both directions, three rounds; every output stage.  Bounds as
+    for the other tiles, of which these have the order of sums."""
+    args, wide = ("bf16", 1, torch.bfloat16, 2e-2), dict(tiles=(256, 128))
     for M, N, K in ((2040, 2296, 1024), (2104, 3840, 1088)):
         say(f"gemm bf16 256x128 ta={ta} tb={tb} {M}x{N}x{K}")
-        _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, True, False, True)
-        _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, False, True, True)
-        _gemm_case(*args, M, N, K, ta, tb, 1, 0, True, True, False, True, res_fp32=1)
-    _gemm_case(*args, 2040, 2296, 512, ta, tb, 1, 1, False, False, False, True)      # sums into C: few tiles, and many
-    _gemm_case(*args, 2048, 4096, 2048, ta, tb, 1, 1, False, False, False, True)
+        _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, True, False, True, **wide)
+        _gemm_case(*args, M, N, K, ta, tb, 0, 0, True, False, True, True, **wide)
+        _gemm_case(*args, M, N, K, ta, tb, 1, 0, True, True, False, True, res_fp32=1, **wide)
+    _gemm_case(*args, 2040, 2296, 512, ta, tb, 1, 1, False, False, False, True, **wide)      # sums into C: few tiles, and many
+    _gemm_case(*args, 2048, 4096, 2048, ta, tb, 1, 1, False, False, False, True, **wide)
     # rows of C that allow no 16-byte access
-    _gemm_case(*args, 2048, 2300 if not tb else 2296, 1024, ta, tb, 1, 0, False, False, False, True)
-    _gemm_case(*args, 2048, 8968, 2048, ta, tb, 0, 0, True, False, False, True)      # three rounds
+    N = 2296 if tb else 2300
+    _gemm_case(*args, 2048, N, 1024, ta, tb, 1, 0, False, False, False, True, ldc=N + 2, **wide)
+    _gemm_case(*args, 2048, 8968, 2048, ta, tb, 0, 0, True, False, False, True, **wide)      # three rounds
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
@@ -355,6 +357,8 @@ def test_gemm_bf16_256x128_tiles_split(ta, tb, M, N, K):
     """Sums so long that they are split over 256x128 tiles: parts of equal length, and a shorter last one; edge tiles in both
     directions."""
     say(f"gemm bf16 256x128 split ta={ta} tb={tb} {M}x{N}x{K}")
+    rows, cols, parts, tail = B.hmy_gemm_tiles(1, M, N, K, ta=ta, tb=tb, c_fp32=1, accumulate=1)
+    assert (rows, cols, tail) == (256, 128, 0) and parts > 1
     _gemm_case("bf16", 1, torch.bfloat16, 2e-2, M, N, K, ta, tb, 1, 1, False, False, False, True)
 
 
@@ -450,8 +454,8 @@ def test_gemm_bf16_small_tiles_sum_like_the_larger_ones(ta, tb, K):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(400, 8248, 480), (400, 8248, 512), (3256, 2528, 736), (1080, 7208, 480), (3664, 3360, 736),
                                    (1352, 8144, 480), (1352, 8144, 1024), (1352, 8144, 32), (1352, 8144, 64), (1352, 8144, 96)])
-def test_gemm_bf16_tiles_of_every_width(ta, tb, M, N, K):
-    """Tiles of 256 rows and 128 to 256 columns (which one, the rule decides by output stage too): edge tiles in both directions,
+def test_gemm_bf16_large_products_a_few_rows_at_a_time(ta, tb, M, N, K):
+    """Large products on the tiles that the rule picks for them and their output stage: edge tiles in both directions,
     contractions that end in half a K tile, of one and of two K tiles.  The rows a few at a time go to 64x64 tiles, which sum in
     the same order: equal bits."""
     say(f"gemm bf16 256 rows ta={ta} tb={tb} {M}x{N}x{K}")
@@ -484,6 +488,43 @@ def test_gemm_bf16_tiles_of_every_width(ta, tb, M, N, K):
         if kind == "stream":
             ref = (a.t() if ta else a).double() @ (b if tb else b.t()).double() + bias.double() + low.double()
             assert float((c.double() - ref).abs().max()) < 6 * math.sqrt(K) * (K / 32 + 2) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("cols", [128, 160, 192, 224, 256])
+@pytest.mark.parametrize("aligned", [True, False])
+def test_gemm_bf16_tiles_of_every_width(aligned, cols, ta, tb):
+    """Tiles of 256 rows and every width, with every output stage: edge tiles in both directions, contractions of one K tile, of
+    half a one, of one and a half, and longer ones that end in half a one.  Rows of C, of the residual and of the activation that
+    allow 16-byte accesses, and ones that allow none and end inside a group of 8 columns.  64x64 tiles sum in the same order and
+    have the same output stages: equal bits, and nothing beyond the last column changes."""
+    M, N = 520, 2 * cols + (72 if aligned else 75)
+    ld, up8 = N + (8 if aligned else 2), (N + 7) // 8 * 8
+    for K in (32, 64, 96, 480, 736):
+        say(f"gemm bf16 256x{cols} ta={ta} tb={tb} {M}x{N}x{K} ld={ld}")
+        g = torch.Generator(device="cuda").manual_seed(N + K)
+        a = torch.randn((K, M) if ta else (M, K), device="cuda", generator=g).bfloat16()
+        b = torch.randn((K, up8) if tb else (N, K), device="cuda", generator=g).bfloat16()
+        bias, low = torch.randn(up8, device="cuda", generator=g).bfloat16(), torch.randn(M, ld, device="cuda", generator=g)
+        for kind in ("bias", "res", "gelu", "gelu alone", "fp32", "stream", "sum", "sum, bias and stream"):
+            c32 = kind in ("fp32", "stream") or "sum" in kind
+            kw = dict(c_fp32=int(c32), accumulate=int("sum" in kind))
+            if kind not in ("fp32", "sum"):
+                kw["bias"] = bias
+            if kind == "res" or "stream" in kind:
+                kw.update(res=low if c32 else low.bfloat16(), ldr=ld, res_fp32=int(c32))
+            out = []
+            for tiles in ((256, cols), (64, 64)):
+                c = low.clone() if c32 else low.bfloat16()
+                act = c if kind == "gelu alone" else low.bfloat16() if kind == "gelu" else None
+                B.hmy_k_gemm(1, M, N, K, a, a.shape[1], b, b.shape[1], c, ld, ta=ta, tb=tb, gelu_out=act, tiles=tiles, **kw)
+                out.append((c, c if act is None else act))
+            for x, y in zip(*out):
+                assert torch.equal(x, y), (kind, K)
+                assert torch.equal(x[:, N:], low.to(x.dtype)[:, N:]), (kind, K)
+            if kind == "stream":
+                ref = (a.t() if ta else a).double() @ (b[:, :N] if tb else b.t()).double() + bias[:N].double() + low[:, :N].double()
+                assert float((out[0][0][:, :N].double() - ref).abs().max()) < 6 * math.sqrt(K) * (K / 32 + 2) * 2.0 ** -24
 
 
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 1)])

@@ -789,3 +789,17 @@ int main() {
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-pthread", "-I", csrc, str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_gemm_tiles_named_and_chosen():
+    """Which tiles a product takes can be asked for without a GPU; sizes that do not exist and products that the named tiles cannot
+    take are errors."""
+    assert B.hmy_gemm_tiles(1, 64, 64, 64)[:2] == (64, 64)
+    assert B.hmy_gemm_tiles(1, 8192, 8192, 8192) == (256, 256, 1, 0)
+    assert B.hmy_gemm_tiles(1, 2048, 1024, 50257, tb=1, c_fp32=1, accumulate=1) == (256, 128, 4, 17)
+    assert B.hmy_gemm_tiles(0, 64, 64, 64)[0] == 0                        # fp32: other kernels
+    assert B.hmy_gemm_tiles(1, 64, 64, 64, lda=68)[0] == 0                # rows of no multiple of 16 bytes
+    for tiles, K in (((256, 96), 64), ((256, 288), 64), ((128, 256), 64), ((512, 512), 64), ((256, 256), 72), ((128, 128), 72)):
+        with pytest.raises(B.HmyError) as e:
+            B.hmy_k_gemm(1, 256, 256, K, 256, K, 256, K, 256, 256, tiles=tiles)
+        assert e.value.code == B.HMY_E_INVALID
