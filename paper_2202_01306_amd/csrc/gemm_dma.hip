@@ -860,29 +860,33 @@ static int64_t tiles_of(const hmy_gemm_desc &g, int rows, int cols) {
 }
 // Estimated time, in us, of a product on tiles of 256 x 32 nb outputs (gemm_tile.hip), or (nb = 0) on the 128x128 ones: rounds
 // of 256 tiles, each of which costs its multiplies, its output stage (longer if it reads as much as it writes; several 128x128
-// workgroups of a compute unit overlap theirs) and its start.  The last round costs most of a whole one, however few tiles it
-// has: fewest outputs in flight for nothing is what the width is chosen for.  Fitted to 746 random products of all layouts and
-// output stages, K = 64 to 8192, on all six tiles: the tile with the smallest estimate takes 0.6 % longer than the fastest on
-// average from K = 480 on, 2.0 % below (where only 128x128 and 256x256 are asked for: there the start and the output stage are
-// everything).  Some, us, on 128x128 | 256x128, 160, 192, 224, 256: 2048x4800x1600 (forward) 56 | 44 33 33 40 38, 512x50257x1024
-// (fp32) 109 | 87 83 84 66 73, 2048x12288x4096 214 | 164 202 157 171 175, 4800x1600x2048 (weight gradient) 46 | 42 52 55 61 63,
-// 8192x4096x256 (weight gradient) 65 | 73 98 91 95 78.
+// workgroups of a compute unit overlap theirs) and its start.  The last of several rounds costs a whole one, however few tiles
+// it has (128x128 tiles, two to a unit, save a little): fewest outputs in flight for nothing is what the width is chosen for.
+// Fitted to 6700 random products of all layouts and output stages, K = 64 to 16384, on all six tiles, for the choice and not for
+// the time itself, one that would be slower than on 128x128 tiles counting double: the tile with the smallest estimate takes
+// 0.3 % longer than the fastest on average from K = 480 on, 1.2 % below, where only 256x128 and 256x256 are asked for besides
+// (with the other widths the mean there is 0.5 % lower, and three times as many take longer than on 128x128).  26 of 4187
+// products that had 128x128 tiles when the others were for whole rounds only are more than 2 % slower, the worst of them 13 %.
+// Some, us, on 128x128 | 256x128, 160, 192, 224, 256: 2048x4800x1600 (forward) 49 | 41 33 33 36 37, 2048x12288x4096 250 | 165
+// 201 156 167 173, 1944x3768x512 (fp32) 17.8 | 16.3 19.3 19.2 20.8 21.3, 3856x4416x704 (input gradient) 40 | 39 38 39 42 44,
+// 5696x4072x832 (weight gradient) 72 | 75 91 80 84 84, 512x25504x192 (fp32 +=) 37 | 34 44 50 35 35.
 static float tile_time(const hmy_gemm_desc &g, int nb) {
-  static constexpr float per_1024_steps[] = {9.f, 0.f, 0.f, 0.f, 10.9f, 15.f, 16.6f, 18.2f, 19.4f};
+  static constexpr float per_1024_steps[] = {8.5f, 0.f, 0.f, 0.f, 11.f, 14.7f, 16.8f, 18.3f, 19.5f};
   const int64_t tiles = nb ? tiles_of(g, 256, 32 * nb) : tiles_of(g, BM, BM), whole = tiles / 256;
-  const float part = float(tiles % 256) / 256.f;
-  const float rounds = float(whole) + (part == 0.f ? 0.f : whole == 0 ? 0.56f + 0.44f * part : 0.78f + 0.22f * part);
+  const float part = float(tiles % 256) / 256.f, least = whole == 0 ? 0.5f : nb ? 0.99f : 0.87f;
+  const float rounds = float(whole) + (part == 0.f ? 0.f : least + (1.f - least) * part);
   const bool both = g.c_fp32 || g.gelu_out;   // twice the bytes of a bf16 C
-  const float kind = g.accumulate ? (nb || !(g.ta && g.tb) ? 2.f : 1.2f) : g.res && g.res_fp32 ? 2.2f : both ? (nb ? 1.35f : 1.9f) : 1.f;
-  float out = 7.9f * kind * (nb ? float(nb) / 8.f : 0.25f);
-  if (nb % 2 && !g.c_fp32) out += 1.f;   // tiles whose rows end inside a cache line
-  return rounds * (per_1024_steps[nb] * float(g.K) / 1024.f + out + (nb ? 5.3f : 0.8f));
+  const float kind = g.accumulate ? (nb ? 2.15f : g.ta && g.tb ? 1.49f : 1.85f)
+                     : g.res && g.res_fp32 ? 2.18f : both ? (nb ? 1.48f : 1.87f) : 1.f;
+  float out = 11.f * kind * (nb ? float(nb) / 8.f : 0.264f);
+  if (nb % 2 && !g.c_fp32) out += 0.3f;   // tiles whose rows end inside a cache line
+  return rounds * (per_1024_steps[nb] * float(g.K) / 1024.f + out + (nb ? 4.9f : 0.95f));
 }
 // Columns, over 32, of the tiles of 256 rows that a product takes, or 0 for 128x128 tiles.
 static int tile_columns(const hmy_gemm_desc &g) {
   if (g.M < 256 || g.N < 128) return 0;
   int best = 0;
-  for (int nb = g.K < 480 ? 8 : 4; nb <= 8; ++nb)
+  for (int nb = 4; nb <= 8; nb += g.K < 480 ? 4 : 1)
     if (tile_time(g, nb) < tile_time(g, best)) best = nb;
   return best;
 }

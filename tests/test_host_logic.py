@@ -803,3 +803,23 @@ def test_gemm_tiles_named_and_chosen():
         with pytest.raises(B.HmyError) as e:
             B.hmy_k_gemm(1, 256, 256, K, 256, K, 256, K, 256, 256, tiles=tiles)
         assert e.value.code == B.HMY_E_INVALID
+
+
+# us on 128x128 | 256x128, 160, 192, 224, 256
+@pytest.mark.parametrize("kind,M,N,K,times", [
+    ("fp32", 1944, 3768, 512, "17.8 16.3 19.3 19.2 20.8 21.3"), ("fp32", 2856, 2368, 704, "20.6 17.7 21.1 21.3 23.4 23.8"),
+    ("gelu", 5272, 1464, 512, "19.0 15.8 22.8 22.8 24.0 24.3"), ("dx", 3272, 1160, 480, "14.1 12.2 16.5 17.0 18.3 19.0"),
+    ("dx", 2464, 3192, 608, "18.1 15.3 19.6 19.9 21.3 21.9"), ("dx", 3856, 4416, 704, "39.7 39.0 38.2 38.7 42.1 43.8"),
+    ("dw", 5696, 4072, 832, "72.0 75.1 90.7 80.0 83.7 84.4"), ("dw", 4672, 4288, 1696, "94.0 99.3 119.7 100.6 109.4 111.1"),
+    ("dw", 8624, 2432, 864, "68.8 74.5 85.3 74.2 79.1 79.0"), ("dw", 3840, 6144, 800, "73.2 73.0 89.2 76.9 81.5 79.9"),
+    ("dw", 1896, 2288, 512, "18.2 16.4 22.8 23.4 25.0 25.7"), ("dw", 1152, 3664, 576, "19.2 17.6 24.0 24.6 26.3 27.0"),
+    ("stream", 2048, 1600, 6400, "63.3 84.5 102.0 101.0 115.9 122.2"), ("bf16", 2048, 12288, 4096, "249.8 165.2 200.6 156.4 166.9 172.6"),
+    ("bf16", 2048, 4800, 1600, "48.9 41.3 33.2 33.2 36.3 36.5"), ("dw", 4800, 1600, 2048, "44.9 41.6 50.3 53.2 59.3 60.2")])
+def test_gemm_tiles_are_the_fastest_or_nearly(kind, M, N, K, times):
+    """Short contractions, where a rule fitted to longer ones took 256-row tiles that were slower than 128x128 ones, weight
+    gradients, and outputs of the workloads: the tile taken is within 4 % of the fastest."""
+    kw = dict(fp32=dict(c_fp32=1), gelu=dict(bias=1, gelu=1), dx=dict(tb=1), dw=dict(ta=1, tb=1, c_fp32=1, accumulate=1),
+              stream=dict(bias=1, c_fp32=1, res=1, res_fp32=1), bf16=dict(bias=1))[kind]
+    us = dict(zip([(128, 128)] + [(256, c) for c in (128, 160, 192, 224, 256)], map(float, times.split())))
+    took = B.hmy_gemm_tiles(1, M, N, K, **kw)[:2]
+    assert us[took] <= 1.04 * min(us.values()), (took, us)
