@@ -802,13 +802,17 @@ bool gemm_small_excluded() {
 //   empty, not at all (1056x992x2048 18.1 -> 20.1, 1320x800 18.8 -> 20.7; x1536 18.5 -> 16.8) and 2304 (1984x1000 26.1 -> 21.6
 //   at 2048, 29.7 -> 28.8 at 3072; 1312x1312x2304 22.2 -> 22.2, x2560 23.1 -> 24.1).
 // Short of a first split, at most 64 tiles of such misaligned rows are the other exception: 504x392x704 8.2 -> 7.7, x768 7.4 ->
-// 7.8, x960 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2).  Contractions that
-// are no multiple of 64 gain more, since the larger kernels take them in two parts (1024x1024x2008 23.3 -> 12.0, 2048x2048x3000
-// 57 -> 45, 4096x1024x3000 54 -> 51).
+// 7.8, x960 8.0 -> 9.0 (416x416x960 7.8 -> 7.9, 600x600x960 10.6 -> 9.2).  Contractions that are no multiple of 32 gain more,
+// since the larger kernels take them in two launches (1024x1024x2008 23.3 -> 12.0, 2048x2048x3000 57 -> 45, 4096x1024x3000 54 ->
+// 51), and have up to 2047 tiles.  Beyond 1024 of them the other side is tiles of 256 rows, and the two meet where tiles x K is 2.6
+// million, from 1408 tiles on 2.2 (tiles of 256 rows and a tail -> these: 4672x1024x824, 1168 tiles, 32.7 -> 23.4, 1856x2304x1813
+// 43.5 -> 36.5, 1120x3920x2216, 1116 tiles, 49.3 -> 49.6, 8960x512x3048 60.2 -> 64.6; 2560x2432x848, 1520 tiles, 34.9 -> 27.5,
+// 5040x1344x1354, 1659 tiles, 44.5 -> 45.1, 4608x1536x3000, 1728 tiles, 67 -> 83, 6400x1280x2968 72 -> 95).
 bool small_sum_pays(const hmy_gemm_desc &g) {
   const int64_t tiles = int64_t((g.M + ST - 1) / ST) * ((g.N + ST - 1) / ST);
   const int splits = small_splits(g), length = g.K / splits;
   const bool half_lines = g.lda % 32 == 0 && g.ldb % 32 == 0;
+  if (tiles > 1024 && tiles * g.K > (tiles <= 1408 ? 2600000 : 2200000)) return false;
   if (length < 1792) return g.K % SK != 0 || half_lines || splits > 1 || tiles > 64 || g.K < 768;
   if (tiles > 256) {
     const bool whole = g.M % ST == 0 && g.N % ST == 0;

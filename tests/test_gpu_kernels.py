@@ -413,10 +413,12 @@ def test_gemm_bf16_small_tiles(ta, tb, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(64, 64, 257), (264, 200, 300), (768, 3072, 600), (1000, 1208, 481), (72, 136, 999),
-                                   (1024, 1024, 2047), (1160, 1024, 2080), (2048, 2048, 1801)])
+                                   (1024, 1024, 2047), (1160, 1024, 2080), (2048, 2048, 1801), (4352, 1024, 2381),
+                                   (4352, 1024, 2393)])
 def test_gemm_bf16_weight_gradients_of_any_length(M, N, K):
     """Contractions that are no multiple of 64 on 64x64 tiles: the rows behind K, which lie in memory and are undefined numbers
-    here, count as zeros; one part, several, more than 512 tiles."""
+    here, count as zeros; one part, several, more than 512 tiles, and either side of where more than 1024 of them give way to
+    tiles of 256 rows and a tail."""
     say(f"gemm bf16 weight gradient {M}x{N}x{K}")
     g = torch.Generator(device="cuda").manual_seed(K)
     a, b = (torch.full((K + 192, n), float("nan"), device="cuda").bfloat16() for n in (M, N))

@@ -823,3 +823,15 @@ def test_gemm_tiles_are_the_fastest_or_nearly(kind, M, N, K, times):
     us = dict(zip([(128, 128)] + [(256, c) for c in (128, 160, 192, 224, 256)], map(float, times.split())))
     took = B.hmy_gemm_tiles(1, M, N, K, **kw)[:2]
     assert us[took] <= 1.04 * min(us.values()), (took, us)
+
+
+# us on tiles of 256 rows and a tail | on 64x64 tiles
+@pytest.mark.parametrize("M,N,K,large,small", [
+    (4608, 1536, 3000, 67.0, 83.4), (4608, 1536, 2600, 62.2, 71.7), (6400, 1280, 2968, 71.5, 95.0), (2560, 2560, 2200, 55.7, 63.7),
+    (1256, 6088, 1208, 49.1, 62.9), (1984, 3768, 2086, 59.4, 80.1), (4096, 1024, 2008, 36.2, 32.0), (2048, 2048, 3000, 54.8, 45.8),
+    (4672, 1024, 824, 32.7, 23.4), (2264, 3520, 776, 41.5, 35.9), (1664, 2880, 1256, 39.4, 28.7)])
+def test_gemm_weight_gradients_of_ragged_length_leave_the_small_tiles_in_time(M, N, K, large, small):
+    """A contraction that is no multiple of 32: on 64x64 tiles in one launch, or its even part on larger tiles and the rest in a
+    launch of its own, whichever is faster."""
+    rows, _, parts, tail = B.hmy_gemm_tiles(1, M, N, K, ta=1, tb=1, c_fp32=1, accumulate=1)
+    assert (rows == 64) == (small < large) and parts == 1 and tail == (0 if rows == 64 else K % 32)
