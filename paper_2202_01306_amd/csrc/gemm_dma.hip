@@ -910,11 +910,11 @@ GemmTiles gemm_128_tiles(const hmy_gemm_desc &g) {
 }
 
 GemmTiles gemm_dma_tiles(const hmy_gemm_desc &g) {
-  // 128 | 256: that block tile for every shape it can take
-  static const int force_bk = env_int("HMY_GEMM_BK", 0), force_s = env_int("HMY_GEMM_STAGES", 0), force_tile = env_int("HMY_GEMM_TILE", 0);
+  // 128 | 256: that block tile for every shape it can take; the other two switches are the 128x128 kernel's
+  static const int force_tile = env_int("HMY_GEMM_BK", 0) || env_int("HMY_GEMM_STAGES", 0) ? 128 : env_int("HMY_GEMM_TILE", 0);
   const bool can_split = small_may_split(g);
   if (force_tile == 256 && g.M >= 256 && g.N >= 256) return {256, 256, 1, 0, 0, 0};
-  if (force_tile == 0 && force_bk == 0 && force_s == 0) {
+  if (force_tile == 0) {
     // Very long sums over few outputs: 256x128 tiles with the contraction split (fp32 atomics into C), where they come to nearly
     // a workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128
     // tiles -> these: 2048x1024, K = 50240 219 -> 184 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280),

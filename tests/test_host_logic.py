@@ -835,3 +835,17 @@ def test_gemm_weight_gradients_of_ragged_length_leave_the_small_tiles_in_time(M,
     launch of its own, whichever is faster."""
     rows, _, parts, tail = B.hmy_gemm_tiles(1, M, N, K, ta=1, tb=1, c_fp32=1, accumulate=1)
     assert (rows == 64) == (small < large) and parts == 1 and tail == (0 if rows == 64 else K % 32)
+
+
+@pytest.mark.parametrize("env,tile", [({}, (256, 256)), (dict(HMY_GEMM_TILE="128"), (128, 128)), (dict(HMY_GEMM_TILE="256"), (256, 256)),
+                                      (dict(HMY_GEMM_BK="64"), (128, 128)), (dict(HMY_GEMM_STAGES="3"), (128, 128)),
+                                      (dict(HMY_GEMM_TILE="256", HMY_GEMM_BK="32"), (128, 128)),
+                                      (dict(HMY_GEMM_TILE="256", HMY_GEMM_STAGES="3"), (128, 128))])
+def test_gemm_tuning_switches(env, tile):
+    """The K tile and the ring's depth are the 128x128 kernel's: with either of them every shape takes it, whatever tile is named."""
+    import subprocess
+    import sys
+    code = "from paper_2202_01306_amd import binding as B; print(*B.hmy_gemm_tiles(1, 8192, 8192, 8192)[:2])"
+    plain = {k: v for k, v in os.environ.items() if not k.startswith("HMY_GEMM_")}
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env={**plain, **env}, check=True, capture_output=True, text=True).stdout
+    assert tuple(map(int, out.split())) == tile
