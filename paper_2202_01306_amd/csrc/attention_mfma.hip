@@ -186,7 +186,12 @@ __device__ __forceinline__ void mask_keys(f32x16 &st, int kb, int qw, int q, int
 // column 32 t + 8 (r / 4) + 4 (l / 32) + r % 4.  The values pass through LDS, 64 columns at a time (rows padded to
 // an odd number of floats so that the lanes of a wave, which hold different rows, fall on different banks); every
 // thread then adds up a share of one column, and one atomic per thread leaves the workgroup -- a few wide atomic
-// instructions instead of one narrow one per value and wave.  Every thread of the workgroup must call this.
+// instructions instead of one narrow one per value and wave.  At head dimension 32 that would be eight atomics on every
+// address from each workgroup, and a launch of many workgroups waits for them: there the shares meet in LDS first, and one
+// atomic per column leaves.  us, the whole backward, with eight -> with one (without the bias gradient): 32 heads of 32, 32
+// sequences of 128 70 -> 42 (38), sixteen of 256 81 -> 52 (48), eight of 1024, causal, 206 -> 150 (142); 4 heads, four of 64
+// 13.1 -> 10.1 (8.1).  Wider heads, four shares, gain nothing (16 heads of 64, sixteen of 512 105.4 -> 105.5) and pay for the
+// barriers (4 heads of 128, s = 128 31.5 -> 32.1).  Every thread of the workgroup must call this.
 constexpr int kBiasCols = 64, kBiasPitch = kBiasCols + 1;
 template <int NT>
 __device__ __forceinline__ void bias_grad_sums(float *db, const f32x16 (&acc)[NT], float scale, bool row_stored, float *lds,
@@ -206,6 +211,16 @@ __device__ __forceinline__ void bias_grad_sums(float *db, const f32x16 (&acc)[NT
     constexpr int kParts = kThreads / W;
     float sum = 0.f;
     for (int rr = part; rr < kBlockRows; rr += kParts) sum += lds[rr * kBiasPitch + col];
+    if constexpr (kParts > 4) {   // (see above)
+      __syncthreads();
+      lds[part * kBiasPitch + col] = sum;
+      __syncthreads();
+      adds = adds && part == 0;
+      if (adds) {
+#pragma unroll
+        for (int k = 1; k < kParts; ++k) sum += lds[k * kBiasPitch + col];
+      }
+    }
     if (adds) atomicAdd(db + 32 * g + col, sum);
     __syncthreads();
   }
