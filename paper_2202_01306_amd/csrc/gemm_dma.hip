@@ -865,26 +865,32 @@ static int64_t tiles_of(const hmy_gemm_desc &g, int rows, int cols) {
 // Estimated time, in us, of a product on tiles of 256 x 32 nb outputs (gemm_tile.hip), or (nb = 0) on the 128x128 ones: rounds
 // of 256 tiles, each of which costs its multiplies, its output stage (longer if it reads as much as it writes; several 128x128
 // workgroups of a compute unit overlap theirs) and its start.  The last of several rounds costs a whole one, however few tiles
-// it has (128x128 tiles, two to a unit, save a little): fewest outputs in flight for nothing is what the width is chosen for.
-// Fitted to 6700 random products of all layouts and output stages, K = 64 to 16384, on all six tiles, for the choice and not for
-// the time itself, one that would be slower than on 128x128 tiles counting double: the tile with the smallest estimate takes
+// it has (128x128 tiles, two to a unit, save a little): fewest outputs in flight for nothing is what the width is chosen for.  A
+// first round that is not full saves up to half of its stores and start, but a workgroup's multiplies take nearly as long
+// beside fewer others: half a round of 256x128 tiles is no match for a whole one of 128x128 (4096x1024x50257, the input
+// gradient of a vocabulary, 128x128 | 256x128, us: 449 | 603; K = 16384 146 | 199).
+// Fitted to 6800 random products of all layouts and output stages, K = 64 to 50240, on all six tiles, for the choice and not for
+// the time itself, one that would be slower than on 128x128 tiles counting three times: the tile with the smallest estimate takes
 // 0.3 % longer than the fastest on average from K = 480 on, 1.2 % below, where only 256x128 and 256x256 are asked for besides
-// (with the other widths the mean there is 0.5 % lower, and three times as many take longer than on 128x128).  26 of 4187
-// products that had 128x128 tiles when the others were for whole rounds only are more than 2 % slower, the worst of them 13 %.
+// (with the other widths the mean there is 0.5 % lower, and three times as many take longer than on 128x128).  56 of the products
+// take more than 2 % longer than on the tiles they had when the widths were 128 for one round and 256 for whole ones, the worst
+// of them 13 %.
 // Some, us, on 128x128 | 256x128, 160, 192, 224, 256: 2048x4800x1600 (forward) 49 | 41 33 33 36 37, 2048x12288x4096 250 | 165
 // 201 156 167 173, 1944x3768x512 (fp32) 17.8 | 16.3 19.3 19.2 20.8 21.3, 3856x4416x704 (input gradient) 40 | 39 38 39 42 44,
 // 5696x4072x832 (weight gradient) 72 | 75 91 80 84 84, 512x25504x192 (fp32 +=) 37 | 34 44 50 35 35.
 static float tile_time(const hmy_gemm_desc &g, int nb) {
-  static constexpr float per_1024_steps[] = {8.5f, 0.f, 0.f, 0.f, 11.f, 14.7f, 16.8f, 18.3f, 19.5f};
+  static constexpr float per_1024_steps[] = {8.5f, 0.f, 0.f, 0.f, 11.1f, 14.7f, 16.8f, 18.6f, 19.6f};
   const int64_t tiles = nb ? tiles_of(g, 256, 32 * nb) : tiles_of(g, BM, BM), whole = tiles / 256;
-  const float part = float(tiles % 256) / 256.f, least = whole == 0 ? 0.5f : nb ? 0.99f : 0.87f;
-  const float rounds = float(whole) + (part == 0.f ? 0.f : least + (1.f - least) * part);
+  const float part = float(tiles % 256) / 256.f;
+  // rounds' worth of time, if the last one's costs `least` at least
+  auto rounds = [&](float least) { return float(whole) + (part == 0.f ? 0.f : least + (1.f - least) * part); };
+  const float last = nb ? 0.99f : 0.85f;
   const bool both = g.c_fp32 || g.gelu_out;   // twice the bytes of a bf16 C
-  const float kind = g.accumulate ? (nb ? 2.15f : g.ta && g.tb ? 1.49f : 1.85f)
-                     : g.res && g.res_fp32 ? 2.18f : both ? (nb ? 1.48f : 1.87f) : 1.f;
-  float out = 11.f * kind * (nb ? float(nb) / 8.f : 0.264f);
-  if (nb % 2 && !g.c_fp32) out += 0.3f;   // tiles whose rows end inside a cache line
-  return rounds * (per_1024_steps[nb] * float(g.K) / 1024.f + out + (nb ? 4.9f : 0.95f));
+  const float kind = g.accumulate ? (g.ta && g.tb ? (nb ? 2.28f : 1.49f) : nb ? 2.35f : 2.05f)
+                     : g.res && g.res_fp32 ? 2.6f : both ? (nb ? 1.58f : 1.96f) : 1.f;
+  float out = 9.5f * kind * (nb ? float(nb) / 8.f : 0.264f);
+  if (nb % 2 && !g.c_fp32) out += 0.1f;   // tiles whose rows end inside a cache line
+  return rounds(whole ? last : 0.65f) * per_1024_steps[nb] * float(g.K) / 1024.f + rounds(whole ? last : 0.5f) * (out + (nb ? 4.7f : 0.98f));
 }
 // Columns, over 32, of the tiles of 256 rows that a product takes, or 0 for 128x128 tiles.
 static int tile_columns(const hmy_gemm_desc &g) {

@@ -812,14 +812,19 @@ def test_gemm_tiles_named_and_chosen():
     ("dx", 2464, 3192, 608, "18.1 15.3 19.6 19.9 21.3 21.9"), ("dx", 3856, 4416, 704, "39.7 39.0 38.2 38.7 42.1 43.8"),
     ("dw", 5696, 4072, 832, "72.0 75.1 90.7 80.0 83.7 84.4"), ("dw", 4672, 4288, 1696, "94.0 99.3 119.7 100.6 109.4 111.1"),
     ("dw", 8624, 2432, 864, "68.8 74.5 85.3 74.2 79.1 79.0"), ("dw", 3840, 6144, 800, "73.2 73.0 89.2 76.9 81.5 79.9"),
-    ("dw", 1896, 2288, 512, "18.2 16.4 22.8 23.4 25.0 25.7"), ("dw", 1152, 3664, 576, "19.2 17.6 24.0 24.6 26.3 27.0"),
+    ("dw", 1152, 3664, 576, "19.2 17.6 24.0 24.6 26.3 27.0"),
     ("stream", 2048, 1600, 6400, "63.3 84.5 102.0 101.0 115.9 122.2"), ("bf16", 2048, 12288, 4096, "249.8 165.2 200.6 156.4 166.9 172.6"),
-    ("bf16", 2048, 4800, 1600, "48.9 41.3 33.2 33.2 36.3 36.5"), ("dw", 4800, 1600, 2048, "44.9 41.6 50.3 53.2 59.3 60.2")])
+    ("bf16", 2048, 4800, 1600, "48.9 41.3 33.2 33.2 36.3 36.5"), ("dw", 4800, 1600, 2048, "44.9 41.6 50.3 53.2 59.3 60.2"),
+    ("dx sum", 4096, 1024, 50240, "449 603 624 655 785 834"), ("dx sum", 2048, 2048, 50240, "443 606 660 674 790 837"),
+    ("dx sum", 4096, 1024, 30528, "272 375 389 407 483 517"), ("dx sum", 8192, 1024, 50240, "1031 678 775 778 874 871"),
+    ("dx", 4096, 1024, 16384, "146 199 212 226 264 284"), ("bf16", 2048, 2048, 16384, "129 167 203 211 256 261")])
 def test_gemm_tiles_are_the_fastest_or_nearly(kind, M, N, K, times):
     """Short contractions, where a rule fitted to longer ones took 256-row tiles that were slower than 128x128 ones, weight
-    gradients, and outputs of the workloads: the tile taken is within 4 % of the fastest."""
+    gradients, outputs of the workloads, and contractions so long that half a round of larger tiles takes longer than a whole one
+    of smaller: the tile taken is within 4 % of the fastest."""
     kw = dict(fp32=dict(c_fp32=1), gelu=dict(bias=1, gelu=1), dx=dict(tb=1), dw=dict(ta=1, tb=1, c_fp32=1, accumulate=1),
-              stream=dict(bias=1, c_fp32=1, res=1, res_fp32=1), bf16=dict(bias=1))[kind]
+              stream=dict(bias=1, c_fp32=1, res=1, res_fp32=1), bf16=dict(bias=1))
+    kw = {**kw, "dx sum": dict(tb=1, c_fp32=1, accumulate=1)}[kind]
     us = dict(zip([(128, 128)] + [(256, c) for c in (128, 160, 192, 224, 256)], map(float, times.split())))
     took = B.hmy_gemm_tiles(1, M, N, K, **kw)[:2]
     assert us[took] <= 1.04 * min(us.values()), (took, us)
