@@ -1000,8 +1000,9 @@ __device__ __forceinline__ void store_host4(float *dst, const float *src) {
   __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(src), reinterpret_cast<f32x4 *>(dst));
 }
 
-// At most 64 registers: the kernel runs beside the compute stream's, and the largest of those leave 64 registers per
-// lane of a compute unit they occupy -- with more, a unit that holds one wave of this kernel could not take their workgroup.
+// At most 64 registers: the kernel runs beside the compute stream's, and the largest of those that are one round of
+// workgroups leave 64 registers per lane of a compute unit they occupy (see k_gemm_tile) -- with more, a unit that holds
+// one wave of this kernel could not take their workgroup.
 template <bool MIXED>
 __global__ __attribute__((amdgpu_waves_per_eu(8))) void k_adam_out(const float *grad, const float *in_master, const float *in_m, const float *in_v,
                            float *out_master, float *out_m, float *out_v, void *out_w, float *out_g, uint64_t n,

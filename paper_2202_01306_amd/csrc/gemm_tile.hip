@@ -80,22 +80,21 @@ struct OpTile {
 // row 16 i + l % 16 and the four consecutive columns 16 j + 4 (l / 16) .. + 3 in acc[i][j].  16 rows of up to 64 columns at a time
 // pass through the wave's own 4 KiB of LDS and leave with 8 consecutive columns per lane.  16-byte chunks of a row of the slab are
 // swizzled by the row: conflict-free both ways.
-// What the output stage reads (residual, C) is fetched kAhead parts ahead, the first before the last K tile.
-template <int MI, int NB>
+// What the output stage reads (residual, C) is fetched AHEAD parts ahead, the first before the last K tile.
+template <int MI, int NB, int AHEAD>
 struct Out {
   static constexpr int CH = NB < 4 ? NB : 4, PER = (NB + CH - 1) / CH, PARTS = MI * PER;   // blocks at a time, parts of a row block
-  static constexpr int kAhead = 3;
   const DmaP &p;
   const Epi &e;
   const int m0, n0, lane, r8, c8;   // lane's place in a part: row 8 q + r8, columns c8 .. + 7
-  Epi::Pre pre[kAhead + 1][2];
+  Epi::Pre pre[AHEAD + 1][2];
   __device__ __forceinline__ Out(const DmaP &p_, const Epi &e_, int m, int n, int l)
       : p(p_), e(e_), m0(m), n0(n), lane(l), r8(l / 8), c8(8 * (l % 8)) {}
   __device__ __forceinline__ void prefetch(int part) {
     const int i = part / PER, j0 = part % PER * CH;
     if (!e.fast || c8 >= 16 * (NB - j0)) return;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) e.prefetch(p, m0 + 16 * i + 8 * q + r8, n0 + 16 * j0 + c8, pre[part % (kAhead + 1)][q]);
+    for (int q = 0; q < 2; ++q) e.prefetch(p, m0 + 16 * i + 8 * q + r8, n0 + 16 * j0 + c8, pre[part % (AHEAD + 1)][q]);
   }
   __device__ __forceinline__ void put(const f32x4 (&acc)[MI][NB], float *slab) {
     float4 bias8[PER];
@@ -106,11 +105,11 @@ struct Out {
         bias8[c] = *reinterpret_cast<const float4 *>(p.bias + n0 + 16 * c * CH + c8);
     }
 #pragma unroll
-    for (int part = 1; part < kAhead; ++part) prefetch(part);
+    for (int part = 1; part < AHEAD; ++part) prefetch(part);
 #pragma unroll
     for (int part = 0; part < PARTS; ++part) {
       const int i = part / PER, j0 = part % PER * CH;
-      if (part + kAhead < PARTS) prefetch(part + kAhead);
+      if (part + AHEAD < PARTS) prefetch(part + AHEAD);
 #pragma unroll
       for (int b = 0; b < CH; ++b)
         if (j0 + b < NB) *reinterpret_cast<f32x4 *>(slab + (lane % 16) * 64 + (((4 * b + lane / 16) ^ (lane % 16)) << 2)) = acc[i][j0 + b];
@@ -118,7 +117,7 @@ struct Out {
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           const int row = 8 * q + r8;
-          e.emit8(p, m0 + 16 * i + row, n0 + 16 * j0 + c8, slab + row * 64, (c8 >> 2) ^ row, pre[part % (kAhead + 1)][q], bias8[part % PER]);
+          e.emit8(p, m0 + 16 * i + row, n0 + 16 * j0 + c8, slab + row * 64, (c8 >> 2) ^ row, pre[part % (AHEAD + 1)][q], bias8[part % PER]);
         }
       }
     }
@@ -130,7 +129,7 @@ struct Out {
 // column by column, so that neighbours in time share operand tiles in it.  With a split (few tiles, long K; NB = 4 only) the part
 // varies fastest, so that an XCD works on one range of the contraction.
 template <bool TA, bool TB, int NB, int SA, int SB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_tile(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
+__device__ __forceinline__ void tile_product(const DmaP &p, int tiles, int grid_n, int tiles_per_split, int splits) {
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   constexpr int NW = 8, TM = 256, TN = 32 * NB;
   typedef OpTile<TA, TM> TileA;
@@ -140,6 +139,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr bool kEven = TileB::kKib % NW == 0;                            // (the last waves one less of B's otherwise)
   constexpr bool kHalves = NB > 4;   // a step's multiplies in two parts, so that B's fragments take half the registers
   constexpr int H0 = kHalves ? (NB + 1) / 2 : NB, H1 = NB - H0;
+  constexpr int kAhead = NB < 8 || (TA && TB) ? 3 : TA || TB ? 1 : 2;   // (see k_gemm_tile)
   static_assert(LA == 4, "four fetches of A's");
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -306,7 +306,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   Epi e;
   e.init(p, m0, n0, TM);
   e.inside = m0 + TM <= p.M && n0 + TN <= p.N;
-  Out<4, NB> out(p, e, m0 + arow, n0 + brow, lane);
+  // (the one layout that has no register left to keep the lane's number in)
+  const int lane_again = TA || !TB ? lane : __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+  Out<4, NB, kAhead> out(p, e, m0 + arow, n0 + brow, lane_again);
   if (!split) out.prefetch(0);
   step(0, sa, sb, sa, sb, sa, true);
   if (!half) step(1, sa, sb, sa, sb, sa, true);
@@ -334,6 +336,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
   out.put(acc, reinterpret_cast<float *>(smem) + wave * 1024);
 }
 
+// At most 224 registers (the attribute counts vector and accumulation registers apart, 112 of each), so that two waves per SIMD
+// leave 64 of 512: k_adam_out, whose waves sit on ten compute units for as long as an update lasts, takes 56, and a launch of 256
+// workgroups that cannot share those units runs a second round.  256 columns would take 238 to 241 registers: the output stage then
+// reads two parts ahead, or one, instead of three.  Iterations of the 24-layer encoder's width with the update on the device and
+// without copy engines: with 241 registers 108.6 ms (input gradient of the second MLP layer 78 us), with 224 106.4 (48; 33 alone).
+// On its own a product takes 0 to 0.9 % longer, with copy engines an iteration as long as before.
+template <bool TA, bool TB, int NB, int SA, int SB>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2), amdgpu_num_vgpr(112))) void k_gemm_tile(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
+  tile_product<TA, TB, NB, SA, SB>(p, tiles, grid_n, tiles_per_split, splits);
+}
+// Weight gradients: 256 columns with all their registers (241).  Held to 224 they read C one part ahead and take 1.7 % longer, up to
+// 5 % on short contractions; outputs that take 256 columns are 2048 and more wide either way, where a launch is several rounds.
+template <int NB, int SA, int SB>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_tile_dw(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
+  tile_product<true, true, NB, SA, SB>(p, tiles, grid_n, tiles_per_split, splits);
+}
+
 inline int check_launch(const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(HMY_E_HIP, "launch of %s failed: %s", what, hipGetErrorString(e));
@@ -352,7 +371,7 @@ int launch_tile(const hmy_gemm_desc &g, const DmaP &p, int splits, hipStream_t s
   if (!g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_tile<false, false, NB, SA, SB>), grid, block, lds, s, p, tiles, gn, tps, splits);
   else if (!g.ta && g.tb) hipLaunchKernelGGL((k_gemm_tile<false, true, NB, SA, SB>), grid, block, lds, s, p, tiles, gn, tps, splits);
   else if (g.ta && !g.tb) hipLaunchKernelGGL((k_gemm_tile<true, false, NB, SA, SB>), grid, block, lds, s, p, tiles, gn, tps, splits);
-  else hipLaunchKernelGGL((k_gemm_tile<true, true, NB, SA, SB>), grid, block, lds, s, p, tiles, gn, tps, splits);
+  else hipLaunchKernelGGL((k_gemm_tile_dw<NB, SA, SB>), grid, block, lds, s, p, tiles, gn, tps, splits);
   return check_launch("gemm_tile");
 }
 

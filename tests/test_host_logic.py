@@ -854,3 +854,29 @@ def test_gemm_tuning_switches(env, tile):
     plain = {k: v for k, v in os.environ.items() if not k.startswith("HMY_GEMM_")}
     out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env={**plain, **env}, check=True, capture_output=True, text=True).stdout
     assert tuple(map(int, out.split())) == tile
+
+
+def kernel_registers():
+    """{kernel: vector registers, bytes of scratch} of the built library, from the notes of its code objects."""
+    import struct
+    import msgpack
+    data, at, out = open(os.path.join(ROOT, "paper_2202_01306_amd", "libhmy.so"), "rb").read(), 0, {}
+    while (at := data.find(b"AMDGPU\0\0", at)) >= 0:
+        name_size, size, kind = struct.unpack_from("<III", data, at - 12)
+        at += 8
+        if (name_size, kind) == (7, 32):
+            for k in msgpack.unpackb(data[at:at + size], strict_map_key=False)["amdhsa.kernels"]:
+                out[k[".name"]] = (k[".vgpr_count"], k[".private_segment_fixed_size"])
+    return out
+
+
+def test_update_kernels_fit_beside_the_matrix_products():
+    """512 registers per SIMD lane, in eights: two waves of a forward product or an input gradient leave room for one of either
+    update kernel."""
+    up8 = lambda n: (n + 7) // 8 * 8
+    regs = kernel_registers()
+    update = [v for k, v in regs.items() if "k_adam" in k]
+    tiles = {k: v for k, v in regs.items() if "k_gemm_tileIL" in k}
+    assert len(update) == 4 and len(tiles) == 15
+    for name, (n, scratch) in tiles.items():
+        assert 2 * up8(n) + max(up8(u) for u, _ in update) <= 512 and scratch == 0, (name, n, scratch)
