@@ -426,7 +426,10 @@ int hmy_destroy(hmy_handle *h);
  * the copies and around the compute stream's waits cost a few percent of the iteration;
  * 1: every copy, every wait of the compute stream on a swap, and the compute span
  * (t_compute_s, t_h2d_busy_s, t_d2h_busy_s, t_stall_s); 2: also every GEMM launch
- * (gemm_s; two more event records per launch).  Where copies take the named engines (see
+ * (gemm_s; two more event records per launch).  At level 2 the input and the weight gradient of a
+ * small bf16 linear layer, which share a launch otherwise, are launched and timed one after the
+ * other: their times are those of kernels that an iteration at level 0 or 1 does not run, and add
+ * up to more than the shared launch takes.  Where copies take the named engines (see
  * hmy_copies_on_engines), level 1 or 2 makes the runtime time every asynchronous copy of the
  * process from then on; that stays on at level 0. */
 int hmy_set_profiling(hmy_handle *h, int32_t level);

@@ -387,7 +387,7 @@ void linear_bwd(hmy_handle *h, const void *dY, const void *X, const void *W, voi
   gw.A = dY; gw.lda = N; gw.ta = 1;
   gw.B = X; gw.ldb = K; gw.tb = 1;
   gw.C = dW; gw.ldc = K; gw.c_fp32 = 1; gw.accumulate = 1;
-  if (dX && !h->profile_gemm) {   // (timed ones go one by one)
+  if (dX && !h->profile_gemm) {   // (timed ones go one by one: a shared launch has no time per kernel variant)
     count_gemm(h, gx);
     count_gemm(h, gw);
     if (!h->dry && !h->err) KCHK(h, launch_gemm_pair(gx, gw, h->s_comp));

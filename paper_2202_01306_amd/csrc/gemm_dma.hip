@@ -533,13 +533,13 @@ __global__ __launch_bounds__(NT) void k_gemm_dma64(DmaP p, int tiles_per_split, 
 }
 
 // The same for contractions that are a multiple of 64, and for any where both operands are stored contraction-major: steps past
-// K of the last tile are rows past the operand, which the descriptors read as zeros.  What bounds a workgroup that has its SIMDs to itself is each wave's
-// own instruction stream: 128 cycles of multiplies per K tile among branches, waits and LDS reads that follow one another.
-// So: no branch in the loop (the fetches go through buffer descriptors, as on tiles of 256 rows, and end by themselves), the
-// next tile's fragments are read while this one's are multiplied, and what the output stage adds is fetched before the loop.
-// Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), 480x768x768 8.2 -> 6.9; weight
-// gradient 1024x1024x1024 12.1 -> 8.7, 768x3072x600 16.2 -> 14.0, 256x1024x480 6.6 -> 5.4.  It takes longer before its first multiply: short contractions stay with the kernel above
-// (`even_pays`).
+// K of the last tile are rows past the operand, which the descriptors read as zeros.  What bounds a workgroup that has its SIMDs to
+// itself is each wave's own instruction stream: 128 cycles of multiplies per K tile among branches, waits and LDS reads that
+// follow one another.  So: no branch in the loop (the fetches go through buffer descriptors, as on tiles of 256 rows, and end by
+// themselves), the next tile's fragments are read while this one's are multiplied, and what the output stage adds is fetched
+// before the loop.  Measured, us, kernel above -> this: 600x768x3072 22.1 -> 15.4 (input gradient 22.6 -> 14.4), 480x768x768 8.2 ->
+// 6.9; weight gradient 1024x1024x1024 12.1 -> 8.7, 768x3072x600 16.2 -> 14.0, 256x1024x480 6.6 -> 5.4.  It takes longer before its
+// first multiply: short contractions stay with the kernel above (`even_pays`).
 // `bid` of `workgroups`: a launch may hold more than this product.
 template <bool TA, bool TB>
 __device__ __forceinline__ void even_tile(const DmaP &p, int tiles_per_split, int grid_n, int splits, int bid, int workgroups,
@@ -827,12 +827,11 @@ bool small_sum_pays(const hmy_gemm_desc &g) {
 // -> 20.4), and for four times as many where the contraction is no multiple of 32 and the larger kernels leave it to
 // register-staged ones (768x3072x600 25 -> 15, 4096x1024x1001 38 -> 24, 2048x4096x1001 (2048 tiles) 41 -> 44).  Contractions
 // that are no multiple of 64, weight gradients aside, go through the kernel with branches: up to 2048 of them beyond 256 tiles
-// (2048x1024x2048 19.6 ->
-// 18.9, 4096 32.5 -> 33.4).  Beyond 256 tiles an operand stored contraction-major loses on long ones what the tiles gain: from
-// 8192 on (input gradients 2048x1024x8192 59.9 -> 58.9, x12288 86.7 -> 89.4), from 4096 on where its rows are no whole half
-// cache lines (1960x1000x4096 36.8 -> 35.5, x8192 63.0 -> 68.1; forward, x16384 109 -> 102). Sums into an fp32 C other than
-// weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the contraction, and so do long
-// weight gradients (above).
+// (2048x1024x2048 19.6 -> 18.9, 4096 32.5 -> 33.4).  Beyond 256 tiles an operand stored contraction-major loses on long ones what
+// the tiles gain: from 8192 on (input gradients 2048x1024x8192 59.9 -> 58.9, x12288 86.7 -> 89.4), from 4096 on where its rows are
+// no whole half cache lines (1960x1000x4096 36.8 -> 35.5, x8192 63.0 -> 68.1; forward, x16384 109 -> 102).  Sums into an fp32 C
+// other than weight gradients (the vocabulary-long input gradient) keep the larger kernels' splits of the contraction, and so do
+// long weight gradients (above).
 bool gemm_prefers_small(const hmy_gemm_desc &g) {
   if (gemm_small_excluded()) return false;
   if (g.accumulate && !(g.ta && g.tb)) return false;
@@ -890,7 +889,8 @@ static float tile_time(const hmy_gemm_desc &g, int nb) {
                      : g.res && g.res_fp32 ? 2.6f : both ? (nb ? 1.58f : 1.96f) : 1.f;
   float out = 9.5f * kind * (nb ? float(nb) / 8.f : 0.264f);
   if (nb % 2 && !g.c_fp32) out += 0.1f;   // tiles whose rows end inside a cache line
-  return rounds(whole ? last : 0.65f) * per_1024_steps[nb] * float(g.K) / 1024.f + rounds(whole ? last : 0.5f) * (out + (nb ? 4.7f : 0.98f));
+  const float multiplies = per_1024_steps[nb] * float(g.K) / 1024.f, around = out + (nb ? 4.7f : 0.98f);
+  return rounds(whole ? last : 0.65f) * multiplies + rounds(whole ? last : 0.5f) * around;
 }
 // Columns, over 32, of the tiles of 256 rows that a product takes, or 0 for 128x128 tiles.
 static int tile_columns(const hmy_gemm_desc &g) {
@@ -946,8 +946,9 @@ int launch_gemm_dma(const hmy_gemm_desc &g, const GemmTiles &t, stream_t st) {
   const int tps = (nk + t.splits - 1) / t.splits, splits = (nk + tps - 1) / tps;
   dim3 grid(gm * gn * splits);
   hipStream_t s = (hipStream_t)st;
-  if (t.bk == 64) return t.stages == 3 ? launch_cfg<64, 3>(g, p, grid, tps, gn, splits, s) : launch_cfg<64, 4>(g, p, grid, tps, gn, splits, s);
-  return t.stages == 3 ? launch_cfg<32, 3>(g, p, grid, tps, gn, splits, s) : launch_cfg<32, 4>(g, p, grid, tps, gn, splits, s);
+  const auto launch = t.bk == 64 ? (t.stages == 3 ? launch_cfg<64, 3> : launch_cfg<64, 4>)
+                                 : (t.stages == 3 ? launch_cfg<32, 3> : launch_cfg<32, 4>);
+  return launch(g, p, grid, tps, gn, splits, s);
 }
 
 }  // namespace hmy

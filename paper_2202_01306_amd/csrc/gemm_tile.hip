@@ -15,7 +15,7 @@
 // 466 us), and a workgroup that went on to its next output tile with two stages filled gained less (773 us for 8192^3).
 //
 // The width: a product is rounds of 256 tiles, and what the last round leaves idle costs as much as what it does (the rule stands
-// at launch_gemm_dma).
+// at tile_time).
 #include <type_traits>
 
 #include "gemm_dma.h"
@@ -343,13 +343,16 @@ __device__ __forceinline__ void tile_product(const DmaP &p, int tiles, int grid_
 // without copy engines: with 241 registers 108.6 ms (input gradient of the second MLP layer 78 us), with 224 106.4 (48; 33 alone).
 // On its own a product takes 0 to 0.9 % longer, with copy engines an iteration as long as before.
 template <bool TA, bool TB, int NB, int SA, int SB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2), amdgpu_num_vgpr(112))) void k_gemm_tile(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2), amdgpu_num_vgpr(112)))
+void k_gemm_tile(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
   tile_product<TA, TB, NB, SA, SB>(p, tiles, grid_n, tiles_per_split, splits);
 }
-// Weight gradients: 256 columns with all their registers (241).  Held to 224 they read C one part ahead and take 1.7 % longer, up to
-// 5 % on short contractions; outputs that take 256 columns are 2048 and more wide either way, where a launch is several rounds.
+// Weight gradients: 256 columns with all their registers (241).  Held to 224 they read C one part ahead, and every launch takes 1.7 %
+// longer, up to 5 % on short contractions.  Layers of width 1024 to 1600 have none on 256 columns; those of wider ones are longer
+// than a round (12288x4096), or a round that shares the device with k_adam_out only where there are no copy engines.
 template <int NB, int SA, int SB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_tile_dw(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+void k_gemm_tile_dw(DmaP p, int tiles, int grid_n, int tiles_per_split, int splits) {
   tile_product<true, true, NB, SA, SB>(p, tiles, grid_n, tiles_per_split, splits);
 }
 
