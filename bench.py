@@ -47,10 +47,10 @@ def attention_flops(cfg, packs) -> float:
 # WRITE_SIZE by 1.0: what the same counters read for a streaming kernel of known size (k_gelu_bwd_colsum, 64 MiB in /
 # 32 MiB plus 4 MiB of atomic additions out).
 GPT2M_FWD_GEMM_TRAFFIC = [   # (what, kernel, grid threads, dispatches, FETCH_SIZE KiB as counted, WRITE_SIZE KiB)
-    ("ffn1", "k_gemm_tile<false, false, 8, 3, 2>", 131072, 384, 24942.5, 49152.0),
-    ("qkv", "k_gemm_tile<false, false, 6, 3, 2>", 131072, 384, 20837.5, 24576.1),
-    ("logits, 512-row chunk", "k_gemm_tile<false, false, 7, 3, 2>", 230400, 64, 59246.8, 100861.5),
-    ("out and ffn2", "k_gemm_dma<false, false, 64, 4>", 65536, 704, 37456.4, 16384.3),
+    ("ffn1", "k_gemm_tile<false, false, 8, 3, 2>", 131072, 384, 24948.0, 49152.0),
+    ("qkv", "k_gemm_tile<false, false, 6, 3, 2>", 131072, 384, 20829.5, 24576.0),
+    ("logits, 512-row chunk", "k_gemm_tile<false, false, 7, 3, 2>", 230400, 64, 59231.7, 100858.1),
+    ("out and ffn2", "k_gemm_dma<false, false, 64, 4>", 65536, 704, 37456.4, 16384.0),
 ]
 
 
