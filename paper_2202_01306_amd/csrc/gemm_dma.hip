@@ -925,8 +925,8 @@ GemmTiles gemm_dma_tiles(const hmy_gemm_desc &g) {
     // a workgroup per compute unit and every part stays long enough to make up for twice the atomics.  Measured, us, 128x128
     // tiles -> these: 2048x1024, K = 50240 219 -> 184 (12560 in each part), 1024x1600 199 -> 164, 1024x1024 115 -> 105 (6280),
     // 512x1600 104 -> 92 (5582); 1024x1024x40960 98 -> 93 (5120), 512x1024x65536 77.7 -> 78.4 (4096), 1024x1024x16384 50 -> 55
-    // (2048).  Not where 128x128 tiles fill the compute units (4096x1024x50257 in two parts 563 -> 465): the logits' input gradient
-    // is rounded to bf16 next, and from another order of its sum every gradient below moves by some 6e-3.
+    // (2048).  Not where 128x128 tiles fill the compute units: 4096x1024x50257 takes 465 in two parts (563 in one, 449 on 128x128
+    // tiles), and an input gradient is rounded to bf16 next: from another order of its sum every gradient below moves by some 6e-3.
     const bool few = tiles_of(g, BM, BM) <= 128;
     if (can_split && few && g.M >= 256 && g.K % 64 == 0) {
       const int w2 = int(tiles_of(g, 256, 128)), splits = 256 / w2;
